@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int N, float alpha, Layout lay, int pairs,
     BlockOrder ord) {
-  constexpr int TILE_BYTES = kQTile * kLdsD<D> * 2;
+  constexpr int TILE_BYTES = kQTile * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   // layout: Q buffers [2][TILE_BYTES], dO buffers [2][TILE_BYTES], L2 [2][64] float, delta [2][64] float
   char* ldsQ = smem;
@@ -104,19 +104,10 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
   const size_t head_off = head_base_kv(lay, bq0);              // K, V, dK, dV
   const float c2 = alpha * kLog2e;
   FragOffsets<D> fo;
-  init_frag_offsets<D>(fo, lane);
-  // Transposing reads of the update products address column block db0 + db: a column block only
-  // enters the offset through chunk bits the swizzle leaves alone, so shifting by db0 blocks is one
-  // XOR per offset (32 columns = 4 chunks = 64 bytes).
+  init_frag_offsets<D>(fo, lane, lds_address(smem));
+  // transposing reads of the update products address column block db0 + db
   FragOffsets<D> fo_upd = fo;
-  if (DS > 1) {
-#pragma unroll
-    for (int half = 0; half < 2; ++half)
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db) fo_upd.col[half][db] ^= 64 * db0;
-  }
-  frag_offsets_add_base<D>(fo, lds_address(smem));
-  frag_offsets_add_base<D>(fo_upd, lds_address(smem));
+  if (DS > 1) { fo_upd.col[0] += 1024 * db0; fo_upd.col[1] += 1024 * db0; }
   TileLoader<D> loader;
   loader.init(tid, sn);
 
@@ -181,8 +172,8 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
         ldsL[buf * kQTile + tid] = l;
       } else if (tid < 2 * kQTile) ldsD[buf * kQTile + tid - kQTile] = -sreg;   // LDS holds -delta
     };
-    loader.template load_rows<RAGGED>(ldsQ, Qh, t0 * kQTile, N, tid);
-    loader.template load_rows<RAGGED>(ldsdO, dOh, t0 * kQTile, N, tid);
+    loader.template load_rows<RAGGED>(ldsQ, Qh, t0 * kQTile, N);
+    loader.template load_rows<RAGGED>(ldsdO, dOh, t0 * kQTile, N);
     load_stats(Lh, Dh, t0);
     store_stats(0);
     wait_vmem();
@@ -205,8 +196,8 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
       const auto pendQ = loader.template prepare<RAGGED>(ldsQ + (buf ^ 1) * TILE_BYTES, Qh, tn * kQTile, N);
       const auto pendD = loader.template prepare<RAGGED>(ldsdO + (buf ^ 1) * TILE_BYTES, dOh, tn * kQTile, N);
       auto issue_part = [&](int i) {
-        if (i < NLD) loader.template issue<RAGGED>(pendQ, tid, i);
-        else if (i < 2 * NLD) loader.template issue<RAGGED>(pendD, tid, i - NLD);
+        if (i < NLD) loader.issue(pendQ, i);
+        else if (i < 2 * NLD) loader.issue(pendD, i - NLD);
       };
       if (has_next) load_stats(Lh, Dh, tn);
       constexpr int tQ = buf * TILE_BYTES;          // byte offsets of this tile's Q and dO in smem
@@ -281,7 +272,7 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
         constexpr int NS = D / 8;            // slots per phase
         constexpr int AH = (D >= 128) ? 8 : 4;  // LDS read-ahead, in slots
         constexpr int R = 2 * AH;            // fragment ring size (> AH)
-        constexpr int EPS = 16 / NS;         // score elements handled per slot
+        // score elements handled in slot sl: [16 sl / NS, 16 (sl + 1) / NS)
         bf16x8 ring[R];
         // slot s of an S/dP phase: kc = s/2, even -> S (Q_i, K_j), odd -> dP (dO_i, V_j)
         auto rd_sdp = [&](int qb, int sl) -> bf16x8 {
@@ -330,8 +321,7 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
           if (sl & 1) dp1 = mfma32(ring[(NS + sl) % R], vf[sl >> 1], dp1);
           else s1 = mfma32(ring[(NS + sl) % R], kf[sl >> 1], s1);
 #pragma unroll
-          for (int e = 0; e < EPS; ++e) {
-            const int i = sl * EPS + e;
+          for (int i = 16 * sl / NS; i < 16 * (sl + 1) / NS; ++i) {
             float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[i], c2, -lq0[i >> 2][i & 3]));
             float ds = p * dp0[i];
             pf0[i >> 3][i & 7] = (bf16_t)p;
@@ -347,8 +337,7 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
           if (sl & 1) dKt[db] = mfma32(ring[(2 * NS + sl) % R], dsf0[cc], dKt[db]);
           else dVt[db] = mfma32(ring[(2 * NS + sl) % R], pf0[cc], dVt[db]);
 #pragma unroll
-          for (int e = 0; e < EPS; ++e) {
-            const int i = sl * EPS + e;
+          for (int i = 16 * sl / NS; i < 16 * (sl + 1) / NS; ++i) {
             float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[i], c2, -lq1[i >> 2][i & 3]));
             float ds = p * dp1[i];
             pf1[i >> 3][i & 7] = (bf16_t)p;
@@ -366,7 +355,7 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
           __builtin_amdgcn_sched_barrier(0);
         }
       };
-      if (DS == 1 && D != 96 && (!CAUSAL || qt0 + shift >= kw + 31) && (!RAGGED || qt0 + kQTile <= N)) {
+      if (DS == 1 && (!CAUSAL || qt0 + shift >= kw + 31) && (!RAGGED || qt0 + kQTile <= N)) {
         tile_pipelined();
       } else {
 #pragma unroll
@@ -440,7 +429,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ O, bf16_t* __restrict__ dQ, float* __restrict__ delta_out, int N,
     float alpha, Layout lay, int pairs, BlockOrder ord) {
   constexpr bool DELTA_MODE = MODE == kRecomputeDelta;
-  constexpr int TILE_BYTES = kKTile * kLdsD<D> * 2;
+  constexpr int TILE_BYTES = kKTile * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* ldsK = smem;
   char* ldsV = smem + 2 * TILE_BYTES;
@@ -469,8 +458,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
   TileLoader<D> loader;
   loader.init(tid, sn);
   FragOffsets<D> fo;
-  init_frag_offsets<D>(fo, lane);
-  frag_offsets_add_base<D>(fo, lds_address(smem));
+  init_frag_offsets<D>(fo, lane, lds_address(smem));
 
   for (int part = 0; part < (pairs ? 2 : 1); ++part) {
   if (part > 0) __syncthreads();                      // the first block's output staging is done with the tile buffers
@@ -497,7 +485,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
     // this lane holds chunks 2kc + h of its row: the chains of its chunks, the tree levels that
     // stay inside one parity class, and the last level (chunk 0 + chunk 1 classes) across the
     // two lanes of the row
-    constexpr int NCS = kLdsD<D> / 16;     // D = 96: the tree of a 128-wide row whose last chunks are zero
+    constexpr int NCS = kPow2D<D> / 16;     // D = 96: the tree of a 128-wide row whose last chunks are zero
     float cs[NCS];
 #pragma unroll
     for (int kc = 0; kc < NCS; ++kc) cs[kc] = 0.f;
@@ -534,8 +522,8 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
   const int kend = !CAUSAL ? NK : !RAGGED ? q0 + kQPerWG : max(0, min(NK, q0 + kQPerWG + shift));
   const int ntiles = RAGGED ? (kend + kKTile - 1) / kKTile : kend / kKTile;
 
-  loader.template load_rows<RAGGED>(ldsK, Kh, 0, NK, tid);
-  loader.template load_rows<RAGGED>(ldsV, Vh, 0, NK, tid);
+  loader.template load_rows<RAGGED>(ldsK, Kh, 0, NK);
+  loader.template load_rows<RAGGED>(ldsV, Vh, 0, NK);
   wait_vmem();
 #pragma unroll
   for (int kc = 0; kc < D / 16; ++kc) { settle(qf[kc]); settle(dof[kc]); }
@@ -557,8 +545,8 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
     const auto pendK = loader.template prepare<RAGGED>(smem + (buf ^ 1) * TILE_BYTES, Kh, jn * kKTile, NK);
     const auto pendV = loader.template prepare<RAGGED>(smem + (2 + (buf ^ 1)) * TILE_BYTES, Vh, jn * kKTile, NK);
     auto issue_part = [&](int i) {
-      if (i < NLD) loader.template issue<RAGGED>(pendK, tid, i);
-      else if (i < 2 * NLD) loader.template issue<RAGGED>(pendV, tid, i - NLD);
+      if (i < NLD) loader.issue(pendK, i);
+      else if (i < 2 * NLD) loader.issue(pendV, i - NLD);
     };
     bool issued = false;
     const int kt0 = j * kKTile;
@@ -669,7 +657,7 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
                               const float* LSE, const float* delta, void* dK, void* dV, int BH,
                               int N, float alpha, Layout lay, hipStream_t st) {
   constexpr int NDB = D / 32 / kDSplit<D>;
-  constexpr int smem = 4 * kQTile * kLdsD<D> * 2 + 4 * kQTile * (int)sizeof(float) +
+  constexpr int smem = 4 * kQTile * D * 2 + 4 * kQTile * (int)sizeof(float) +
                        (kStagedDkDv<D> ? 4 * 32 * kStagePitch<NDB> : 0);
   static std::atomic<bool> set{false};
   auto k = attn_bwd_dkdv_kernel<D, CAUSAL, RAGGED, GROUPED>;
@@ -697,7 +685,7 @@ template <int D, bool CAUSAL, bool RAGGED, int MODE>
 static hipError_t launch_dq(const void* Q, const void* K, const void* V, const void* dO,
                             const float* LSE, const float* delta, const void* O, void* dQ,
                             float* delta_out, int BH, int N, float alpha, Layout lay, hipStream_t st) {
-  constexpr int smem = 4 * kKTile * kLdsD<D> * 2;
+  constexpr int smem = 4 * kKTile * D * 2;
   static std::atomic<bool> set{false};
   auto k = attn_bwd_dq_kernel<D, CAUSAL, RAGGED, MODE>;
   hipError_t e;

@@ -1,5 +1,5 @@
 // Shared device helpers for the gfx950 attention kernels: vector types, the matrix-core
-// wrappers, the LDS tile layout (16-byte-chunk XOR swizzle) and cross-lane exchanges.
+// wrappers, the LDS tile layout (macro blocks with permuted 16-byte chunks) and cross-lane exchanges.
 //
 // Matrix-core fragment layouts used throughout (wave64, v_mfma_f32_32x32x16_bf16,
 // D[32x32] += A[32x16] * B[16x32]; lane l, r = l & 31, h = l >> 5):
@@ -32,123 +32,69 @@ DEVI f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// Width of an LDS tile row, in elements, for head size D.  The swizzle and the tile loader work on
-// power-of-two rows; D = 96 uses 128-wide rows of which the last 32 columns are never read.
-template <int D> constexpr int kLdsD = (D == 96) ? 128 : D;
+// ---- LDS tile layout.  A tile of R rows x D bf16 columns is cut into macro blocks of 16 rows x 32
+// columns (64 bytes per row), 1024 bytes each: block (rg, cg) lies at (rg * D/32 + cg) * 1024.  Inside a
+// block row r (0..15) takes 64 consecutive bytes and its four 16-byte chunks are permuted by
+// chunk ^ (r >> 2), so that (a) 16 lanes reading the same chunk of the block's 16 rows and (b) a
+// transposing read of 8 rows x 64 bytes (512 consecutive bytes) both spread over all 64 LDS banks.
+// Everything a fragment's address depends on besides the lane - row block, column block, tile
+// buffer - adds a multiple of 1024 bytes: two per-lane registers serve every row-major fragment and
+// two every column-major one, the rest is the instruction's immediate offset.  (With whole rows of
+// D columns and the chunk index XOR-ed over the full row, D/16 + D/16 such registers were
+// needed, and rows had to be a power of two wide: D = 96 moved and held a third more.)
+template <int D> constexpr int kColBlocks = D / 32;
+// D rounded up to a power of two: the lanes (and the summation tree) of one row in rowsum(dO o O)
+template <int D> constexpr int kPow2D = (D == 96) ? 128 : D;
+// bytes from one 16-row block of a tile to the next
+template <int D> constexpr int kRowBlockBytes = kColBlocks<D> * 1024;
 
-// Swizzle of the 16-byte chunk index inside one tile row, chosen so that (a) 16 lanes reading
-// the same chunk of 16 consecutive rows and (b) a transposing read touching 8 consecutive rows
-// x 64 bytes both spread over all 64 LDS banks.
-template <int D> DEVI int swz(int row);
-template <> DEVI int swz<128>(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-// D = 256: rows are 512 bytes, as at D = 128 every row starts on bank 0: the same permutation of
-// the low four chunk-index bits serves (the fifth bit is left alone).
-template <> DEVI int swz<256>(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-// D = 32: a row is 4 chunks (64 bytes), four consecutive rows span the 64 banks once; rows r and
-// r + 4 would collide in (a) unless their chunk positions differ.  (b) touches 8 whole rows there.
-template <> DEVI int swz<32>(int row) { return (row >> 2) & 3; }
-template <> DEVI int swz<64>(int row) {
-  int t = row >> 1;
-  return ((t & 1) << 2) | (t & 2) | ((t >> 2) & 1);
-}
-
-// Byte offset of element (row, col) of a [rows][D] bf16 tile in LDS; col must be a multiple of 4
-// for 8-byte accesses and of 8 for 16-byte accesses.
-template <int D> DEVI int tile_off(int row, int col) {
-  constexpr int DL = kLdsD<D>;
-  int chunk = col >> 3;
-  return row * (DL * 2) + ((chunk ^ swz<DL>(row)) << 4) + ((col & 7) << 1);
-}
-
-// 16-byte natural read: 8 consecutive columns of one row (an A/B fragment whose contraction
-// index runs along the tile's columns).
-template <int D> DEVI bf16x8 lds_read_row8(const char* tile, int row, int col) {
-  return *reinterpret_cast<const bf16x8*>(tile + tile_off<D>(row, col));
-}
-
-// Transposing read: returns, for this lane, 4 consecutive ROWS (row0..row0+3) of column
-// col0 + (lane & 15).  ds_read_b64_tr_b16 works on groups of 16 lanes: lane i of a group
-// supplies the address of 4 consecutive columns (4*(i&3)..) of row (i>>2), and receives
-// column i of rows 0..3.  col0 must be a multiple of 16.
-template <int D> DEVI s16x4 lds_read_tr4(const char* tile, int row0, int col0, int lane) {
-  int i = lane & 15;
-  int off = tile_off<D>(row0 + (i >> 2), col0 + ((i & 3) << 2));
-  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tile + off));
-}
-
-// Fragment whose contraction index runs along the tile's ROWS: k-slots (h, 0..7) of the
-// 16-row chunk starting at row_base are rows row_base + 8*(j/4) + 4h + (j%4), j = 0..7;
-// the lane's own index (lane & 31) selects column col_base + (lane & 31).
-template <int D> DEVI bf16x8 lds_read_col8(const char* tile, int row_base, int col_base, int lane) {
-  int h = lane >> 5;
-  int c0 = col_base + (lane & 16);
-  union { struct { s16x4 lo, hi; } p; bf16x8 v; } u;
-  u.p.lo = lds_read_tr4<D>(tile, row_base + 4 * h, c0, lane);
-  u.p.hi = lds_read_tr4<D>(tile, row_base + 8 + 4 * h, c0, lane);
-  return u.v;
-}
-
-// ---- The same two fragment reads with the lane-dependent part of the address precomputed.
-// The swizzle only looks at row bits 0..3, so moving a fragment by a multiple of 16 rows adds a
-// constant to the byte offset: per lane, D/16 offsets serve every row-major (natural) fragment
-// and 2 x D/32 offsets every column-major (transposing) one; the rest folds into the
-// instruction's immediate offset when the tile address is a compile-time constant.
-// The offsets are made absolute LDS addresses once (frag_offsets_add_base); the fragment readers
-// below then address LDS as "per-lane register + compile-time constant", which the compiler
-// turns into the instruction's immediate offset.  (With the shared-memory symbol in the address
-// expression instead, it re-adds the symbol's address - a link-time value - in a vector
-// instruction in front of every read.)
 template <int D> struct FragOffsets {
-  int row[D / 16];          // natural read of columns 16kc + 8h .. +7 of row (lane & 31)
-  int col[2][D / 32];       // transposing reads: rows 4h + 8*half + 0..3, column 32db + (lane & 31)
+  int row[2];               // natural read of row (lane & 31), columns 16kc + 8h .. +7, by parity of kc
+  int col[2];               // transposing reads: rows 4h + 8*half + 0..3, column 32db + (lane & 31)
 };
 // 32-bit LDS address of a pointer into shared memory
 DEVI int lds_address(const void* p) {
   typedef __attribute__((address_space(3))) const char lds_char;
   return (int)(unsigned)(unsigned long)((lds_char*)p);
 }
-template <int D> DEVI void init_frag_offsets(FragOffsets<D>& fo, int lane) {
+// shared_base: LDS address of the array the tiles live in (lds_address(smem)).  The offsets are
+// absolute LDS addresses, each passed through an empty asm statement: otherwise the compiler,
+// rather than keep the sum in a register, re-adds the array's address (a link-time value) in front of
+// every read.
+template <int D> DEVI void init_frag_offsets(FragOffsets<D>& fo, int lane, int shared_base) {
   const int r = lane & 31, h = lane >> 5, i = lane & 15;
 #pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) fo.row[kc] = tile_off<D>(r, 16 * kc + 8 * h);
-#pragma unroll
-  for (int half = 0; half < 2; ++half)
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-      fo.col[half][db] = tile_off<D>(4 * h + 8 * half + (i >> 2), 32 * db + (lane & 16) + ((i & 3) << 2));
-}
-// shared_base: LDS address of the array the tiles live in (lds_address(smem))
-// (each sum passes through an empty asm statement: otherwise the compiler, rather than keep it in
-// a register, re-adds the base in front of every use)
-template <int D> DEVI void frag_offsets_add_base(FragOffsets<D>& fo, int shared_base) {
-#pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) {
-    fo.row[kc] += shared_base;
-    asm volatile("" : "+v"(fo.row[kc]));
+  for (int p = 0; p < 2; ++p) {
+    fo.row[p] = shared_base + (r >> 4) * kRowBlockBytes<D> + (r & 15) * 64 + (((2 * p + h) ^ ((r & 15) >> 2)) << 4);
+    asm volatile("" : "+v"(fo.row[p]));
   }
 #pragma unroll
-  for (int half = 0; half < 2; ++half)
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
-      fo.col[half][db] += shared_base;
-      asm volatile("" : "+v"(fo.col[half][db]));
-    }
+  for (int half = 0; half < 2; ++half) {
+    const int row = 4 * h + 8 * half + (i >> 2);              // row >> 2 = h + 2 half
+    const int chunk = ((lane & 16) >> 3) + ((i & 3) >> 1);
+    fo.col[half] = shared_base + row * 64 + ((chunk ^ (h + 2 * half)) << 4) + ((i & 1) << 3);
+    asm volatile("" : "+v"(fo.col[half]));
+  }
 }
 // `tile`: byte offset of the tile inside the shared-memory array (fo holds absolute addresses).
-// rows row_base + (lane & 31), row_base a multiple of 16
+// 16-byte natural read: 8 consecutive columns (16kc + 8h ..) of row row_base + (lane & 31), row_base
+// a multiple of 16: an A/B fragment whose contraction index runs along the tile's columns.
 template <int D> DEVI bf16x8 lds_row8(int tile, const FragOffsets<D>& fo, int row_base, int kc) {
   typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
-  return *reinterpret_cast<lds_bf16x8*>((unsigned long)(unsigned)(fo.row[kc] + tile + row_base * (kLdsD<D> * 2)));
+  return *reinterpret_cast<lds_bf16x8*>((unsigned long)(unsigned)(
+      fo.row[kc & 1] + tile + (row_base >> 4) * kRowBlockBytes<D> + (kc >> 1) * 1024));
 }
-// k-slots = rows row_base + 8*(j/4) + 4h + (j%4), column 32db + (lane & 31); row_base a multiple of 16
+// Fragment whose contraction index runs along the tile's ROWS: k-slots (h, 0..7) of the 16-row chunk at
+// row_base (a multiple of 16) are rows row_base + 8*(j/4) + 4h + (j%4), j = 0..7; the lane's own
+// index selects column 32db + (lane & 31).  Two transposing reads: ds_read_b64_tr_b16 works on groups
+// of 16 lanes, lane i of a group supplies the address of 4 consecutive columns (4*(i&3)..) of row
+// (i>>2) and receives column i of the four rows.
 template <int D> DEVI bf16x8 lds_col8(int tile, const FragOffsets<D>& fo, int row_base, int db) {
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   union { struct { s16x4 lo, hi; } p; bf16x8 v; } u;
-  u.p.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (lds_s16x4*)(unsigned long)(unsigned)(fo.col[0][db] + tile + row_base * (kLdsD<D> * 2)));
-  u.p.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (lds_s16x4*)(unsigned long)(unsigned)(fo.col[1][db] + tile + row_base * (kLdsD<D> * 2)));
+  const int at = tile + (row_base >> 4) * kRowBlockBytes<D> + db * 1024;
+  u.p.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(unsigned long)(unsigned)(fo.col[0] + at));
+  u.p.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(unsigned long)(unsigned)(fo.col[1] + at));
   return u.v;
 }
 
@@ -197,11 +143,13 @@ DEVI size_t head_base_kv(const Layout& lay, int bh) {
   return (size_t)(bh / lay.H) * (size_t)lay.sb_kv + (size_t)((bh % lay.H) / lay.group) * (size_t)lay.sh_kv;
 }
 
-// Asynchronous copy of a 64-row x D bf16 tile from global memory straight into swizzled LDS
+// Asynchronous copy of a R-row x D bf16 tile from global memory straight into LDS
 // (global_load_lds_dwordx4: no registers are involved; completion is tracked by vmcnt).
-// One wave-instruction moves 64 x 16 bytes to LDS base + 16*lane, i.e. 1024 consecutive bytes =
-// 64/CH whole tile rows; the XOR swizzle is applied on the GLOBAL side: the lane that lands in
-// chunk slot s of row r fetches chunk s ^ swz(r) of that row.  256 threads (4 waves).
+// One wave-instruction moves 64 x 16 bytes to LDS base + 16*lane, i.e. one macro block of the layout
+// above: 16 rows x 64 bytes.  The chunk permutation is applied on the GLOBAL side: the lane that
+// lands in slot s of row r fetches chunk s ^ (r >> 2) of that row.  256 threads (4 waves) share a
+// tile; a wave stays inside its own 16-row block(s), so that one per-lane offset (per row block) serves
+// all its instructions and only the scalar base moves along the columns.
 // The caller must execute wait_vmem() and a barrier before any wave reads the tile.
 //
 // The instruction is emitted through inline assembly on purpose: when the compiler itself sees a
@@ -219,97 +167,62 @@ DEVI const bf16_t* wave_uniform(const bf16_t* p) {
   return reinterpret_cast<const bf16_t*>(((unsigned long long)hi << 32) | lo);
 }
 
-template <int D> struct TileLoader {
-  static constexpr int DL = kLdsD<D>;            // LDS row width
-  static constexpr int CH = DL / 8;              // 16-byte chunk slots per LDS row
-  // source chunk that lands in slot `slot` of LDS row `row`; slots whose chunk lies beyond the D
-  // columns (D < DL) re-fetch one of the row's real chunks, which nobody reads
-  static DEVI int src_chunk(int slot, int row) {
-    const int c = slot ^ swz<DL>(row);
-    return (D < DL && c >= D / 8) ? (c & 7) : c;
-  }
-  static constexpr int RPI = 64 / CH;            // rows per wave-instruction
-  static constexpr int NI = 64 / RPI / 4;        // instructions per wave (4 waves share a tile)
-  unsigned voff[NI];                             // per-lane byte offset inside the source tile
-  unsigned lds_wave;                             // byte offset of this wave's first row in the LDS tile
+template <int D, int R = 64> struct TileLoader {
+  static_assert(R == 32 || R == 64 || R == 128, "rows per tile");
+  static constexpr int NCB = kColBlocks<D>;
+  static constexpr int WPR = R >= 64 ? 1 : 2;    // waves that share a 16-row block ...
+  static constexpr int RPW = R >= 64 ? R / 64 : 1;   // ... or row blocks per wave
+  static constexpr int CPW = (NCB + WPR - 1) / WPR;  // column blocks per wave and row block
+  static constexpr int NI = RPW * CPW;           // instructions per wave
+  static constexpr int kBytes = R * D * 2;
+  int row, chunk;                                // per lane: first row of the tile it fetches, byte offset of its chunk
+  int col0;                                      // first column block of this wave (scalar)
   int sn;                                        // distance between consecutive rows of the source, in elements
+  unsigned lds_wave;                             // LDS offset of the wave's first macro block (scalar)
   DEVI void init(int tid, int row_stride) {
-    const int wave = tid >> 6, lane = tid & 63;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = wave / WPR * RPW;             // first row block of this wave
+    col0 = wave % WPR;
     sn = row_stride;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int row = (wave * NI + i) * RPI + lane / CH;
-      const int c = src_chunk(lane % CH, row);
-      voff[i] = (unsigned)(row * sn + c * 8) * 2u;
-    }
-    lds_wave = (unsigned)(wave * NI * RPI * DL * 2);
+    row = rg * 16 + (lane >> 2);
+    chunk = ((lane & 3) ^ (lane >> 4)) * 16;
+    lds_wave = (unsigned)(rg * kRowBlockBytes<D> + col0 * 1024);
   }
-  // Same for a source tile of which only the first `valid` rows (1..64) exist: rows beyond them
-  // re-read the last valid row, so that nothing is fetched out of bounds and the LDS tile holds
-  // finite values everywhere (the kernels mask those rows / columns out).
-  DEVI void load_clamped(const char* tile, const bf16_t* src, int valid, int tid) const {
-    typedef __attribute__((address_space(3))) const char lds_char;
-    const int wave = tid >> 6, lane = tid & 63;
-    const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long)((lds_char*)tile) + lds_wave);
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int row = (wave * NI + i) * RPI + lane / CH;
-      const int c = src_chunk(lane % CH, row);
-      const int rc = row < valid ? row : valid - 1;
-      const unsigned vo = (unsigned)(rc * sn + c * 8) * 2u;
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :
-                   : "s"(base + (unsigned)(i * RPI * DL * 2)), "v"(vo), "s"(src)
-                   : "m0");
-    }
-  }
-  // Tile starting at row `row0` of a tensor with `N` rows (row0 < N).  RAGGED: the tile may
-  // reach past row N-1 and is then loaded clamped; otherwise every tile is known to be full.
-  template <bool RAGGED>
-  DEVI void load_rows(const char* tile, const bf16_t* tensor, int row0, int N, int tid) const {
-    const bf16_t* src = wave_uniform(tensor + (size_t)row0 * sn);
-    if (!RAGGED || row0 + 64 <= N) load(tile, src);
-    else load_clamped(tile, src, N - row0, tid);
-  }
-  // A tile transfer prepared once (scalar operands) and issued one instruction at a time, so that a
-  // caller can spread it over its matrix instructions instead of issuing it in one burst.
-  struct Pending { const bf16_t* src; unsigned base; int valid; };
+  // A tile transfer prepared once (operands) and issued one instruction at a time, so that a caller
+  // can spread it over its matrix instructions instead of issuing it in one burst.
+  // RAGGED: of the source tile only the first N - row0 rows may exist: rows beyond them re-read the
+  // last valid row, so that nothing is fetched out of bounds and the LDS tile holds finite values
+  // everywhere (the kernels mask those rows / columns out).
+  struct Pending { const bf16_t* src; unsigned base; unsigned voff[RPW]; };
+  // tile starting at row `row0` of a tensor with `N` rows (row0 < N)
   template <bool RAGGED>
   DEVI Pending prepare(const char* tile, const bf16_t* tensor, int row0, int N) const {
-    typedef __attribute__((address_space(3))) const char lds_char;
     Pending p;
-    p.src = wave_uniform(tensor + (size_t)row0 * sn);
-    p.base = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long)((lds_char*)tile) + lds_wave);
-    p.valid = RAGGED ? N - row0 : 64;
+    p.src = wave_uniform(tensor + (size_t)row0 * sn + col0 * 32);
+    p.base = __builtin_amdgcn_readfirstlane((unsigned)lds_address(tile)) + lds_wave;
+#pragma unroll
+    for (int g = 0; g < RPW; ++g) {
+      const int rr = row + 16 * g;
+      p.voff[g] = (unsigned)((RAGGED ? min(rr, N - 1 - row0) : rr) * (2 * sn) + chunk);
+    }
     return p;
   }
   // instruction i (0 .. NI-1) of the prepared transfer
-  template <bool RAGGED>
-  DEVI void issue(const Pending& p, int tid, int i) const {
-    unsigned vo = voff[i];
-    if (RAGGED && p.valid < 64) {
-      const int wave = tid >> 6, lane = tid & 63;
-      const int row = (wave * NI + i) * RPI + lane / CH;
-      const int c = src_chunk(lane % CH, row);
-      const int rc = row < p.valid ? row : p.valid - 1;
-      vo = (unsigned)(rc * sn + c * 8) * 2u;
-    }
+  DEVI void issue(const Pending& p, int i) const {
+    const int g = i / CPW, c = (i % CPW) * WPR;  // row block and column block, relative to the wave's first
+    if (NCB % WPR != 0 && col0 + c >= NCB) return;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
-                 : "s"(p.base + (unsigned)(i * RPI * DL * 2)), "v"(vo), "s"(p.src)
+                 : "s"(p.base + (unsigned)(g * kRowBlockBytes<D> + c * 1024)), "v"(p.voff[g]), "s"(p.src + c * 32)
                  : "m0");
   }
-  // tile: LDS address of the destination tile; src: first row of the 64-row source tile (wave-uniform)
-  DEVI void load(const char* tile, const bf16_t* src) const {
-    typedef __attribute__((address_space(3))) const char lds_char;
-    const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long)((lds_char*)tile) + lds_wave);
+  // the whole transfer at once
+  template <bool RAGGED>
+  DEVI void load_rows(const char* tile, const bf16_t* tensor, int row0, int N) const {
+    const Pending p = prepare<RAGGED>(tile, tensor, row0, N);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :
-                   : "s"(base + (unsigned)(i * RPI * DL * 2)), "v"(voff[i]), "s"(src)
-                   : "m0");
-    }
+    for (int i = 0; i < NI; ++i) issue(p, i);
   }
 };
 

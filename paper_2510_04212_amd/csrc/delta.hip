@@ -15,7 +15,7 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const void* __restrict_
                                                          int N, Layout lay) {
   const bf16_t* O = static_cast<const bf16_t*>(Ov);
   const float* Of = static_cast<const float*>(Ov);
-  constexpr int LPR = kLdsD<D> / 8;      // lanes per row (a power of two; D = 96: lanes 12..15 of a row idle)
+  constexpr int LPR = kPow2D<D> / 8;      // lanes per row (a power of two; D = 96: lanes 12..15 of a row idle)
   constexpr int RPB = 256 / LPR;         // rows per block per step
   const int sub = threadIdx.x % LPR;
   const int rib = threadIdx.x / LPR;

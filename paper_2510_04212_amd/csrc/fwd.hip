@@ -65,11 +65,11 @@ constexpr int kRowStats = 3, kFixedNorm = 2;
 // keep room for on issuing LDS fragment reads ahead of their matrix instructions.
 template <int D, bool CAUSAL, int VARIANT, bool RAGGED, bool EXTRAS>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, kLdsD<D> == 128 ? 2 : (D > 128 ? 1 : 8)))) void attn_fwd_kernel(
+__attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 : (D > 128 ? 1 : 8)))) void attn_fwd_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, int N, float alpha, float beta, float eps,
     FwdExtras ex, Layout lay, int pairs, BlockOrder ord) {
-  constexpr int TILE_BYTES = kBc * kLdsD<D> * 2;
+  constexpr int TILE_BYTES = kBc * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   // layout: K buffers [2][TILE_BYTES], then V buffers [2][TILE_BYTES]
 
@@ -103,8 +103,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, kLdsD<D> == 128 ? 2 : (D > 
   TileLoader<D> loader;
   loader.init(tid, sn);
   FragOffsets<D> fo;
-  init_frag_offsets<D>(fo, lane);
-  frag_offsets_add_base<D>(fo, lds_address(smem));
+  init_frag_offsets<D>(fo, lane, lds_address(smem));
   const float c2 = alpha * kLog2e;
   // Alg. 3's test  r_m - alpha*s <= eps  in terms of the raw score s:  s >= (r_m - eps) / alpha
   const float inv_alpha = 1.0f / alpha;
@@ -123,8 +122,8 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, kLdsD<D> == 128 ? 2 : (D > 
   // keys [0, kend) can matter to this block
   const int kend = !CAUSAL ? NK : !RAGGED ? q0 + kBr : max(0, min(NK, q0 + kBr + shift));
   const int ntiles = RAGGED ? (kend + kBc - 1) / kBc : kend / kBc;
-  loader.template load_rows<RAGGED>(smem, Kh, 0, NK, tid);
-  if (VARIANT != kRowStats) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, 0, NK, tid);
+  loader.template load_rows<RAGGED>(smem, Kh, 0, NK);
+  if (VARIANT != kRowStats) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, 0, NK);
 
   // Q_i^T fragments: lane (r,h) holds Q[qw + r][16kc + 8h .. +7] for every kc.
   bf16x8 qf[D / 16];
@@ -168,8 +167,8 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, kLdsD<D> == 128 ? 2 : (D > 
     const auto pendK = loader.template prepare<RAGGED>(smem + (BUF ^ 1) * TILE_BYTES, Kh, jn * kBc, NK);
     const auto pendV = loader.template prepare<RAGGED>(smem + (2 + (BUF ^ 1)) * TILE_BYTES, Vh, jn * kBc, NK);
     auto issue_part = [&](int i) {
-      if (i < NLD) loader.template issue<RAGGED>(pendK, tid, i);
-      else if (i < 2 * NLD && VARIANT != kRowStats) loader.template issue<RAGGED>(pendV, tid, i - NLD);
+      if (i < NLD) loader.issue(pendK, i);
+      else if (i < 2 * NLD && VARIANT != kRowStats) loader.issue(pendV, i - NLD);
     };
     bool issued = false;
     const int k0 = j * kBc;
@@ -451,7 +450,7 @@ template <int D, bool CAUSAL, int VARIANT, bool RAGGED, bool EXTRAS>
 static hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
                              int BH, int N, float alpha, float beta, float eps, FwdExtras ex,
                              Layout lay, hipStream_t st) {
-  constexpr int smem = 4 * kBc * kLdsD<D> * 2;
+  constexpr int smem = 4 * kBc * D * 2;
   static std::atomic<bool> attr_set{false};   // (calls from several host threads may race to set it: harmless, the call is idempotent)
   auto kern = attn_fwd_kernel<D, CAUSAL, VARIANT, RAGGED, EXTRAS>;
   if (!attr_set.load(std::memory_order_acquire)) {

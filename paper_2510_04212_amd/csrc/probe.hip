@@ -68,14 +68,18 @@ __global__ __launch_bounds__(256, 1) void lds_probe_kernel(long long* __restrict
     }
   } else {
     typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    // the access pattern of the kernels' transposing reads on a 128-column tile: 16 lanes cover
-    // 4 rows x 32 bytes, the four 16-lane groups of a wave four different 4-row bands
+    // transposing reads of a tile stored as 256-byte rows (128 columns): 16 lanes cover 4 rows x 32
+    // bytes, the four 16-lane groups of a wave four different 4-row bands, 16-byte chunks permuted
+    // over the row so that no bank is hit twice.  (The kernels' own tiles are laid out in blocks of
+    // 64-byte rows, common.hpp, where the instruction takes 3.1 clocks instead of the 4 seen here.)
     // (16 different addresses per pass: identical ones would be merged by the compiler)
-    const int i = lane & 15;
+    const int i = lane & 15, row = 4 * (lane >> 4) + (i >> 2);
     const char* base[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-      base[c] = lds + tile_off<128>(4 * (lane >> 4) + (i >> 2), 32 * c + ((i & 3) << 2));
+    for (int c = 0; c < 4; ++c) {
+      const int chunk = 4 * c + ((i & 3) >> 1);
+      base[c] = lds + row * 256 + ((chunk ^ (((row & 3) << 2) | ((row >> 2) & 3))) << 4) + ((i & 1) << 3);
+    }
     for (int it = 0; it < iters; ++it) {
       s16x4 t[16];
 #pragma unroll
