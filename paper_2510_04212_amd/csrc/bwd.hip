@@ -4,8 +4,8 @@
 //   attn_bwd_dkdv_kernel  one work-group per (batch, head, 128-key block) -- under the causal mask
 //                         per pair of mirrored blocks, one after the other, unless the grid is
 //                         small (then one block each, in a balanced order); K_j / V_j fragments
-//                         stay in registers, query tiles (Q_i, dO_i, L_i, delta_i; 64 rows) stream
-//                         through LDS.  Per tile:  S = Q_i K_j^T,  P = exp(S - L),  dP = dO_i V_j^T,
+//                         stay in registers (V_j in LDS at D = 128), query tiles (Q_i, dO_i, L_i,
+//                         delta_i; 64 rows, 32 at D = 128) stream through LDS.  Per tile:  S = Q_i K_j^T,  P = exp(S - L),  dP = dO_i V_j^T,
 //                         dS = P o (dP - delta),  dV_j^T += dO_i^T P,  dK_j^T += Q_i^T dS.
 //   attn_bwd_dq_kernel    one work-group per (batch, head, 128-query block); Q_i / dO_i fragments,
 //                         L_i and delta_i stay in registers, key tiles (K_j, V_j; 64 rows) stream
@@ -28,7 +28,6 @@
 namespace {
 
 constexpr int kKeysPerWG = 128;   // dK/dV kernel: keys per work-group (32 per wave)
-constexpr int kQTile = 64;        // dK/dV kernel: query rows per streamed tile
 constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per wave)
 constexpr int kKTile = 64;        // dQ kernel: key rows per streamed tile
 
@@ -50,31 +49,61 @@ DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, in
 // Kept out of the ordinary kernel so that its tile loop has a fixed head and no bookkeeping.
 // At D = 256 the two accumulator sets of a full key block would not fit the register file next
 // to the K / V fragments: a work-group then owns 128 of the 256 columns of dK and dV (kDSplit
-// work-groups per key block, each recomputing S and dP), and the four-phase pipeline, whose
-// phases assume as many update as score instructions, is not used.
+// work-groups per key block, each recomputing S and dP).
 template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
+// The kernel wants two waves on every SIMD: one wave alone leaves the matrix cores idle whenever
+// any of its instructions waits.  That means at most 256 registers per lane.  At D = 128 the
+// accumulators (128) and the K fragments (32) leave no room for the V fragments: V_j is kept in LDS
+// for the whole block (8 more fragment reads per 32 queries to 48) and the query tiles shrink to 32
+// rows per wave group, so that two work-groups fit a CU.  Measured against one wave per SIMD with
+// 430 registers and a hand-made four-phase pipeline (us, bit-identical): B4 H32 N4096 d128 causal
+// 1043 -> 990, B4 H16 N2048 d128 full 281 -> 234, B4 H16 N1999 d128 causal 157 -> 132 and full
+// 602 -> 235 (that one spilled), B4 H16 N4096 d96 causal 484 -> 369.  At D = 256 (one wave per SIMD all
+// the same) the single code path for masked and unmasked blocks alone took 140 -> 109.
+template <int D> constexpr bool kVInLds = D == 128;
+template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
+// G: wave groups of 4 waves.  G = 2 (512 threads) is for grids that give a CU only one work-group:
+// the groups share the work-group's keys and take alternate 32-query blocks, each into accumulators
+// of its own, which are added through LDS at the end.
+template <int D, int G> constexpr int kQTile = D == 128 ? 32 * G : 64;   // query rows per streamed tile
+// D <= 64 has the registers for both 32-query blocks of a tile at once in a software pipeline.
+template <int D, int G> constexpr bool kPipelined = D <= 64 && G == 1;
 // dK / dV rows leave through a per-wave LDS staging area (store_rows_staged) where the row width
-// allows it and LDS has room for it next to the tiles (not at D = 256).
+// allows it; it overlays the tile buffers where it would otherwise cost a resident work-group, and
+// is left out at D = 256 (no room).
 template <int D> constexpr bool kStagedDkDv = kCanStage<D / 32 / kDSplit<D>> && D <= 128;
+template <int D, int G> constexpr bool kStageOverTiles = D == 128 || G > 1;
+// LDS: V_j (kVInLds), Q buffers [2], dO buffers [2], L [2][kQTile], delta [2][kQTile], staging.  With two
+// wave groups the start of the array serves the exchange of partial sums (and the staging) at the end.
+template <int D> constexpr int kVBytes = kVInLds<D> ? kKeysPerWG * D * 2 : 0;
+template <int D, int G> constexpr int kTilesEnd = kVBytes<D> + 4 * kQTile<D, G> * D * 2 + 4 * kQTile<D, G> * 4;
+template <int D> constexpr int kStageBytes = kStagedDkDv<D> ? 4 * 32 * kStagePitch<D / 32 / kDSplit<D>> : 0;
+template <int D, int G> constexpr int kExchangeBytes = G > 1 ? 2 * 4 * (D / 32) * 4096 : 0;
+constexpr int max_int(int a, int b) { return a > b ? a : b; }
+template <int D, int G> constexpr int kSmemDkDv =
+    G > 1 ? max_int(kTilesEnd<D, G>, kExchangeBytes<D, G>)
+          : kStageOverTiles<D, G> ? max_int(kTilesEnd<D, G>, kVBytes<D> + kStageBytes<D>) : kTilesEnd<D, G> + kStageBytes<D>;
 
-template <int D, bool CAUSAL, bool RAGGED, bool GROUPED>
-__global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
+template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G>
+__global__ __launch_bounds__(256 * G)
+__attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void attn_bwd_dkdv_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int N, float alpha, Layout lay, int pairs,
     BlockOrder ord) {
-  constexpr int TILE_BYTES = kQTile * D * 2;
+  constexpr int QT = kQTile<D, G>;
+  constexpr int TILE_BYTES = QT * D * 2;
+  constexpr int T0 = kVBytes<D>;                       // the tile buffers follow V_j
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  // layout: Q buffers [2][TILE_BYTES], dO buffers [2][TILE_BYTES], L2 [2][64] float, delta [2][64] float
-  char* ldsQ = smem;
-  char* ldsdO = smem + 2 * TILE_BYTES;
-  float* ldsL = reinterpret_cast<float*>(smem + 4 * TILE_BYTES);
-  float* ldsD = ldsL + 2 * kQTile;
-  // behind them: one staging area per wave for the output rows (store_rows_staged)
+  char* ldsQ = smem + T0;
+  char* ldsdO = ldsQ + 2 * TILE_BYTES;
+  float* ldsL = reinterpret_cast<float*>(smem + T0 + 4 * TILE_BYTES);
+  float* ldsD = ldsL + 2 * QT;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = (tid >> 6) & 3;                     // which 32 keys
+  const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;   // which 32-query blocks
   const int r = lane & 31, h = lane >> 5;
 
   // RAGGED: the bounds-checking instantiation: N queries and NK keys, neither need be a multiple
@@ -105,26 +134,40 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
   const float c2 = alpha * kLog2e;
   FragOffsets<D> fo;
   init_frag_offsets<D>(fo, lane, lds_address(smem));
-  // transposing reads of the update products address column block db0 + db
-  FragOffsets<D> fo_upd = fo;
-  if (DS > 1) { fo_upd.col[0] += 1024 * db0; fo_upd.col[1] += 1024 * db0; }
-  TileLoader<D> loader;
+  FragOffsets<D> fo_v = fo;                            // V_j fragments of this wave's keys
+  FragOffsets<D> fo_upd = fo;                          // update products: columns from block db0 on
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    if (kVInLds<D>) fo_v.row[p] += 2 * wave * kRowBlockBytes<D>;
+    if (DS > 1) fo_upd.col[p] += 1024 * db0;
+    if (G > 1) {                                       // group 1 reads the second 32 rows of a tile
+      fo.row[p] += 2 * grp * kRowBlockBytes<D>;
+      fo_upd.col[p] += 2 * grp * kRowBlockBytes<D>;
+    }
+  }
+  TileLoader<D, QT, 4 * G> loader;
   loader.init(tid, sn);
 
   for (int part = 0; part < (CAUSAL ? 2 : 1); ++part) {
     const int kt = (part == 0) ? kt_first : nkt - 1 - kt_first;
     if (part == 1 && (!pairs || kt == kt_first)) break;   // no partner: one block per work-group, or the middle one of an odd number
+    if (kStageOverTiles<D, G> && part > 0) __syncthreads();   // the first block's staging is done with the tile buffers
     const int k0 = kt * kKeysPerWG;
     const int kw = k0 + 32 * wave;
 
+    if constexpr (kVInLds<D>) {
+      TileLoader<D, kKeysPerWG, 4 * G> v_loader;
+      v_loader.init(tid, sn);
+      v_loader.template load_rows<RAGGED>(smem, V + head_off, k0, NK);
+    }
     // K_j^T / V_j^T fragments (B operands): lane (r,h) holds K[kw + r][16kc + 8h .. +7]
     // (keys past the sequence end read the last row; their gradients are not stored)
     const int keyc = (RAGGED && kw + r >= NK) ? NK - 1 : kw + r;
-    bf16x8 kf[D / 16], vf[D / 16];
+    bf16x8 kf[D / 16], vf[kVInLds<D> ? 1 : D / 16];
 #pragma unroll
     for (int kc = 0; kc < D / 16; ++kc) {
       kf[kc] = *reinterpret_cast<const bf16x8*>(K + head_off + (size_t)keyc * sn + 16 * kc + 8 * h);
-      vf[kc] = *reinterpret_cast<const bf16x8*>(V + head_off + (size_t)keyc * sn + 16 * kc + 8 * h);
+      if constexpr (!kVInLds<D>) vf[kc] = *reinterpret_cast<const bf16x8*>(V + head_off + (size_t)keyc * sn + 16 * kc + 8 * h);
     }
     f32x16 dVt[NDB], dKt[NDB];
 #pragma unroll
@@ -133,8 +176,8 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
       for (int i = 0; i < 16; ++i) { dVt[db][i] = 0.f; dKt[db][i] = 0.f; }
 
     // first query tile that sees any key of this block
-    const int t0 = !CAUSAL ? 0 : !RAGGED ? k0 / kQTile : max(0, k0 - shift) / kQTile;
-    const int nt = RAGGED ? (N + kQTile - 1) / kQTile : N / kQTile;
+    const int t0 = !CAUSAL ? 0 : !RAGGED ? k0 / QT : max(0, k0 - shift) / QT;
+    const int nt = RAGGED ? (N + QT - 1) / QT : N / QT;
     if (RAGGED && t0 >= nt) {                        // no query sees these keys (more keys than queries reach): zero gradients
       if (kw + r < NK) {
         store_acc_T<NDB>(dV + 32 * db0 + head_off + (size_t)(kw + r) * sn, dVt, 1.0f, h);
@@ -156,27 +199,32 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
     const float* Dh = delta + (size_t)bq0 * N;
     const int total = group * (nt - t0);
     auto load_stats = [&](const float* Lp, const float* Dp, int t) {
-      const int row = t * kQTile + (tid & (kQTile - 1));
+      const int row = t * QT + (tid & (QT - 1));
       const int rowc = (RAGGED && row >= N) ? N - 1 : row;
-      if (tid < kQTile) {
+      if (tid < QT) {
         sreg = Lp[rowc];
-      } else if (tid < 2 * kQTile) sreg = Dp[rowc];
+      } else if (tid < 2 * QT) sreg = Dp[rowc];
       // (The loaded values are not touched before store_stats: any arithmetic on them here would
       // make the wave wait, at the start of the tile, for these loads and for the tile transfer
       // issued just before them.)
     };
     auto store_stats = [&](int buf) {
-      if (tid < kQTile) {
+      if (tid < QT) {
         float l = sreg * kLog2e;
         if (RAGGED && l == -INFINITY) l = 0.f;         // a query that sees no key: all its scores are masked below
-        ldsL[buf * kQTile + tid] = l;
-      } else if (tid < 2 * kQTile) ldsD[buf * kQTile + tid - kQTile] = -sreg;   // LDS holds -delta
+        ldsL[buf * QT + tid] = l;
+      } else if (tid < 2 * QT) ldsD[buf * QT + tid - QT] = -sreg;   // LDS holds -delta
     };
-    loader.template load_rows<RAGGED>(ldsQ, Qh, t0 * kQTile, N);
-    loader.template load_rows<RAGGED>(ldsdO, dOh, t0 * kQTile, N);
+    loader.template load_rows<RAGGED>(ldsQ, Qh, t0 * QT, N);
+    loader.template load_rows<RAGGED>(ldsdO, dOh, t0 * QT, N);
     load_stats(Lh, Dh, t0);
     store_stats(0);
     wait_vmem();
+#pragma unroll
+    for (int kc = 0; kc < D / 16; ++kc) {
+      settle(kf[kc]);
+      if constexpr (!kVInLds<D>) settle(vf[kc]);
+    }
     __syncthreads();
 
     // One query tile; BUF (which LDS buffer holds it) is a compile-time constant so that every LDS
@@ -185,45 +233,56 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
       constexpr int buf = decltype(buf_c)::value;
       const bool has_next = (step + 1 < total);
       // The next tile (after the last one: this tile once more, harmlessly) goes into the other
-      // buffer.  On the pipelined path its transfer instructions are issued one per two slots of
-      // the first phase instead of in one burst behind the barrier.
+      // buffer.  Its transfer instructions are issued between the matrix instructions of the first
+      // score products instead of in one burst behind the barrier.
       int tn = has_next ? t + 1 : t;
       if (GROUPED && has_next && t + 1 == nt) {   // on to the next query head of the group
         Qh += lay.sh; dOh += lay.sh; Lh += N; Dh += N;
         tn = t0;
       }
-      constexpr int NLD = TileLoader<D>::NI;
-      const auto pendQ = loader.template prepare<RAGGED>(ldsQ + (buf ^ 1) * TILE_BYTES, Qh, tn * kQTile, N);
-      const auto pendD = loader.template prepare<RAGGED>(ldsdO + (buf ^ 1) * TILE_BYTES, dOh, tn * kQTile, N);
+      constexpr int NLD = decltype(loader)::NI;
+      const auto pendQ = loader.template prepare<RAGGED>(ldsQ + (buf ^ 1) * TILE_BYTES, Qh, tn * QT, N);
+      const auto pendD = loader.template prepare<RAGGED>(ldsdO + (buf ^ 1) * TILE_BYTES, dOh, tn * QT, N);
       auto issue_part = [&](int i) {
         if (i < NLD) loader.issue(pendQ, i);
         else if (i < 2 * NLD) loader.issue(pendD, i - NLD);
       };
+      bool issued = false;
       if (has_next) load_stats(Lh, Dh, tn);
-      constexpr int tQ = buf * TILE_BYTES;          // byte offsets of this tile's Q and dO in smem
-      constexpr int tdO = (2 + buf) * TILE_BYTES;
-      const float* tL = reinterpret_cast<const float*>(smem + 4 * TILE_BYTES) + buf * kQTile;
-      const float* tD = reinterpret_cast<const float*>(smem + 4 * TILE_BYTES) + 2 * kQTile + buf * kQTile;
-      const int qt0 = t * kQTile;
-      // one 32-query block against this wave's 32 keys; DIAG: the block crosses the diagonal
-      auto qblock = [&](auto diag_c, int qb) {
-        constexpr bool DIAG = decltype(diag_c)::value;
-        const int qb0 = qt0 + 32 * qb;
+      constexpr int tQ = T0 + buf * TILE_BYTES;     // byte offsets of this tile's Q and dO in smem
+      constexpr int tdO = T0 + (2 + buf) * TILE_BYTES;
+      const float* tL = ldsL + buf * QT;
+      const float* tD = ldsD + buf * QT;
+      const int qt0 = t * QT;
+      // One 32-query block against this wave's 32 keys (one code path: the block that crosses the
+      // diagonal only adds a masking step).  The group's first block of a tile also issues the
+      // next tile's transfer.  qb is a compile-time constant except for the group's offset, which is
+      // part of the base addresses.
+      auto qblock = [&](int qb) {
+        const int qb0 = qt0 + 32 * (qb + grp);
         const bool tail = RAGGED && qb0 + 32 > N;              // some query rows lie past the sequence end
         // ---- S = Q_i K_j^T and dP = dO_i V_j^T (Alg. 2 steps 8, 11); rows = queries, lane = key
         f32x16 s, dp;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + 32 * qb + 8 * g + 4 * h);
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + 32 * (qb + grp) + 8 * g + 4 * h);
 #pragma unroll
           for (int e = 0; e < 4; ++e) { s[4 * g + e] = 0.f; dp[4 * g + e] = d4[e]; }
         }
 #pragma unroll
         for (int kc = 0; kc < D / 16; ++kc) {
           s = mfma32(lds_row8<D>(tQ, fo, 32 * qb, kc), kf[kc], s);
-          dp = mfma32(lds_row8<D>(tdO, fo, 32 * qb, kc), vf[kc], dp);
+          if constexpr (kVInLds<D>) dp = mfma32(lds_row8<D>(tdO, fo, 32 * qb, kc), lds_row8<D>(0, fo_v, 0, kc), dp);
+          else dp = mfma32(lds_row8<D>(tdO, fo, 32 * qb, kc), vf[kc], dp);
+          if (qb == 0) issue_part(kc);
         }
-        sched_reads_ahead_of_mfma<D / 8, 1, 4>();
+        if (qb == 0) {
+#pragma unroll
+          for (int i = D / 16; i < 2 * NLD; ++i) issue_part(i);
+          issued = true;
+        }
+        if constexpr (kVInLds<D>) sched_3_reads_per_2_mfma<D / 16, 8>();
+        else sched_reads_ahead_of_mfma<D / 8, 1, 8>();
         // element i of this lane is query qb0 + 4h + c with c = 8 (i / 4) + i % 4 a compile-time constant
         if (tail) {   // rows past the sequence end: P = exp(-inf) = 0, so they add nothing to dK, dV
           const int lim = N - qb0 - 4 * h;
@@ -233,21 +292,24 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
         }
         // ---- P = exp(S - L) (step 9), dS = P o (dP - delta) (step 12)
         bf16x8 pf[2], dsf[2];
-        const int first_seen = kw + r - shift - qb0 - 4 * h;   // DIAG: queries with c below it do not see this lane's key
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(tL + 32 * qb + 8 * g + 4 * h);
+          const f32x4 l4 = *reinterpret_cast<const f32x4*>(tL + 32 * (qb + grp) + 8 * g + 4 * h);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int i = 4 * g + e;
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c2, -l4[e]));
-            float ds = p * dp[i];                     // dp already holds dP - delta
-            if (DIAG) {   // a masked entry contributes exactly nothing, whatever its row holds
-              if (8 * g + e < first_seen) { p = 0.f; ds = 0.f; }
-            }
-            pf[i >> 3][i & 7] = (bf16_t)p;
-            dsf[i >> 3][i & 7] = (bf16_t)ds;
-          }
+          for (int e = 0; e < 4; ++e) s[4 * g + e] = __builtin_fmaf(s[4 * g + e], c2, -l4[e]);
+        }
+        if (CAUSAL && qb0 + shift < kw + 31) {
+          // the block crosses the diagonal: a masked entry contributes exactly nothing, whatever its row holds
+          const int first_seen = kw + r - shift - qb0 - 4 * h;   // queries with c below it do not see this lane's key
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (8 * (i >> 2) + (i & 3) < first_seen) { s[i] = -INFINITY; dp[i] = 0.f; }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float p = __builtin_amdgcn_exp2f(s[i]);
+          pf[i >> 3][i & 7] = (bf16_t)p;
+          dsf[i >> 3][i & 7] = (bf16_t)(p * dp[i]);     // dp already holds dP - delta
         }
         // ---- dV_j^T += dO_i^T P ,  dK_j^T += Q_i^T dS  (steps 10, 14)
 #pragma unroll
@@ -355,18 +417,19 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
           __builtin_amdgcn_sched_barrier(0);
         }
       };
-      if (DS == 1 && (!CAUSAL || qt0 + shift >= kw + 31) && (!RAGGED || qt0 + kQTile <= N)) {
-        tile_pipelined();
+      if (kPipelined<D, G> && (!CAUSAL || qt0 + shift >= kw + 31) && (!RAGGED || qt0 + QT <= N)) {
+        if constexpr (kPipelined<D, G>) tile_pipelined();
       } else {
 #pragma unroll
-        for (int i = 0; i < 2 * NLD; ++i) issue_part(i);
-#pragma unroll
-        for (int qb = 0; qb < kQTile / 32; ++qb) {
-          const int qb0 = qt0 + 32 * qb;
+        for (int qb = 0; qb < QT / 32 / G; ++qb) {
+          const int qb0 = qt0 + 32 * (qb + grp);
           if (CAUSAL && qb0 + shift + 31 < kw) continue;   // no query of the block sees a key of the wave
           if (RAGGED && qb0 >= N) continue;                    // nothing but padding
-          if (CAUSAL && qb0 + shift < kw + 31) qblock(std::true_type{}, qb);
-          else qblock(std::false_type{}, qb);
+          qblock(qb);
+        }
+        if (!issued) {    // a wave that skipped the group's first block still has its share of the transfer to issue
+#pragma unroll
+          for (int i = 0; i < 2 * NLD; ++i) issue_part(i);
         }
       }
       if (has_next) store_stats(buf ^ 1);
@@ -389,17 +452,56 @@ __global__ __launch_bounds__(256, D <= 64 ? 2 : 1) void attn_bwd_dkdv_kernel(
         }
       }
     }
-    if constexpr (kStagedDkDv<D>) {
-      char* stage = smem + 4 * TILE_BYTES + 4 * kQTile * (int)sizeof(float);
-      const int rows_valid = RAGGED ? NK - kw : 32;
-      auto rounded = [&](const f32x16 (&acc)[NDB], float scale) {
-        return [&acc, scale](int db, int g) {
-          bf16x4 o4;
+    const int rows_valid = RAGGED ? NK - kw : 32;
+    auto rounded = [&](const f32x16 (&acc)[NDB], float scale) {
+      return [&acc, scale](int db, int g) {
+        bf16x4 o4;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(acc[db][4 * g + e] * scale);
-          return o4;
-        };
+        for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(acc[db][4 * g + e] * scale);
+        return o4;
       };
+    };
+    if constexpr (G > 1) {
+      // The groups add their partial sums: group 1 hands over its dV, group 0 its dK, each through an
+      // area of its own per wave (16 bytes per lane, lanes consecutive), and group 0 finishes dV,
+      // group 1 dK.  Every wave is past the last tile's barrier: the whole array is free.
+      // (the lane index passes through an empty asm: addresses formed from the kernel's own copy would
+      // be hoisted above the tile loop and held in registers through it)
+      constexpr int AREA = NDB * 4096;
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      char* give = smem + (grp * 4 + wave) * AREA;
+      char* take = smem + ((grp ^ 1) * 4 + wave) * AREA;
+      auto put = [&](const f32x16 (&acc)[NDB]) {
+#pragma unroll
+        for (int i = 0; i < 4 * NDB; ++i) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = acc[i >> 2][4 * (i & 3) + e];
+          *reinterpret_cast<f32x4*>(give + (i * 64 + ln) * 16) = v;
+        }
+      };
+      auto add = [&](f32x16 (&acc)[NDB]) {
+#pragma unroll
+        for (int i = 0; i < 4 * NDB; ++i) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(take + (i * 64 + ln) * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[i >> 2][4 * (i & 3) + e] += v[e];
+        }
+      };
+      // one output per group; the wave's `take` area, read out by then, serves as its staging area
+      auto finish = [&](f32x16 (&acc)[NDB], float scale, bf16_t* out) {
+        add(acc);
+        if constexpr (kStagedDkDv<D>)
+          store_rows_staged<NDB>(take, rounded(acc, scale), out + head_off + (size_t)kw * sn, sn, rows_valid, ln);
+        else if (!RAGGED || kw + r < NK)
+          store_acc_T<NDB>(out + head_off + (size_t)(kw + r) * sn, acc, scale, h);
+      };
+      if (grp == 0) put(dKt); else put(dVt);
+      __syncthreads();
+      if (grp == 0) finish(dVt, 1.0f, dV); else finish(dKt, alpha, dK);
+    } else if constexpr (kStagedDkDv<D>) {
+      char* stage = smem + T0 + (kStageOverTiles<D, G> ? 0 : 4 * TILE_BYTES + 4 * QT * (int)sizeof(float));
       store_rows_staged<NDB>(stage, rounded(dVt, 1.0f), dV + 32 * db0 + head_off + (size_t)kw * sn, sn, rows_valid, tid);
       store_rows_staged<NDB>(stage, rounded(dKt, alpha), dK + 32 * db0 + head_off + (size_t)kw * sn, sn, rows_valid, tid);
     } else if (!RAGGED || kw + r < NK) {
@@ -652,15 +754,13 @@ static hipError_t set_smem(KernT kern, int smem, std::atomic<bool>& done) {
   return e;
 }
 
-template <int D, bool CAUSAL, bool RAGGED, bool GROUPED>
-static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const void* dO,
-                              const float* LSE, const float* delta, void* dK, void* dV, int BH,
-                              int N, float alpha, Layout lay, hipStream_t st) {
-  constexpr int NDB = D / 32 / kDSplit<D>;
-  constexpr int smem = 4 * kQTile * D * 2 + 4 * kQTile * (int)sizeof(float) +
-                       (kStagedDkDv<D> ? 4 * 32 * kStagePitch<NDB> : 0);
+template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G>
+static hipError_t launch_dkdv_g(const void* Q, const void* K, const void* V, const void* dO,
+                                const float* LSE, const float* delta, void* dK, void* dV, int BH,
+                                int N, float alpha, Layout lay, hipStream_t st) {
+  constexpr int smem = kSmemDkDv<D, G>;
   static std::atomic<bool> set{false};
-  auto k = attn_bwd_dkdv_kernel<D, CAUSAL, RAGGED, GROUPED>;
+  auto k = attn_bwd_dkdv_kernel<D, CAUSAL, RAGGED, GROUPED, G>;
   hipError_t e;
   if ((e = set_smem(k, smem, set)) != hipSuccess) return e;
   const int nkt = ((RAGGED ? lay.Nk : N) + kKeysPerWG - 1) / kKeysPerWG;
@@ -671,14 +771,34 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
   static thread_local OrderCache cache;
   const BlockOrder* ord = &kNoOrder;
   if (CAUSAL && kDSplit<D> == 1) {
-    const int res = resident_per_cu(k, smem, resident);
+    const int res = resident_per_cu(k, smem, resident, 256 * G);
     ord = &small_grid_order(cache, (BH / lay.group) * nkt, nkt, res, 3LL * kNumCUs * res / 2);
   }
   const int pairs = (CAUSAL && ord->n == 0) ? 1 : 0;
-  hipLaunchKernelGGL(k, dim3((BH / lay.group) * (pairs ? (nkt + 1) / 2 : nkt) * kDSplit<D>), dim3(256), smem, st, (const bf16_t*)Q,
+  hipLaunchKernelGGL(k, dim3((BH / lay.group) * (pairs ? (nkt + 1) / 2 : nkt) * kDSplit<D>), dim3(256 * G), smem, st, (const bf16_t*)Q,
                      (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, LSE, delta,
                      (bf16_t*)dK, (bf16_t*)dV, N, alpha, lay, pairs, *ord);
   return hipGetLastError();
+}
+
+template <int D, bool CAUSAL, bool RAGGED, bool GROUPED>
+static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const void* dO,
+                              const float* LSE, const float* delta, void* dK, void* dV, int BH,
+                              int N, float alpha, Layout lay, hipStream_t st) {
+  // Two wave groups where one-group work-groups would leave the SIMDs with a single wave each: up to
+  // one block per CU; up to two under the causal mask at D >= 96, where the blocks differ in work
+  // and the CU with the heaviest one decides (D = 64 fits two work-groups with 64-row tiles and a
+  // pipeline on a CU and gains nothing there).  Short sequences do not pay for the final exchange.
+  // Measured, one group -> two (us): B1 H1 N16384 d128 causal 582 -> 376, B2 H8 N2048 d128 causal
+  // 77 -> 55, B4 H8 the same 88 -> 73, B2 H16 N2048 d96 61 -> 58, B1 H4 N3000 d64 54 -> 50; beyond the
+  // limits: B3 H8 N2048 d128 full 104 -> 112, B4 H12 N1024 d64 causal 23.0 -> 24.3, N = 128 5.4 -> 6.5.
+  if constexpr (D <= 128) {
+    const int NK = RAGGED ? lay.Nk : N;      // (the rule looks at the keys only: a chunk of queries gets the sums of the square problem)
+    const long long blocks = (long long)(BH / lay.group) * ((NK + kKeysPerWG - 1) / kKeysPerWG);
+    if (blocks <= (CAUSAL && D >= 96 ? 2 : 1) * kNumCUs && NK >= 512)
+      return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 2>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+  }
+  return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
 }
 
 template <int D, bool CAUSAL, bool RAGGED, int MODE>

@@ -147,8 +147,7 @@ DEVI size_t head_base_kv(const Layout& lay, int bh) {
 // (global_load_lds_dwordx4: no registers are involved; completion is tracked by vmcnt).
 // One wave-instruction moves 64 x 16 bytes to LDS base + 16*lane, i.e. one macro block of the layout
 // above: 16 rows x 64 bytes.  The chunk permutation is applied on the GLOBAL side: the lane that
-// lands in slot s of row r fetches chunk s ^ (r >> 2) of that row.  256 threads (4 waves) share a
-// tile; a wave stays inside its own 16-row block(s), so that one per-lane offset (per row block) serves
+// lands in slot s of row r fetches chunk s ^ (r >> 2) of that row.  NW waves share a tile; a wave stays inside its own 16-row block(s), so that one per-lane offset (per row block) serves
 // all its instructions and only the scalar base moves along the columns.
 // The caller must execute wait_vmem() and a barrier before any wave reads the tile.
 //
@@ -167,11 +166,12 @@ DEVI const bf16_t* wave_uniform(const bf16_t* p) {
   return reinterpret_cast<const bf16_t*>(((unsigned long long)hi << 32) | lo);
 }
 
-template <int D, int R = 64> struct TileLoader {
+template <int D, int R = 64, int NW = 4> struct TileLoader {
   static_assert(R == 32 || R == 64 || R == 128, "rows per tile");
+  static constexpr int NRB = R / 16;             // 16-row blocks
   static constexpr int NCB = kColBlocks<D>;
-  static constexpr int WPR = R >= 64 ? 1 : 2;    // waves that share a 16-row block ...
-  static constexpr int RPW = R >= 64 ? R / 64 : 1;   // ... or row blocks per wave
+  static constexpr int WPR = NW > NRB ? NW / NRB : 1;    // waves that share a 16-row block ...
+  static constexpr int RPW = NRB > NW ? NRB / NW : 1;    // ... or row blocks per wave
   static constexpr int CPW = (NCB + WPR - 1) / WPR;  // column blocks per wave and row block
   static constexpr int NI = RPW * CPW;           // instructions per wave
   static constexpr int kBytes = R * D * 2;
@@ -319,6 +319,21 @@ template <int N, int PER, int AHEAD_> DEVI void sched_reads_ahead_of_mfma() {
   for (int i = 0; i < AHEAD; ++i) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
 }
 
+// As above for STEPS steps of two matrix instructions that take three LDS fragment reads between
+// them (one has both operands in LDS): reads are issued AHEAD (even) matrix instructions early.
+template <int STEPS, int AHEAD> DEVI void sched_3_reads_per_2_mfma() {
+  __builtin_amdgcn_sched_group_barrier(0x100, 3 * AHEAD / 2, 0);
+#pragma unroll
+  for (int i = 0; i < STEPS - AHEAD / 2; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+}
+
 // Work-group index remap: consecutive hardware work-group ids go round-robin over the 8 XCDs
 // (each with its own L2).  Give every XCD a contiguous range of logical ids so that the
 // work-groups sharing one head's K/V run on the same L2.  Only applied when the grid is a
@@ -353,13 +368,13 @@ DEVI int small_grid_rotation(int bh, int nblk, int grid, int capacity) {
 // ---- host side of the order table --------------------------------------------------------------
 constexpr int kNumCUs = 256;
 
-// Work-groups of `kern` (256 threads, `smem` bytes of dynamic LDS) that a compute unit holds at
+// Work-groups of `kern` (`threads` threads, `smem` bytes of dynamic LDS) that a compute unit holds at
 // once; asked of the runtime once per kernel instantiation.
 template <class KernT>
-static int resident_per_cu(KernT kern, int smem, std::atomic<int>& cached) {
+static int resident_per_cu(KernT kern, int smem, std::atomic<int>& cached, int threads = 256) {
   int r = cached.load(std::memory_order_relaxed);
   if (r == 0) {
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, reinterpret_cast<const void*>(kern), 256, smem) != hipSuccess || r <= 0) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, reinterpret_cast<const void*>(kern), threads, smem) != hipSuccess || r <= 0) {
       (void)hipGetLastError();   // the answer only steers the block order: not an error of the launch that follows
       r = 1;
     }
