@@ -286,6 +286,26 @@ int attn_bwd_rect(const void* Q, const void* K, const void* V, const void* O, co
                   int B, int H, int Nq, int Nk, int d, int causal, float softmax_scale, int variant,
                   void* stream);
 
+/*
+ * The forward with a workspace, for grids of few query blocks (few heads, or a chunk of queries
+ * against a long context): there the key tiles of a block are shared out to several work-groups,
+ * whose float32 partial sums pass through the workspace and are joined by a second kernel.  Same
+ * algorithms, rounding points, checks and error codes as attn_fwd_ex / _strided / _gqa / _rect; only
+ * the order of the float32 sums over key tiles differs.
+ *   attn_fwd_workspace_bytes  the bytes attn_fwd_ws needs for this problem; 0: nothing is gained (or
+ *                        the shape is unsupported) and attn_fwd_ws runs the ordinary kernel.
+ *   workspace            16-byte aligned, free for reuse once the stream has passed the call; NULL:
+ *                        the ordinary kernel.  Too small: ATTN_ERR_WORKSPACE.
+ *   stride_*             0: contiguous layouts; otherwise as in attn_fwd_strided (H_kv == H, Nq == Nk).
+ *   H_kv                 key/value heads (H for ordinary attention)
+ */
+size_t attn_fwd_workspace_bytes(int B, int H, int Nq, int Nk, int d, int causal, int variant);
+int attn_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE,
+                void* workspace, size_t workspace_bytes,
+                long long stride_b, long long stride_h, long long stride_n,
+                int B, int H, int H_kv, int Nq, int Nk, int d, int causal, float softmax_scale,
+                int variant, float beta, float eps, void* stream);
+
 /* Human-readable name of an attn_status (static storage, never NULL). */
 const char* attn_status_string(int status);
 

@@ -51,6 +51,10 @@ _lib.attn_fwd_rect.argtypes = [_vp] * 5 + [_i, _i, _i, _i, _i, _i, _f, _i, _f, _
 _lib.attn_fwd_rect.restype = _i
 _lib.attn_bwd_rect.argtypes = [_vp] * 9 + [_vp, _sz, _i, _i, _i, _i, _i, _i, _f, _i, _vp]
 _lib.attn_bwd_rect.restype = _i
+_lib.attn_fwd_ws.argtypes = [_vp] * 6 + [_sz, _ll, _ll, _ll] + [_i] * 7 + [_f, _i, _f, _f, _vp]
+_lib.attn_fwd_ws.restype = _i
+_lib.attn_fwd_workspace_bytes.argtypes = [_i] * 7
+_lib.attn_fwd_workspace_bytes.restype = _sz
 _lib.attn_bwd.argtypes = [_vp] * 9 + [_vp, _sz, _i, _i, _i, _i, _i, _f, _i, _vp]
 _lib.attn_bwd.restype = _i
 _lib.attn_bwd_noalloc.argtypes = [_vp] * 9 + [_i, _i, _i, _i, _i, _f, _i, _vp]
@@ -78,7 +82,7 @@ EXPORTS = ["attn_fwd", "attn_fwd_ex", "attn_fwd_opt", "attn_delta", "attn_delta_
            "attn_delta_recompute", "attn_bwd", "attn_bwd_noalloc", "attn_bwd_noalloc_max_rows",
            "attn_bwd_dkdv", "attn_bwd_dq", "attn_bwd_dq_delta", "attn_fwd_strided", "attn_bwd_strided",
            "attn_fwd_gqa", "attn_bwd_gqa", "attn_fwd_rect", "attn_bwd_rect",
-           "attn_bwd_workspace_bytes",
+           "attn_bwd_workspace_bytes", "attn_fwd_ws", "attn_fwd_workspace_bytes",
            "attn_status_string", "attn_fwd_key_tile"]
 
 
@@ -126,6 +130,25 @@ def _bhnd(t, name):
     return t.shape
 
 
+def _fwd_shared_out(Q, K, V, O, LSE, strides, H_kv, Nk, causal, softmax_scale, variant, beta, eps, stream):
+    """attn_fwd_ws of the C ABI where the library wants a workspace for this problem (grids of few
+    query blocks); False, and nothing done, otherwise."""
+    B, H, N, d = Q.shape
+    need = _lib.attn_fwd_workspace_bytes(B, H, N, Nk, d, int(bool(causal)), int(variant))
+    if need == 0:
+        return False
+    if stream is not None and stream != torch.cuda.current_stream():
+        with torch.cuda.stream(stream):          # the workspace belongs to the stream that uses it
+            ws = torch.empty(need, dtype=torch.uint8, device=Q.device)
+    else:
+        ws = torch.empty(need, dtype=torch.uint8, device=Q.device)
+    _check(_lib.attn_fwd_ws(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(ws), need, *strides, B, H, H_kv,
+                            N, Nk, d, int(bool(causal)), float(softmax_scale), int(variant),
+                            float(DEFAULT_BETA if beta is None else beta),
+                            float(DEFAULT_EPS if eps is None else eps), _stream(stream)))
+    return True
+
+
 def attn_fwd(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=None,
              O=None, LSE=None, stream=None):
     """O, LSE = attention forward (attn_fwd / attn_fwd_ex of the C ABI)."""
@@ -137,6 +160,8 @@ def attn_fwd(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=No
         O = torch.empty_like(Q)
     if LSE is None:
         LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
+    if _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), H, N, causal, softmax_scale, variant, beta, eps, stream):
+        return O, LSE
     if beta is None and eps is None:
         st = _lib.attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), B, H, N, d, int(bool(causal)),
                            float(softmax_scale), int(variant), _stream(stream))
@@ -301,6 +326,8 @@ def attn_fwd_strided(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None
     _strided_bhnd(O, "O", Q)
     if LSE is None:
         LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
+    if _fwd_shared_out(Q, K, V, O, LSE, (sb, sh, sn), H, N, causal, softmax_scale, variant, beta, eps, stream):
+        return O, LSE
     _check(_lib.attn_fwd_strided(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), sb, sh, sn, B, H, N, d,
                                  int(bool(causal)), float(softmax_scale), int(variant),
                                  float(DEFAULT_BETA if beta is None else beta),
@@ -338,6 +365,8 @@ def attn_fwd_gqa(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, ep
         raise ValueError("K and V must be [B,H_kv,N,d] with the batch, length and head size of Q")
     O = torch.empty_like(Q)
     LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
+    if _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), Hkv, N, causal, softmax_scale, variant, beta, eps, stream):
+        return O, LSE
     _check(_lib.attn_fwd_gqa(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), B, H, Hkv, N, d,
                              int(bool(causal)), float(softmax_scale), int(variant),
                              float(DEFAULT_BETA if beta is None else beta),
@@ -373,6 +402,8 @@ def attn_fwd_rect(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, e
         raise ValueError("K and V must be [B,H,Nk,d] with the batch, heads and head size of Q")
     O = torch.empty_like(Q)
     LSE = torch.empty((B, H, Nq), dtype=torch.float32, device=Q.device)
+    if _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), H, Nk, causal, softmax_scale, variant, beta, eps, stream):
+        return O, LSE
     _check(_lib.attn_fwd_rect(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), B, H, Nq, Nk, d,
                               int(bool(causal)), float(softmax_scale), int(variant),
                               float(DEFAULT_BETA if beta is None else beta),

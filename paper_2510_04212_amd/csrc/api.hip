@@ -19,6 +19,10 @@ struct Layout {
 hipError_t attn_fwd_dispatch(const void*, const void*, const void*, void*, float*, int, int, int,
                              int, float, int, float, float, float*, int*, int*, int, Layout,
                              hipStream_t);
+int attn_fwd_splits(int, int, int, int, int, int);
+size_t attn_fwd_part_bytes(int, int, int, int);
+hipError_t attn_fwd_split_dispatch(const void*, const void*, const void*, void*, float*, int, int, int,
+                                   int, float, int, float, float, Layout, float*, int, hipStream_t);
 hipError_t attn_delta_dispatch(const void*, const void*, float*, long, int, int, int, Layout,
                                hipStream_t);
 hipError_t attn_bwd_dkdv_dispatch(const void*, const void*, const void*, const void*, const float*,
@@ -82,7 +86,7 @@ static int fwd_entry(const void* Q, const void* K, const void* V, void* O, float
                      float* O_hp, int* ones_count, int* fired_count,
                      int B, int H, int N, int d, int causal, float softmax_scale,
                      int variant, float beta, float eps, unsigned flags, const Layout* user_lay,
-                     void* stream) {
+                     void* stream, void* workspace = nullptr, size_t workspace_bytes = 0) {
   bool empty;
   if (flags & ~(unsigned)(ATTN_FWD_SINGLE_ROUNDING | ATTN_FWD_PV_E4M3 | ATTN_FWD_GUARD_UNDERFLOW)) return ATTN_ERR_BAD_ARG;
   int st = check_shape(B, H, N, d, &empty);
@@ -102,11 +106,18 @@ static int fwd_entry(const void* Q, const void* K, const void* V, void* O, float
   if (O_hp && (O_hp == Q || O_hp == K || O_hp == V || O_hp == O)) return ATTN_ERR_BAD_ARG;
   if (ones_count && ones_count == fired_count) return ATTN_ERR_BAD_ARG;
   const Layout lay = user_lay ? *user_lay : contiguous(H, N, d);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const int splits = workspace ? attn_fwd_splits(B * H, N, lay.Nk, d, causal, variant) : 1;
+  if (splits > 1) {
+    if (workspace_bytes < attn_fwd_part_bytes(B * H, N, d, splits) || !aligned16(workspace)) return ATTN_ERR_WORKSPACE;
+    hipError_t e = attn_fwd_split_dispatch(Q, K, V, O, LSE, B * H, N, d, causal, softmax_scale, variant, beta,
+                                           eps, lay, static_cast<float*>(workspace), splits, s);
+    return e == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
+  }
   hipError_t e = attn_fwd_dispatch(Q, K, V, O, LSE, B * H, N, d, causal, softmax_scale, variant,
                                    beta, eps, O_hp, ones_count, fired_count,
                                    ((flags & ATTN_FWD_SINGLE_ROUNDING) ? 1 : 0) | ((flags & ATTN_FWD_PV_E4M3) ? 2 : 0) |
-                                       ((flags & ATTN_FWD_GUARD_UNDERFLOW) ? 4 : 0), lay,
-                                   static_cast<hipStream_t>(stream));
+                                       ((flags & ATTN_FWD_GUARD_UNDERFLOW) ? 4 : 0), lay, s);
   return e == hipSuccess ? ATTN_OK : ATTN_ERR_LAUNCH;
 }
 
@@ -414,4 +425,28 @@ extern "C" int attn_bwd_rect(const void* Q, const void* K, const void* V, const 
   const Layout lay = (B > 0 && H > 0) ? contiguous(H, Nq, d, 0, Nk) : contiguous(1, 1, d);
   return bwd_entry(Q, K, V, O, dO, LSE, dQ, dK, dV, workspace, workspace_bytes, B, H, Nq, d, causal,
                    softmax_scale, variant, &lay, stream);
+}
+
+extern "C" size_t attn_fwd_workspace_bytes(int B, int H, int Nq, int Nk, int d, int causal, int variant) {
+  bool empty;
+  if (check_rect(B, H, Nq, Nk, d) != ATTN_OK || check_shape(B, H, Nq, d, &empty) != ATTN_OK || empty) return 0;
+  const int splits = attn_fwd_splits(B * H, Nq, Nk, d, causal, variant);
+  return splits > 1 ? attn_fwd_part_bytes(B * H, Nq, d, splits) : 0;
+}
+
+extern "C" int attn_fwd_ws(const void* Q, const void* K, const void* V, void* O, float* LSE,
+                           void* workspace, size_t workspace_bytes, long long stride_b, long long stride_h,
+                           long long stride_n, int B, int H, int H_kv, int Nq, int Nk, int d, int causal,
+                           float softmax_scale, int variant, float beta, float eps, void* stream) {
+  if (H_kv < 0) return ATTN_ERR_BAD_ARG;
+  int st = check_rect(B, H, Nq, Nk, d);
+  if (st != ATTN_OK) return st;
+  if (B > 0 && H > 0 && !gqa_heads_ok(H, H_kv)) return ATTN_ERR_BAD_ARG;
+  Layout lay = (B > 0 && H > 0) ? contiguous(H, Nq, d, H_kv, Nk) : contiguous(1, 1, d);
+  if (stride_n != 0) {
+    if (H_kv != H || Nq != Nk || !strides_ok(stride_b, stride_h, stride_n, d)) return ATTN_ERR_BAD_ARG;
+    lay = Layout{stride_b, stride_h, (int)stride_n, H, stride_b, stride_h, 1, Nk};
+  }
+  return fwd_entry(Q, K, V, O, LSE, nullptr, nullptr, nullptr, B, H, Nq, d, causal, softmax_scale,
+                   variant, beta, eps, 0u, &lay, stream, workspace, workspace_bytes);
 }

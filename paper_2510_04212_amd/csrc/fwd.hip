@@ -60,15 +60,30 @@ DEVI long pack_e4m3(const float (&v)[8]) {
 //               maximum, no accumulator rescale), LSE[] then receives m + log l as usual.
 constexpr int kRowStats = 3, kFixedNorm = 2;
 
+// ---- sharing a block's key tiles out to several work-groups (SPLIT below)
+constexpr int kMinShare = 4;          // tiles: below, a share's start-up costs more than it takes off
+// shares of a block of `tiles` key tiles when the grid has `splits` work-groups per block
+__host__ DEVI int split_shares(int tiles, int splits) {
+  const int most = tiles / kMinShare;
+  return most < 1 ? 1 : most < splits ? most : splits;
+}
+// floats a wave leaves per share: its 32 x D accumulator, 32 normalisers, 32 row sums
+template <int D> constexpr int kPartFloats = 32 * D + 64;
+
 // Waves per SIMD are stated as a range, not only as a minimum: at D = 128 two work-groups fit a
 // CU (LDS), and told so the compiler spends the registers of the third wave it would otherwise
 // keep room for on issuing LDS fragment reads ahead of their matrix instructions.
-template <int D, bool CAUSAL, int VARIANT, bool RAGGED, bool EXTRAS>
+//
+// SPLIT: grids of so few query blocks that most of the chip would idle (few heads, a chunk of queries
+// against a long context).  The key tiles of a block are shared out to `splits` work-groups; each
+// leaves its float32 accumulator, normaliser and row sum in `part` and attn_fwd_merge_kernel
+// joins them.
+template <int D, bool CAUSAL, int VARIANT, bool RAGGED, bool EXTRAS, bool SPLIT = false>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 : (D > 128 ? 1 : 8)))) void attn_fwd_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, int N, float alpha, float beta, float eps,
-    FwdExtras ex, Layout lay, int pairs, BlockOrder ord) {
+    FwdExtras ex, Layout lay, int pairs, float* __restrict__ part, int splits, BlockOrder ord) {
   constexpr int TILE_BYTES = kBc * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   // layout: K buffers [2][TILE_BYTES], then V buffers [2][TILE_BYTES]
@@ -90,7 +105,9 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   // end of the grid, and half as many work-groups have to start and drain.  pairs == 0: one
   // block per work-group, for causal grids in the order the table `ord` gives (or, where the
   // table does not apply, heavy blocks first with a per-lap rotation on small grids).
-  const int wg = logical_wg(ord, blockIdx.x, gridDim.x);
+  const int wg_all = logical_wg(ord, blockIdx.x, gridDim.x);
+  const int split = SPLIT ? wg_all % splits : 0;        // neighbours share a block (and its Q)
+  const int wg = SPLIT ? wg_all / splits : wg_all;
   const int npw = pairs ? (nqt + 1) / 2 : nqt;          // work-groups per head
   const int bh = wg / npw;
   const int idx = wg % npw;
@@ -108,22 +125,26 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   // Alg. 3's test  r_m - alpha*s <= eps  in terms of the raw score s:  s >= (r_m - eps) / alpha
   const float inv_alpha = 1.0f / alpha;
 
-  for (int part = 0; part < (pairs ? 2 : 1); ++part) {
-  if (part > 0) __syncthreads();                      // the first block's output staging is done with the tile buffers
+  for (int half = 0; half < (pairs ? 2 : 1); ++half) {
+  if (half > 0) __syncthreads();                      // the first block's output staging is done with the tile buffers
   // heavy (late) query blocks first under the causal mask
-  const int qt = pairs ? (part == 0 ? nqt - 1 - idx : idx)
-                       : nqt - 1 - (idx + (CAUSAL && ord.n == 0 ? small_grid_rotation(bh, nqt, gridDim.x, D == 128 ? 768 : 1536) : 0)) % nqt;
-  if (part == 1 && qt == nqt - 1 - idx) break;        // odd number of blocks: the middle one has no partner
+  const int qt = pairs ? (half == 0 ? nqt - 1 - idx : idx)
+                       : nqt - 1 - (idx + (CAUSAL && !SPLIT && ord.n == 0 ? small_grid_rotation(bh, nqt, gridDim.x, D == 128 ? 768 : 1536) : 0)) % nqt;
+  if (half == 1 && qt == nqt - 1 - idx) break;        // odd number of blocks: the middle one has no partner
   const int q0 = qt * kBr;
   const int qw = q0 + 32 * wave;                 // first query row of this wave
   const int q = qw + r;
   const int qc = (RAGGED && q >= N) ? N - 1 : q;   // row actually read for this lane
 
-  // keys [0, kend) can matter to this block
+  // keys [0, kend) can matter to this block; its tiles, or this work-group's share of them
   const int kend = !CAUSAL ? NK : !RAGGED ? q0 + kBr : max(0, min(NK, q0 + kBr + shift));
-  const int ntiles = RAGGED ? (kend + kBc - 1) / kBc : kend / kBc;
-  loader.template load_rows<RAGGED>(smem, Kh, 0, NK);
-  if (VARIANT != kRowStats) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, 0, NK);
+  const int all_tiles = RAGGED ? (kend + kBc - 1) / kBc : kend / kBc;
+  const int shares = SPLIT ? split_shares(all_tiles, splits) : 1;
+  if (SPLIT && split >= shares) return;          // the block is too short for all of them
+  const int tile0 = SPLIT ? all_tiles * split / shares : 0;
+  const int ntiles = SPLIT ? all_tiles * (split + 1) / shares : all_tiles;
+  loader.template load_rows<RAGGED>(smem, Kh, tile0 * kBc, NK);
+  if (VARIANT != kRowStats) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, tile0 * kBc, NK);
 
   // Q_i^T fragments: lane (r,h) holds Q[qw + r][16kc + 8h .. +7] for every kc.
   bf16x8 qf[D / 16];
@@ -302,7 +323,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
               }
             }
           lsum = lsum * corr + psum8;
-          if (VARIANT != kFixedNorm && j > 0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+          if (VARIANT != kFixedNorm && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -342,7 +363,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
         lsum = lsum * corr + psum;
         // ---- O^T <- diag(corr) O^T + V_j^T P-bar^T (Alg. 1 step 8); in the first tile the
         // accumulator is still zero (corr = exp(-inf) = 0 there), nothing to rescale
-        if (VARIANT != kFixedNorm && j > 0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+        if (VARIANT != kFixedNorm && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
           for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -366,11 +387,30 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
     __syncthreads();
   };
 
-  for (int j = 0; j < ntiles; j += 2) {
+  for (int j = tile0; j < ntiles; j += 2) {
     tile_step(std::integral_constant<int, 0>{}, j);
     if (j + 1 < ntiles) tile_step(std::integral_constant<int, 1>{}, j + 1);
   }
 
+  if constexpr (SPLIT) {
+    // the share's results, as the registers hold them (16 bytes per lane, lanes consecutive)
+    const float l_share = sum_with_partner32(lsum);
+    if (qw < N) {
+      const size_t slot = ((size_t)bh * ((N + 31) / 32) + qw / 32) * splits + split;
+      float* p = part + slot * kPartFloats<D>;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = acc[db][4 * g + e];
+          *reinterpret_cast<f32x4*>(p + ((db * 4 + g) * 64 + lane) * 4) = v;
+        }
+      p[32 * D + lane] = h == 0 ? m : l_share;
+    }
+    return;
+  }
   if (VARIANT == kRowStats) {
     // merge the two lanes of a row, then the rule of Sec. 4 on the whole row
     const float o1 = partner32(top1), o2 = partner32(top2);
@@ -442,6 +482,62 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   }   // part
 }
 
+// Joins the shares of the SPLIT forward: one wave per 32 rows x 32 columns.  The normaliser of a row
+// is the largest of its shares' (every share's is the largest its tiles asked for, so this is what
+// one sequential pass ends with), accumulators and row sums are brought to it in float32, and
+// the roundings of the ordinary epilogue follow.  Streams the shares once (HBM / Infinity Cache
+// bound).
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256) void attn_fwd_merge_kernel(
+    const float* __restrict__ part, bf16_t* __restrict__ O, float* __restrict__ LSE, int BH, int N,
+    Layout lay, int splits) {
+  constexpr int NDB = D / 32;
+  const int lane = threadIdx.x & 63;
+  const int r = lane & 31, h = lane >> 5;
+  const int nrb = (N + 31) / 32;
+  const long long id = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (id >= (long long)BH * nrb * NDB) return;
+  const int db = (int)(id % NDB);
+  const int rows = (int)(id / NDB);                  // 32-row block: head and place in it
+  const int bh = rows / nrb, qw = rows % nrb * 32;
+  const int shift = lay.Nk - N;
+  const int kend = !CAUSAL ? lay.Nk : max(0, min(lay.Nk, qw / kBr * kBr + kBr + shift));
+  const int shares = split_shares((kend + kBc - 1) / kBc, splits);
+  const float* p = part + (size_t)rows * splits * kPartFloats<D>;
+  float m = -INFINITY;
+  for (int s = 0; s < shares; ++s) m = fmaxf(m, p[(size_t)s * kPartFloats<D> + 32 * D + r]);
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  float l = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < shares; ++s) {
+    const float* ps = p + (size_t)s * kPartFloats<D>;
+    const float ms = ps[32 * D + r], ls = ps[32 * D + 32 + r];
+    // a share whose tiles the row does not see has normaliser -inf and adds nothing
+    const float w = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ms - m) * kLog2e);
+    l += m == -INFINITY ? ls : w * ls;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(ps + ((db * 4 + g) * 64 + lane) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[4 * g + e] = __builtin_fmaf(w, v[e], acc[4 * g + e]);
+    }
+  }
+  if (qw + r >= N) return;
+  const bool unseen_row = m == -INFINITY && l == 0.f;      // no visible key: O = 0, LSE = -inf
+  const Divisor by_l = make_divisor(l);
+  bf16_t* Oq = O + head_base(lay, bh) + (size_t)(qw + r) * lay.sn + 32 * db + 4 * h;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    bf16x4 o4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(unseen_row ? 0.f : divide((float)(bf16_t)acc[4 * g + e], by_l));
+    *reinterpret_cast<bf16x4*>(Oq + 8 * g) = o4;
+  }
+  if (db == 0 && h == 0) LSE[(size_t)bh * N + qw + r] = m + __logf(l);
+}
+
 }  // namespace
 
 extern "C" int attn_fwd_key_tile(int d) { return (d == 32 || d == 64 || d == 96 || d == 128 || d == 256) ? kBc : 0; }
@@ -473,8 +569,69 @@ static hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* 
   const BlockOrder& ord = (CAUSAL && !pairs)
       ? small_grid_order(cache, (int)grid.x, nqt, resident_per_cu(kern, smem, resident), 8 * kMaxOrder) : kNoOrder;
   hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, (const bf16_t*)Q, (const bf16_t*)K,
-                     (const bf16_t*)V, (bf16_t*)O, LSE, N, alpha, beta, eps, ex, lay, pairs, ord);
+                     (const bf16_t*)V, (bf16_t*)O, LSE, N, alpha, beta, eps, ex, lay, pairs,
+                     (float*)nullptr, 1, ord);
   return hipGetLastError();
+}
+
+template <int D, bool CAUSAL, int VARIANT>
+static hipError_t launch_fwd_split(const void* Q, const void* K, const void* V, void* O, float* LSE,
+                                   int BH, int N, float alpha, float beta, float eps, Layout lay,
+                                   float* part, int splits, hipStream_t st) {
+  constexpr int smem = 4 * kBc * D * 2;
+  static std::atomic<bool> attr_set{false};
+  auto kern = attn_fwd_kernel<D, CAUSAL, VARIANT, true, false, true>;
+  if (!attr_set.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    attr_set.store(true, std::memory_order_release);
+  }
+  const int nqt = (N + kBr - 1) / kBr;
+  hipLaunchKernelGGL(kern, dim3(BH * nqt * splits), dim3(256), smem, st, (const bf16_t*)Q, (const bf16_t*)K,
+                     (const bf16_t*)V, (bf16_t*)O, LSE, N, alpha, beta, eps, FwdExtras{}, lay, 0, part,
+                     splits, kNoOrder);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int waves = BH * ((N + 31) / 32) * (D / 32);
+  hipLaunchKernelGGL((attn_fwd_merge_kernel<D, CAUSAL>), dim3((waves + 3) / 4), dim3(256), 0, st, part,
+                     (bf16_t*)O, LSE, BH, N, lay, splits);
+  return hipGetLastError();
+}
+
+// Work-groups per query block of the SPLIT forward; 1: the ordinary kernel.
+// The chip is filled once (256 work-groups); twice under the causal mask when blocks differ in work.
+// Shares pay from 1024 keys on (16 tiles), and from 2048 where half of the chip has a block already:
+// a tile takes a lone work-group about 1 us, merging costs 5 us.  Measured, one work-group per block -> shares
+// (us, launches included; B*H, Nq x Nk): 32, 64 x 8192 d128 158 -> 36 (twice the shares: 39), 32, 1 x 8192
+// d128 152 -> 35, 8, 1 x 16384 298 -> 36, 16, 256 x 4096 83 -> 28, 8, 2048 x 2048 causal d128 45 -> 31
+// (once the chip: 36), 1, 16384 x 16384 causal 294 -> 142, 4, 2048 x 2048 full d256 84 -> 41; beyond
+// the limits: 16, 1024 x 1024 d64 causal 19.6 -> 22.5, 16, 2048 x 2048 d128 causal 45 -> 45.
+int attn_fwd_splits(int BH, int Nq, int Nk, int d, int causal, int variant) {
+  const long long blocks = (long long)BH * ((Nq + kBr - 1) / kBr);
+  if (variant == 2 || Nk < 1024 || 2 * blocks > (Nk < 2048 ? kNumCUs / 2 : kNumCUs)) return 1;
+  const long long s = (causal && 2LL * Nq > Nk ? 2 : 1) * kNumCUs / blocks;
+  return split_shares((Nk + kBc - 1) / kBc, s < 32 ? (int)s : 32);
+}
+
+size_t attn_fwd_part_bytes(int BH, int Nq, int d, int splits) {
+  return (size_t)BH * ((Nq + 31) / 32) * splits * (32 * d + 64) * sizeof(float);
+}
+
+hipError_t attn_fwd_split_dispatch(const void* Q, const void* K, const void* V, void* O, float* LSE,
+                                   int BH, int N, int d, int causal, float alpha, int variant,
+                                   float beta, float eps, Layout lay, float* part, int splits,
+                                   hipStream_t st) {
+#define CASE(DD, CC, VV)                                  \
+  if (d == DD && (causal != 0) == CC && variant == VV)    \
+    return launch_fwd_split<DD, CC, VV>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, lay, part, splits, st);
+  CASE(32, false, 0) CASE(32, false, 1) CASE(32, true, 0) CASE(32, true, 1)
+  CASE(64, false, 0) CASE(64, false, 1) CASE(64, true, 0) CASE(64, true, 1)
+  CASE(128, false, 0) CASE(128, false, 1) CASE(128, true, 0) CASE(128, true, 1)
+  CASE(256, false, 0) CASE(256, false, 1) CASE(256, true, 0) CASE(256, true, 1)
+  CASE(96, false, 0) CASE(96, false, 1) CASE(96, true, 0) CASE(96, true, 1)
+#undef CASE
+  return hipErrorInvalidValue;
 }
 
 // Host-side dispatch used by the C ABI (api.hip).  Shapes are validated by the caller.

@@ -38,3 +38,36 @@ def test_grouped_queries_with_two_wave_groups(lib, N, d):
         want = per.double().view(B, Hkv, H // Hkv, N, d).sum(2)
         # each addend was rounded to bf16 (half an ulp, 2^-9 of its size), so was the result
         assert ((got.double() - want).norm() / want.norm()).item() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Nq,Nk", [(1, 1024), (33, 1090), (64, 4097), (1024, 1024), (1100, 1500), (1500, 1030)])
+def test_forward_shared_out_over_key_tiles(lib, Nq, Nk, d, causal):
+    """Few query blocks and at least 1024 keys: shares of a block's key tiles, some of them without a
+    visible key, partial last tiles and blocks, rows that see no key at all."""
+    assert lib.raw().attn_fwd_workspace_bytes(1, 2, Nq, Nk, d, int(causal), 1) > 0
+    x = _inputs(5 * Nq + Nk + d, 1, 2, Nq, Nk, d, scale=1.25)
+    for variant in (0, 1):
+        got = _run(lib, x, causal, d ** -0.5, variant)
+        for h in range(2):
+            check_head(got, x, 0, h, causal, d ** -0.5, variant, label=f"shares {Nq}x{Nk} d{d} c{causal} v{variant}")
+
+
+def test_forward_shared_out_takes_strides_and_grouped_heads(lib):
+    """The same shares whatever the layout: strided views and grouped heads give the bits of the
+    contiguous call on repeated heads; a workspace that is too small is refused."""
+    B, H, Hkv, N, d = 1, 4, 2, 1200, 64
+    x = _inputs(9, B, H, N, N, d)
+    rep = lambda t: t[:, :Hkv].repeat_interleave(H // Hkv, 1).contiguous()
+    K, V = rep(x["K"]), rep(x["V"])
+    O, L = lib.attn_fwd(x["Q"], K, V, True, 0.125, 1)
+    Og, Lg = lib.attn_fwd_gqa(x["Q"], x["K"][:, :Hkv].contiguous(), x["V"][:, :Hkv].contiguous(), True, 0.125, 1)
+    s = lambda t: t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    Os, Ls = lib.attn_fwd_strided(s(x["Q"]), s(K), s(V), True, 0.125, 1)
+    for o, l in ((Og, Lg), (Os, Ls)):
+        assert torch.equal(o, O) and torch.equal(l, L)
+    p = lambda t: t.data_ptr()
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+    assert lib.raw().attn_fwd_ws(p(x["Q"]), p(K), p(V), p(O), p(L), p(ws), 256, 0, 0, 0, B, H, H, N, N, d, 1,
+                                 0.125, 1, 2.0, 1e-3, None) == 4
