@@ -2,7 +2,9 @@
 
 Argument marshalling only: the forward pass is attn_fwd / attn_fwd_strided and the backward
 pass attn_bwd / attn_bwd_strided of the library (Alg. 1 or Alg. 3 forward, Alg. 2 backward of
-arXiv 2510.04212); nothing is computed here.  q, k, v are bfloat16 CUDA tensors of logical
+arXiv 2510.04212); nothing is computed here.  Plain calls go to the same node in C++
+(csrc/autograd.cpp: short sequences are bound by the host); tensor subclasses, transforms, tracing and
+whatever the library refuses take the Python node below.  q, k, v are bfloat16 CUDA tensors of logical
 shape [B, H, N, d]; they may be contiguous or share any batch / head / row strides with a
 contiguous last dimension (for instance `x.view(B, N, H, d).permute(0, 2, 1, 3)`), in which case
 no copy is made.  k and v may have fewer heads than q (grouped-query attention), or a different
@@ -13,6 +15,12 @@ import math
 import torch
 
 from . import binding
+
+try:
+    from . import _autograd
+except ImportError as e:
+    raise ImportError("the autograd node is missing or does not fit this torch: build it with "
+                      "`python -m paper_2510_04212_amd.build`") from e
 
 
 def _same_layout(*ts):
@@ -66,6 +74,16 @@ class _FlashAttention(torch.autograd.Function):
         return dq, dk, dv, None, None, None, None, None
 
 
+_PLAIN_TYPES = (torch.Tensor, torch.nn.Parameter)
+
+
+def _untransformed():
+    """Nothing looks at the operators of this call: no tracing, compilation, function transform or
+    forward-mode level (those see the Python node, as it defines what they may do with it)."""
+    return (torch._C._get_tracing_state() is None and not torch._C._are_functorch_transforms_active()
+            and torch.autograd.forward_ad._current_level < 0 and not torch.compiler.is_compiling())
+
+
 def attention(q, k, v, causal=True, softmax_scale=None, variant=binding.MITIGATED, beta=None, eps=None):
     """softmax(softmax_scale * q k^T) v with gradients, on the HIP kernels.
 
@@ -74,4 +92,10 @@ def attention(q, k, v, causal=True, softmax_scale=None, variant=binding.MITIGATE
     softmax_scale defaults to 1/sqrt(d)."""
     if softmax_scale is None:
         softmax_scale = 1.0 / math.sqrt(q.shape[-1])
+    if type(q) in _PLAIN_TYPES and type(k) in _PLAIN_TYPES and type(v) in _PLAIN_TYPES and _untransformed():
+        o = _autograd.apply(q, k, v, bool(causal), float(softmax_scale), int(variant),
+                            binding.DEFAULT_BETA if beta is None else float(beta),
+                            binding.DEFAULT_EPS if eps is None else float(eps))
+        if o is not None:
+            return o
     return _FlashAttention.apply(q, k, v, bool(causal), float(softmax_scale), int(variant), beta, eps)

@@ -1,18 +1,21 @@
 """Builds the HIP library in-tree:  python -m paper_2510_04212_amd.build
 
-One hipcc invocation per source (gfx950 only).  Two libraries come out:
+One hipcc invocation per source (gfx950 only).  Three libraries come out:
   libattn_gfx950.so         the attention library (the C ABI of include/attn.h);
-  libattn_probe_gfx950.so   measurement aids that only the benchmark loads (csrc/probe.h).
+  libattn_probe_gfx950.so   measurement aids that only the benchmark loads (csrc/probe.h);
+  _autograd.so              the autograd node of attention() (host code, linked against the first).
 Packed-fp32 code generation is switched off for all device code.
 """
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattn_gfx950.so")
 PROBE_LIB = os.path.join(HERE, "libattn_probe_gfx950.so")
+NODE_LIB = os.path.join(HERE, "_autograd.so")
 SOURCES = ["api.hip", "fwd.hip", "delta.hip", "bwd.hip"]
 PROBE_SOURCES = ["probe.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -26,6 +29,19 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # one: measured 2-3 % on the dK/dV kernel at d = 128, nothing lost elsewhere.  The forward is
 # faster with the default strategy.
 EXTRA_FLAGS = {"bwd.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+
+
+def _node_command():
+    """One g++ call: csrc/autograd.cpp against torch's C++ interface."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+            + [a for p in (os.path.join(root, "include"), os.path.join(root, "include/torch/csrc/api/include"),
+                           sysconfig.get_paths()["include"], "/opt/rocm/include") for a in ("-isystem", p)]
+            + [os.path.join(CSRC, "autograd.cpp"), "-o", NODE_LIB, "-L" + HERE, "-l:" + os.path.basename(LIB),
+               "-Wl,-rpath,$ORIGIN", "-L" + os.path.join(root, "lib"),
+               "-ltorch_python", "-ltorch_cpu", "-ltorch_hip", "-lc10_hip", "-lc10"])
 
 
 def build(verbose=True):
@@ -53,6 +69,10 @@ def build(verbose=True):
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
+    cmd = _node_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
     return LIB
 
 
