@@ -1,7 +1,7 @@
 // Flash-attention backward for gfx950 (Alg. 2 of arXiv 2510.04212), as two kernels so that no
 // gradient needs a cross-work-group reduction (no atomics, deterministic):
 //
-//   attn_bwd_dkdv_kernel  one work-group per (batch, head, 128-key block) -- under the causal mask
+//   attn_bwd_dkdv_kernel  one work-group per (batch, head, 128-key block; 64 on small grids) -- under the causal mask
 //                         per pair of mirrored blocks, one after the other, unless the grid is
 //                         small (then one block each, in a balanced order); K_j / V_j fragments
 //                         stay in registers (V_j in LDS at D = 128), query tiles (Q_i, dO_i, L_i,
@@ -27,7 +27,7 @@
 
 namespace {
 
-constexpr int kKeysPerWG = 128;   // dK/dV kernel: keys per work-group (32 per wave)
+constexpr int kKeysPerWG = 128;   // dK/dV kernel: keys per work-group (32 per wave); 64 with four wave groups
 constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per wave)
 constexpr int kKTile = 64;        // dQ kernel: key rows per streamed tile
 
@@ -62,10 +62,13 @@ template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // the same) the single code path for masked and unmasked blocks alone took 140 -> 109.
 template <int D> constexpr bool kVInLds = D == 128;
 template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
-// G: wave groups of 4 waves.  G = 2 (512 threads) is for grids that give a CU only one work-group:
+// G: wave groups.  G = 2 (512 threads) is for grids that give a CU only one work-group:
 // the groups share the work-group's keys and take alternate 32-query blocks, each into accumulators
-// of its own, which are added through LDS at the end.
-template <int D, int G> constexpr int kQTile = D == 128 ? 32 * G : 64;   // query rows per streamed tile
+// of its own, which are added through LDS at the end.  G = 4 splits further: 64 keys (two waves) per
+// group, so that a grid has twice the work-groups of half the length; a query tile is then read
+// from L2 for half as many keys.
+template <int G> constexpr int kKeyWaves = G == 4 ? 2 : 4;               // waves per group, 32 keys each
+template <int D, int G> constexpr int kQTile = D == 128 || G == 4 ? 32 * G : 64;   // query rows per streamed tile
 // D <= 64 has the registers for both 32-query blocks of a tile at once in a software pipeline.
 template <int D, int G> constexpr bool kPipelined = D <= 64 && G == 1;
 // dK / dV rows leave through a per-wave LDS staging area (store_rows_staged) where the row width
@@ -75,17 +78,17 @@ template <int D> constexpr bool kStagedDkDv = kCanStage<D / 32 / kDSplit<D>> && 
 template <int D, int G> constexpr bool kStageOverTiles = D == 128 || G > 1;
 // LDS: V_j (kVInLds), Q buffers [2], dO buffers [2], L [2][kQTile], delta [2][kQTile], staging.  With two
 // wave groups the start of the array serves the exchange of partial sums (and the staging) at the end.
-template <int D> constexpr int kVBytes = kVInLds<D> ? kKeysPerWG * D * 2 : 0;
-template <int D, int G> constexpr int kTilesEnd = kVBytes<D> + 4 * kQTile<D, G> * D * 2 + 4 * kQTile<D, G> * 4;
+template <int D, int G> constexpr int kVBytes = kVInLds<D> ? 32 * kKeyWaves<G> * D * 2 : 0;
+template <int D, int G> constexpr int kTilesEnd = kVBytes<D, G> + 4 * kQTile<D, G> * D * 2 + 4 * kQTile<D, G> * 4;
 template <int D> constexpr int kStageBytes = kStagedDkDv<D> ? 4 * 32 * kStagePitch<D / 32 / kDSplit<D>> : 0;
 template <int D, int G> constexpr int kExchangeBytes = G > 1 ? 2 * 4 * (D / 32) * 4096 : 0;
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
 template <int D, int G> constexpr int kSmemDkDv =
     G > 1 ? max_int(kTilesEnd<D, G>, kExchangeBytes<D, G>)
-          : kStageOverTiles<D, G> ? max_int(kTilesEnd<D, G>, kVBytes<D> + kStageBytes<D>) : kTilesEnd<D, G> + kStageBytes<D>;
+          : kStageOverTiles<D, G> ? max_int(kTilesEnd<D, G>, kVBytes<D, G> + kStageBytes<D>) : kTilesEnd<D, G> + kStageBytes<D>;
 
 template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G>
-__global__ __launch_bounds__(256 * G)
+__global__ __launch_bounds__(64 * kKeyWaves<G> * G)
 __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void attn_bwd_dkdv_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
@@ -93,7 +96,8 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
     BlockOrder ord) {
   constexpr int QT = kQTile<D, G>;
   constexpr int TILE_BYTES = QT * D * 2;
-  constexpr int T0 = kVBytes<D>;                       // the tile buffers follow V_j
+  constexpr int T0 = kVBytes<D, G>;                    // the tile buffers follow V_j
+  constexpr int KW = kKeyWaves<G>, KEYS = 32 * KW;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* ldsQ = smem + T0;
   char* ldsdO = ldsQ + 2 * TILE_BYTES;
@@ -102,15 +106,15 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = (tid >> 6) & 3;                     // which 32 keys
-  const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;   // which 32-query blocks
+  const int wave = (tid >> 6) % KW;                    // which 32 keys
+  const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(tid / (64 * KW)) : 0;   // which 32-query blocks
   const int r = lane & 31, h = lane >> 5;
 
   // RAGGED: the bounds-checking instantiation: N queries and NK keys, neither need be a multiple
   // of the block; causal mask  key <= query + shift.
   const int NK = RAGGED ? lay.Nk : N;
   const int shift = RAGGED ? NK - N : 0;
-  const int nkt = (NK + kKeysPerWG - 1) / kKeysPerWG;
+  const int nkt = (NK + KEYS - 1) / KEYS;
   // Under the causal mask key block kt meets nkt - kt query blocks' worth of tiles.  pairs != 0: a
   // work-group takes block kt and then its mirror image nkt - 1 - kt, so that all work-groups
   // carry the same load (and there are half as many to start and drain).  pairs == 0 (grids so
@@ -140,23 +144,23 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
   for (int p = 0; p < 2; ++p) {
     if (kVInLds<D>) fo_v.row[p] += 2 * wave * kRowBlockBytes<D>;
     if (DS > 1) fo_upd.col[p] += 1024 * db0;
-    if (G > 1) {                                       // group 1 reads the second 32 rows of a tile
+    if (G > 1) {                                       // group g reads the g-th 32 rows of a tile
       fo.row[p] += 2 * grp * kRowBlockBytes<D>;
       fo_upd.col[p] += 2 * grp * kRowBlockBytes<D>;
     }
   }
-  TileLoader<D, QT, 4 * G> loader;
+  TileLoader<D, QT, KW * G> loader;
   loader.init(tid, sn);
 
   for (int part = 0; part < (CAUSAL ? 2 : 1); ++part) {
     const int kt = (part == 0) ? kt_first : nkt - 1 - kt_first;
     if (part == 1 && (!pairs || kt == kt_first)) break;   // no partner: one block per work-group, or the middle one of an odd number
     if (kStageOverTiles<D, G> && part > 0) __syncthreads();   // the first block's staging is done with the tile buffers
-    const int k0 = kt * kKeysPerWG;
+    const int k0 = kt * KEYS;
     const int kw = k0 + 32 * wave;
 
     if constexpr (kVInLds<D>) {
-      TileLoader<D, kKeysPerWG, 4 * G> v_loader;
+      TileLoader<D, KEYS, KW * G> v_loader;
       v_loader.init(tid, sn);
       v_loader.template load_rows<RAGGED>(smem, V + head_off, k0, NK);
     }
@@ -464,15 +468,14 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
     if constexpr (G > 1) {
       // The groups add their partial sums: group 1 hands over its dV, group 0 its dK, each through an
       // area of its own per wave (16 bytes per lane, lanes consecutive), and group 0 finishes dV,
-      // group 1 dK.  Every wave is past the last tile's barrier: the whole array is free.
+      // group 1 dK; before that groups 2 and 3 hand both over to groups 0 and 1.  Every wave is past
+      // the last tile's barrier: the whole array is free.
       // (the lane index passes through an empty asm: addresses formed from the kernel's own copy would
       // be hoisted above the tile loop and held in registers through it)
       constexpr int AREA = NDB * 4096;
       int ln = lane;
       asm volatile("" : "+v"(ln));
-      char* give = smem + (grp * 4 + wave) * AREA;
-      char* take = smem + ((grp ^ 1) * 4 + wave) * AREA;
-      auto put = [&](const f32x16 (&acc)[NDB]) {
+      auto put = [&](const f32x16 (&acc)[NDB], char* give) {
 #pragma unroll
         for (int i = 0; i < 4 * NDB; ++i) {
           f32x4 v;
@@ -481,7 +484,7 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
           *reinterpret_cast<f32x4*>(give + (i * 64 + ln) * 16) = v;
         }
       };
-      auto add = [&](f32x16 (&acc)[NDB]) {
+      auto add = [&](f32x16 (&acc)[NDB], const char* take) {
 #pragma unroll
         for (int i = 0; i < 4 * NDB; ++i) {
           const f32x4 v = *reinterpret_cast<const f32x4*>(take + (i * 64 + ln) * 16);
@@ -489,17 +492,26 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
           for (int e = 0; e < 4; ++e) acc[i >> 2][4 * (i & 3) + e] += v[e];
         }
       };
+      if constexpr (G == 4) {
+        char* area = smem + ((grp & 1) * KW + wave) * 2 * AREA;
+        if (grp >= 2) { put(dVt, area); put(dKt, area + AREA); }
+        __syncthreads();
+        if (grp < 2) { add(dVt, area); add(dKt, area + AREA); }
+        __syncthreads();
+      }
+      char* give = smem + (grp * KW + wave) * AREA;
+      char* take = smem + ((grp ^ 1) * KW + wave) * AREA;
       // one output per group; the wave's `take` area, read out by then, serves as its staging area
       auto finish = [&](f32x16 (&acc)[NDB], float scale, bf16_t* out) {
-        add(acc);
+        add(acc, take);
         if constexpr (kStagedDkDv<D>)
           store_rows_staged<NDB>(take, rounded(acc, scale), out + head_off + (size_t)kw * sn, sn, rows_valid, ln);
         else if (!RAGGED || kw + r < NK)
           store_acc_T<NDB>(out + head_off + (size_t)(kw + r) * sn, acc, scale, h);
       };
-      if (grp == 0) put(dKt); else put(dVt);
+      if (grp == 0) put(dKt, give); else if (grp == 1) put(dVt, give);
       __syncthreads();
-      if (grp == 0) finish(dVt, 1.0f, dV); else finish(dKt, alpha, dK);
+      if (grp == 0) finish(dVt, 1.0f, dV); else if (grp == 1) finish(dKt, alpha, dK);
     } else if constexpr (kStagedDkDv<D>) {
       char* stage = smem + T0 + (kStageOverTiles<D, G> ? 0 : 4 * TILE_BYTES + 4 * QT * (int)sizeof(float));
       store_rows_staged<NDB>(stage, rounded(dVt, 1.0f), dV + 32 * db0 + head_off + (size_t)kw * sn, sn, rows_valid, tid);
@@ -763,7 +775,8 @@ static hipError_t launch_dkdv_g(const void* Q, const void* K, const void* V, con
   auto k = attn_bwd_dkdv_kernel<D, CAUSAL, RAGGED, GROUPED, G>;
   hipError_t e;
   if ((e = set_smem(k, smem, set)) != hipSuccess) return e;
-  const int nkt = ((RAGGED ? lay.Nk : N) + kKeysPerWG - 1) / kKeysPerWG;
+  constexpr int KEYS = 32 * kKeyWaves<G>, THREADS = 64 * kKeyWaves<G> * G;
+  const int nkt = ((RAGGED ? lay.Nk : N) + KEYS - 1) / KEYS;
   // Under the causal mask: one block per work-group in a balanced order when that grid is at most
   // one and a half rounds of work-groups (measured: beyond that, mirrored pairs of blocks are as
   // fast or 2 % faster for this kernel), mirrored pairs otherwise.
@@ -771,11 +784,11 @@ static hipError_t launch_dkdv_g(const void* Q, const void* K, const void* V, con
   static thread_local OrderCache cache;
   const BlockOrder* ord = &kNoOrder;
   if (CAUSAL && kDSplit<D> == 1) {
-    const int res = resident_per_cu(k, smem, resident, 256 * G);
+    const int res = resident_per_cu(k, smem, resident, THREADS);
     ord = &small_grid_order(cache, (BH / lay.group) * nkt, nkt, res, 3LL * kNumCUs * res / 2);
   }
   const int pairs = (CAUSAL && ord->n == 0) ? 1 : 0;
-  hipLaunchKernelGGL(k, dim3((BH / lay.group) * (pairs ? (nkt + 1) / 2 : nkt) * kDSplit<D>), dim3(256 * G), smem, st, (const bf16_t*)Q,
+  hipLaunchKernelGGL(k, dim3((BH / lay.group) * (pairs ? (nkt + 1) / 2 : nkt) * kDSplit<D>), dim3(THREADS), smem, st, (const bf16_t*)Q,
                      (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, LSE, delta,
                      (bf16_t*)dK, (bf16_t*)dV, N, alpha, lay, pairs, *ord);
   return hipGetLastError();
@@ -785,18 +798,28 @@ template <int D, bool CAUSAL, bool RAGGED, bool GROUPED>
 static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const void* dO,
                               const float* LSE, const float* delta, void* dK, void* dV, int BH,
                               int N, float alpha, Layout lay, hipStream_t st) {
-  // Two wave groups where one-group work-groups would leave the SIMDs with a single wave each: up to
-  // one block per CU; up to two under the causal mask at D >= 96, where the blocks differ in work
-  // and the CU with the heaviest one decides (D = 64 fits two work-groups with 64-row tiles and a
-  // pipeline on a CU and gains nothing there).  Short sequences do not pay for the final exchange.
-  // Measured, one group -> two (us): B1 H1 N16384 d128 causal 582 -> 376, B2 H8 N2048 d128 causal
-  // 77 -> 55, B4 H8 the same 88 -> 73, B2 H16 N2048 d96 61 -> 58, B1 H4 N3000 d64 54 -> 50; beyond the
-  // limits: B3 H8 N2048 d128 full 104 -> 112, B4 H12 N1024 d64 causal 23.0 -> 24.3, N = 128 5.4 -> 6.5.
+  // Wave groups where one-group work-groups would leave the SIMDs with a single wave each.  Short
+  // sequences do not pay for the final exchange.
+  // Four groups on 64 keys, up to one 128-key block per CU (half of that without a mask, where all
+  // blocks are equal and two per CU would run one after the other).  Measured, two groups -> four (us): B2
+  // H32/8 N2048 d128 causal 210 -> 157, B2 H8 N2048 d128 causal 57 -> 47, d96 44 -> 36, d64 34 -> 27, B1 H4 N4096
+  // d128 causal 106 -> 64, B1 H8 N2048 d128 full 50 -> 38, B1 H1 N1024 d64 full 17.5 -> 12.8; beyond the
+  // limits: B2 H12 N2048 d128 causal 62 -> 82, B4 H12 N1024 d64 causal 24 -> 35.
+  // Two groups on 128 keys up to one block per CU; up to two under the causal mask at D >= 96, where the
+  // blocks differ in work and the CU with the heaviest one decides (D = 64 fits two work-groups with
+  // 64-row tiles and a pipeline on a CU and gains nothing there).  Measured, one group -> two (us): B2
+  // H16 N2048 d128 causal 89 -> 74, d96 64 -> 60; beyond the limits: B3 H8 N2048 d128 full 104 -> 112,
+  // B4 H12 N1024 d64 causal 23.0 -> 24.3.
   if constexpr (D <= 128) {
     const int NK = RAGGED ? lay.Nk : N;      // (the rule looks at the keys only: a chunk of queries gets the sums of the square problem)
     const long long blocks = (long long)(BH / lay.group) * ((NK + kKeysPerWG - 1) / kKeysPerWG);
-    if (blocks <= (CAUSAL && D >= 96 ? 2 : 1) * kNumCUs && NK >= 512)
-      return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 2>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+    if (NK >= 512) {
+      if (blocks <= (CAUSAL ? kNumCUs : kNumCUs / 2))
+        return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 4>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+      if constexpr (!CAUSAL || D >= 96)
+        if (blocks <= (CAUSAL ? 2 : 1) * kNumCUs)
+          return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 2>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+    }
   }
   return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
 }

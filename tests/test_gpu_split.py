@@ -13,18 +13,29 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d", [32, 64, 96, 128])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("Nq,Nk", [(511, 511), (512, 512), (545, 545), (640, 640), (33, 600), (700, 520)])
-def test_dkdv_with_two_wave_groups(lib, Nq, Nk, d, causal):
-    """From 512 keys on, few heads: two wave groups take alternate 32-query blocks (odd numbers of
-    them, partial ones, a group that meets none at all) and add their dK, dV."""
+def test_dkdv_with_wave_groups(lib, Nq, Nk, d, causal):
+    """From 512 keys on, few heads: four wave groups take alternate 32-query blocks (numbers of
+    them no group count divides, partial ones, groups that meet none at all) and add their dK, dV."""
     x = _inputs(3 * Nq + Nk + d, 1, 2, Nq, Nk, d, scale=1.25)
     got = _run(lib, x, causal, d ** -0.5, 1)
     for h in range(2):
         check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"groups {Nq}x{Nk} d{d} c{causal}")
 
 
+@pytest.mark.parametrize("d", [32, 64, 96, 128])
+@pytest.mark.parametrize("H,N,causal", [(33, 1024, True), (40, 897, True), (17, 1024, False), (20, 1000, False)])
+def test_dkdv_with_two_wave_groups(lib, H, N, d, causal):
+    """More blocks than the four-group rule takes (256 with, 128 without a mask): two groups, or one at
+    d < 96 under the mask."""
+    x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
+    got = _run(lib, x, causal, d ** -0.5, 1)
+    for h in (0, H - 1):
+        check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"two groups H{H} N{N} d{d} c{causal}")
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("N", [512, 577])
-def test_grouped_queries_with_two_wave_groups(lib, N, d):
+def test_grouped_queries_with_wave_groups(lib, N, d):
     """dK, dV of a shared head are the float32 sum over its query heads: per head the oracle-checked
     path on repeated K, V (same kernels, one head at a time), summed in float64."""
     B, H, Hkv = 1, 4, 2
