@@ -7,7 +7,7 @@
 //                         stay in registers (V_j in LDS at D = 128), query tiles (Q_i, dO_i, L_i,
 //                         delta_i; 64 rows, 32 at D = 128) stream through LDS.  Per tile:  S = Q_i K_j^T,  P = exp(S - L),  dP = dO_i V_j^T,
 //                         dS = P o (dP - delta),  dV_j^T += dO_i^T P,  dK_j^T += Q_i^T dS.
-//   attn_bwd_dq_kernel    one work-group per (batch, head, 128-query block); Q_i / dO_i fragments,
+//   attn_bwd_dq_kernel    one work-group per (batch, head, 128-query block; 64 on small grids); Q_i / dO_i fragments,
 //                         L_i and delta_i stay in registers, key tiles (K_j, V_j; 64 rows) stream
 //                         through LDS.  Per tile:  S^T = K_j Q_i^T,  dP^T = V_j dO_i^T,
 //                         dS^T = P^T o (dP^T - delta),  dQ_i^T += K_j^T dS^T.
@@ -28,8 +28,7 @@
 namespace {
 
 constexpr int kKeysPerWG = 128;   // dK/dV kernel: keys per work-group (32 per wave); 64 with four wave groups
-constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per wave)
-constexpr int kKTile = 64;        // dQ kernel: key rows per streamed tile
+constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per wave); 64 with wave groups
 
 template <int NDB>
 DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, int h) {
@@ -536,26 +535,37 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
 //                   over chunks at distances D/16 ... 1), so both give the same bits.
 constexpr int kGivenDelta = 0, kRecomputeDelta = 1, kOwnDelta = 2;
 
-template <int D, bool CAUSAL, bool RAGGED, int MODE>
-__global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
+// G: wave groups, for grids that leave the SIMDs with a wave or less each.  The groups share a
+// work-group's queries, take alternate 32-key blocks of every tile and add their sums through LDS at the
+// end.  kQueryWaves waves of 32 queries per group; a tile has as many 32-key blocks as there are groups
+// (two with one group).
+template <int G> constexpr int kQueryWaves = G == 1 ? 4 : 2;
+template <int G> constexpr int kKeysPerTile = G == 4 ? 128 : 64;
+template <int D, int G> constexpr int kSmemDq = 4 * kKeysPerTile<G> * D * 2;
+
+template <int D, bool CAUSAL, bool RAGGED, int MODE, int G>
+__global__ __launch_bounds__(64 * kQueryWaves<G> * G, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     const bf16_t* __restrict__ O, bf16_t* __restrict__ dQ, float* __restrict__ delta_out, int N,
     float alpha, Layout lay, int pairs, BlockOrder ord) {
   constexpr bool DELTA_MODE = MODE == kRecomputeDelta;
-  constexpr int TILE_BYTES = kKTile * D * 2;
+  constexpr int QW = kQueryWaves<G>, QUERIES = 32 * QW, KT = kKeysPerTile<G>;
+  constexpr int TILE_BYTES = KT * D * 2;
+  constexpr int NDB = D / 32;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* ldsK = smem;
   char* ldsV = smem + 2 * TILE_BYTES;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = (tid >> 6) % QW;                   // which 32 queries
+  const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(tid / (64 * QW)) : 0;   // which 32-key blocks
   const int r = lane & 31, h = lane >> 5;
 
   const int NK = RAGGED ? lay.Nk : N;                 // bounds-checking instantiation: N queries, NK keys,
   const int shift = RAGGED ? NK - N : 0;              // causal mask  key <= query + shift
-  const int nqt = (N + kQPerWG - 1) / kQPerWG;
+  const int nqt = (N + QUERIES - 1) / QUERIES;
   // pairs != 0 (causal problems with enough work-groups): a work-group takes query block
   // nqt-1-idx and then its mirror image idx; together they always meet the same number of key
   // tiles, so every work-group carries the same load and the grid has no tail of heavy blocks.
@@ -569,17 +579,24 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
   const bf16_t* Kh = K + head_base_kv(lay, bh);
   const bf16_t* Vh = V + head_base_kv(lay, bh);
   const float c2 = alpha * kLog2e;
-  TileLoader<D> loader;
+  TileLoader<D, KT, QW * G> loader;
   loader.init(tid, sn);
   FragOffsets<D> fo;
   init_frag_offsets<D>(fo, lane, lds_address(smem));
+  if (G > 1) {                                        // group g reads the g-th 32 rows of a tile
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      fo.row[p] += 2 * grp * kRowBlockBytes<D>;
+      fo.col[p] += 2 * grp * kRowBlockBytes<D>;
+    }
+  }
 
   for (int part = 0; part < (pairs ? 2 : 1); ++part) {
   if (part > 0) __syncthreads();                      // the first block's output staging is done with the tile buffers
   const int qt = pairs ? (part == 0 ? nqt - 1 - idx : idx)
                        : nqt - 1 - (idx + (CAUSAL && ord.n == 0 ? small_grid_rotation(bh, nqt, gridDim.x, D == 128 ? 768 : 1152) : 0)) % nqt;
   if (part == 1 && qt == nqt - 1 - idx) break;        // odd number of blocks: the middle one has no partner
-  const int q0 = qt * kQPerWG;
+  const int q0 = qt * QUERIES;
   const int qw = q0 + 32 * wave;
 
   // Q_i^T / dO_i^T fragments (B operands): lane (r,h) holds Q[qw + r][16kc + 8h .. +7]
@@ -616,7 +633,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
 #pragma unroll
       for (int kc = 0; kc < off; ++kc) cs[kc] += cs[kc + off];
     dl = sum_with_partner32(cs[0]);
-    if (h == 0 && (!RAGGED || qw + r < N)) delta_out[(size_t)bh * N + qw + r] = dl;
+    if (h == 0 && grp == 0 && (!RAGGED || qw + r < N)) delta_out[(size_t)bh * N + qw + r] = dl;
   }
   float pdp = 0.f;                                   // DELTA_MODE: this lane's share of sum_k P dP
   // -delta_i in all 16 accumulator slots of the lane: the third operand of the first dP^T matrix
@@ -633,8 +650,8 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) dQt[db][i] = 0.f;
 
-  const int kend = !CAUSAL ? NK : !RAGGED ? q0 + kQPerWG : max(0, min(NK, q0 + kQPerWG + shift));
-  const int ntiles = RAGGED ? (kend + kKTile - 1) / kKTile : kend / kKTile;
+  const int kend = !CAUSAL ? NK : !RAGGED ? q0 + QUERIES : max(0, min(NK, q0 + QUERIES + shift));
+  const int ntiles = RAGGED || KT > QUERIES ? (kend + KT - 1) / KT : kend / KT;
 
   loader.template load_rows<RAGGED>(ldsK, Kh, 0, NK);
   loader.template load_rows<RAGGED>(ldsV, Vh, 0, NK);
@@ -655,22 +672,22 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
     // burst behind the barrier.  After the last tile the current one is fetched once more into the
     // idle buffer (harmless; keeps the instruction stream free of branches).
     const int jn = (j + 1 < ntiles) ? j + 1 : j;
-    constexpr int NLD = TileLoader<D>::NI;
-    const auto pendK = loader.template prepare<RAGGED>(smem + (buf ^ 1) * TILE_BYTES, Kh, jn * kKTile, NK);
-    const auto pendV = loader.template prepare<RAGGED>(smem + (2 + (buf ^ 1)) * TILE_BYTES, Vh, jn * kKTile, NK);
+    constexpr int NLD = decltype(loader)::NI;
+    const auto pendK = loader.template prepare<RAGGED>(smem + (buf ^ 1) * TILE_BYTES, Kh, jn * KT, NK);
+    const auto pendV = loader.template prepare<RAGGED>(smem + (2 + (buf ^ 1)) * TILE_BYTES, Vh, jn * KT, NK);
     auto issue_part = [&](int i) {
       if (i < NLD) loader.issue(pendK, i);
       else if (i < 2 * NLD) loader.issue(pendV, i - NLD);
     };
     bool issued = false;
-    const int kt0 = j * kKTile;
+    const int kt0 = j * KT;
     if (!CAUSAL || (kt0 <= qw + shift + 31)) {
       // one 32-key block against this wave's 32 queries (one code path: the block that crosses the
       // diagonal only adds a masking step, so that the fragment reads stay next to their matrix
       // instructions instead of being merged in front of a branch)
       auto kblock = [&](int kb, auto first_c) {
         constexpr bool first = decltype(first_c)::value;     // the block that also issues the tile transfer
-        const int kb0 = kt0 + 32 * kb;
+        const int kb0 = kt0 + 32 * (kb + grp);
         // ---- S^T = K_j Q_i^T, dP^T = V_j dO_i^T ; rows = keys, lane = query
         f32x16 s, dp;
 #pragma unroll
@@ -716,8 +733,8 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
         }
       };
 #pragma unroll
-      for (int kb = 0; kb < kKTile / 32; ++kb) {
-        const int kb0 = kt0 + 32 * kb;
+      for (int kb = 0; kb < KT / 32 / G; ++kb) {
+        const int kb0 = kt0 + 32 * (kb + grp);
         if (CAUSAL && (kb0 > qw + shift + 31)) continue;   // no query of the wave sees a key of the block
         if (RAGGED && kb0 >= NK) continue;                   // nothing but padding
         if (kb == 0) kblock(kb, std::true_type{});
@@ -736,9 +753,44 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
     if (j + 1 < ntiles) tile_step(std::integral_constant<int, 1>{}, j + 1);
   }
   if (DELTA_MODE) {
+    static_assert(!DELTA_MODE || G == 1, "the recomputed delta has no wave groups");
     const float dsum = sum_with_partner32(pdp);      // the partner lane holds the other keys of every block
     if (h == 0 && (!RAGGED || qw + r < N)) delta_out[(size_t)bh * N + qw + r] = dsum;
     continue;
+  }
+  if constexpr (G > 1) {
+    // The upper half of the groups hands its sums to the lower half, until group 0 has the total;
+    // every wave is past the last tile's barrier, the tile buffers are free.  (Opaque lane index:
+    // see the dK/dV kernel.)
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int half = G / 2; half >= 1; half >>= 1) {
+      if (grp < 2 * half) {
+        char* area = smem + ((grp % half) * QW + wave) * (NDB * 4096);
+        if (grp >= half) {
+#pragma unroll
+          for (int i = 0; i < 4 * NDB; ++i) {
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = dQt[i >> 2][4 * (i & 3) + e];
+            *reinterpret_cast<f32x4*>(area + (i * 64 + ln) * 16) = v;
+          }
+        }
+      }
+      __syncthreads();
+      if (grp < half) {
+        const char* area = smem + (grp * QW + wave) * (NDB * 4096);
+#pragma unroll
+        for (int i = 0; i < 4 * NDB; ++i) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(area + (i * 64 + ln) * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dQt[i >> 2][4 * (i & 3) + e] += v[e];
+        }
+      }
+      __syncthreads();
+    }
+    if (grp != 0) continue;
   }
   if constexpr (kCanStage<D / 32>) {
     // the tile buffers are free now (every wave is past the last tile's barrier): they serve as
@@ -824,28 +876,47 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
   return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
 }
 
-template <int D, bool CAUSAL, bool RAGGED, int MODE>
-static hipError_t launch_dq(const void* Q, const void* K, const void* V, const void* dO,
-                            const float* LSE, const float* delta, const void* O, void* dQ,
-                            float* delta_out, int BH, int N, float alpha, Layout lay, hipStream_t st) {
-  constexpr int smem = 4 * kKTile * D * 2;
+template <int D, bool CAUSAL, bool RAGGED, int MODE, int G>
+static hipError_t launch_dq_g(const void* Q, const void* K, const void* V, const void* dO,
+                              const float* LSE, const float* delta, const void* O, void* dQ,
+                              float* delta_out, int BH, int N, float alpha, Layout lay, hipStream_t st) {
+  constexpr int smem = kSmemDq<D, G>;
+  constexpr int QUERIES = 32 * kQueryWaves<G>, THREADS = 64 * kQueryWaves<G> * G;
   static std::atomic<bool> set{false};
-  auto k = attn_bwd_dq_kernel<D, CAUSAL, RAGGED, MODE>;
+  auto k = attn_bwd_dq_kernel<D, CAUSAL, RAGGED, MODE, G>;
   hipError_t e;
   if ((e = set_smem(k, smem, set)) != hipSuccess) return e;
   // as in the forward: mirrored pairs of query blocks under the causal mask when that still
   // leaves at least two full rounds of work-groups
-  const int nqt = (N + kQPerWG - 1) / kQPerWG;
+  const int nqt = (N + QUERIES - 1) / QUERIES;
   const int pairs = (CAUSAL && (long long)BH * ((nqt + 1) / 2) >= 1024) ? 1 : 0;
   const int grid = BH * (pairs ? (nqt + 1) / 2 : nqt);
   static std::atomic<int> resident{0};
   static thread_local OrderCache cache;
   const BlockOrder& ord = (CAUSAL && !pairs)
-      ? small_grid_order(cache, grid, nqt, resident_per_cu(k, smem, resident), 8 * kMaxOrder) : kNoOrder;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(256), smem, st, (const bf16_t*)Q,
+      ? small_grid_order(cache, grid, nqt, resident_per_cu(k, smem, resident, THREADS), 8 * kMaxOrder) : kNoOrder;
+  hipLaunchKernelGGL(k, dim3(grid), dim3(THREADS), smem, st, (const bf16_t*)Q,
                      (const bf16_t*)K, (const bf16_t*)V, (const bf16_t*)dO, LSE, delta,
                      (const bf16_t*)O, (bf16_t*)dQ, delta_out, N, alpha, lay, pairs, ord);
   return hipGetLastError();
+}
+
+template <int D, bool CAUSAL, bool RAGGED, int MODE>
+static hipError_t launch_dq(const void* Q, const void* K, const void* V, const void* dO,
+                            const float* LSE, const float* delta, const void* O, void* dQ,
+                            float* delta_out, int BH, int N, float alpha, Layout lay, hipStream_t st) {
+  // Wave groups on small grids, as in launch_dkdv: up to one 128-query block per CU under the causal mask,
+  // half of that without one, from 512 keys on.  Measured, one group -> four groups on 64 queries (us): B2 H8
+  // N2048 d128 causal 50 -> 45, B1 H8 the same 44 -> 30, d64 30 -> 18, B1 H4 N4096 d128 79 -> 48, B1 H8
+  // N2048 d128 full 44 -> 32, B1 H1 N8192 d64 101 -> 47; beyond the limits: B2 H12 N2048 d128 causal 52 -> 66,
+  // B2 H8 N2048 d128 full 57 -> 64.  At D = 256 (one wave per SIMD) two groups on 64 queries are what fits:
+  // B1 H8 N2048 full 73 -> 57, beyond the limit B2 H8 95 -> 109.
+  if constexpr (MODE != kRecomputeDelta) {
+    const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
+    if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (CAUSAL && D <= 128 ? kNumCUs : kNumCUs / 2))
+      return launch_dq_g<D, CAUSAL, RAGGED, MODE, (D <= 128 ? 4 : 2)>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+  }
+  return launch_dq_g<D, CAUSAL, RAGGED, MODE, 1>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
 }
 
 }  // namespace

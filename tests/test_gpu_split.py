@@ -10,12 +10,13 @@ from test_gpu_rect import _inputs, _run
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d", [32, 64, 96, 128])
+@pytest.mark.parametrize("d", [32, 64, 96, 128, 256])
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("Nq,Nk", [(511, 511), (512, 512), (545, 545), (640, 640), (33, 600), (700, 520)])
-def test_dkdv_with_wave_groups(lib, Nq, Nk, d, causal):
-    """From 512 keys on, few heads: four wave groups take alternate 32-query blocks (numbers of
-    them no group count divides, partial ones, groups that meet none at all) and add their dK, dV."""
+@pytest.mark.parametrize("Nq,Nk", [(511, 511), (512, 512), (545, 545), (640, 640), (33, 600), (700, 520), (1, 513)])
+def test_backward_with_wave_groups(lib, Nq, Nk, d, causal):
+    """From 512 keys on, few heads: wave groups take alternate 32-query blocks (dK/dV) or 32-key blocks
+    (dQ) - numbers of them no group count divides, partial ones, groups that meet none at all -
+    and add their sums."""
     x = _inputs(3 * Nq + Nk + d, 1, 2, Nq, Nk, d, scale=1.25)
     got = _run(lib, x, causal, d ** -0.5, 1)
     for h in range(2):
