@@ -296,7 +296,8 @@ int attn_bwd_rect(const void* Q, const void* K, const void* V, const void* O, co
  *                        the shape is unsupported) and attn_fwd_ws runs the ordinary kernel.
  *   workspace            16-byte aligned, free for reuse once the stream has passed the call; NULL:
  *                        the ordinary kernel.  Too small: ATTN_ERR_WORKSPACE.
- *   stride_*             0: contiguous layouts; otherwise as in attn_fwd_strided (H_kv == H, Nq == Nk).
+ *   stride_*             all three 0: contiguous layouts; otherwise as in attn_fwd_strided (none may be
+ *                        0 then; H_kv == H, Nq == Nk).
  *   H_kv                 key/value heads (H for ordinary attention)
  */
 size_t attn_fwd_workspace_bytes(int B, int H, int Nq, int Nk, int d, int causal, int variant);

@@ -326,7 +326,9 @@ def attn_fwd_strided(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None
     _strided_bhnd(O, "O", Q)
     if LSE is None:
         LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
-    if _fwd_shared_out(Q, K, V, O, LSE, (sb, sh, sn), H, N, causal, softmax_scale, variant, beta, eps, stream):
+    # an expanded dimension (stride 0) is for attn_fwd_strided to refuse: to attn_fwd_ws three zeros mean contiguous
+    if min(sb, sh, sn) > 0 and _fwd_shared_out(Q, K, V, O, LSE, (sb, sh, sn), H, N, causal, softmax_scale, variant,
+                                               beta, eps, stream):
         return O, LSE
     _check(_lib.attn_fwd_strided(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), sb, sh, sn, B, H, N, d,
                                  int(bool(causal)), float(softmax_scale), int(variant),

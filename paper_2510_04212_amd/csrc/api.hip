@@ -443,7 +443,9 @@ extern "C" int attn_fwd_ws(const void* Q, const void* K, const void* V, void* O,
   if (st != ATTN_OK) return st;
   if (B > 0 && H > 0 && !gqa_heads_ok(H, H_kv)) return ATTN_ERR_BAD_ARG;
   Layout lay = (B > 0 && H > 0) ? contiguous(H, Nq, d, H_kv, Nk) : contiguous(1, 1, d);
-  if (stride_n != 0) {
+  // contiguous only when all three are 0: one zero among other strides is an expanded dimension, refused
+  // like everywhere else
+  if (stride_b != 0 || stride_h != 0 || stride_n != 0) {
     if (H_kv != H || Nq != Nk || !strides_ok(stride_b, stride_h, stride_n, d)) return ATTN_ERR_BAD_ARG;
     lay = Layout{stride_b, stride_h, (int)stride_n, H, stride_b, stride_h, 1, Nk};
   }

@@ -80,3 +80,15 @@ def test_what_was_refused_is_refused_the_same_way(lib):
         attention(torch.autograd.forward_ad.make_dual(q, q), k, v)
     empty = torch.zeros((0, 2, 64, 64), dtype=torch.bfloat16, device=DEV)
     assert attention(empty, empty, empty).shape == empty.shape
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1, 64), (1, 2, 1, 64), (2, 1, 2048, 64)], ids=str)
+def test_expanded_dimensions_are_refused(lib, shape):
+    """Rows (or heads, or a batch) that share storage: refused by both routes before any launch, also
+    at the sizes where the forward takes a workspace."""
+    from paper_2510_04212_amd.autograd import attention
+    x = torch.zeros(shape, dtype=torch.bfloat16, device=DEV).expand(2, 2, 2048, 64)
+    for call in (lambda: attention(x, x, x), lambda: lib.attn_fwd_strided(x, x, x, True, 0.125, 1)):
+        with pytest.raises(lib.AttnError) as e:
+            call()
+        assert e.value.status == 2

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -97,6 +98,10 @@ def test_argument_validation_happens_on_the_host(binding):
     assert fs(0, 64, 64) == BAD and fs(8192, 8192, 60) == BAD and fs(8192, 8192, 32) == BAD   # zero, not a multiple of 8, rows overlap
     assert fs(8192, 8192, 1 << 24) == BAD and fs(8192, 8192, 80, d=80) == UNSUP
     assert lib.attn_bwd_strided(*ptrs_for_strided, ws_for_strided, 4096, 8192, 8192, 4, 1, 1, 128, 64, 1, 0.125, 0, None) == BAD
+    # the forward with a workspace: three zero strides mean contiguous, a single one is an expanded dimension
+    fw = lambda sb, sh, sn: lib.attn_fwd_ws(p, p, p, q, p, ws_for_strided, 1 << 30, sb, sh, sn, 1, 1, 1, 2048, 2048, 64, 1, 0.125, 1, 2.0, 1e-3, None)
+    assert lib.attn_fwd_workspace_bytes(1, 1, 2048, 2048, 64, 1, 1) > 0
+    assert fw(64, 64, 0) == BAD and fw(0, 131072, 64) == BAD and fw(131072, 0, 64) == BAD and fw(131072, 0, 0) == BAD
     gq = lambda H, Hkv: lib.attn_fwd_gqa(p, p, p, q, p, 1, H, Hkv, 128, 64, 1, 0.125, 0, 2.0, 1e-3, None)
     assert gq(6, 4) == BAD and gq(4, 0) == BAD and gq(2, 4) == BAD and gq(0, 0) == OK
     assert lib.attn_bwd_gqa(*ptrs_for_strided, ws_for_strided, 4096, 1, 6, 4, 128, 64, 1, 0.125, 0, None) == BAD
@@ -131,6 +136,21 @@ def test_argument_validation_happens_on_the_host(binding):
     assert bwd(alias, ws, 4096) == BAD                       # dK aliases dV
     nul = list(ptrs); nul[5] = None
     assert bwd(nul, ws, 4096) == NULL
+
+
+@pytest.mark.parametrize("expand", [(2, 2, 1, 64), (2, 1, 2048, 64), (1, 2, 2048, 64), (1, 1, 1, 64)], ids=str)
+def test_binding_refuses_expanded_dimensions(binding, monkeypatch, expand):
+    """Tensors expanded along the rows, heads, batch or all of them share storage between rows: refused by
+    attn_fwd_strided also where the forward would take a workspace (from 1024 keys on, few blocks).
+    The device checks of the marshalling are bypassed; the library refuses before any launch."""
+    monkeypatch.setattr(binding, "_strided_bhnd", lambda t, name, like=None: (t.shape, t.stride()))
+    monkeypatch.setattr(binding, "_stream", lambda s: None)
+    x = torch.zeros(expand, dtype=torch.bfloat16)
+    x = x.as_strided((2, 2, 2048, 64), tuple(s if n > 1 else 0 for n, s in zip(expand, x.stride())))
+    assert 0 in x.stride()[:3]
+    with pytest.raises(binding.AttnError) as e:
+        binding.attn_fwd_strided(x, x, x, True, 0.125, 1)
+    assert e.value.status == 2
 
 
 def test_binding_refuses_to_import_without_the_built_library(tmp_path):
