@@ -289,9 +289,12 @@ int attn_bwd_rect(const void* Q, const void* K, const void* V, const void* O, co
 /*
  * The forward with a workspace, for grids of few query blocks (few heads, or a chunk of queries
  * against a long context): there the key tiles of a block are shared out to several work-groups,
- * whose float32 partial sums pass through the workspace and are joined by a second kernel.  Same
- * algorithms, rounding points, checks and error codes as attn_fwd_ex / _strided / _gqa / _rect; only
- * the order of the float32 sums over key tiles differs.
+ * whose float32 partial sums pass through the workspace and are joined by another kernel.  Same
+ * algorithms, rounding points, checks and error codes as attn_fwd_ex / _strided / _gqa / _rect: a first
+ * kernel finds the running normaliser each share starts from, so that every rounded P-bar (and what
+ * attn_fwd_opt counts) is that of the ordinary kernel.  Only the order of the float32 sums over key tiles
+ * differs, and with it one bf16 step in a few of 10^4 elements of O: for this entry point those depend on
+ * the number of heads and queries, which decide how many shares there are.
  *   attn_fwd_workspace_bytes  the bytes attn_fwd_ws needs for this problem; 0: nothing is gained (or
  *                        the shape is unsupported) and attn_fwd_ws runs the ordinary kernel.
  *   workspace            16-byte aligned, free for reuse once the stream has passed the call; NULL:

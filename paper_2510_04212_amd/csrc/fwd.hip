@@ -61,23 +61,101 @@ DEVI long pack_e4m3(const float (&v)[8]) {
 constexpr int kRowStats = 3, kFixedNorm = 2;
 
 // ---- sharing a block's key tiles out to several work-groups (SPLIT below)
-constexpr int kMinShare = 4;          // tiles: below, a share's start-up costs more than it takes off
-// shares of a block of `tiles` key tiles when the grid has `splits` work-groups per block
+// Shares of a block of `tiles` key tiles when the grid has `splits` work-groups per block: of two tiles at least,
+// three from 2048 keys on (below that, start-up and merging cost more than a shorter chain takes off).
 __host__ DEVI int split_shares(int tiles, int splits) {
-  const int most = tiles / kMinShare;
+  const int most = tiles / (tiles < 32 ? 2 : 3);
   return most < 1 ? 1 : most < splits ? most : splits;
 }
-// floats a wave leaves per share: its 32 x D accumulator, 32 normalisers, 32 row sums
+// floats of a share of 32 rows in the workspace: the 32 x D accumulator, 32 normalisers, 32 row sums
 template <int D> constexpr int kPartFloats = 32 * D + 64;
+// largest normaliser the first n shares of a 32-row block ask for in row r (eight loads in flight)
+template <int D> DEVI float largest_norm(const float* rows, int n, int r) {
+  float m = -INFINITY;
+  for (int s0 = 0; s0 < n; s0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = rows[(size_t)min(s0 + i, n - 1) * kPartFloats<D> + 32 * D + r];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = fmaxf(m, v[i]);
+  }
+  return m;
+}
+// first tile of share s (share `shares` would be the end)
+DEVI int share_begin(int tiles, int s, int shares) { return tiles * s / shares; }
+
+// Mask of a tile that crosses the diagonal or the sequence end: element (kb, i) of the lane is key
+// k0 + 4h + c with c = 32 kb + 8 (i / 4) + i % 4 a compile-time constant; keys with c > lim become -inf.
+DEVI void mask_scores(f32x16 (&s)[2], int lim) {
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
+}
+
+// Normaliser a row asks for in one key tile (the two lanes of the row get the same): Alg. 1 (VARIANT 0) its
+// maximum r_m, Alg. 3 (VARIANT 1) what the rule makes of it.  s: raw scores, masked ones -inf.
+// may_be_unseen: a row may see no key of the tile.  allowed(r_m): whether a guard lets the rule apply.
+template <int VARIANT, class AllowedF>
+DEVI float tile_normaliser(const f32x16 (&s)[2], float alpha, float inv_alpha, float beta, float eps,
+                           bool may_be_unseen, AllowedF&& allowed, float& r_m) {
+  if (VARIANT == 1) {
+    // Alg. 3: r_s = #{ r_m - S <= eps } over the tile row; a repeated maximum moves the
+    // normaliser to beta*r_m (r_m > 0) or to 0 (r_m < 0).  The count only matters through
+    // "more than one", i.e. through whether the SECOND largest score of the row passes the
+    // test: the lane keeps the two largest of its 32 scores (two chains of 16; a value met
+    // twice is both), then the two lanes that share a query row are merged.  Three vector
+    // instructions per two scores and no mask bookkeeping.
+    float a1[2], a2[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      a1[kb] = fmaxf(s[kb][0], s[kb][1]);
+      a2[kb] = fminf(s[kb][0], s[kb][1]);
+#pragma unroll
+      for (int i = 2; i < 16; i += 2) {
+        // two more scores x, y: the largest of {a1, x, y} is the new a1; the second largest
+        // of {a1, a2, x, y} is the median of {a1, x, y} or the old a2 (a2 <= a1)
+        const float x = s[kb][i], y = s[kb][i + 1];
+        const float mid = __builtin_amdgcn_fmed3f(a1[kb], x, y);
+        a1[kb] = fmaxf(fmaxf(a1[kb], x), y);
+        a2[kb] = fmaxf(mid, a2[kb]);
+      }
+    }
+    const float t1 = fmaxf(a1[0], a1[1]);
+    const float t2 = fmaxf(fminf(a1[0], a1[1]), fmaxf(a2[0], a2[1]));
+    const float o1 = partner32(t1), o2 = partner32(t2);
+    const float mx = fmaxf(t1, o1);
+    const float second = fmaxf(fminf(t1, o1), fmaxf(t2, o2));
+    // the test  r_m - alpha*s <= eps  in terms of the raw score:  s >= (r_m - eps) / alpha
+    // (a row with nothing visible in this tile has r_m = -inf: no rule, no update)
+    r_m = mx * alpha;
+    const bool repeated = second >= (mx * alpha - eps) * inv_alpha && (!may_be_unseen || mx > -INFINITY) && allowed(r_m);
+    const float m_prime = (repeated && r_m > 0.f) ? beta * r_m : r_m;
+    return (repeated && r_m < 0.f) ? 0.f : m_prime;
+  }
+  float mx = s[0][0];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
+  r_m = max_with_partner32(mx) * alpha;
+  return r_m;
+}
 
 // Waves per SIMD are stated as a range, not only as a minimum: at D = 128 two work-groups fit a
 // CU (LDS), and told so the compiler spends the registers of the third wave it would otherwise
 // keep room for on issuing LDS fragment reads ahead of their matrix instructions.
 //
 // SPLIT: grids of so few query blocks that most of the chip would idle (few heads, a chunk of queries
-// against a long context).  The key tiles of a block are shared out to `splits` work-groups; each
-// leaves its float32 accumulator, normaliser and row sum in `part` and attn_fwd_merge_kernel
-// joins them.
+// against a long context).  The key tiles of a block are shared out to `splits` work-groups, in
+// three launches: attn_fwd_norms_kernel leaves in `part` the largest normaliser each share's tiles ask for;
+// this kernel starts every share from the largest normaliser of the shares before it and leaves the
+// float32 accumulator and row sum; attn_fwd_merge_kernel joins them.  The running normaliser, and
+// with it every rounded P-bar, is then the one of a single pass over the tiles (Alg. 3: a moved
+// normaliser stays for the rest of the row), and only the order of the float32 sums differs: 3e-5 .. 1e-4
+// relative in O, one bf16 step in 1 .. 5 of 10^4 elements.  Without the first launch a share would
+// round P-bar against its own maximum: other roundings, more unit probabilities, 1e-3 .. 2e-3 relative.
 template <int D, bool CAUSAL, int VARIANT, bool RAGGED, bool EXTRAS, bool SPLIT = false>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 : (D > 128 ? 1 : 8)))) void attn_fwd_kernel(
@@ -98,6 +176,9 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   // past the end are masked like future keys; the causal mask is  key <= query + shift.
   const int NK = RAGGED ? lay.Nk : N;
   const int shift = RAGGED ? NK - N : 0;
+  // A score of -inf in a row that does see keys (overflowed inputs) is no "nothing visible": the aligned
+  // instantiation treats it like any other, and so does SPLIT (always bounds-checking) at its sizes.
+  const bool may_be_unseen = RAGGED && !(SPLIT && shift == 0 && N % kBr == 0);
   const int nqt = (N + kBr - 1) / kBr;
   // pairs != 0 (causal problems with enough work-groups): a work-group takes query block
   // nqt-1-idx and then its mirror image idx, which together always meet the same number of key
@@ -141,8 +222,8 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   const int all_tiles = RAGGED ? (kend + kBc - 1) / kBc : kend / kBc;
   const int shares = SPLIT ? split_shares(all_tiles, splits) : 1;
   if (SPLIT && split >= shares) return;          // the block is too short for all of them
-  const int tile0 = SPLIT ? all_tiles * split / shares : 0;
-  const int ntiles = SPLIT ? all_tiles * (split + 1) / shares : all_tiles;
+  const int tile0 = SPLIT ? share_begin(all_tiles, split, shares) : 0;
+  const int ntiles = SPLIT ? share_begin(all_tiles, split + 1, shares) : all_tiles;
   loader.template load_rows<RAGGED>(smem, Kh, tile0 * kBc, NK);
   if (VARIANT != kRowStats) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, tile0 * kBc, NK);
 
@@ -163,12 +244,14 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   // running normaliser, natural-log units of the alpha-scaled scores (kFixedNorm: the row's
   // normaliser chosen by the kRowStats pass)
   float m = (VARIANT == kFixedNorm) ? LSE[(size_t)bh * N + qc] : -INFINITY;
+  float* share = SPLIT ? part + ((size_t)bh * ((N + 31) / 32) + qw / 32) * splits * kPartFloats<D> : nullptr;   // the rows' first share
+  if (SPLIT && qw < N) m = largest_norm<D>(share, split, r);
   float lsum = 0.f;         // this lane's share of the running row sum (its 32 of the 64 keys per tile)
 
   wait_vmem();
 #pragma unroll
   for (int kc = 0; kc < D / 16; ++kc) settle(qf[kc]);
-  if (VARIANT == kFixedNorm) settle(m);
+  if (VARIANT == kFixedNorm || SPLIT) settle(m);
   __syncthreads();
 
   // One key tile; BUF (which LDS buffer holds it) is a compile-time constant so that every LDS
@@ -214,15 +297,10 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
       // ---- mask: causal (key > query) in the tile that crosses the diagonal, and keys beyond
       // the sequence end in the last, partial tile -> -inf
       if ((CAUSAL && (k0 + kBc - 1 > qw + shift)) || (RAGGED && k0 + kBc > NK)) {
-        // element (kb, i) of this lane is key k0 + 4h + c with c = 32 kb + 8 (i / 4) + i % 4 a
-        // compile-time constant: masked <=> c > lim, one per-lane limit for both conditions
+        // one per-lane limit for both conditions
         int lim = CAUSAL ? q + shift - k0 - 4 * h : 0x7fffffff;
         if (RAGGED) lim = min(lim, NK - 1 - k0 - 4 * h);
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
+        mask_scores(s, lim);
       }
       if (VARIANT == kRowStats) {
         // two largest values seen by this lane (duplicates count: a value met twice is both)
@@ -239,57 +317,13 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
         if (VARIANT == kFixedNorm) {
           mneg = (RAGGED && m == -INFINITY) ? 0.f : -m * kLog2e;   // a query that sees no key at all
         } else {
-          // ---- tile row maximum r_m (of the alpha-scaled scores)
-          float mx;
-          bool repeated = false;
-          if (VARIANT == 1) {
-            // Alg. 3: r_s = #{ r_m - S <= eps } over the tile row; a repeated maximum moves the
-            // normaliser to beta*r_m (r_m > 0) or to 0 (r_m < 0).  The count only matters through
-            // "more than one", i.e. through whether the SECOND largest score of the row passes the
-            // test: the lane keeps the two largest of its 32 scores (two chains of 16; a value met
-            // twice is both), then the two lanes that share a query row are merged.  Three vector
-            // instructions per two scores and no mask bookkeeping.
-            float a1[2], a2[2];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-              a1[kb] = fmaxf(s[kb][0], s[kb][1]);
-              a2[kb] = fminf(s[kb][0], s[kb][1]);
-#pragma unroll
-              for (int i = 2; i < 16; i += 2) {
-                // two more scores x, y: the largest of {a1, x, y} is the new a1; the second largest
-                // of {a1, a2, x, y} is the median of {a1, x, y} or the old a2 (a2 <= a1)
-                const float x = s[kb][i], y = s[kb][i + 1];
-                const float mid = __builtin_amdgcn_fmed3f(a1[kb], x, y);
-                a1[kb] = fmaxf(fmaxf(a1[kb], x), y);
-                a2[kb] = fmaxf(mid, a2[kb]);
-              }
-            }
-            const float t1 = fmaxf(a1[0], a1[1]);
-            const float t2 = fmaxf(fminf(a1[0], a1[1]), fmaxf(a2[0], a2[1]));
-            const float o1 = partner32(t1), o2 = partner32(t2);
-            mx = fmaxf(t1, o1);
-            const float second = fmaxf(fminf(t1, o1), fmaxf(t2, o2));
-            // the test  r_m - alpha*s <= eps  in terms of the raw score:  s >= (r_m - eps) / alpha
-            // (a row with nothing visible in this tile has r_m = -inf: no rule, no update)
-            repeated = second >= (mx * alpha - eps) * inv_alpha && (!RAGGED || mx > -INFINITY);
-            if (EXTRAS && ex.guard != 0) repeated = repeated && guard_allows(mx * alpha, beta);
-          } else {
-            mx = s[0][0];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-              for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
-            mx = max_with_partner32(mx);
-          }
-          const float r_m = mx * alpha;
-          float m_prime = r_m;
-          if (VARIANT == 1) {
-            m_prime = (repeated && r_m > 0.f) ? beta * r_m : r_m;
-            m_prime = (repeated && r_m < 0.f) ? 0.f : m_prime;
-            if (EXTRAS) fired_cnt += (m_prime != r_m) ? 1 : 0;
-          }
+          float r_m;         // tile row maximum of the alpha-scaled scores
+          const float m_prime = tile_normaliser<VARIANT>(s, alpha, inv_alpha, beta, eps, may_be_unseen, [&](float r) {
+            return !EXTRAS || ex.guard == 0 || guard_allows(r, beta);
+          }, r_m);
+          if (EXTRAS && VARIANT == 1) fired_cnt += (m_prime != r_m) ? 1 : 0;
           const float m_new = fmaxf(m, m_prime);         // Alg. 1 step 7 / Alg. 3
-          const bool unseen = RAGGED && m_new == -INFINITY;   // nothing visible so far: P-bar = 0, nothing to rescale
+          const bool unseen = may_be_unseen && m_new == -INFINITY;   // nothing visible so far: P-bar = 0, nothing to rescale
           corr = unseen ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * kLog2e);
           m = m_new;
           mneg = unseen ? 0.f : -m_new * kLog2e;
@@ -393,11 +427,10 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   }
 
   if constexpr (SPLIT) {
-    // the share's results, as the registers hold them (16 bytes per lane, lanes consecutive)
+    // the share's sums, as the registers hold them (16 bytes per lane, lanes consecutive)
     const float l_share = sum_with_partner32(lsum);
     if (qw < N) {
-      const size_t slot = ((size_t)bh * ((N + 31) / 32) + qw / 32) * splits + split;
-      float* p = part + slot * kPartFloats<D>;
+      float* p = share + (size_t)split * kPartFloats<D>;
 #pragma unroll
       for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -407,7 +440,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
           for (int e = 0; e < 4; ++e) v[e] = acc[db][4 * g + e];
           *reinterpret_cast<f32x4*>(p + ((db * 4 + g) * 64 + lane) * 4) = v;
         }
-      p[32 * D + lane] = h == 0 ? m : l_share;
+      if (h == 0) p[32 * D + 32 + r] = l_share;
     }
     return;
   }
@@ -482,11 +515,86 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   }   // part
 }
 
+// First launch of the SPLIT forward: per row and share the largest normaliser its tiles ask for (the same
+// score products and rule as the kernel above, bit for bit).  Shares are few tiles long and only K is
+// read, so latency bounds it: K comes 128 rows at a time, in the LDS of the other launch's K and V.
+template <int D, bool CAUSAL, int VARIANT>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, D <= 128 ? 2 : 1))) void attn_fwd_norms_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, int N, float alpha, float beta, float eps,
+    Layout lay, float* __restrict__ part, int splits) {
+  constexpr int STEP = 2 * kBc, STEP_BYTES = STEP * D * 2;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const int r = lane & 31, h = lane >> 5;
+  const int NK = lay.Nk, shift = NK - N;
+  const bool may_be_unseen = !(shift == 0 && N % kBr == 0);
+  const int nqt = (N + kBr - 1) / kBr;
+  const int wg_all = xcd_remap(blockIdx.x, gridDim.x);
+  const int split = wg_all % splits, wg = wg_all / splits;
+  const int bh = wg / nqt, q0 = (nqt - 1 - wg % nqt) * kBr;
+  const int qw = q0 + 32 * wave, q = qw + r, qc = min(q, N - 1);
+  const int kend = !CAUSAL ? NK : max(0, min(NK, q0 + kBr + shift));
+  const int all_tiles = (kend + kBc - 1) / kBc;
+  const int shares = split_shares(all_tiles, splits);
+  if (split >= shares) return;
+  const int tile0 = share_begin(all_tiles, split, shares), ntiles = share_begin(all_tiles, split + 1, shares);
+  const bf16_t* Kh = K + head_base_kv(lay, bh);
+  TileLoader<D, STEP> loader;
+  loader.init(tid, lay.sn);
+  loader.template load_rows<true>(smem, Kh, tile0 * kBc, NK);
+  const bf16_t* Qr = Q + head_base(lay, bh) + (size_t)qc * lay.sn + 8 * h;
+  bf16x8 qf[D / 16];
+#pragma unroll
+  for (int kc = 0; kc < D / 16; ++kc) qf[kc] = *reinterpret_cast<const bf16x8*>(Qr + 16 * kc);
+  FragOffsets<D> fo;
+  init_frag_offsets<D>(fo, lane, lds_address(smem));
+  const float inv_alpha = 1.0f / alpha;
+  float m = -INFINITY;
+  wait_vmem();
+#pragma unroll
+  for (int kc = 0; kc < D / 16; ++kc) settle(qf[kc]);
+  __syncthreads();
+  auto step = [&](auto buf_c, int j0) {
+    constexpr int BUF = decltype(buf_c)::value;
+    if (j0 + 2 < ntiles) loader.template load_rows<true>(smem + (BUF ^ 1) * STEP_BYTES, Kh, (j0 + 2) * kBc, NK);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int k0 = (j0 + t) * kBc;
+      if (j0 + t >= ntiles || (CAUSAL && k0 > qw + shift + 31)) continue;
+      f32x16 s[2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+#pragma unroll
+      for (int kc = 0; kc < D / 16; ++kc)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+          s[kb] = mfma32(lds_row8<D>(BUF * STEP_BYTES, fo, kBc * t + 32 * kb, kc), qf[kc], s[kb]);
+      sched_reads_ahead_of_mfma<D / 8, 1, 4>();
+      if ((CAUSAL && k0 + kBc - 1 > qw + shift) || k0 + kBc > NK)
+        mask_scores(s, min(CAUSAL ? q + shift - k0 - 4 * h : 0x7fffffff, NK - 1 - k0 - 4 * h));
+      float r_m;
+      m = fmaxf(m, tile_normaliser<VARIANT>(s, alpha, inv_alpha, beta, eps, may_be_unseen, [](float) { return true; }, r_m));
+    }
+    wait_vmem();
+    __syncthreads();
+  };
+  for (int j = tile0; j < ntiles; j += 4) {
+    step(std::integral_constant<int, 0>{}, j);
+    if (j + 2 < ntiles) step(std::integral_constant<int, 1>{}, j + 2);
+  }
+  if (qw < N && h == 0)
+    part[(((size_t)bh * ((N + 31) / 32) + qw / 32) * splits + split) * kPartFloats<D> + 32 * D + r] = m;
+}
+
 // Joins the shares of the SPLIT forward: one wave per 32 rows x 32 columns.  The normaliser of a row
-// is the largest of its shares' (every share's is the largest its tiles asked for, so this is what
-// one sequential pass ends with), accumulators and row sums are brought to it in float32, and
-// the roundings of the ordinary epilogue follow.  Streams the shares once (HBM / Infinity Cache
-// bound).
+// is the largest any of its shares asked for; a share's sums stand relative to the largest of its own
+// and the shares before it.  They are brought to the row's normaliser in float32, and the roundings of
+// the ordinary epilogue follow.  Streams the shares once (HBM / Infinity Cache bound).
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256) void attn_fwd_merge_kernel(
     const float* __restrict__ part, bf16_t* __restrict__ O, float* __restrict__ LSE, int BH, int N,
@@ -504,19 +612,18 @@ __global__ __launch_bounds__(256) void attn_fwd_merge_kernel(
   const int kend = !CAUSAL ? lay.Nk : max(0, min(lay.Nk, qw / kBr * kBr + kBr + shift));
   const int shares = split_shares((kend + kBc - 1) / kBc, splits);
   const float* p = part + (size_t)rows * splits * kPartFloats<D>;
-  float m = -INFINITY;
-  for (int s = 0; s < shares; ++s) m = fmaxf(m, p[(size_t)s * kPartFloats<D> + 32 * D + r]);
+  const float m = largest_norm<D>(p, shares, r);
   f32x16 acc;
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  float l = 0.f;
+  float l = 0.f, m_here = -INFINITY;
 #pragma unroll 4
   for (int s = 0; s < shares; ++s) {
     const float* ps = p + (size_t)s * kPartFloats<D>;
-    const float ms = ps[32 * D + r], ls = ps[32 * D + 32 + r];
-    // a share whose tiles the row does not see has normaliser -inf and adds nothing
-    const float w = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ms - m) * kLog2e);
-    l += m == -INFINITY ? ls : w * ls;
+    m_here = fmaxf(m_here, ps[32 * D + r]);
+    // as long as the row has seen nothing its normaliser is -inf and its sums are zero
+    const float w = m_here == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_here - m) * kLog2e);
+    l = __builtin_fmaf(w, ps[32 * D + 32 + r], l);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const f32x4 v = *reinterpret_cast<const f32x4*>(ps + ((db * 4 + g) * 64 + lane) * 4);
@@ -525,7 +632,7 @@ __global__ __launch_bounds__(256) void attn_fwd_merge_kernel(
     }
   }
   if (qw + r >= N) return;
-  const bool unseen_row = m == -INFINITY && l == 0.f;      // no visible key: O = 0, LSE = -inf
+  const bool unseen_row = m == -INFINITY && l == 0.f;      // no visible key: O = 0, LSE = -inf (l is NaN where scores were -inf)
   const Divisor by_l = make_divisor(l);
   bf16_t* Oq = O + head_base(lay, bh) + (size_t)(qw + r) * lay.sn + 32 * db + 4 * h;
 #pragma unroll
@@ -580,19 +687,20 @@ static hipError_t launch_fwd_split(const void* Q, const void* K, const void* V, 
                                    float* part, int splits, hipStream_t st) {
   constexpr int smem = 4 * kBc * D * 2;
   static std::atomic<bool> attr_set{false};
-  auto kern = attn_fwd_kernel<D, CAUSAL, VARIANT, true, false, true>;
+  auto norms = attn_fwd_norms_kernel<D, CAUSAL, VARIANT>;
+  auto sums = attn_fwd_kernel<D, CAUSAL, VARIANT, true, false, true>;
+  hipError_t e;
   if (!attr_set.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
+    for (const void* kern : {reinterpret_cast<const void*>(norms), reinterpret_cast<const void*>(sums)})
+      if ((e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem)) != hipSuccess) return e;
     attr_set.store(true, std::memory_order_release);
   }
-  const int nqt = (N + kBr - 1) / kBr;
-  hipLaunchKernelGGL(kern, dim3(BH * nqt * splits), dim3(256), smem, st, (const bf16_t*)Q, (const bf16_t*)K,
-                     (const bf16_t*)V, (bf16_t*)O, LSE, N, alpha, beta, eps, FwdExtras{}, lay, 0, part,
-                     splits, kNoOrder);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const dim3 grid(BH * ((N + kBr - 1) / kBr) * splits);
+  hipLaunchKernelGGL(norms, grid, dim3(256), smem, st, (const bf16_t*)Q, (const bf16_t*)K, N, alpha, beta, eps, lay, part, splits);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(sums, grid, dim3(256), smem, st, (const bf16_t*)Q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)O, LSE, N,
+                     alpha, beta, eps, FwdExtras{}, lay, 0, part, splits, kNoOrder);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   const int waves = BH * ((N + 31) / 32) * (D / 32);
   hipLaunchKernelGGL((attn_fwd_merge_kernel<D, CAUSAL>), dim3((waves + 3) / 4), dim3(256), 0, st, part,
                      (bf16_t*)O, LSE, BH, N, lay, splits);
@@ -601,16 +709,24 @@ static hipError_t launch_fwd_split(const void* Q, const void* K, const void* V, 
 
 // Work-groups per query block of the SPLIT forward; 1: the ordinary kernel.
 // The chip is filled once (256 work-groups); twice under the causal mask when blocks differ in work.
-// Shares pay from 1024 keys on (16 tiles), and from 2048 where half of the chip has a block already:
-// a tile takes a lone work-group about 1 us, merging costs 5 us.  Measured, one work-group per block -> shares
-// (us, launches included; B*H, Nq x Nk): 32, 64 x 8192 d128 158 -> 36 (twice the shares: 39), 32, 1 x 8192
-// d128 152 -> 35, 8, 1 x 16384 298 -> 36, 16, 256 x 4096 83 -> 28, 8, 2048 x 2048 causal d128 45 -> 31
-// (once the chip: 36), 1, 16384 x 16384 causal 294 -> 142, 4, 2048 x 2048 full d256 84 -> 41; beyond
-// the limits: 16, 1024 x 1024 d64 causal 19.6 -> 22.5, 16, 2048 x 2048 d128 causal 45 -> 45.
+// A tile takes a lone work-group about 1 us (2 us at d = 256); the two extra launches cost 6 to 10 us,
+// and up to a third of the score products is done twice.  Measured, one work-group per block -> shares (us,
+// launches included; B*H, Nq x Nk):
+//   up to 64 blocks: 32, 64 x 8192 d128 154 -> 46, 8, 1 x 16384 d128 296 -> 40, 16, 256 x 4096 d128 81 -> 33, 4, 2048 x 2048 causal
+//     d128 41 -> 33, full 39 -> 34, d32 24 -> 20, 1, 8192 x 8192 causal d64 113 -> 46, 64, 64 x 1024 d128 25 -> 22, d64 19.1 -> 18.7;
+//   65 to 128 blocks, from 2048 keys on and three work-groups per block (two at d = 256): 8, 2048 x 2048 causal
+//     d128 42 -> 38, d256 88 -> 71, 80, 64 x 2048 d128 43 -> 35, 1, 16384 x 16384 causal 288 -> 200, 128, 64 x 2048 d256 99 -> 88;
+//     beyond the limits: 8, 2048 x 2048 full d64 30 -> 35, d128 40 -> 48, 10, 1536 x 1536 causal d128 33 -> 36;
+//   1024 to 1535 keys and many queries, d <= 128, only with 10 work-groups per block: 2, 1024 x 1024 causal d64
+//     18.7 -> 17.4, d128 23.4 -> 19.9, 4, 1024 x 1024 causal d128 23.7 -> 22.2, even at the limit (2, 1500 x 1030 full d128
+//     25.5 -> 24.6, d64 19.2 -> 19.9, 3, 1024 x 1024 full d64 17.0 -> 18.3); beyond it: 8, 1024 x 1024 causal d64
+//     18.9 -> 22.5, 16, 512 x 1024 causal d128 26 -> 28.
 int attn_fwd_splits(int BH, int Nq, int Nk, int d, int causal, int variant) {
   const long long blocks = (long long)BH * ((Nq + kBr - 1) / kBr);
-  if (variant == 2 || Nk < 1024 || 2 * blocks > (Nk < 2048 ? kNumCUs / 2 : kNumCUs)) return 1;
+  if (variant == 2 || Nk < 1024 || 2 * blocks > kNumCUs) return 1;
   const long long s = (causal && 2LL * Nq > Nk ? 2 : 1) * kNumCUs / blocks;
+  if (4 * blocks > kNumCUs && (Nk < 2048 || (s < 3 && d <= 128))) return 1;
+  if (4LL * Nq > Nk && Nk < 1536 && d <= 128 && s < 10) return 1;
   return split_shares((Nk + kBc - 1) / kBc, s < 32 ? (int)s : 32);
 }
 

@@ -83,3 +83,62 @@ def test_forward_shared_out_takes_strides_and_grouped_heads(lib):
     ws = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
     assert lib.raw().attn_fwd_ws(p(x["Q"]), p(K), p(V), p(O), p(L), p(ws), 256, 0, 0, 0, B, H, H, N, N, d, 1,
                                  0.125, 1, 2.0, 1e-3, None) == 4
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("H,Nq,Nk,d,causal", [(2, 1024, 1024, 64, True), (2, 64, 4097, 128, True), (3, 1, 1500, 96, False),
+                                              (1, 2100, 2100, 32, True), (8, 2048, 2048, 256, False)])
+def test_shares_round_the_probabilities_of_the_one_pass_kernel(lib, H, Nq, Nk, d, causal, variant):
+    """Every share starts from the normaliser a single pass would have reached, so P-bar is rounded the same
+    and only float32 sums change their order.  T tiles in another order differ by about sqrt(T) 2^-24
+    sum|terms| / |sum| <= 2e-5; an element takes another bf16 value (2^-8 off at most) when that crosses a
+    boundary of one of its two roundings: 4 x 2e-5 / 2^-8 = 2e-2 of them at most, sqrt(2e-2) 2^-8 = 6e-4 in the
+    2-norm (P-bar rounded against the share's own maximum: 1e-3 to 3e-3).  Seen: 2e-5 .. 4e-5, and 3.8e-4 where
+    Alg. 1 adds two unit probabilities, whose sums lie on those boundaries.
+    Repeated keys in the first tile make Alg. 3 move the normaliser there: it has to stay moved in
+    all later shares."""
+    x = _inputs(11 * H + Nq + Nk + d, 1, H, Nq, Nk, d, scale=1.5)
+    x["K"][:, :, 1:16:2] = x["K"][:, :, 0:16:2]
+    x["Q"][:, :, ::2] = x["K"][:, :, 3:4] + 0.5 * x["Q"][:, :, ::2]
+    assert lib.raw().attn_fwd_workspace_bytes(1, H, Nq, Nk, d, int(causal), variant) > 0
+    if Nq == Nk:
+        O, L = lib.attn_fwd(x["Q"], x["K"], x["V"], causal, d ** -0.5, variant)
+        ref = lib.attn_fwd_opt(x["Q"], x["K"], x["V"], causal, d ** -0.5, variant, want_counts=True)
+        O1, L1 = ref["O"], ref["LSE"]
+        assert variant == 0 or ref["fired"].sum() > 0
+    else:
+        O, L = lib.attn_fwd_rect(x["Q"], x["K"], x["V"], causal, d ** -0.5, variant)
+        O1, L1 = torch.empty_like(O), torch.empty_like(L)
+        p = lambda t: t.data_ptr()
+        assert lib.raw().attn_fwd_rect(p(x["Q"]), p(x["K"]), p(x["V"]), p(O1), p(L1), 1, H, Nq, Nk, d, int(causal), d ** -0.5,
+                                       variant, 2.0, 1e-3, torch.cuda.current_stream().cuda_stream) == 0
+    differ = (O != O1).double().mean().item()
+    rel = ((O.double() - O1.double()).norm() / O1.double().norm()).item()
+    print(f"shares H{H} {Nq}x{Nk} d{d} c{causal} v{variant}: differ {differ:.1e} rel {rel:.1e}")
+    assert differ <= 2e-2 and rel <= 6e-4
+    assert torch.allclose(L, L1, rtol=0, atol=2e-6 * L1.abs().max().item())
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("N", [1024, 1030])
+def test_shares_with_infinite_scores(lib, N, variant):
+    """Rows whose scores overflow to -inf, to +inf, or in some tiles only, give what the one-pass kernel
+    gives (NaN or 0, by the instantiation that serves the size)."""
+    x = _inputs(N, 1, 2, N, N, 64)
+    x["Q"][:, :, 5] = 3e38
+    x["Q"][:, :, 700] = -3e38
+    x["Q"][:, :, 900] = 3e38
+    x["K"][:, 0] = -x["K"][:, 0].abs()
+    x["K"][:, 1, :640] = -x["K"][:, 1, :640].abs()
+    x["K"][:, 1, 640:] = 0
+    O, L = lib.attn_fwd(x["Q"], x["K"], x["V"], True, 0.125, variant)
+    ref_O, ref_L = torch.empty_like(O), torch.empty_like(L)
+    p = lambda t: t.data_ptr()
+    assert lib.raw().attn_fwd_workspace_bytes(1, 2, N, N, 64, 1, variant) > 0
+    assert lib.raw().attn_fwd_ex(p(x["Q"]), p(x["K"]), p(x["V"]), p(ref_O), p(ref_L), 1, 2, N, 64, 1, 0.125, variant,
+                                 2.0, 1e-3, torch.cuda.current_stream().cuda_stream) == 0
+    for a, b in ((O, ref_O), (L, ref_L)):
+        assert torch.equal(a.isnan(), b.isnan())
+        ok = ~b.isnan()
+        assert torch.allclose(a[ok].float(), b[ok].float(), rtol=2.0 ** -7, atol=1e-4)
+    assert ref_O[0, 0, 5].isnan().all().item() == (N % 128 == 0)
