@@ -4,6 +4,7 @@
 #include <atomic>
 #include <cmath>
 #include "../../include/attn.h"
+#include "row_offset.hpp"
 
 // Mirrors the device-side struct of the same name (common.hpp): element (b,h,n,k) of a bf16
 // tensor lives at b*sb + h*sh + n*sn + k.
@@ -47,12 +48,12 @@ Layout contiguous(int H, int N, int d, int H_kv = 0, int Nk = 0) {
 }
 
 // Strides of the strided entry points: positive multiples of 8 elements (rows start on 16-byte
-// boundaries), rows at least d apart, and small enough for the 32-bit per-lane offsets the tile
-// loader uses inside a 64-row tile.
+// boundaries), rows at least d apart, and small enough for the unsigned 32-bit per-lane offsets the
+// tile loader uses inside a tile of up to 128 rows (row_offset.hpp).
 bool strides_ok(long long sb, long long sh, long long sn, int d) {
   if (sb <= 0 || sh <= 0 || sn <= 0) return false;
   if ((sb & 7) || (sh & 7) || (sn & 7)) return false;
-  return sn >= d && sn < (1ll << 24);
+  return sn >= d && sn < kRowStrideLimit;
 }
 
 // Shape check shared by all entry points.  Returns ATTN_OK with *empty = true for B*H == 0.

@@ -17,6 +17,7 @@
 #include <cmath>
 #include <optional>
 #include "../../include/attn.h"
+#include "row_offset.hpp"
 
 namespace {
 
@@ -112,7 +113,7 @@ struct Attention : torch::autograd::Function<Attention> {
 bool strides_fit(const Tensor& t, int64_t d) {
   for (int i = 0; i < 3; ++i)
     if (t.stride(i) <= 0 || t.stride(i) % 8 != 0) return false;
-  return t.stride(2) >= d && t.stride(2) < (1ll << 24);
+  return t.stride(2) >= d && t.stride(2) < kRowStrideLimit;
 }
 
 bool plain(const Tensor& t, c10::DeviceIndex device) {

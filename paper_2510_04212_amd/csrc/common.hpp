@@ -11,6 +11,7 @@
 // of 16-wide k-chunk c, i.e. k-slot (h, j) of chunk c  <->  tile row 16c + 8*(j/4) + 4h + (j%4).
 #pragma once
 #include "block_order.hpp"
+#include "row_offset.hpp"
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <atomic>
@@ -167,7 +168,7 @@ DEVI const bf16_t* wave_uniform(const bf16_t* p) {
 }
 
 template <int D, int R = 64, int NW = 4> struct TileLoader {
-  static_assert(R == 32 || R == 64 || R == 128, "rows per tile");
+  static_assert((R == 32 || R == 64 || R == 128) && R <= kMaxTileRows, "rows per tile");
   static constexpr int NRB = R / 16;             // 16-row blocks
   static constexpr int NCB = kColBlocks<D>;
   static constexpr int WPR = NW > NRB ? NW / NRB : 1;    // waves that share a 16-row block ...
@@ -204,7 +205,7 @@ template <int D, int R = 64, int NW = 4> struct TileLoader {
 #pragma unroll
     for (int g = 0; g < RPW; ++g) {
       const int rr = row + 16 * g;
-      p.voff[g] = (unsigned)((RAGGED ? min(rr, N - 1 - row0) : rr) * (2 * sn) + chunk);
+      p.voff[g] = row_offset(RAGGED ? min(rr, N - 1 - row0) : rr, sn, chunk);
     }
     return p;
   }

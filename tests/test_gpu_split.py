@@ -142,3 +142,22 @@ def test_shares_with_infinite_scores(lib, N, variant):
         ok = ~b.isnan()
         assert torch.allclose(a[ok].float(), b[ok].float(), rtol=2.0 ** -7, atol=1e-4)
     assert ref_O[0, 0, 5].isnan().all().item() == (N % 128 == 0)
+
+
+@pytest.mark.parametrize("N,stride", [(200, (1 << 24) - 8), (512, 9_000_000)])
+def test_rows_far_apart(lib, N, stride):
+    """Row strides at which the last rows of a 128-row tile lie 2 to 4 GiB behind its first (V_j at d = 128,
+    and the 128-row tiles of four wave groups): the bits of the contiguous call."""
+    d = 128
+    x = _inputs(N, 1, 1, N, N, d)
+    far = torch.empty((N - 1) * stride + 8 * d, dtype=torch.bfloat16, device=DEV)
+    view = lambda i: far[i * d:].as_strided((1, 1, N, d), (8, 8, stride, 1))
+    t = {n: view(i) for i, n in enumerate(("Q", "K", "V", "dO", "O", "dQ", "dK", "dV"))}
+    for n in ("Q", "K", "V", "dO"):
+        t[n].copy_(x[n])
+    want = _run(lib, x, True, d ** -0.5, 1)
+    _, L = lib.attn_fwd_strided(t["Q"], t["K"], t["V"], True, d ** -0.5, 1, O=t["O"])
+    lib.attn_bwd_strided(t["Q"], t["K"], t["V"], t["O"], t["dO"], L, True, d ** -0.5, 1, dQ=t["dQ"], dK=t["dK"], dV=t["dV"])
+    assert torch.equal(L, want["L"])
+    for n in ("O", "dQ", "dK", "dV"):
+        assert torch.equal(t[n], want[n]), n
