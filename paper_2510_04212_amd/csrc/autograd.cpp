@@ -9,6 +9,7 @@
 // apply() takes the plain case - bf16 tensors on the current GPU with shapes, strides, alignments and
 // parameters the library accepts - and returns nothing for any other: the caller's Python node then
 // handles it, or raises what it always raised.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/utils/pybind.h>
 #include <ATen/ATen.h>
@@ -31,7 +32,18 @@ void* current_stream(const Tensor& t) {
   return static_cast<void*>(c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(t.get_device()).stream());
 }
 
-void check(int status) { TORCH_CHECK(status == ATTN_OK, attn_status_string(status)); }
+// binding.AttnError(status), as the Python node raises it.  Called without the interpreter lock, in the
+// backward on the engine's thread: the error travels as torch's python_error.
+void check(int status) {
+  if (status == ATTN_OK) return;
+  pybind11::gil_scoped_acquire lock;
+  const auto type = pybind11::module_::import("paper_2510_04212_amd.binding").attr("AttnError");
+  const pybind11::object error = type(status);
+  PyErr_SetObject(type.ptr(), error.ptr());
+  python_error e;
+  e.persist();
+  throw e;
+}
 
 struct Attention : torch::autograd::Function<Attention> {
   static Tensor forward(AutogradContext* ctx, const Tensor& q_in, const Tensor& k_in, const Tensor& v_in,
@@ -136,8 +148,13 @@ std::optional<Tensor> apply(const Tensor& q, const Tensor& k, const Tensor& v, b
   const float s = (float)scale, b = (float)beta, e = (float)eps;
   if (!(s > 0.f) || !std::isfinite(s) || !(b > 1.f) || !std::isfinite(b) || !(e >= 0.f) || !std::isfinite(e)) return std::nullopt;
   if (!(q.is_contiguous() && k.is_contiguous() && v.is_contiguous()) && !strides_fit(q, d)) return std::nullopt;
-  pybind11::gil_scoped_release release;
-  return Attention::apply(q, k, v, causal, scale, variant, beta, eps);
+  try {
+    pybind11::gil_scoped_release release;
+    return Attention::apply(q, k, v, causal, scale, variant, beta, eps);
+  } catch (python_error& e) {        // pybind11 does not know the type
+    e.restore();
+    throw pybind11::error_already_set();
+  }
 }
 
 }  // namespace

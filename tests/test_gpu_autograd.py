@@ -74,9 +74,9 @@ def test_what_was_refused_is_refused_the_same_way(lib):
     with pytest.raises(lib.AttnError):                        # a misaligned view
         flat = torch.zeros(64 * 64 + 8, dtype=torch.bfloat16, device=DEV)[4:4 + 64 * 64].view(1, 1, 64, 64)
         attention(flat, flat, flat)
-    with pytest.raises(RuntimeError):                         # function transforms: the Python node's own error
+    with pytest.raises(RuntimeError, match="setup_context"):  # function transforms: the Python node's own error
         torch.func.vmap(lambda a: attention(a, k, v))(q[None])
-    with torch.autograd.forward_ad.dual_level(), pytest.raises(Exception):
+    with torch.autograd.forward_ad.dual_level(), pytest.raises(NotImplementedError, match="jvp"):
         attention(torch.autograd.forward_ad.make_dual(q, q), k, v)
     empty = torch.zeros((0, 2, 64, 64), dtype=torch.bfloat16, device=DEV)
     assert attention(empty, empty, empty).shape == empty.shape
@@ -92,3 +92,23 @@ def test_expanded_dimensions_are_refused(lib, shape):
         with pytest.raises(lib.AttnError) as e:
             call()
         assert e.value.status == 2
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[2], CASES[3], CASES[5]], ids=str)     # every form of the node
+def test_a_refused_gradient_is_refused_the_same_way(lib, case):
+    """An incoming gradient that is not 16-byte aligned: AttnError with its status from both nodes."""
+    from paper_2510_04212_amd import autograd as A
+    data = _qkv(*case)
+    for node in (lambda q, k, v: A.attention(q, k, v, True, 0.1, 1),
+                 lambda q, k, v: A._FlashAttention.apply(q, k, v, True, 0.1, 1, None, None)):
+        q, k, v = (t.detach().requires_grad_(True) for t in data)
+        o = node(q, k, v)
+        span = sum((n - 1) * s for n, s in zip(o.shape, o.stride())) + 1
+        bad = torch.zeros(span + 4, dtype=torch.bfloat16, device=DEV)[4:].as_strided(o.shape, o.stride(), 4)
+        assert bad.data_ptr() % 16 == 8
+        for call in (lambda: torch.autograd.grad(o, q, bad, retain_graph=True), lambda: o.backward(bad, retain_graph=True)):
+            with pytest.raises(lib.AttnError) as e:
+                call()
+            assert e.value.status == 2 and "misaligned" in str(e.value)
+        good = torch.autograd.grad(o, (q, k, v), torch.ones_like(o))     # the graph is intact afterwards
+        assert all(g.isfinite().all() for g in good)
