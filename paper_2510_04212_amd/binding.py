@@ -130,19 +130,29 @@ def _bhnd(t, name):
     return t.shape
 
 
-def _fwd_shared_out(Q, K, V, O, LSE, strides, H_kv, Nk, causal, softmax_scale, variant, beta, eps, stream):
+def fwd_workspace_bytes(B, H, Nq, Nk, d, causal, variant=STANDARD):
+    """Workspace the forward can use for this problem (0: none, one pass over the keys is as fast)."""
+    return int(_lib.attn_fwd_workspace_bytes(B, H, Nq, Nk, d, int(bool(causal)), int(variant)))
+
+
+def _fwd_shared_out(Q, K, V, O, LSE, strides, H_kv, Nk, causal, softmax_scale, variant, beta, eps, stream,
+                    workspace, allocate):
     """attn_fwd_ws of the C ABI where the library wants a workspace for this problem (grids of few
-    query blocks); False, and nothing done, otherwise."""
+    query blocks) and there is one, the caller's or (`allocate`) a new one; False, and nothing done, otherwise."""
     B, H, N, d = Q.shape
-    need = _lib.attn_fwd_workspace_bytes(B, H, N, Nk, d, int(bool(causal)), int(variant))
-    if need == 0:
+    need = fwd_workspace_bytes(B, H, N, Nk, d, causal, variant)
+    if need == 0 or (workspace is None and not allocate):
         return False
-    if stream is not None and stream != torch.cuda.current_stream():
+    if workspace is not None:
+        if not workspace.is_cuda or not workspace.is_contiguous():
+            raise ValueError("workspace must be a contiguous CUDA tensor")
+        need = workspace.numel() * workspace.element_size()
+    elif stream is not None and stream != torch.cuda.current_stream():
         with torch.cuda.stream(stream):          # the workspace belongs to the stream that uses it
-            ws = torch.empty(need, dtype=torch.uint8, device=Q.device)
+            workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
     else:
-        ws = torch.empty(need, dtype=torch.uint8, device=Q.device)
-    _check(_lib.attn_fwd_ws(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(ws), need, *strides, B, H, H_kv,
+        workspace = torch.empty(need, dtype=torch.uint8, device=Q.device)
+    _check(_lib.attn_fwd_ws(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(workspace), need, *strides, B, H, H_kv,
                             N, Nk, d, int(bool(causal)), float(softmax_scale), int(variant),
                             float(DEFAULT_BETA if beta is None else beta),
                             float(DEFAULT_EPS if eps is None else eps), _stream(stream)))
@@ -150,17 +160,25 @@ def _fwd_shared_out(Q, K, V, O, LSE, strides, H_kv, Nk, causal, softmax_scale, v
 
 
 def attn_fwd(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=None,
-             O=None, LSE=None, stream=None):
-    """O, LSE = attention forward (attn_fwd / attn_fwd_ex of the C ABI)."""
+             O=None, LSE=None, stream=None, workspace=None, one_pass=False):
+    """O, LSE = attention forward: attn_fwd_ws of the C ABI where few query blocks meet many keys
+    (fwd_workspace_bytes(...) > 0), attn_fwd / attn_fwd_ex otherwise.  The two add the same terms in
+    another float32 order (a bf16 step in a few of 10^4 elements of O).
+
+    workspace: a CUDA tensor of at least fwd_workspace_bytes(...) bytes; one is allocated when absent, unless
+    both O and LSE are given: such a call allocates nothing and runs the one-pass kernel.
+    one_pass: the one-pass kernel (that of attn_fwd_opt, bit for bit) in any case."""
     B, H, N, d = _bhnd(Q, "Q")
     for n, t in (("K", K), ("V", V)):
         if _bhnd(t, n) != (B, H, N, d):
             raise ValueError(f"{n} shape differs from Q")
+    allocate = O is None or LSE is None
     if O is None:
         O = torch.empty_like(Q)
     if LSE is None:
         LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
-    if _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), H, N, causal, softmax_scale, variant, beta, eps, stream):
+    if not one_pass and _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), H, N, causal, softmax_scale, variant, beta, eps,
+                                        stream, workspace, allocate):
         return O, LSE
     if beta is None and eps is None:
         st = _lib.attn_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), B, H, N, d, int(bool(causal)),
@@ -316,19 +334,20 @@ def _strided_bhnd(t, name, like=None):
 
 
 def attn_fwd_strided(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=None,
-                     O=None, LSE=None, stream=None):
+                     O=None, LSE=None, stream=None, workspace=None, one_pass=False):
     """attn_fwd_strided of the C ABI.  Q, K, V (and O, when given) share one set of strides;
-    O defaults to a tensor laid out like Q."""
+    O defaults to a tensor laid out like Q.  workspace, one_pass: as in attn_fwd."""
     (B, H, N, d), (sb, sh, sn, _) = _strided_bhnd(Q, "Q")
     for n, t in (("K", K), ("V", V)):
         _strided_bhnd(t, n, Q)
+    allocate = O is None or LSE is None
     O = torch.empty_strided(Q.shape, Q.stride(), dtype=Q.dtype, device=Q.device) if O is None else O
     _strided_bhnd(O, "O", Q)
     if LSE is None:
         LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
     # an expanded dimension (stride 0) is for attn_fwd_strided to refuse: to attn_fwd_ws three zeros mean contiguous
-    if min(sb, sh, sn) > 0 and _fwd_shared_out(Q, K, V, O, LSE, (sb, sh, sn), H, N, causal, softmax_scale, variant,
-                                               beta, eps, stream):
+    if not one_pass and min(sb, sh, sn) > 0 and _fwd_shared_out(Q, K, V, O, LSE, (sb, sh, sn), H, N, causal, softmax_scale,
+                                                                variant, beta, eps, stream, workspace, allocate):
         return O, LSE
     _check(_lib.attn_fwd_strided(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), sb, sh, sn, B, H, N, d,
                                  int(bool(causal)), float(softmax_scale), int(variant),
@@ -359,15 +378,18 @@ def attn_bwd_strided(Q, K, V, O, dO, LSE, causal, softmax_scale, variant=STANDAR
     return dQ, dK, dV
 
 
-def attn_fwd_gqa(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=None, stream=None):
-    """Grouped-query forward: Q [B,H,N,d], K and V [B,H_kv,N,d] (contiguous)."""
+def attn_fwd_gqa(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=None, stream=None,
+                 workspace=None, one_pass=False):
+    """Grouped-query forward: Q [B,H,N,d], K and V [B,H_kv,N,d] (contiguous).
+    workspace, one_pass: as in attn_fwd."""
     B, H, N, d = _bhnd(Q, "Q")
     Bk, Hkv, Nk, dk = _bhnd(K, "K")
     if _bhnd(V, "V") != K.shape or (Bk, Nk, dk) != (B, N, d):
         raise ValueError("K and V must be [B,H_kv,N,d] with the batch, length and head size of Q")
     O = torch.empty_like(Q)
     LSE = torch.empty((B, H, N), dtype=torch.float32, device=Q.device)
-    if _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), Hkv, N, causal, softmax_scale, variant, beta, eps, stream):
+    if not one_pass and _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), Hkv, N, causal, softmax_scale, variant, beta, eps,
+                                        stream, workspace, True):
         return O, LSE
     _check(_lib.attn_fwd_gqa(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), B, H, Hkv, N, d,
                              int(bool(causal)), float(softmax_scale), int(variant),
@@ -395,16 +417,18 @@ def attn_bwd_gqa(Q, K, V, O, dO, LSE, causal, softmax_scale, variant=STANDARD, w
     return dQ, dK, dV
 
 
-def attn_fwd_rect(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=None, stream=None):
+def attn_fwd_rect(Q, K, V, causal, softmax_scale, variant=STANDARD, beta=None, eps=None, stream=None,
+                  workspace=None, one_pass=False):
     """Forward with different numbers of queries and keys: Q [B,H,Nq,d], K and V [B,H,Nk,d]
-    (contiguous); the causal mask is aligned at the bottom right."""
+    (contiguous); the causal mask is aligned at the bottom right.  workspace, one_pass: as in attn_fwd."""
     B, H, Nq, d = _bhnd(Q, "Q")
     Bk, Hk, Nk, dk = _bhnd(K, "K")
     if _bhnd(V, "V") != K.shape or (Bk, Hk, dk) != (B, H, d):
         raise ValueError("K and V must be [B,H,Nk,d] with the batch, heads and head size of Q")
     O = torch.empty_like(Q)
     LSE = torch.empty((B, H, Nq), dtype=torch.float32, device=Q.device)
-    if _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), H, Nk, causal, softmax_scale, variant, beta, eps, stream):
+    if not one_pass and _fwd_shared_out(Q, K, V, O, LSE, (0, 0, 0), H, Nk, causal, softmax_scale, variant, beta, eps,
+                                        stream, workspace, True):
         return O, LSE
     _check(_lib.attn_fwd_rect(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), B, H, Nq, Nk, d,
                               int(bool(causal)), float(softmax_scale), int(variant),

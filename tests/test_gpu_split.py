@@ -161,3 +161,46 @@ def test_rows_far_apart(lib, N, stride):
     assert torch.equal(L, want["L"])
     for n in ("O", "dQ", "dK", "dV"):
         assert torch.equal(t[n], want[n]), n
+
+
+def test_the_caller_decides_about_the_workspace(lib):
+    """Few heads, 1200 keys.  Own outputs: nothing is allocated and one pass runs, as the C entry points
+    without a workspace do; own workspace: used, or refused when it is too small or misaligned; one_pass: the bits
+    of attn_fwd_opt.  In every layout."""
+    B, H, N, d = 1, 4, 1200, 64
+    x = _inputs(9, B, H, N, N, d)
+    args = (x["Q"], x["K"], x["V"], True, 0.125, 1)
+    need = lib.fwd_workspace_bytes(B, H, N, N, d, True, 1)
+    assert need > 0
+    ws = torch.empty(need + 256, dtype=torch.uint8, device=DEV)
+    O, L = lib.attn_fwd(*args)
+    one = lib.attn_fwd_opt(*args)
+    s = lambda t: t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    st = (s(x["Q"]), s(x["K"]), s(x["V"]), True, 0.125, 1)
+    forms = {"plain": (lib.attn_fwd, args), "strided": (lib.attn_fwd_strided, st), "gqa": (lib.attn_fwd_gqa, args),
+             "rect": (lib.attn_fwd_rect, args)}
+    for name, (f, a) in forms.items():
+        o, l = f(*a, one_pass=True)
+        assert torch.equal(o, one["O"]) and torch.equal(l, one["LSE"]), name
+        o, l = f(*a, workspace=ws[:need])
+        assert torch.equal(o, O) and torch.equal(l, L), name
+        for bad in (ws[:need - 16], ws[8:]):
+            with pytest.raises(lib.AttnError) as e:
+                f(*a, workspace=bad)
+            assert e.value.status == 4, name
+        if name in ("plain", "strided"):
+            o, l = torch.empty_like(a[0]), torch.empty_like(L)
+            count = lambda: torch.cuda.memory_stats()["allocation.all.allocated"]
+            before = count()
+            f(*a, O=o, LSE=l)
+            f(*a, O=o, LSE=l, workspace=ws)
+            assert count() == before, name
+            f(*a, O=o, LSE=l)
+            assert torch.equal(o, one["O"]) and torch.equal(l, one["LSE"]), name
+    with pytest.raises(ValueError):
+        lib.attn_fwd(*args, workspace=torch.empty(need, dtype=torch.uint8))
+    p = lambda t: t.data_ptr()
+    o, l = torch.empty_like(O), torch.empty_like(L)
+    assert lib.raw().attn_fwd_ws(p(x["Q"]), p(x["K"]), p(x["V"]), p(o), p(l), None, 0, 0, 0, 0, B, H, H, N, N, d, 1, 0.125, 1,
+                                 2.0, 1e-3, torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(o, one["O"]) and torch.equal(l, one["LSE"])
