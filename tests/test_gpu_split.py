@@ -1,10 +1,12 @@
 """GPU tests of the paths that share one block's work between wave groups or work-groups and add
 partial results: sizes on both sides of the rules that choose them, remainders of tiles and blocks,
 against the fp64 oracle (the tolerances are those of the other parity tests)."""
+import numpy as np
 import pytest
 import torch
 
-from test_gpu_parity import DEV, check_head
+from oracle import exact, metrics
+from test_gpu_parity import DEV, TOL_ABS, TOL_REL, check_head
 from test_gpu_rect import _inputs, _run
 
 pytestmark = pytest.mark.gpu
@@ -204,3 +206,59 @@ def test_the_caller_decides_about_the_workspace(lib):
     assert lib.raw().attn_fwd_ws(p(x["Q"]), p(x["K"]), p(x["V"]), p(o), p(l), None, 0, 0, 0, 0, B, H, H, N, N, d, 1, 0.125, 1,
                                  2.0, 1e-3, torch.cuda.current_stream().cuda_stream) == 0
     assert torch.equal(o, one["O"]) and torch.equal(l, one["LSE"])
+
+
+@pytest.mark.parametrize("layout", ["bnhd", "fused"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("H,N,d", [(2, 512, 32), (2, 512, 64), (3, 700, 64), (2, 640, 96), (2, 512, 128), (3, 1025, 128),
+                                   (2, 512, 256), (2, 600, 256), (33, 1024, 96), (33, 1024, 128), (17, 1000, 128)], ids=str)
+def test_strides_with_wave_groups(lib, H, N, d, causal, layout):
+    """The wave-group kernels (four groups, two groups, dQ's two at d = 256) on strided tensors: the bits of
+    the contiguous call, which the oracle tests above cover."""
+    x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
+    O, L = lib.attn_fwd(x["Q"], x["K"], x["V"], causal, d ** -0.5, 1)
+    want = lib.attn_bwd(x["Q"], x["K"], x["V"], O, x["dO"], L, causal, d ** -0.5, 1)
+    if layout == "fused":       # every bf16 tensor a slice of one [1, N, 5, H, d] buffer (outputs: of another)
+        buf, out = (torch.full((1, N, 5, H, d), float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        part = lambda t, i: t[:, :, i].permute(0, 2, 1, 3)
+    else:
+        buf, out = (torch.full((5, 1, N, H, d), float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        part = lambda t, i: t[i].permute(0, 2, 1, 3)
+    q, k, v, do, o = (part(buf, i) for i in range(5))
+    for t, src in ((q, "Q"), (k, "K"), (v, "V"), (do, "dO")):
+        t.copy_(x[src])
+    assert q.stride(2) != d
+    _, Ls = lib.attn_fwd_strided(q, k, v, causal, d ** -0.5, 1, O=o)
+    got = lib.attn_bwd_strided(q, k, v, o, do, Ls, causal, d ** -0.5, 1, *(part(out, i) for i in range(3)))
+    assert torch.equal(o, O) and torch.equal(Ls, L)
+    for n, a, b in zip(("dQ", "dK", "dV"), got, want):
+        assert torch.equal(a, b), n
+    for i in (3, 4):            # nothing is written beside the outputs
+        assert part(out, i).isnan().all()
+
+
+@pytest.mark.parametrize("Hkv,group,N,d,causal", [
+    (2, 2, 512, 32, False), (2, 2, 512, 32, True), (2, 4, 577, 64, False), (2, 2, 545, 96, True), (2, 2, 512, 96, False),
+    (1, 4, 700, 128, False), (2, 2, 640, 128, True),                                  # four groups
+    (52, 2, 640, 96, True), (52, 2, 640, 128, True), (65, 2, 500 + 12, 128, True),    # two groups (257 to 512 key blocks)
+    (27, 2, 640, 32, False), (27, 2, 640, 64, False), (27, 3, 600, 96, False), (33, 2, 512, 128, False),   # two (129 to 256)
+    (52, 2, 640, 64, True), (2, 2, 640, 256, False)], ids=str)                        # one
+def test_grouped_queries_with_wave_groups_against_the_oracle(lib, Hkv, group, N, d, causal):
+    """dQ per query head, dK and dV of a shared head the sum over its query heads, all in 64 bits."""
+    H = Hkv * group
+    x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
+    x["K"], x["V"] = x["K"][:, :Hkv].contiguous(), x["V"][:, :Hkv].contiguous()
+    x["dO"] = x["dO"] / group                      # sums stay in the range the tolerances are for
+    O, L = lib.attn_fwd_gqa(x["Q"], x["K"], x["V"], causal, d ** -0.5, 1)
+    dQ, dK, dV = lib.attn_bwd_gqa(x["Q"], x["K"], x["V"], O, x["dO"], L, causal, d ** -0.5, 1)
+    f64 = lambda t, h: t[0, h].double().cpu().numpy()
+    for hk in sorted({0, Hkv - 1}):
+        sums = [0.0, 0.0]
+        for h in range(hk * group, (hk + 1) * group):
+            ref = exact.forward_backward(f64(x["Q"], h), f64(x["K"], hk), f64(x["V"], hk), f64(x["dO"], h), d ** -0.5, causal)
+            for n, got, want in (("O", O, ref[0]), ("dQ", dQ, ref[2])):
+                assert metrics.max_abs(f64(got, h), want) <= TOL_ABS and metrics.rel_l2(f64(got, h), want) <= TOL_REL, (n, h)
+            sums = [a + b for a, b in zip(sums, ref[3:5])]
+        for n, got, want in (("dK", dK, sums[0]), ("dV", dV, sums[1])):
+            g = f64(got, hk)
+            assert np.isfinite(g).all() and metrics.max_abs(g, want) <= TOL_ABS and metrics.rel_l2(g, want) <= TOL_REL, (n, hk)
