@@ -68,8 +68,10 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 // from L2 for half as many keys.
 template <int G> constexpr int kKeyWaves = G == 4 ? 2 : 4;               // waves per group, 32 keys each
 template <int D, int G> constexpr int kQTile = D == 128 || G == 4 ? 32 * G : 64;   // query rows per streamed tile
-// D <= 64 has the registers for both 32-query blocks of a tile at once in a software pipeline.
-template <int D, int G> constexpr bool kPipelined = D <= 64 && G == 1;
+// D <= 64 has the registers for both 32-query blocks of a tile at once in a software pipeline, except with
+// grouped queries and no mask at D = 64, where 29 registers spilled (whole backward, pipeline -> plain blocks, us:
+// B8 H32/8 N2048 985 -> 867, B4 H32/8 N1111 229 -> 188).
+template <int D, int G, bool CAUSAL, bool GROUPED> constexpr bool kPipelined = D <= 64 && G == 1 && !(D == 64 && GROUPED && !CAUSAL);
 // dK / dV rows leave through a per-wave LDS staging area (store_rows_staged) where the row width
 // allows it; it overlays the tile buffers where it would otherwise cost a resident work-group, and
 // is left out at D = 256 (no room).
@@ -420,8 +422,9 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
           __builtin_amdgcn_sched_barrier(0);
         }
       };
-      if (kPipelined<D, G> && (!CAUSAL || qt0 + shift >= kw + 31) && (!RAGGED || qt0 + QT <= N)) {
-        if constexpr (kPipelined<D, G>) tile_pipelined();
+      constexpr bool pipelined = kPipelined<D, G, CAUSAL, GROUPED>;
+      if (pipelined && (!CAUSAL || qt0 + shift >= kw + 31) && (!RAGGED || qt0 + QT <= N)) {
+        if constexpr (pipelined) tile_pipelined();
       } else {
 #pragma unroll
         for (int qb = 0; qb < QT / 32 / G; ++qb) {

@@ -242,7 +242,7 @@ def test_strides_with_wave_groups(lib, H, N, d, causal, layout):
     (1, 4, 700, 128, False), (2, 2, 640, 128, True),                                  # four groups
     (52, 2, 640, 96, True), (52, 2, 640, 128, True), (65, 2, 500 + 12, 128, True),    # two groups (257 to 512 key blocks)
     (27, 2, 640, 32, False), (27, 2, 640, 64, False), (27, 3, 600, 96, False), (33, 2, 512, 128, False),   # two (129 to 256)
-    (52, 2, 640, 64, True), (2, 2, 640, 256, False)], ids=str)                        # one
+    (52, 2, 640, 64, True), (52, 2, 640, 64, False), (2, 2, 640, 256, False)], ids=str)                        # one
 def test_grouped_queries_with_wave_groups_against_the_oracle(lib, Hkv, group, N, d, causal):
     """dQ per query head, dK and dV of a shared head the sum over its query heads, all in 64 bits."""
     H = Hkv * group
