@@ -130,6 +130,10 @@ def _bhnd(t, name):
     return t.shape
 
 
+# below, the library wants no workspace whatever the grid: not worth asking (1 us of host time in a 12 us call)
+_MIN_SHARED_KEYS = 1024
+
+
 def fwd_workspace_bytes(B, H, Nq, Nk, d, causal, variant=STANDARD):
     """Workspace the forward can use for this problem (0: none, one pass over the keys is as fast)."""
     return int(_lib.attn_fwd_workspace_bytes(B, H, Nq, Nk, d, int(bool(causal)), int(variant)))
@@ -139,9 +143,11 @@ def _fwd_shared_out(Q, K, V, O, LSE, strides, H_kv, Nk, causal, softmax_scale, v
                     workspace, allocate):
     """attn_fwd_ws of the C ABI where the library wants a workspace for this problem (grids of few
     query blocks) and there is one, the caller's or (`allocate`) a new one; False, and nothing done, otherwise."""
+    if Nk < _MIN_SHARED_KEYS or (workspace is None and not allocate):
+        return False
     B, H, N, d = Q.shape
     need = fwd_workspace_bytes(B, H, N, Nk, d, causal, variant)
-    if need == 0 or (workspace is None and not allocate):
+    if need == 0:
         return False
     if workspace is not None:
         if not workspace.is_cuda or not workspace.is_contiguous():

@@ -62,6 +62,18 @@ def test_key_tile_and_workspace_queries(binding):
     assert binding.bwd_workspace_bytes(0, 4, 128, 64) == 0
 
 
+def test_no_forward_workspace_below_the_length_the_binding_asks_from(binding):
+    """Below binding._MIN_SHARED_KEYS keys the library never wants a workspace, at it it does: the binding need not ask."""
+    n = binding._MIN_SHARED_KEYS
+    for d in (32, 64, 96, 128, 256):
+        for causal in (False, True):
+            for variant in (0, 1, 2):
+                for Nk in (1, 63, 64, 512, 1000, n - 1):
+                    assert all(binding.fwd_workspace_bytes(B, H, Nq, Nk, d, causal, variant) == 0
+                               for B, H in ((1, 1), (1, 8), (4, 32)) for Nq in (1, 64, Nk, 2 * Nk))
+                assert (binding.fwd_workspace_bytes(1, 1, 64, n, d, causal, variant) > 0) == (variant != 2)
+
+
 def test_argument_validation_happens_on_the_host(binding):
     """None of these calls reaches a kernel launch (no GPU is needed to run them)."""
     lib = binding.raw()
