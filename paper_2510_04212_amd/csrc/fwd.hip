@@ -84,16 +84,6 @@ template <int D> DEVI float largest_norm(const float* rows, int n, int r) {
 // first tile of share s (share `shares` would be the end)
 DEVI int share_begin(int tiles, int s, int shares) { return tiles * s / shares; }
 
-// Mask of a tile that crosses the diagonal or the sequence end: element (kb, i) of the lane is key
-// k0 + 4h + c with c = 32 kb + 8 (i / 4) + i % 4 a compile-time constant; keys with c > lim become -inf.
-DEVI void mask_scores(f32x16 (&s)[2], int lim) {
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
-}
-
 // Normaliser a row asks for in one key tile (the two lanes of the row get the same): Alg. 1 (VARIANT 0) its
 // maximum r_m, Alg. 3 (VARIANT 1) what the rule makes of it.  s: raw scores, masked ones -inf.
 // may_be_unseen: a row may see no key of the tile.  allowed(r_m): whether a guard lets the rule apply.
@@ -297,10 +287,16 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
       // ---- mask: causal (key > query) in the tile that crosses the diagonal, and keys beyond
       // the sequence end in the last, partial tile -> -inf
       if ((CAUSAL && (k0 + kBc - 1 > qw + shift)) || (RAGGED && k0 + kBc > NK)) {
-        // one per-lane limit for both conditions
+        // element (kb, i) of this lane is key k0 + 4h + c with c = 32 kb + 8 (i / 4) + i % 4 a
+        // compile-time constant: masked <=> c > lim, one per-lane limit for both conditions.  (Written
+        // out here and not called: as a function its 32 comparisons come first and spill scalar registers.)
         int lim = CAUSAL ? q + shift - k0 - 4 * h : 0x7fffffff;
         if (RAGGED) lim = min(lim, NK - 1 - k0 - 4 * h);
-        mask_scores(s, lim);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
       }
       if (VARIANT == kRowStats) {
         // two largest values seen by this lane (duplicates count: a value met twice is both)
@@ -575,8 +571,14 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, D <= 128 ? 2 : 1))) void at
         for (int kb = 0; kb < 2; ++kb)
           s[kb] = mfma32(lds_row8<D>(BUF * STEP_BYTES, fo, kBc * t + 32 * kb, kc), qf[kc], s[kb]);
       sched_reads_ahead_of_mfma<D / 8, 1, 4>();
-      if ((CAUSAL && k0 + kBc - 1 > qw + shift) || k0 + kBc > NK)
-        mask_scores(s, min(CAUSAL ? q + shift - k0 - 4 * h : 0x7fffffff, NK - 1 - k0 - 4 * h));
+      if ((CAUSAL && k0 + kBc - 1 > qw + shift) || k0 + kBc > NK) {
+        const int lim = min(CAUSAL ? q + shift - k0 - 4 * h : 0x7fffffff, NK - 1 - k0 - 4 * h);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
+      }
       float r_m;
       m = fmaxf(m, tile_normaliser<VARIANT>(s, alpha, inv_alpha, beta, eps, may_be_unseen, [](float) { return true; }, r_m));
     }
