@@ -716,9 +716,12 @@ static hipError_t launch_fwd_split(const void* Q, const void* K, const void* V, 
 // launches included; B*H, Nq x Nk):
 //   up to 64 blocks: 32, 64 x 8192 d128 154 -> 46, 8, 1 x 16384 d128 296 -> 40, 16, 256 x 4096 d128 81 -> 33, 4, 2048 x 2048 causal
 //     d128 41 -> 33, full 39 -> 34, d32 24 -> 20, 1, 8192 x 8192 causal d64 113 -> 46, 64, 64 x 1024 d128 25 -> 22, d64 19.1 -> 18.7;
-//   65 to 128 blocks, from 2048 keys on and three work-groups per block (two at d = 256): 8, 2048 x 2048 causal
-//     d128 42 -> 38, d256 88 -> 71, 80, 64 x 2048 d128 43 -> 35, 1, 16384 x 16384 causal 288 -> 200, 128, 64 x 2048 d256 99 -> 88;
-//     beyond the limits: 8, 2048 x 2048 full d64 30 -> 35, d128 40 -> 48, 10, 1536 x 1536 causal d128 33 -> 36;
+//   65 to 128 blocks, from 2048 keys on with three work-groups per block (two at d = 256), from 2560 on with two: 8,
+//     2048 x 2048 causal d128 42 -> 38, d256 88 -> 71, 80, 64 x 2048 d128 43 -> 35, 1, 16384 x 16384 causal 288 -> 200, 128,
+//     64 x 2048 d256 99 -> 88; with two 96, 128 x 3000 causal d32 42 -> 39, d128 63 -> 60, 128, 64 x 4096 d64 59 -> 51, d128
+//     80 -> 71, 16, 1000 x 6000 causal d96 100 -> 87, 1, 16000 x 16000 full d64 203 -> 166; even at the limit (4, 4096 x 4096
+//     full d64 55.3 -> 53.8, d96 62.2 -> 63.5, 30, 300 x 2500 d32 32.2 -> 31.6); beyond the limits: 8, 2048 x 2048 full d64
+//     30 -> 35, d128 40 -> 49, 96, 128 x 2048 causal d96 38.0 -> 39.4, 10, 1536 x 1536 causal d128 33 -> 36;
 //   1024 to 1535 keys and many queries, d <= 128, only with 10 work-groups per block: 2, 1024 x 1024 causal d64
 //     18.7 -> 17.4, d128 23.4 -> 19.9, 4, 1024 x 1024 causal d128 23.7 -> 22.2, even at the limit (2, 1500 x 1030 full d128
 //     25.5 -> 24.6, d64 19.2 -> 19.9, 3, 1024 x 1024 full d64 17.0 -> 18.3); beyond it: 8, 1024 x 1024 causal d64
@@ -727,7 +730,7 @@ int attn_fwd_splits(int BH, int Nq, int Nk, int d, int causal, int variant) {
   const long long blocks = (long long)BH * ((Nq + kBr - 1) / kBr);
   if (variant == 2 || Nk < 1024 || 2 * blocks > kNumCUs) return 1;
   const long long s = (causal && 2LL * Nq > Nk ? 2 : 1) * kNumCUs / blocks;
-  if (4 * blocks > kNumCUs && (Nk < 2048 || (s < 3 && d <= 128))) return 1;
+  if (4 * blocks > kNumCUs && (Nk < 2048 || (s < 3 && d <= 128 && Nk < 2560))) return 1;
   if (4LL * Nq > Nk && Nk < 1536 && d <= 128 && s < 10) return 1;
   return split_shares((Nk + kBc - 1) / kBc, s < 32 ? (int)s : 32);
 }

@@ -89,7 +89,8 @@ def test_forward_shared_out_takes_strides_and_grouped_heads(lib):
 
 @pytest.mark.parametrize("variant", [0, 1])
 @pytest.mark.parametrize("H,Nq,Nk,d,causal", [(2, 1024, 1024, 64, True), (2, 64, 4097, 128, True), (3, 1, 1500, 96, False),
-                                              (1, 2100, 2100, 32, True), (8, 2048, 2048, 256, False)])
+                                              (1, 2100, 2100, 32, True), (8, 2048, 2048, 256, False),
+                                              (48, 130, 2560, 64, True), (43, 200, 2600, 128, False)])
 def test_shares_round_the_probabilities_of_the_one_pass_kernel(lib, H, Nq, Nk, d, causal, variant):
     """Every share starts from the normaliser a single pass would have reached, so P-bar is rounded the same
     and only float32 sums change their order.  T tiles in another order differ by about sqrt(T) 2^-24
