@@ -22,13 +22,12 @@ extern "C" {
 int attn_probe_matrix_clock(long long* out, int workgroups, int iters, void* stream);
 
 /*
- * The same kind of aid for the LDS: `workgroups` work-groups of 4 waves, each wave issuing
- * 16 * iters conflict-free LDS reads and nothing else; kind 0: ds_read_b128 (1 KB per instruction,
- * one matrix-instruction operand fragment), kind 1: ds_read_b64_tr_b16 (the transposing read,
- * 512 bytes per instruction).  out[0], out[1] (DEVICE, 4 x int64, 16-byte aligned): shader-clock
- * cycles and 100 MHz ticks of the first wave's loop.  With one work-group per CU,
- * 4 waves * 16 * iters * bytes-per-instruction / out[0] is the LDS read bandwidth of a CU in bytes
- * per clock.
+ * The same kind of aid for the LDS: `workgroups` work-groups of 4 waves, each wave reading
+ * 16 * iters matrix-instruction operand fragments (1 KB each) of a tile in the kernels' layout and
+ * nothing else; kind 0: one ds_read_b128 per fragment, kind 1: two ds_read_b64_tr_b16 (the
+ * transposing read, 512 bytes per instruction).  out[0], out[1] (DEVICE, 4 x int64, 16-byte
+ * aligned): shader-clock cycles and 100 MHz ticks of the first work-group's loop.  With one work-group per
+ * CU, 4 waves * 16 * iters * 1024 / out[0] is the LDS read bandwidth of a CU in bytes per clock.
  */
 int attn_probe_lds_clock(long long* out, int kind, int workgroups, int iters, void* stream);
 

@@ -43,52 +43,30 @@ __global__ __launch_bounds__(256, 2) void mfma_probe_kernel(long long* __restric
   }
 }
 
-// The same for the LDS: four waves per work-group, each issuing 16 * iters conflict-free LDS
-// reads from a 16 KB window and nothing else.  KIND 0: ds_read_b128 (64 lanes x 16 bytes = 1 KB
-// per instruction, one matrix-instruction operand fragment); KIND 1: ds_read_b64_tr_b16 (the
-// transposing read, 512 bytes per instruction, two per fragment).  Bytes read / elapsed shader
-// cycles is the LDS read bandwidth per CU the kernels' fragment traffic has to fit into.
+// The same for the LDS: four waves per work-group, each reading the 16 matrix-instruction operand
+// fragments (1 KB each) of a 64 x 128 tile in the kernels' own layout iters times and nothing else.
+// KIND 0: fragments along the rows, one ds_read_b128 each (lds_row8); KIND 1: along the columns, two
+// transposing ds_read_b64_tr_b16 each (lds_col8).  Bytes read / elapsed shader cycles is the LDS
+// read bandwidth per CU the kernels' fragment traffic has to fit into.
 template <int KIND>
 __global__ __launch_bounds__(256, 1) void lds_probe_kernel(long long* __restrict__ out, int iters) {
-  __shared__ __attribute__((aligned(16))) char lds[16384];
-  for (int i = threadIdx.x; i < 4096; i += 256) reinterpret_cast<float*>(lds)[i] = (float)i;
+  __shared__ __attribute__((aligned(1024))) char lds[64 * kRowBlockBytes<128> / 16];
+  for (int i = threadIdx.x; i < (int)sizeof(lds) / 4; i += 256) reinterpret_cast<float*>(lds)[i] = (float)i;
   __syncthreads();
-  const int lane = threadIdx.x & 63;
+  FragOffsets<128> fo;
+  init_frag_offsets<128>(fo, threadIdx.x & 63, lds_address(lds));
   const long long c0 = clock64(), w0 = wall_clock64();
-  if (KIND == 0) {
-    const char* base = lds + lane * 16;
-    for (int it = 0; it < iters; ++it) {
-      u32x4 t[16];
+  for (int it = 0; it < iters; ++it) {
+    bf16x8 t[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) t[j] = *reinterpret_cast<const u32x4*>(base + j * 1024);
-      // all 16 bytes of every read are "used" by an empty asm statement: no vector instruction
-      // competes with the reads, and the compiler cannot narrow them
+    for (int j = 0; j < 16; ++j)
+      t[j] = KIND == 0 ? lds_row8<128>(0, fo, 32 * (j >> 3), j & 7) : lds_col8<128>(0, fo, 16 * (j >> 2), j & 3);
+    // all 16 bytes of every read are "used" by an empty asm statement: no vector instruction
+    // competes with the reads, and the compiler cannot narrow them
 #pragma unroll
-      for (int j = 0; j < 16; ++j) asm volatile("" : : "v"(t[j]));
-    }
-  } else {
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    // transposing reads of a tile stored as 256-byte rows (128 columns): 16 lanes cover 4 rows x 32
-    // bytes, the four 16-lane groups of a wave four different 4-row bands, 16-byte chunks permuted
-    // over the row so that no bank is hit twice.  (The kernels' own tiles are laid out in blocks of
-    // 64-byte rows, common.hpp, where the instruction takes 3.1 clocks instead of the 4 seen here.)
-    // (16 different addresses per pass: identical ones would be merged by the compiler)
-    const int i = lane & 15, row = 4 * (lane >> 4) + (i >> 2);
-    const char* base[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int chunk = 4 * c + ((i & 3) >> 1);
-      base[c] = lds + row * 256 + ((chunk ^ (((row & 3) << 2) | ((row >> 2) & 3))) << 4) + ((i & 1) << 3);
-    }
-    for (int it = 0; it < iters; ++it) {
-      s16x4 t[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        t[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base[j >> 2] + (j & 3) * 4096));
-#pragma unroll
-      for (int j = 0; j < 16; ++j) asm volatile("" : : "v"(t[j]));
-    }
+    for (int j = 0; j < 16; ++j) asm volatile("" : : "v"(t[j]));
   }
+  __syncthreads();                                  // the four waves share the LDS unevenly: the last one counts
   const long long c1 = clock64(), w1 = wall_clock64();
   if (blockIdx.x == 0 && threadIdx.x == 0) { out[0] = c1 - c0; out[1] = w1 - w0; }
 }

@@ -70,9 +70,10 @@ def matrix_clock(workgroups=512, iters=50000, stream=None):
 
 
 def lds_clock(kind=0, workgroups=256, iters=20000, stream=None):
-    """Runs the LDS read loop (kind 0: ds_read_b128, kind 1: ds_read_b64_tr_b16), by default one
-    work-group per CU, and returns a dict: LDS read bandwidth in bytes per shader clock and CU as
-    seen by the first wave's own clock, and the aggregate rate in TB/s from the launch time."""
+    """Runs the LDS loop over operand fragments (kind 0: one ds_read_b128 each, kind 1: two
+    ds_read_b64_tr_b16), by default one work-group per CU, and returns a dict: LDS read bandwidth in
+    bytes per shader clock and CU as the first work-group's clock saw it, and the aggregate rate in
+    TB/s from the launch time."""
     out = torch.zeros(4, dtype=torch.int64, device="cuda")
     e0 = torch.cuda.Event(enable_timing=True); e1 = torch.cuda.Event(enable_timing=True)
     s = torch.cuda.current_stream() if stream is None else stream
@@ -83,7 +84,7 @@ def lds_clock(kind=0, workgroups=256, iters=20000, stream=None):
     e1.synchronize()
     ms = e0.elapsed_time(e1)
     cyc, ticks = out[0].item(), out[1].item()
-    per_wg = 4 * 16 * float(iters) * (1024.0 if kind == 0 else 512.0)
+    per_wg = 4 * 16 * float(iters) * 1024.0
     return {"bytes_per_clk_per_cu": per_wg / cyc if cyc else float("nan"),
             "shader_clock_ghz": cyc / (ticks / 1e8) / 1e9 if ticks else float("nan"),
             "ms": ms, "TB/s": per_wg * workgroups / (ms * 1e-3) / 1e12}
