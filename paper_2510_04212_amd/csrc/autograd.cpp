@@ -1,7 +1,7 @@
 // The autograd node of attention() in C++ (host code only; every computation is behind the C ABI).
 //
 // What bounds a training step on short sequences is the host: one sequence of 128 tokens takes the
-// GPU 17 us and took the Python node 75 to 145 us, depending on the machine (argument checks, allocations and
+// GPU 15 us and took the Python node 75 to 145 us, depending on the machine (argument checks, allocations and
 // ctypes conversions of both directions, and the interpreter lock the engine's thread has to wait for
 // in the backward).  Forward + backward, Python node -> this one, on one machine (us): B1 H1 N128 d64
 // 145 -> 76, B8 H12 N1024 d64 causal 164 -> 96 (92 of them on the GPU).

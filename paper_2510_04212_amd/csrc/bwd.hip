@@ -51,7 +51,8 @@ DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, in
 // work-groups per key block, each recomputing S and dP).
 template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // The kernel wants two waves on every SIMD: one wave alone leaves the matrix cores idle whenever
-// any of its instructions waits.  That means at most 256 registers per lane.  At D = 128 the
+// any of its instructions waits.  That means at most 256 registers per lane (a few wave-group instantiations
+// at D = 128 spill one to six).  At D = 128 the
 // accumulators (128) and the K fragments (32) leave no room for the V fragments: V_j is kept in LDS
 // for the whole block (8 more fragment reads per 32 queries to 48) and the query tiles shrink to 32
 // rows per wave group, so that two work-groups fit a CU.  Measured against one wave per SIMD with
@@ -180,10 +181,13 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
 #pragma unroll
       for (int i = 0; i < 16; ++i) { dVt[db][i] = 0.f; dKt[db][i] = 0.f; }
 
-    // first query tile that sees any key of this block
+    // first query tile that sees any key of this block (the last query sees every key: t0 < nt)
     const int t0 = !CAUSAL ? 0 : !RAGGED ? k0 / QT : max(0, k0 - shift) / QT;
     const int nt = RAGGED ? (N + QT - 1) / QT : N / QT;
-    if (RAGGED && t0 >= nt) {                        // no query sees these keys (more keys than queries reach): zero gradients
+    if (RAGGED && t0 >= nt) {
+      // Never taken (t0 < nt), kept for what the compiler makes of the rest: without this branch it waits for every
+      // fragment read at once in the grouped, unmasked D = 256 kernel (us, B1 H8/1 N8192 3063 -> 4566, B8 H32/8
+      // N2048 4536 -> 5496); the others move by 3 % either way.
       if (kw + r < NK) {
         store_acc_T<NDB>(dV + 32 * db0 + head_off + (size_t)(kw + r) * sn, dVt, 1.0f, h);
         store_acc_T<NDB>(dK + 32 * db0 + head_off + (size_t)(kw + r) * sn, dKt, alpha, h);
@@ -192,7 +196,7 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
     }
 
     // Q_i / dO_i tiles go global -> LDS asynchronously; L_i (pre-multiplied by log2 e) and -delta_i
-    // (64 floats each) pass through one register of threads 0..127.  The dP accumulator starts
+    // (QT floats each) pass through one register of the first 2 QT threads.  The dP accumulator starts
     // from -delta, so that the matrix instructions deliver dP - delta directly (Alg. 2 step 12).
     float sreg = 0.f;
     // Current query head: its first element in Q / dO and in LSE / delta.  With GROUPED the
@@ -337,7 +341,7 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
       // and every LDS fragment read is issued AH slots before the matrix instruction that uses it.
       auto tile_pipelined = [&]() {
         constexpr int NS = D / 8;            // slots per phase
-        constexpr int AH = (D >= 128) ? 8 : 4;  // LDS read-ahead, in slots
+        constexpr int AH = 4;                // LDS read-ahead, in slots
         constexpr int R = 2 * AH;            // fragment ring size (> AH)
         // score elements handled in slot sl: [16 sl / NS, 16 (sl + 1) / NS)
         bf16x8 ring[R];
