@@ -34,10 +34,10 @@ PEAK_HBM_GBS = 8000.0
 # scaled by the same counter's reading for a 1 GiB device copy (see profiles/mid_hbm_traffic.txt).
 # Keyed by (workload, kernel); None = not measured.
 MEASURED_TRAFFIC_BYTES = {
-    ("mid", "fwd"): 676315946,
-    ("mid", "delta"): 270662893,
-    ("mid", "bwd_dkdv"): 816209224,
-    ("mid", "bwd_dq"): 951223775,
+    ("mid", "fwd"): 680194753,
+    ("mid", "delta"): 270663783,
+    ("mid", "bwd_dkdv"): 1331669244,
+    ("mid", "bwd_dq"): 951431029,
 }
 
 
@@ -264,15 +264,16 @@ def main():
                                         "clock; rate = mean clock x 4096 FLOP/clk/CU x 256 CUs x 32 / clocks_per_instruction; "
                                         f"nominal peak {PEAK_BF16_TFLOPS:.0f} TFLOP/s assumes 2.4 GHz"}
 
-    # and what the LDS delivers: every matrix instruction of the three kernels takes one fresh
-    # 1 KB operand fragment from LDS, as one ds_read_b128 or as two transposing ds_read_b64_tr_b16
+    # and what the LDS delivers to the operand fragments of the kernels' tile layout: every matrix
+    # instruction of the three kernels takes a fresh 1 KB fragment from LDS, as one ds_read_b128 or
+    # as two transposing ds_read_b64_tr_b16
     lds128 = probe.lds_clock(kind=0, workgroups=256, iters=20000)
     ldstr = probe.lds_clock(kind=1, workgroups=256, iters=20000)
     out["lds_probe"] = {"ds_read_b128_bytes_per_clk_per_cu": round(lds128["bytes_per_clk_per_cu"], 1),
                         "ds_read_b64_tr_b16_bytes_per_clk_per_cu": round(ldstr["bytes_per_clk_per_cu"], 1),
-                        "note": "read-only loops, 4 waves per CU: one wave-wide LDS read instruction per 4 clocks and CU "
-                                "whatever its width; a matrix instruction (32 clocks per SIMD, 8 per CU) leaves room for "
-                                "two such reads"}
+                        "note": "read-only loops over the operand fragments of a tile, 4 waves per CU: 4 clocks per fragment read with "
+                                "ds_read_b128 (64 banks x 4 bytes per clock), about 4.8 to 5 with two transposing reads; the four SIMDs "
+                                "start a matrix instruction every 8 clocks"}
 
     # the other two throughput workloads of the build target, same step, fewer repetitions
     also = {}
