@@ -32,17 +32,43 @@ void* current_stream(const Tensor& t) {
   return static_cast<void*>(c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(t.get_device()).stream());
 }
 
-// binding.AttnError(status), as the Python node raises it.  Called without the interpreter lock, in the
-// backward on the engine's thread: the error travels as torch's python_error.
+// A Python exception, thrown without the interpreter lock (in the backward on the engine's thread): it travels as
+// torch's python_error.  Called with the lock held.
+[[noreturn]] void raise(PyObject* type, PyObject* value) {
+  PyErr_SetObject(type, value);
+  python_error e;
+  e.persist();
+  throw e;
+}
+
+// binding.AttnError(status), as the Python node raises it.
 void check(int status) {
   if (status == ATTN_OK) return;
   pybind11::gil_scoped_acquire lock;
   const auto type = pybind11::module_::import("paper_2510_04212_amd.binding").attr("AttnError");
   const pybind11::object error = type(status);
-  PyErr_SetObject(type.ptr(), error.ptr());
-  python_error e;
-  e.persist();
-  throw e;
+  raise(type.ptr(), error.ptr());
+}
+
+// What the backward gets from saved_tensors_hooks and hooks on the node can be anything: the ValueError of the
+// Python node's checks instead of kernels on host memory or on strides that are not the tensor's.
+void check_backward(Form form, const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& o,
+                    const Tensor& lse, const Tensor& dout) {
+  auto bf16 = [&](const Tensor& t) {
+    return t.defined() && t.layout() == at::kStrided && t.is_cuda() && t.device() == q.device() &&
+           t.scalar_type() == at::kBFloat16 && t.dim() == 4 &&
+           (form == kStrided ? t.stride(3) == 1 && t.strides() == q.strides() : t.is_contiguous());
+  };
+  const bool ok = bf16(q) && bf16(k) && bf16(v) && bf16(o) && bf16(dout) && o.sizes() == q.sizes() &&
+                  dout.sizes() == q.sizes() && v.sizes() == k.sizes() && k.size(0) == q.size(0) &&
+                  k.size(3) == q.size(3) && (form == kGrouped || k.size(1) == q.size(1)) &&
+                  (form == kRect || k.size(2) == q.size(2)) && lse.defined() && lse.is_cuda() &&
+                  lse.device() == q.device() && lse.scalar_type() == at::kFloat && lse.is_contiguous() &&
+                  lse.numel() * q.size(3) == q.numel();
+  if (ok) return;
+  pybind11::gil_scoped_acquire lock;
+  raise(PyExc_ValueError, pybind11::str("the tensors saved for the backward and the incoming gradient must be CUDA tensors of the "
+                                        "shapes, types and layout of the forward").ptr());
 }
 
 struct Attention : torch::autograd::Function<Attention> {
@@ -83,7 +109,6 @@ struct Attention : torch::autograd::Function<Attention> {
     const auto form = (Form)args[0];
     const int causal = (int)args[1], variant = (int)args[2];
     const float scale = (float)ctx->saved_data["scale"].toDouble();
-    const int B = (int)q.size(0), H = (int)q.size(1), Nq = (int)q.size(2), d = (int)q.size(3);
     Tensor dout = grads[0];
     auto like = [&](const Tensor& t) {
       return form == kStrided ? at::empty_strided(t.sizes(), t.strides(), t.options()) : at::empty_like(t);
@@ -95,6 +120,8 @@ struct Attention : torch::autograd::Function<Attention> {
       copy.copy_(dout);
       dout = copy;
     }
+    check_backward(form, q, k, v, o, lse, dout);
+    const int B = (int)q.size(0), H = (int)q.size(1), Nq = (int)q.size(2), d = (int)q.size(3);
     Tensor dq = like(q), dk = like(k), dv = like(v);
     const size_t bytes = std::max<size_t>(attn_bwd_workspace_bytes(B, H, Nq, d), 256);
     Tensor ws = at::empty({(int64_t)bytes}, q.options().dtype(at::kByte));

@@ -112,3 +112,26 @@ def test_a_refused_gradient_is_refused_the_same_way(lib, case):
             assert e.value.status == 2 and "misaligned" in str(e.value)
         good = torch.autograd.grad(o, (q, k, v), torch.ones_like(o))     # the graph is intact afterwards
         assert all(g.isfinite().all() for g in good)
+
+
+CHANGES = {"host": lambda t: t.cpu(), "type": lambda t: t.double(), "shape": lambda t: t[:, :, :-1].contiguous(),
+           "layout": lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)}
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[2], CASES[3], CASES[5]], ids=str)     # every form of the node
+@pytest.mark.parametrize("change", CHANGES)
+def test_what_a_hook_hands_back_is_checked(lib, case, change):
+    """K or O come back from a hook on saved tensors in host memory, or as another type, shape or layout than the
+    kernels take: ValueError from both nodes, and nothing is launched."""
+    from paper_2510_04212_amd import autograd as A
+    data = _qkv(*case)
+    for node in (lambda q, k, v: A.attention(q, k, v, True, 0.1, 1),
+                 lambda q, k, v: A._FlashAttention.apply(q, k, v, True, 0.1, 1, None, None)):
+        for which in (1, 3):                                  # of q, k, v, o, lse
+            q, k, v = (t.detach().requires_grad_(True) for t in data)
+            order = iter(range(5))
+            unpack = lambda p: CHANGES[change](p[1]) if p[0] == which else p[1]
+            with torch.autograd.graph.saved_tensors_hooks(lambda t: (next(order), t), unpack):
+                o = node(q, k, v)
+            with pytest.raises(ValueError):
+                torch.autograd.grad(o, (q, k, v), torch.ones_like(o))
