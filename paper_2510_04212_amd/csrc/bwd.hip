@@ -52,7 +52,7 @@ DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, in
 template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // The kernel wants two waves on every SIMD: one wave alone leaves the matrix cores idle whenever
 // any of its instructions waits.  That means at most 256 registers per lane (a few wave-group instantiations
-// at D = 128 spill one to six).  At D = 128 the
+// at D = 96 and 128 spill two to eleven, outside their loops or one read a tile).  At D = 128 the
 // accumulators (128) and the K fragments (32) leave no room for the V fragments: V_j is kept in LDS
 // for the whole block (8 more fragment reads per 32 queries to 48) and the query tiles shrink to 32
 // rows per wave group, so that two work-groups fit a CU.  Measured against one wave per SIMD with
@@ -69,10 +69,8 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 // from L2 for half as many keys.
 template <int G> constexpr int kKeyWaves = G == 4 ? 2 : 4;               // waves per group, 32 keys each
 template <int D, int G> constexpr int kQTile = D == 128 || G == 4 ? 32 * G : 64;   // query rows per streamed tile
-// D <= 64 has the registers for both 32-query blocks of a tile at once in a software pipeline, except with
-// grouped queries and no mask at D = 64, where 29 registers spilled (whole backward, pipeline -> plain blocks, us:
-// B8 H32/8 N2048 985 -> 867, B4 H32/8 N1111 229 -> 188).
-template <int D, int G, bool CAUSAL, bool GROUPED> constexpr bool kPipelined = D <= 64 && G == 1 && !(D == 64 && GROUPED && !CAUSAL);
+// LDS fragments are read this many matrix instructions before their use.
+template <int D> constexpr int kReadAhead = D == 256 ? 6 : 4;
 // dK / dV rows leave through a per-wave LDS staging area (store_rows_staged) where the row width
 // allows it; it overlays the tile buffers where it would otherwise cost a resident work-group, and
 // is left out at D = 256 (no room).
@@ -184,17 +182,6 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
     // first query tile that sees any key of this block (the last query sees every key: t0 < nt)
     const int t0 = !CAUSAL ? 0 : !RAGGED ? k0 / QT : max(0, k0 - shift) / QT;
     const int nt = RAGGED ? (N + QT - 1) / QT : N / QT;
-    if (RAGGED && t0 >= nt) {
-      // Never taken (t0 < nt), kept for what the compiler makes of the rest: without this branch it waits for every
-      // fragment read at once in the grouped, unmasked D = 256 kernel (us, B1 H8/1 N8192 3063 -> 4566, B8 H32/8
-      // N2048 4536 -> 5496); the others move by 3 % either way.
-      if (kw + r < NK) {
-        store_acc_T<NDB>(dV + 32 * db0 + head_off + (size_t)(kw + r) * sn, dVt, 1.0f, h);
-        store_acc_T<NDB>(dK + 32 * db0 + head_off + (size_t)(kw + r) * sn, dKt, alpha, h);
-      }
-      continue;
-    }
-
     // Q_i / dO_i tiles go global -> LDS asynchronously; L_i (pre-multiplied by log2 e) and -delta_i
     // (QT floats each) pass through one register of the first 2 QT threads.  The dP accumulator starts
     // from -delta, so that the matrix instructions deliver dP - delta directly (Alg. 2 step 12).
@@ -217,17 +204,18 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
       // make the wave wait, at the start of the tile, for these loads and for the tile transfer
       // issued just before them.)
     };
-    auto store_stats = [&](int buf) {
+    auto store_stats = [&](int buf, int tn) {      // tn: the tile they belong to
       if (tid < QT) {
         float l = sreg * kLog2e;
         if (RAGGED && l == -INFINITY) l = 0.f;         // a query that sees no key: all its scores are masked below
+        if (RAGGED && tn * QT + tid >= N) l = INFINITY;    // a row past the sequence end: P = exp(-inf) = 0, so it adds nothing to dK, dV
         ldsL[buf * QT + tid] = l;
       } else if (tid < 2 * QT) ldsD[buf * QT + tid - QT] = -sreg;   // LDS holds -delta
     };
     loader.template load_rows<RAGGED>(ldsQ, Qh, t0 * QT, N);
     loader.template load_rows<RAGGED>(ldsdO, dOh, t0 * QT, N);
     load_stats(Lh, Dh, t0);
-    store_stats(0);
+    store_stats(0, t0);
     wait_vmem();
 #pragma unroll
     for (int kc = 0; kc < D / 16; ++kc) {
@@ -263,47 +251,36 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
       const float* tL = ldsL + buf * QT;
       const float* tD = ldsD + buf * QT;
       const int qt0 = t * QT;
-      // One 32-query block against this wave's 32 keys (one code path: the block that crosses the
-      // diagonal only adds a masking step).  The group's first block of a tile also issues the
-      // next tile's transfer.  qb is a compile-time constant except for the group's offset, which is
-      // part of the base addresses.
-      auto qblock = [&](int qb) {
-        const int qb0 = qt0 + 32 * (qb + grp);
-        const bool tail = RAGGED && qb0 + 32 > N;              // some query rows lie past the sequence end
+      // V_j in LDS (no registers for what qblocks below keeps live): one 32-query block against this wave's 32 keys,
+      // in one code path (the block that crosses the diagonal only adds a masking step).  The next tile's transfer is
+      // issued on the way.
+      auto qblock = [&]() {
+        const int qb0 = qt0 + 32 * grp;
         // ---- S = Q_i K_j^T and dP = dO_i V_j^T (Alg. 2 steps 8, 11); rows = queries, lane = key
         f32x16 s, dp;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + 32 * (qb + grp) + 8 * g + 4 * h);
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + 32 * grp + 8 * g + 4 * h);
 #pragma unroll
           for (int e = 0; e < 4; ++e) { s[4 * g + e] = 0.f; dp[4 * g + e] = d4[e]; }
         }
 #pragma unroll
         for (int kc = 0; kc < D / 16; ++kc) {
-          s = mfma32(lds_row8<D>(tQ, fo, 32 * qb, kc), kf[kc], s);
-          if constexpr (kVInLds<D>) dp = mfma32(lds_row8<D>(tdO, fo, 32 * qb, kc), lds_row8<D>(0, fo_v, 0, kc), dp);
-          else dp = mfma32(lds_row8<D>(tdO, fo, 32 * qb, kc), vf[kc], dp);
-          if (qb == 0) issue_part(kc);
+          s = mfma32(lds_row8<D>(tQ, fo, 0, kc), kf[kc], s);
+          dp = mfma32(lds_row8<D>(tdO, fo, 0, kc), lds_row8<D>(0, fo_v, 0, kc), dp);
+          issue_part(kc);
         }
-        if (qb == 0) {
 #pragma unroll
-          for (int i = D / 16; i < 2 * NLD; ++i) issue_part(i);
-          issued = true;
-        }
-        if constexpr (kVInLds<D>) sched_3_reads_per_2_mfma<D / 16, 8>();
-        else sched_reads_ahead_of_mfma<D / 8, 1, 8>();
+        for (int i = D / 16; i < 2 * NLD; ++i) issue_part(i);
+        issued = true;
+        sched_3_reads_per_2_mfma<D / 16, 8>();
+        __builtin_amdgcn_sched_barrier(0);          // (2 to 5 % faster than leaving the compiler to mix the phases)
         // element i of this lane is query qb0 + 4h + c with c = 8 (i / 4) + i % 4 a compile-time constant
-        if (tail) {   // rows past the sequence end: P = exp(-inf) = 0, so they add nothing to dK, dV
-          const int lim = N - qb0 - 4 * h;
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (8 * (i >> 2) + (i & 3) >= lim) s[i] = -INFINITY;
-        }
         // ---- P = exp(S - L) (step 9), dS = P o (dP - delta) (step 12)
         bf16x8 pf[2], dsf[2];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(tL + 32 * (qb + grp) + 8 * g + 4 * h);
+          const f32x4 l4 = *reinterpret_cast<const f32x4*>(tL + 32 * grp + 8 * g + 4 * h);
 #pragma unroll
           for (int e = 0; e < 4; ++e) s[4 * g + e] = __builtin_fmaf(s[4 * g + e], c2, -l4[e]);
         }
@@ -325,124 +302,117 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
         for (int cc = 0; cc < 2; ++cc)
 #pragma unroll
           for (int db = 0; db < NDB; ++db) {
-            dVt[db] = mfma32(lds_col8<D>(tdO, fo_upd, 32 * qb + 16 * cc, db), pf[cc], dVt[db]);
-            dKt[db] = mfma32(lds_col8<D>(tQ, fo_upd, 32 * qb + 16 * cc, db), dsf[cc], dKt[db]);
+            dVt[db] = mfma32(lds_col8<D>(tdO, fo_upd, 16 * cc, db), pf[cc], dVt[db]);
+            dKt[db] = mfma32(lds_col8<D>(tQ, fo_upd, 16 * cc, db), dsf[cc], dKt[db]);
           }
         sched_reads_ahead_of_mfma<4 * NDB, 2, 4>();
       };
-      // Both 32-query blocks of a tile that lies entirely below the diagonal for this wave, as one
-      // software-pipelined sequence of 4 x NS "slots" (one matrix instruction each).  The phase
-      // order is fixed by hand (scheduling fences between the phases and between the slots of the
-      // two pure matrix phases; inside the mixed phases the compiler interleaves):
-      //   phase 1  S,dP of block 0
-      //   phase 2  S,dP of block 1        | vector work of block 0 (P, dS), one element per slot
-      //   phase 3  dV,dK += block 0       | vector work of block 1
-      //   phase 4  dV,dK += block 1
-      // and every LDS fragment read is issued AH slots before the matrix instruction that uses it.
-      auto tile_pipelined = [&]() {
-        constexpr int NS = D / 8;            // slots per phase
-        constexpr int AH = 4;                // LDS read-ahead, in slots
-        constexpr int R = 2 * AH;            // fragment ring size (> AH)
-        // score elements handled in slot sl: [16 sl / NS, 16 (sl + 1) / NS)
-        bf16x8 ring[R];
-        // slot s of an S/dP phase: kc = s/2, even -> S (Q_i, K_j), odd -> dP (dO_i, V_j)
-        auto rd_sdp = [&](int qb, int sl) -> bf16x8 {
-          return lds_row8<D>((sl & 1) ? tdO : tQ, fo, 32 * qb, sl >> 1);
+      // The NB 32-query blocks of a tile that belong to this wave's group against its 32 keys, as one stream of matrix
+      // instructions ("slots"):  S (D/16 slots) | dP | dV (2 NDB) | dK, block after block.  The vector work of a
+      // block lies under its own matrix instructions: P = exp(S - L) under dP, dS = P o (dP - delta) under dV,
+      // and every LDS fragment is read AHEAD slots before its use (a fence per slot keeps that order).  Same bits as
+      // phase after phase; us, whole kernel: B2 H8 N2048 d256 causal 120 -> 116, B1 H8 N1000 d256 causal 74 -> 59,
+      // B2 H16 N2048 d96 causal 68 -> 66, B4 H32 N4096 d64 causal 519 -> 510, B32 H12 N512 d64 full 67.5 -> 66.0.
+      // The next tile's transfer is issued on the way.
+      // MASKED: a block crosses the diagonal.
+      auto qblocks = [&](auto masked_c, auto nb_c, auto qb_c) {
+        constexpr bool MASKED = decltype(masked_c)::value;
+        constexpr int NB = decltype(nb_c)::value, qb = decltype(qb_c)::value;
+        constexpr int NS = D / 16, NU = 2 * NDB, PB = 2 * NS + 2 * NU;    // slots of S or dP, of dV or dK, of a block
+        constexpr int AHEAD = kReadAhead<D>, RING = AHEAD + 1;
+        auto fragment = [&](int i) -> bf16x8 {
+          const int b = qb + i / PB, u = i % PB;
+          if (u < NS) return lds_row8<D>(tQ, fo, 32 * b, u);
+          if (u < 2 * NS) return lds_row8<D>(tdO, fo, 32 * b, u - NS);
+          const int w = (u - 2 * NS) % NU;
+          return lds_col8<D>(u < 2 * NS + NU ? tdO : tQ, fo_upd, 32 * b + 16 * (w / NDB), w % NDB);
         };
-        // slot s of a dV/dK phase: cc = s / (2 NDB), db = (s/2) % NDB, even -> dV (dO_i^T), odd -> dK (Q_i^T)
-        // (this path is only taken when the work-group owns all columns, NDB = D/32)
-        auto rd_dvdk = [&](int qb, int sl) -> bf16x8 {
-          return lds_col8<D>((sl & 1) ? tQ : tdO, fo_upd, 32 * qb + 16 * ((sl / (2 * NDB)) & 1),
-                             (sl >> 1) % NDB);
-        };
-        f32x16 s0, dp0, s1, dp1;
-        bf16x8 pf0[2], dsf0[2], pf1[2], dsf1[2];
-        f32x4 lq0[4], lq1[4];                        // L_i log2e of the 16 rows a lane sees
+        bf16x8 ring[RING];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {                // the dP accumulators start from -delta_i
-          lq0[g] = *reinterpret_cast<const f32x4*>(tL + 8 * g + 4 * h);
-          const f32x4 d0 = *reinterpret_cast<const f32x4*>(tD + 8 * g + 4 * h);
-          const f32x4 d1 = *reinterpret_cast<const f32x4*>(tD + 32 + 8 * g + 4 * h);
+        for (int i = 0; i < AHEAD; ++i) ring[i] = fragment(i);
+        f32x16 s, dp;
+        f32x4 l4[4];
+        bf16x8 pf[2], dsf[2];
+        int first_seen = 0;              // MASKED: entry c = 8 (i / 4) + i % 4 counts if c >= first_seen
+        static_for<NB * PB>([&](auto slot) {
+          constexpr int sl = decltype(slot)::value, u = sl % PB, b = qb + sl / PB;
+          const int stat = 32 * (b + grp) + 4 * h;
+          if (sl + AHEAD < NB * PB) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+          if (u == 0) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            s0[4 * g + e] = 0.f; s1[4 * g + e] = 0.f;
-            dp0[4 * g + e] = d0[e]; dp1[4 * g + e] = d1[e];
+            for (int i = 0; i < 16; ++i) s[i] = 0.f;
+            if (MASKED) first_seen = kw + r - shift - qt0 - 32 * (b + grp) - 4 * h;
           }
-        }
+          // -delta_i seeds the dP accumulator; L_i of the rows a lane sees
 #pragma unroll
-        for (int a = 0; a < AH; ++a) ring[a] = rd_sdp(0, a);
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- phase 1
+          for (int g = 0; g < 4; ++g)
+            if (u == g * (NS < 4 ? NS : 4) / 4) {
+              const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + stat + 8 * g);
 #pragma unroll
-        for (int sl = 0; sl < NS; ++sl) {
-          ring[(sl + AH) % R] = (sl + AH < NS) ? rd_sdp(0, sl + AH) : rd_sdp(1, sl + AH - NS);
-          if (sl & 1) dp0 = mfma32(ring[sl % R], vf[sl >> 1], dp0);
-          else s0 = mfma32(ring[sl % R], kf[sl >> 1], s0);
-          if (sl & 1) issue_part(sl >> 1);
+              for (int e = 0; e < 4; ++e) dp[4 * g + e] = d4[e];
+            }
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            if (u == NS + g * NS / 4) l4[g] = *reinterpret_cast<const f32x4*>(tL + stat + 8 * g);
+          const bf16x8 a = ring[sl % RING];
+          if constexpr (u < NS) {
+            s = mfma32(a, kf[u], s);
+          } else if constexpr (u < 2 * NS) {
+            dp = mfma32(a, vf[u - NS], dp);
+          } else if constexpr (u < 2 * NS + NU) {
+            constexpr int w = u - 2 * NS;
+            dVt[w % NDB] = mfma32(a, pf[w / NDB], dVt[w % NDB]);
+          } else {
+            constexpr int w = u - 2 * NS - NU;
+            dKt[w % NDB] = mfma32(a, dsf[w / NDB], dKt[w % NDB]);
+          }
+          if (b == 0) issue_part(sl);
+          if (u > NS && u <= 2 * NS) {           // P = exp(S - L) (step 9)
+#pragma unroll
+            for (int i = 16 * (u - NS - 1) / NS; i < 16 * (u - NS) / NS; ++i) {
+              float x = __builtin_fmaf(s[i], c2, -l4[i >> 2][i & 3]);
+              const int c = 8 * (i >> 2) + (i & 3);
+              if (MASKED && c < first_seen) x = -INFINITY;
+              s[i] = __builtin_amdgcn_exp2f(x);
+              pf[i >> 3][i & 7] = (bf16_t)s[i];
+            }
+          }
+          if (u > 2 * NS && u <= 2 * NS + NU) {  // dS = P o (dP - delta) (step 12); dp already holds dP - delta
+#pragma unroll
+            for (int i = 16 * (u - 2 * NS - 1) / NU; i < 16 * (u - 2 * NS) / NU; ++i) {
+              float ds = s[i] * dp[i];
+              // a masked entry contributes exactly nothing, whatever its row holds
+              const int c = 8 * (i >> 2) + (i & 3);
+              if (MASKED && c < first_seen) ds = 0.f;
+              dsf[i >> 3][i & 7] = (bf16_t)ds;
+            }
+          }
           __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int i = NS / 2; i < 2 * NLD; ++i) issue_part(i);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) lq1[g] = *reinterpret_cast<const f32x4*>(tL + 32 + 8 * g + 4 * h);
-        // ---- phase 2
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl) {
-          ring[(NS + sl + AH) % R] = (sl + AH < NS) ? rd_sdp(1, sl + AH) : rd_dvdk(0, sl + AH - NS);
-          if (sl & 1) dp1 = mfma32(ring[(NS + sl) % R], vf[sl >> 1], dp1);
-          else s1 = mfma32(ring[(NS + sl) % R], kf[sl >> 1], s1);
-#pragma unroll
-          for (int i = 16 * sl / NS; i < 16 * (sl + 1) / NS; ++i) {
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[i], c2, -lq0[i >> 2][i & 3]));
-            float ds = p * dp0[i];
-            pf0[i >> 3][i & 7] = (bf16_t)p;
-            dsf0[i >> 3][i & 7] = (bf16_t)ds;
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- phase 3
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl) {
-          ring[(2 * NS + sl + AH) % R] = (sl + AH < NS) ? rd_dvdk(0, sl + AH) : rd_dvdk(1, sl + AH - NS);
-          const int cc = (sl / (2 * NDB)) & 1, db = (sl >> 1) % NDB;
-          if (sl & 1) dKt[db] = mfma32(ring[(2 * NS + sl) % R], dsf0[cc], dKt[db]);
-          else dVt[db] = mfma32(ring[(2 * NS + sl) % R], pf0[cc], dVt[db]);
-#pragma unroll
-          for (int i = 16 * sl / NS; i < 16 * (sl + 1) / NS; ++i) {
-            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[i], c2, -lq1[i >> 2][i & 3]));
-            float ds = p * dp1[i];
-            pf1[i >> 3][i & 7] = (bf16_t)p;
-            dsf1[i >> 3][i & 7] = (bf16_t)ds;
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- phase 4
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl) {
-          if (sl + AH < NS) ring[(3 * NS + sl + AH) % R] = rd_dvdk(1, sl + AH);
-          const int cc = (sl / (2 * NDB)) & 1, db = (sl >> 1) % NDB;
-          if (sl & 1) dKt[db] = mfma32(ring[(3 * NS + sl) % R], dsf1[cc], dKt[db]);
-          else dVt[db] = mfma32(ring[(3 * NS + sl) % R], pf1[cc], dVt[db]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        });
       };
-      constexpr bool pipelined = kPipelined<D, G, CAUSAL, GROUPED>;
-      if (pipelined && (!CAUSAL || qt0 + shift >= kw + 31) && (!RAGGED || qt0 + QT <= N)) {
-        if constexpr (pipelined) tile_pipelined();
+      constexpr int NBT = QT / 32 / G;                       // blocks of this wave's group in a tile
+      const int q_first = qt0 + 32 * grp, q_last = q_first + 32 * NBT - 1;     // first and last query of them
+      if ((CAUSAL && q_last + shift < kw) || (RAGGED && q_first >= N)) {
+        // no query sees a key of the wave, or nothing but padding
+      } else if constexpr (kVInLds<D>) {
+        qblock();
+      } else if (!CAUSAL || q_first + shift >= kw + 31) {
+        asm volatile("; every entry counts");                // (differs from the other path: nothing is merged in front of the branch)
+        qblocks(std::false_type{}, std::integral_constant<int, NBT>{}, std::integral_constant<int, 0>{});
+        issued = true;
       } else {
-#pragma unroll
-        for (int qb = 0; qb < QT / 32 / G; ++qb) {
-          const int qb0 = qt0 + 32 * (qb + grp);
-          if (CAUSAL && qb0 + shift + 31 < kw) continue;   // no query of the block sees a key of the wave
-          if (RAGGED && qb0 >= N) continue;                    // nothing but padding
-          qblock(qb);
-        }
-        if (!issued) {    // a wave that skipped the group's first block still has its share of the transfer to issue
-#pragma unroll
-          for (int i = 0; i < 2 * NLD; ++i) issue_part(i);
-        }
+        asm volatile("; masked");
+        static_for<NBT>([&](auto qb) {
+          if (q_first + 32 * decltype(qb)::value + 31 + shift < kw) return;     // no query of the block sees a key of the wave
+          qblocks(std::true_type{}, std::integral_constant<int, 1>{}, qb);
+          if (decltype(qb)::value == 0) issued = true;
+        });
       }
-      if (has_next) store_stats(buf ^ 1);
+      if (!issued) {      // a wave that skipped the tile's first block still has its share of the transfer to issue
+#pragma unroll
+        for (int i = 0; i < 2 * NLD; ++i) issue_part(i);
+      }
+      if (has_next) store_stats(buf ^ 1, tn);
       wait_vmem();
       __syncthreads();
     };
@@ -549,9 +519,15 @@ constexpr int kGivenDelta = 0, kRecomputeDelta = 1, kOwnDelta = 2;
 template <int G> constexpr int kQueryWaves = G == 1 ? 4 : 2;
 template <int G> constexpr int kKeysPerTile = G == 4 ? 128 : 64;
 template <int D, int G> constexpr int kSmemDq = 4 * kKeysPerTile<G> * D * 2;
+// Small head sizes need more waves per SIMD next to one another (four at D = 32, three at D = 64) than a long
+// read-ahead: dQ at D = 64 with two waves and fragments read four slots ahead -> three and two (us): B8 H12 N1024
+// causal 33.1 -> 30.9, B4 H32 N4096 causal 395 -> 379, B16 H16 N999 full 114 -> 109.
+template <int D, int G> constexpr int kDqWavesPerSimd = D == 32 && G == 1 ? 4 : D == 64 && G == 1 ? 3 : kWavesPerSimd<D>;
+template <int D> constexpr int kReadAheadDq = D <= 64 ? 2 : D == 256 ? 6 : 4;
 
 template <int D, bool CAUSAL, bool RAGGED, int MODE, int G>
-__global__ __launch_bounds__(64 * kQueryWaves<G> * G, D <= 128 ? 2 : 1) void attn_bwd_dq_kernel(
+__global__ __launch_bounds__(64 * kQueryWaves<G> * G)
+__attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     const bf16_t* __restrict__ O, bf16_t* __restrict__ dQ, float* __restrict__ delta_out, int N,
@@ -688,65 +664,99 @@ __global__ __launch_bounds__(64 * kQueryWaves<G> * G, D <= 128 ? 2 : 1) void att
     };
     bool issued = false;
     const int kt0 = j * KT;
-    if (!CAUSAL || (kt0 <= qw + shift + 31)) {
-      // one 32-key block against this wave's 32 queries (one code path: the block that crosses the
-      // diagonal only adds a masking step, so that the fragment reads stay next to their matrix
-      // instructions instead of being merged in front of a branch)
-      auto kblock = [&](int kb, auto first_c) {
-        constexpr bool first = decltype(first_c)::value;     // the block that also issues the tile transfer
-        const int kb0 = kt0 + 32 * (kb + grp);
-        // ---- S^T = K_j Q_i^T, dP^T = V_j dO_i^T ; rows = keys, lane = query
-        f32x16 s, dp;
+    // The NB 32-key blocks of a tile that belong to this wave's group against its 32 queries, as one stream of matrix
+    // instructions ("slots") in phases of D/16:  S^T, dP^T of each block, then the dQ products.  The vector work
+    // lies under matrix instructions: P = exp(S - L) under the block's dP^T, dS = P o (dP - delta) under the next
+    // phase (with one block only its second half), and every LDS fragment is read AHEAD slots
+    // before its use (a fence per slot keeps that order).  The next tile's transfer is issued on the way.  Same bits as
+    // block after block and phase after phase; us, whole kernel: B4 H32 N4096 d128 causal 716 -> 682, B2 H16 N2048 d96
+    // causal 52.3 -> 50.0, B2 H8 N2048 d256 causal 89 -> 80, B4 H12 N1024 d64 causal 22.0 -> 19.9, B8 H12 N1024 d64
+    // causal 32.4 -> 30.7.
+    // MASKED: a block crosses the diagonal or the sequence end.
+constexpr int NBT = KT / 32 / G;                         // blocks of this wave's group in a tile
+        auto kblocks = [&](auto masked_c, auto nb_c, auto kb_c) {
+      constexpr bool MASKED = decltype(masked_c)::value;
+      constexpr int NB = decltype(nb_c)::value;
+      constexpr int kb = decltype(kb_c)::value;
+      constexpr int NS = D / 16, SLOTS = (DELTA_MODE ? 2 : 3) * NB * NS;
+      constexpr int AHEAD = kReadAheadDq<D>, RING = AHEAD + 1;
+      auto fragment = [&](int i) -> bf16x8 {
+        const int phase = i / NS, u = i % NS;
+        if (phase < 2 * NB) return lds_row8<D>(phase % 2 ? tV : tK, fo, 32 * (kb + phase / 2), u);
+        return lds_col8<D>(tK, fo, 32 * (kb + phase - 2 * NB) + 16 * (u / NDB), u % NDB);
+      };
+      bf16x8 ring[RING], dsf[NB][2];
+      f32x16 s[NB], dp[NB];
+      int lim[NB];                       // MASKED: last visible entry, c = 8 (i / 4) + i % 4
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+      for (int i = 0; i < AHEAD; ++i) ring[i] = fragment(i);
 #pragma unroll
-        for (int kc = 0; kc < D / 16; ++kc) {
-          s = mfma32(lds_row8<D>(tK, fo, 32 * kb, kc), qf[kc], s);
-          dp = mfma32(lds_row8<D>(tV, fo, 32 * kb, kc), dof[kc], kc == 0 ? neg_delta : dp);
-          if (first) issue_part(kc);
-        }
-        if (first) {
+      for (int b = 0; b < NB; ++b) {
 #pragma unroll
-          for (int i = D / 16; i < 2 * NLD; ++i) issue_part(i);
-          issued = true;
-        }
-        sched_reads_ahead_of_mfma<D / 8, 1, 4>();
-        // element i of this lane is key kb0 + 4h + c with c = 8 (i / 4) + i % 4 a compile-time
-        // constant.  Keys in this lane's future (the block crosses the diagonal) and keys past the
-        // sequence end get S = -inf: P = exp(-inf) = 0, so they add nothing to dQ.
-        if ((CAUSAL && kb0 + 31 > qw + shift) || (RAGGED && kb0 + 32 > NK)) {
-          int lim = CAUSAL ? qw + r + shift - kb0 - 4 * h : 0x7fffffff;     // last visible c
-          if (RAGGED) lim = min(lim, NK - 1 - kb0 - 4 * h);
+        for (int i = 0; i < 16; ++i) s[b][i] = 0.f;
+        const int kb0 = kt0 + 32 * (kb + b + grp);
+        lim[b] = CAUSAL ? qw + r + shift - kb0 - 4 * h : 0x7fffffff;
+        if (RAGGED) lim[b] = min(lim[b], NK - 1 - kb0 - 4 * h);
+      }
+      // P of entries i0 .. i1 - 1 of block b: keys in this lane's future and keys past the sequence end get
+      // S = -inf, P = exp(-inf) = 0
+      auto form_p = [&](int b, int i0, int i1) {
 #pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (8 * (i >> 2) + (i & 3) > lim) s[i] = -INFINITY;
-        }
-        bf16x8 dsf[2];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], c2, -l2));
-          if (DELTA_MODE) pdp = __builtin_fmaf(p, dp[i], pdp);
-          else dsf[i >> 3][i & 7] = (bf16_t)(p * dp[i]);      // dp already holds dP - delta
-        }
-        if (!DELTA_MODE) {
-          // ---- dQ_i^T += K_j^T dS^T (step 13)
-#pragma unroll
-          for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-            for (int db = 0; db < D / 32; ++db) {
-              dQt[db] = mfma32(lds_col8<D>(tK, fo, 32 * kb + 16 * cc, db), dsf[cc], dQt[db]);
-            }
-          sched_reads_ahead_of_mfma<D / 16, 2, 4>();
+        for (int i = i0; i < i1; ++i) {
+          if (MASKED && 8 * (i >> 2) + (i & 3) > lim[b]) s[b][i] = -INFINITY;
+          s[b][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][i], c2, -l2));
         }
       };
+      // dS of the same; dp already holds dP - delta
+      auto form_ds = [&](int b, int i0, int i1) {
 #pragma unroll
-      for (int kb = 0; kb < KT / 32 / G; ++kb) {
-        const int kb0 = kt0 + 32 * (kb + grp);
-        if (CAUSAL && (kb0 > qw + shift + 31)) continue;   // no query of the wave sees a key of the block
-        if (RAGGED && kb0 >= NK) continue;                   // nothing but padding
-        if (kb == 0) kblock(kb, std::true_type{});
-        else kblock(kb, std::false_type{});
+        for (int i = i0; i < i1; ++i) {
+          if (DELTA_MODE) pdp = __builtin_fmaf(s[b][i], dp[b][i], pdp);
+          else dsf[b][i >> 3][i & 7] = (bf16_t)(s[b][i] * dp[b][i]);
+        }
+      };
+      static_for<SLOTS>([&](auto slot) {
+        constexpr int sl = decltype(slot)::value, phase = sl / NS, u = sl % NS;
+        if (sl + AHEAD < SLOTS) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+        if (NB == 1 && sl == 2 * NS) form_ds(0, 0, 8);
+        const bf16x8 a = ring[sl % RING];
+        if constexpr (phase >= 2 * NB) dQt[u % NDB] = mfma32(a, dsf[phase - 2 * NB][u / NDB], dQt[u % NDB]);   // step 13
+        else if constexpr (phase % 2 == 0) s[phase / 2] = mfma32(a, qf[u], s[phase / 2]);
+        else dp[phase / 2] = mfma32(a, dof[u], u == 0 ? neg_delta : dp[phase / 2]);
+        if (kb == 0) issue_part(sl);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const int e = sl - 2 * NS * b - NS - 1;            // P of block b lies under the slots after its first dP^T
+          if (e >= 0 && e < NS) form_p(b, 16 * e / NS, 16 * (e + 1) / NS);
+          const int f = e - NS;                              // dS of block b
+          if (NB > 1 && !DELTA_MODE && f >= 0 && f < NS) form_ds(b, 16 * f / NS, 16 * (f + 1) / NS);
+        }
+        if (NB == 1 && sl == 2 * NS) form_ds(0, 8, 16);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if (DELTA_MODE) {
+        form_p(NB - 1, 16 * (NS - 1) / NS, 16);              // (the slot these would lie under is a dQ product)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) form_ds(b, 0, 16);
       }
+    };
+    int k0 = kt0 + 32 * grp;                                 // first key of them
+    // (in a vector register: behind a branch that the compiler knows to be uniform it needs 30 registers more)
+    if (RAGGED && !CAUSAL) asm volatile("" : "+v"(k0));
+    const int last = k0 + 32 * NBT - 1;
+    if ((!CAUSAL || last <= qw + shift) && (!RAGGED || last < NK)) {
+      asm volatile("; every key counts");                    // (differs from the other path: nothing is merged in front of the branch)
+      constexpr int NB = D == 32 ? 1 : NBT;
+      static_for<NBT / NB>([&](auto i) { kblocks(std::false_type{}, std::integral_constant<int, NB>{}, std::integral_constant<int, NB * decltype(i)::value>{}); });
+      issued = true;
+    } else {
+      asm volatile("; masked");
+      static_for<NBT>([&](auto kb) {
+        const int kb0 = k0 + 32 * decltype(kb)::value;
+        if ((CAUSAL && kb0 > qw + shift + 31) || (RAGGED && kb0 >= NK)) return;    // nothing to see in the block
+        kblocks(std::true_type{}, std::integral_constant<int, 1>{}, kb);
+        if (decltype(kb)::value == 0) issued = true;
+      });
     }
     if (!issued) {      // a wave that skipped the tile's first block still has its share of the transfer to issue
 #pragma unroll
@@ -932,7 +942,10 @@ hipError_t attn_bwd_dkdv_dispatch(const void* Q, const void* K, const void* V, c
                                   const float* LSE, const float* delta, void* dK, void* dV,
                                   int BH, int N, int d, int causal, float alpha, Layout lay,
                                   hipStream_t st) {
-  const bool ragged = (N % kKeysPerWG) != 0 || lay.Nk != N;   // the aligned kernels carry no bounds handling
+  // The aligned kernels carry no bounds handling.  At D = 256 without a mask there is none: with nothing that
+  // parts the tile from what follows, its registers spill (us, aligned -> bounds-checking: dK/dV B2 H8 N2048
+  // 204 -> 191, dQ 208 -> 96).
+  const bool ragged = (N % kKeysPerWG) != 0 || lay.Nk != N || (d == 256 && !causal);
   if (lay.group > 1) {   // grouped queries: the bounds-checking instantiation serves every N
 #define CASEG(DD, CC)                                 \
   if (d == DD && (causal != 0) == CC)                 \
@@ -948,7 +961,7 @@ hipError_t attn_bwd_dkdv_dispatch(const void* Q, const void* K, const void* V, c
   CASE(32, false, false) CASE(32, false, true) CASE(32, true, false) CASE(32, true, true)
   CASE(64, false, false) CASE(64, false, true) CASE(64, true, false) CASE(64, true, true)
   CASE(128, false, false) CASE(128, false, true) CASE(128, true, false) CASE(128, true, true)
-  CASE(256, false, false) CASE(256, false, true) CASE(256, true, false) CASE(256, true, true)
+  CASE(256, false, true) CASE(256, true, false) CASE(256, true, true)
   CASE(96, false, false) CASE(96, false, true) CASE(96, true, false) CASE(96, true, true)
 #undef CASE
   return hipErrorInvalidValue;
@@ -960,7 +973,7 @@ hipError_t attn_bwd_dq_dispatch(const void* Q, const void* K, const void* V, con
                                 const float* LSE, const float* delta, const void* O, void* dQ,
                                 float* delta_out, int BH, int N, int d, int causal, float alpha,
                                 Layout lay, hipStream_t st) {
-  const bool ragged = (N % kQPerWG) != 0 || lay.Nk != N;
+  const bool ragged = (N % kQPerWG) != 0 || lay.Nk != N || (d == 256 && !causal);   // (see attn_bwd_dkdv_dispatch)
   const bool own = O != nullptr;
 #define CASE(DD, CC, RR)                                                \
   if (d == DD && (causal != 0) == CC && ragged == RR)                   \
@@ -969,7 +982,7 @@ hipError_t attn_bwd_dq_dispatch(const void* Q, const void* K, const void* V, con
   CASE(32, false, false) CASE(32, false, true) CASE(32, true, false) CASE(32, true, true)
   CASE(64, false, false) CASE(64, false, true) CASE(64, true, false) CASE(64, true, true)
   CASE(128, false, false) CASE(128, false, true) CASE(128, true, false) CASE(128, true, true)
-  CASE(256, false, false) CASE(256, false, true) CASE(256, true, false) CASE(256, true, true)
+  CASE(256, false, true) CASE(256, true, false) CASE(256, true, true)
   CASE(96, false, false) CASE(96, false, true) CASE(96, true, false) CASE(96, true, true)
 #undef CASE
   return hipErrorInvalidValue;
