@@ -244,13 +244,44 @@ DEVI void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // the wave at the start of each tile until they have landed.
 template <class T> DEVI void settle(T& x) { asm volatile("" : "+v"(x)); }
 
-// Sum of the two bf16 values of a packed pair, added to acc in float32 (v_dot2c_f32_bf16 with
-// a (1,1) second operand).
-DEVI float add_pair_bf16(bf16x2 p, float acc) {
+// Sum of the eight bf16 values a lane holds in p, added to acc in float32 (v_dot2c_f32_bf16 with (1,1)).
+DEVI float add_values(bf16x8 p, float acc) {
   bf16x2 one;
-  one[0] = (bf16_t)1.0f;
-  one[1] = (bf16_t)1.0f;
-  return __builtin_amdgcn_fdot2_f32_bf16(p, one, acc, false);
+  one[0] = one[1] = (bf16_t)1.0f;
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    bf16x2 v;
+    v[0] = p[j];
+    v[1] = p[j + 1];
+    acc = __builtin_amdgcn_fdot2_f32_bf16(v, one, acc, false);
+  }
+  return acc;
+}
+
+// Row sums of a fragment p of 32 rows x 16 columns in operand layout (lane (r, h): columns 8h .. 8h+7 of row r),
+// added to acc[0], in float32; both lanes of a row get the whole sum.  One v_mfma_f32_16x16x32_bf16: that
+// instruction takes the four 16-lane groups of p as k-slots 8g .. 8g+7 of columns (lane & 15), so that groups g and
+// g + 2 hold the same rows; the selector (make_row_select) is 1 where the result's row, which lane group
+// (row / 4) receives, asks for groups of its own parity, and 0 elsewhere.  A value that is not finite makes the
+// sum of row r ^ 16 NaN as well (0 x inf): the caller looks for NaN and takes row_sum_apart instead.
+// 16 matrix clocks; the four v_dot2c_f32_bf16 of add_values take 17 vector clocks and do not overlap with matrix
+// instructions (a 32x32x16 product and eight of them: 76 clocks, with eight of any other vector instruction 40
+// to 44).  (v_mfma_f32_4x4x4_16b_bf16, which keeps the rows apart, made the forward 2 to 8 % slower than either.)
+DEVI bf16x8 make_row_select(int lane) {
+  bf16x8 a;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) a[j] = (bf16_t)((((lane >> 2) ^ (lane >> 4)) & 1) ? 0.f : 1.f);
+  return a;
+}
+DEVI f32x4 add_rows(bf16x8 p, bf16x8 select, f32x4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(select, p, acc, 0, 0, 0);
+}
+// Row sum of the four fragments of a tile without add_rows.
+DEVI float row_sum_apart(const bf16x8 (&p)[4]) {
+  float s = 0.f;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) s = add_values(p[c], s);
+  return sum_with_partner32(s);
 }
 
 // x / l for the many x that share one divisor l (a row's outputs): a reciprocal of l refined by

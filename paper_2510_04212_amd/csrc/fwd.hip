@@ -20,13 +20,13 @@ constexpr int kBr = 128;   // query rows per work-group
 constexpr int kBc = 64;    // key rows per tile
 
 // Optional outputs and switches of the forward (the experiments of Sec. 3.2 / 3.3.2 and the
-// tie statistics of Sec. 3.3.2 / 4).  Only kernels instantiated with EXTRAS look at them.
+// tie statistics of Sec. 3.3.2 / 4).  Only kernels instantiated with EXTRAS look at them (EXTRAS = 1; 2: with the
+// P-bar V product in E4M3, which costs registers).
 struct FwdExtras {
   float* O_hp;          // [B,H,N,d] float32: accumulator / l with no bf16 rounding, or null
   int* ones;            // [B,H,N]: number of keys whose rounded P-bar was exactly 1, or null
   int* fired;           // [B,H,N]: number of key tiles in which Alg. 3 moved the normaliser, or null
   int single_rounding;  // nonzero: O-bar is NOT rounded to bf16 before the division by l
-  int pv_e4m3;          // nonzero: the P-bar V product takes both operands in 8-bit E4M3
   int guard;            // nonzero: Alg. 3's rule is not applied where it would move the normaliser
                         // by more than kGuardLimit (a labelled deviation from Sec. 4, see attn.h)
 };
@@ -60,6 +60,13 @@ DEVI long pack_e4m3(const float (&v)[8]) {
 //               maximum, no accumulator rescale), LSE[] then receives m + log l as usual.
 constexpr int kRowStats = 3, kFixedNorm = 2;
 
+// Which kernels run as a software pipeline over tiles.  It needs 32 more registers for the next tile's scores: at
+// D <= 64 that costs a wave per SIMD.  Measured, tile after tile -> pipeline (us): causal B2 H8 N2048 d256 93.5 -> 87.9,
+// B4 H16 N4096 d256 774 -> 729, B2 H16 N2048 d96 47.7 -> 46.3, B2 H32/8 N2048 d128 90.5 -> 89.1, B16 H16 N200 d128
+// 16.8 -> 16.5; not taken: B4 H32 N4096 d64 342 -> 353, B8 H12 N1024 d64 27.4 -> 28.4, and without a mask B4 H16
+// N2048 d128 149 -> 152, B2 H16 N2000 d96 65.5 -> 68.3, B2 H8 N2000 d256 99 -> 110.
+template <int D, bool CAUSAL> constexpr bool kPipelined = CAUSAL && D >= 96;
+
 // ---- sharing a block's key tiles out to several work-groups (SPLIT below)
 // Shares of a block of `tiles` key tiles when the grid has `splits` work-groups per block: of two tiles at least,
 // three from 2048 keys on (below that, start-up and merging cost more than a shorter chain takes off).
@@ -84,39 +91,54 @@ template <int D> DEVI float largest_norm(const float* rows, int n, int r) {
 // first tile of share s (share `shares` would be the end)
 DEVI int share_begin(int tiles, int s, int shares) { return tiles * s / shares; }
 
+// Running maxima of a lane's 32 scores of a tile, fed in 2 x kMaxSteps steps (kb, st) so that a caller can spread
+// them over its matrix instructions.  Alg. 3's rule (TWO) needs the two largest (a value met twice is both): two
+// more scores x, y make max3(a1, x, y) the largest, and the second largest is the median of {a1, x, y} or the
+// old a2 (a2 <= a1): 2.5 vector instructions per two scores and no mask bookkeeping.
+constexpr int kMaxSteps = 8;
+template <bool TWO> struct TileMax {
+  float a1[2], a2[2], mid;
+  // step 0 takes scores 0 .. 2, step st = 1 .. 6 scores 2 st + 1 and 2 st + 2, step 7 score 15
+  template <int ST> DEVI void step(int kb, const f32x16& s) {
+    if constexpr (ST == 0) {
+      if (TWO) a2[kb] = __builtin_amdgcn_fmed3f(s[0], s[1], s[2]);
+      a1[kb] = fmaxf(fmaxf(s[0], s[1]), s[2]);
+    } else if constexpr (ST < 7) {
+      const float x = s[2 * ST + 1], y = s[2 * ST + 2];
+      if (TWO) {
+        const float m = __builtin_amdgcn_fmed3f(a1[kb], x, y);
+        if (ST % 2) mid = m; else a2[kb] = fmaxf(fmaxf(a2[kb], mid), m);
+      }
+      a1[kb] = fmaxf(fmaxf(a1[kb], x), y);
+    } else {
+      if (TWO) a2[kb] = __builtin_amdgcn_fmed3f(a1[kb], a2[kb], s[15]);
+      a1[kb] = fmaxf(a1[kb], s[15]);
+    }
+  }
+  DEVI void all(const f32x16 (&s)[2]) {
+    static_for<2>([&](auto kb) { static_for<kMaxSteps>([&](auto st) { step<decltype(st)::value>(decltype(kb)::value, s[decltype(kb)::value]); }); });
+  }
+  DEVI float largest() const { return fmaxf(a1[0], a1[1]); }
+  DEVI float second() const { return fmaxf(fmaxf(fminf(a1[0], a1[1]), a2[0]), a2[1]); }
+};
+
 // Normaliser a row asks for in one key tile (the two lanes of the row get the same): Alg. 1 (VARIANT 0) its
-// maximum r_m, Alg. 3 (VARIANT 1) what the rule makes of it.  s: raw scores, masked ones -inf.
+// maximum r_m, Alg. 3 (VARIANT 1) what the rule makes of it.  tm: maxima of the raw scores, masked ones -inf.
 // may_be_unseen: a row may see no key of the tile.  allowed(r_m): whether a guard lets the rule apply.
 template <int VARIANT, class AllowedF>
-DEVI float tile_normaliser(const f32x16 (&s)[2], float alpha, float inv_alpha, float beta, float eps,
+DEVI float tile_normaliser(const TileMax<VARIANT == 1>& tm, float alpha, float inv_alpha, float beta, float eps,
                            bool may_be_unseen, AllowedF&& allowed, float& r_m) {
   if (VARIANT == 1) {
     // Alg. 3: r_s = #{ r_m - S <= eps } over the tile row; a repeated maximum moves the
     // normaliser to beta*r_m (r_m > 0) or to 0 (r_m < 0).  The count only matters through
     // "more than one", i.e. through whether the SECOND largest score of the row passes the
-    // test: the lane keeps the two largest of its 32 scores (two chains of 16; a value met
-    // twice is both), then the two lanes that share a query row are merged.  Three vector
-    // instructions per two scores and no mask bookkeeping.
-    float a1[2], a2[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      a1[kb] = fmaxf(s[kb][0], s[kb][1]);
-      a2[kb] = fminf(s[kb][0], s[kb][1]);
-#pragma unroll
-      for (int i = 2; i < 16; i += 2) {
-        // two more scores x, y: the largest of {a1, x, y} is the new a1; the second largest
-        // of {a1, a2, x, y} is the median of {a1, x, y} or the old a2 (a2 <= a1)
-        const float x = s[kb][i], y = s[kb][i + 1];
-        const float mid = __builtin_amdgcn_fmed3f(a1[kb], x, y);
-        a1[kb] = fmaxf(fmaxf(a1[kb], x), y);
-        a2[kb] = fmaxf(mid, a2[kb]);
-      }
-    }
-    const float t1 = fmaxf(a1[0], a1[1]);
-    const float t2 = fmaxf(fminf(a1[0], a1[1]), fmaxf(a2[0], a2[1]));
-    const float o1 = partner32(t1), o2 = partner32(t2);
-    const float mx = fmaxf(t1, o1);
-    const float second = fmaxf(fminf(t1, o1), fmaxf(t2, o2));
+    // test: the two lanes that share a query row merge the two largest of their 32 scores.
+    const float t1 = tm.largest(), t2 = tm.second();
+    const auto w1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(t1), __float_as_uint(t1), false, false);
+    const auto w2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(t2), __float_as_uint(t2), false, false);
+    const float x1 = __uint_as_float(w1[0]), y1 = __uint_as_float(w1[1]);       // the largest of either lane
+    const float mx = fmaxf(x1, y1);
+    const float second = fmaxf(fmaxf(fminf(x1, y1), __uint_as_float(w2[0])), __uint_as_float(w2[1]));
     // the test  r_m - alpha*s <= eps  in terms of the raw score:  s >= (r_m - eps) / alpha
     // (a row with nothing visible in this tile has r_m = -inf: no rule, no update)
     r_m = mx * alpha;
@@ -124,12 +146,7 @@ DEVI float tile_normaliser(const f32x16 (&s)[2], float alpha, float inv_alpha, f
     const float m_prime = (repeated && r_m > 0.f) ? beta * r_m : r_m;
     return (repeated && r_m < 0.f) ? 0.f : m_prime;
   }
-  float mx = s[0][0];
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
-  r_m = max_with_partner32(mx) * alpha;
+  r_m = max_with_partner32(tm.largest()) * alpha;
   return r_m;
 }
 
@@ -146,13 +163,19 @@ DEVI float tile_normaliser(const f32x16 (&s)[2], float alpha, float inv_alpha, f
 // normaliser stays for the rest of the row), and only the order of the float32 sums differs: 3e-5 .. 1e-4
 // relative in O, one bf16 step in 1 .. 5 of 10^4 elements.  Without the first launch a share would
 // round P-bar against its own maximum: other roundings, more unit probabilities, 1e-3 .. 2e-3 relative.
-template <int D, bool CAUSAL, int VARIANT, bool RAGGED, bool EXTRAS, bool SPLIT = false>
+template <int D, bool CAUSAL, int VARIANT, bool RAGGED, int EXTRAS, bool SPLIT = false>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 : (D > 128 ? 1 : 8)))) void attn_fwd_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, int N, float alpha, float beta, float eps,
     FwdExtras ex, Layout lay, int pairs, float* __restrict__ part, int splits, BlockOrder ord) {
   constexpr int TILE_BYTES = kBc * D * 2;
+  constexpr bool PIPE = kPipelined<D, CAUSAL> && VARIANT <= 1 && !EXTRAS && !SPLIT;
+  // Row sums by matrix instruction (add_rows) where the vector work is what bounds the kernel: at D <= 64, and without a
+  // mask at D <= 128 (us, dot products -> matrix instructions: B4 H16 N2048 d128 full 151 -> 148, B2 H16 N2000 d96 full
+  // 68.5 -> 67.0; not taken: B2 H8 N2000 d256 full 99 -> 106, B4 H32 N4096 d128 causal in the pipeline 601 -> 611).
+  // (One rule for all kernels of a head size and mask: they give the same bits.)
+  constexpr bool MFMA_SUMS = D <= 64 || (D <= 128 && !CAUSAL);
   extern __shared__ __attribute__((aligned(16))) char smem[];
   // layout: K buffers [2][TILE_BYTES], then V buffers [2][TILE_BYTES]
 
@@ -190,9 +213,10 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
 
   TileLoader<D> loader;
   loader.init(tid, sn);
-  FragOffsets<D> fo;
-  init_frag_offsets<D>(fo, lane, lds_address(smem));
+  FragOffsets<D> fo0;
+  init_frag_offsets<D>(fo0, lane, lds_address(smem));
   const float c2 = alpha * kLog2e;
+  const bf16x8 row_select = make_row_select(lane);
   // Alg. 3's test  r_m - alpha*s <= eps  in terms of the raw score s:  s >= (r_m - eps) / alpha
   const float inv_alpha = 1.0f / alpha;
 
@@ -216,6 +240,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   const int ntiles = SPLIT ? share_begin(all_tiles, split + 1, shares) : all_tiles;
   loader.template load_rows<RAGGED>(smem, Kh, tile0 * kBc, NK);
   if (VARIANT != kRowStats) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, tile0 * kBc, NK);
+  if (PIPE) loader.template load_rows<RAGGED>(smem + TILE_BYTES, Kh, (ntiles > 1 ? 1 : 0) * kBc, NK);
 
   // Q_i^T fragments: lane (r,h) holds Q[qw + r][16kc + 8h .. +7] for every kc.
   bf16x8 qf[D / 16];
@@ -236,7 +261,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   float m = (VARIANT == kFixedNorm) ? LSE[(size_t)bh * N + qc] : -INFINITY;
   float* share = SPLIT ? part + ((size_t)bh * ((N + 31) / 32) + qw / 32) * splits * kPartFloats<D> : nullptr;   // the rows' first share
   if (SPLIT && qw < N) m = largest_norm<D>(share, split, r);
-  float lsum = 0.f;         // this lane's share of the running row sum (its 32 of the 64 keys per tile)
+  float lsum = 0.f;         // running row sum (the same in both lanes of a row; without MFMA_SUMS this lane's share of it)
 
   wait_vmem();
 #pragma unroll
@@ -244,6 +269,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   if (VARIANT == kFixedNorm || SPLIT) settle(m);
   __syncthreads();
 
+  FragOffsets<D> fo = fo0;
   // One key tile; BUF (which LDS buffer holds it) is a compile-time constant so that every LDS
   // address is a precomputed per-lane offset plus an immediate.
   auto tile_step = [&](auto buf_c, int j) {
@@ -299,14 +325,11 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
             if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
       }
       if (VARIANT == kRowStats) {
-        // two largest values seen by this lane (duplicates count: a value met twice is both)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            top2 = __builtin_amdgcn_fmed3f(top1, top2, s[kb][i]);
-            top1 = fmaxf(top1, s[kb][i]);
-          }
+        TileMax<true> tm;                // merged into the two largest this lane has seen
+        tm.all(s);
+        const float t1 = tm.largest(), t2 = tm.second();
+        top2 = fmaxf(fmaxf(fminf(top1, t1), top2), t2);
+        top1 = fmaxf(top1, t1);
       } else {
         float corr = 1.f;    // factor the accumulated output and row sum are multiplied by
         float mneg;          // -m log2(e) of the normaliser used for this tile
@@ -314,7 +337,9 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
           mneg = (RAGGED && m == -INFINITY) ? 0.f : -m * kLog2e;   // a query that sees no key at all
         } else {
           float r_m;         // tile row maximum of the alpha-scaled scores
-          const float m_prime = tile_normaliser<VARIANT>(s, alpha, inv_alpha, beta, eps, may_be_unseen, [&](float r) {
+          TileMax<VARIANT == 1> tm;
+          tm.all(s);
+          const float m_prime = tile_normaliser<VARIANT>(tm, alpha, inv_alpha, beta, eps, may_be_unseen, [&](float r) {
             return !EXTRAS || ex.guard == 0 || guard_allows(r, beta);
           }, r_m);
           if (EXTRAS && VARIANT == 1) fired_cnt += (m_prime != r_m) ? 1 : 0;
@@ -324,7 +349,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
           m = m_new;
           mneg = unseen ? 0.f : -m_new * kLog2e;
         }
-        if (EXTRAS && ex.pv_e4m3 != 0) {
+        if constexpr (EXTRAS == 2) {
           // ---- exploration beyond the paper (its future-work remark on FP8): the same step with
           // P-bar and V_j rounded to E4M3 and multiplied by the FP8 matrix instruction; the row sum
           // is of the rounded P-bar, everything downstream is unchanged.  Same k-slot order in
@@ -352,7 +377,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
                 ones_cnt += back[jj] == 1.0f ? 1 : 0;
               }
             }
-          lsum = lsum * corr + psum8;
+          lsum = lsum * corr + (MFMA_SUMS ? sum_with_partner32(psum8) : psum8);
           if (VARIANT != kFixedNorm && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
@@ -373,24 +398,20 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
               }
         } else {
         // ---- P-bar = exp(S - m), rounded to bf16; row sum of the ROUNDED values
-        bf16x8 pf[2][2];
-        float psum = 0.f;
+        bf16x8 pf[4];
+        f32x4 psum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int c = 0; c < 4; ++c) {
 #pragma unroll
-          for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-            for (int jj = 0; jj < 8; jj += 2) {
-              bf16x2 pp;
-#pragma unroll
-              for (int e = 0; e < 2; ++e)
-                pp[e] = (bf16_t)__builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][8 * cc + jj + e], c2, mneg));
-              pf[kb][cc][jj] = pp[0];
-              pf[kb][cc][jj + 1] = pp[1];
-              psum = add_pair_bf16(pp, psum);
-              if (EXTRAS) ones_cnt += ((float)pp[0] == 1.0f ? 1 : 0) + ((float)pp[1] == 1.0f ? 1 : 0);
-            }
-        lsum = lsum * corr + psum;
+          for (int jj = 0; jj < 8; ++jj) {
+            const bf16_t p = (bf16_t)__builtin_amdgcn_exp2f(__builtin_fmaf(s[c >> 1][8 * (c & 1) + jj], c2, mneg));
+            pf[c][jj] = p;
+            if (EXTRAS) ones_cnt += (float)p == 1.0f ? 1 : 0;
+          }
+          if (MFMA_SUMS) psum = add_rows(pf[c], row_select, psum);
+          else psum[0] = add_values(pf[c], psum[0]);
+        }
+        if (!MFMA_SUMS) lsum = lsum * corr + psum[0];
         // ---- O^T <- diag(corr) O^T + V_j^T P-bar^T (Alg. 1 step 8); in the first tile the
         // accumulator is still zero (corr = exp(-inf) = 0 there), nothing to rescale
         if (VARIANT != kFixedNorm && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
@@ -399,13 +420,15 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[db][i] *= corr;
         }
+        const bool not_finite = MFMA_SUMS && __builtin_amdgcn_ballot_w64(psum[0] != psum[0]) != 0;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
-          for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-            for (int db = 0; db < D / 32; ++db)
-              acc[db] = mfma32(lds_col8<D>(tV, fo, 32 * kb + 16 * cc, db), pf[kb][cc], acc[db]);
+          for (int db = 0; db < D / 32; ++db) acc[db] = mfma32(lds_col8<D>(tV, fo, 16 * c, db), pf[c], acc[db]);
+        if (MFMA_SUMS) {
+          if (not_finite) psum[0] = row_sum_apart(pf);
+          lsum = lsum * corr + psum[0];
+        }
         }
       }
     }
@@ -417,14 +440,181 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
     __syncthreads();
   };
 
-  for (int j = tile0; j < ntiles; j += 2) {
-    tile_step(std::integral_constant<int, 0>{}, j);
-    if (j + 1 < ntiles) tile_step(std::integral_constant<int, 1>{}, j + 1);
+  // The same tiles as a software pipeline over tiles: one step holds the scores of tile j + 1 and the output product
+  // of tile j as one stream of 4 x D/16 matrix instructions ("slots", a fence each, LDS fragments read AHEAD
+  // slots before their use), with the vector work under them: P-bar of tile j under the scores of tile j + 1,
+  // the row maxima of tile j + 1 under the output product.  K is read one tile ahead of V.
+  static_assert(!PIPE || !MFMA_SUMS, "row sums of the pipeline");
+  if constexpr (PIPE) {
+    constexpr int NS = D / 16, NDB = D / 32, AHEAD = 4, RING = AHEAD + 1;
+    // tiles this wave has anything to do with
+    const int qu = __builtin_amdgcn_readfirstlane(qw) + shift;      // last key its first row sees
+    const int seen = qu + 31 < 0 ? 0 : min(ntiles, (qu + 31) / kBc + 1);
+    f32x16 s0[2], s1[2];                               // raw scores of even and odd tiles
+    float corr = 1.f, mneg = 0.f;                      // of the tile whose P-bar is next
+    auto masked_tile = [&](int j) { return j * kBc + kBc - 1 > qu || (RAGGED && (j + 1) * kBc > NK); };
+    auto limit = [&](int j) {                          // last visible c = 32 kb + 8 (i / 4) + i % 4 of tile j
+      const int lim = q + shift - j * kBc - 4 * h;
+      return RAGGED ? min(lim, NK - 1 - j * kBc - 4 * h) : lim;
+    };
+    // scores 16 kb + lo .. of a tile that crosses the diagonal or the sequence end
+    auto mask = [&](f32x16& s, int kb, int lo, int hi, int lim) {
+#pragma unroll
+      for (int i = lo; i < hi; ++i)
+        s[i] = 32 * kb + 8 * (i >> 2) + (i & 3) > lim ? -INFINITY : s[i];
+    };
+    // running normaliser after a tile, and what its P-bar needs
+    auto advance = [&](const TileMax<VARIANT == 1>& tm) {
+      float r_m;         // tile row maximum of the alpha-scaled scores
+      const float m_prime = tile_normaliser<VARIANT>(tm, alpha, inv_alpha, beta, eps, may_be_unseen, [](float) { return true; }, r_m);
+      const float m_new = fmaxf(m, m_prime);         // Alg. 1 step 7 / Alg. 3
+      const bool unseen = may_be_unseen && m_new == -INFINITY;   // nothing visible so far: P-bar = 0, nothing to rescale
+      corr = unseen ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * kLog2e);
+      m = m_new;
+      mneg = unseen ? 0.f : -m_new * kLog2e;
+    };
+    // The LDS buffers change by adding to the fragment addresses (fo.row: the next tile's K, fo.col: this tile's V).
+    int par = 0, turn = TILE_BYTES;                    // parity of the tile: its V buffer, the other K buffer
+    constexpr int NLD = TileLoader<D>::NI;
+    typename TileLoader<D>::Pending pendK, pendV;
+    // K of tile j + 2 and V of tile j + 1 (past the last tile: that one once more, harmlessly)
+    auto prepare = [&](int j) {
+      pendK = loader.template prepare<RAGGED>(smem + par * TILE_BYTES, Kh, min(j + 2, ntiles - 1) * kBc, NK);
+      pendV = loader.template prepare<RAGGED>(smem + (2 + (par ^ 1)) * TILE_BYTES, Vh, min(j + 1, ntiles - 1) * kBc, NK);
+    };
+    auto issue_part = [&](int i) {
+      if (i < NLD) loader.issue(pendK, i);
+      else if (i < 2 * NLD) loader.issue(pendV, i - NLD);
+    };
+    auto finish = [&]() {
+      wait_vmem();
+      __syncthreads();
+      par ^= 1;
+    };
+    auto step = [&](auto next_c, auto masked_c, int j, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
+      constexpr bool NEXT = decltype(next_c)::value, MASKED = decltype(masked_c)::value;
+      constexpr int FIRST = NEXT ? 0 : 2 * NS, SLOTS = 4 * NS;
+      auto fragment = [&](int i) -> bf16x8 {
+        if (i < 2 * NS) return lds_row8<D>(0, fo, 32 * (i / NS), i % NS);
+        return lds_col8<D>(0, fo, 16 * ((i - 2 * NS) / NDB), (i - 2 * NS) % NDB);
+      };
+      prepare(j);
+      // O^T <- diag(corr) O^T (Alg. 1 step 8); in the first tile the accumulator is still zero
+      if (j > 0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[db][i] *= corr;
+      }
+      bf16x8 ring[RING], pf[4];
+      float psum = 0.f;
+      TileMax<VARIANT == 1> tm;
+      const int lim = MASKED ? limit(j + 1) : 0;
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) ring[(FIRST + i) % RING] = fragment(FIRST + i);
+      if (NEXT) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sn[kb][i] = 0.f;
+      }
+      // P-bar = exp(S - m) of entries e0 .. e1 - 1 (of 32), rounded to bf16; row sum of the ROUNDED values
+      auto form_p = [&](int e0, int e1) {
+#pragma unroll
+        for (int e = e0; e < e1; ++e) {
+          const bf16_t p = (bf16_t)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[e >> 4][e & 15], c2, mneg));
+          pf[e >> 3][e & 7] = p;
+          if (e % 8 == 7) psum = add_values(pf[e >> 3], psum);
+        }
+      };
+      if (!NEXT) form_p(0, 8);
+      static_for<SLOTS - FIRST>([&](auto slot) {
+        constexpr int sl = FIRST + decltype(slot)::value;
+        if (sl + AHEAD < SLOTS) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+        const bf16x8 a = ring[sl % RING];
+        if constexpr (sl < 2 * NS) sn[sl / NS] = mfma32(a, qf[sl % NS], sn[sl / NS]);
+        else acc[(sl - 2 * NS) % NDB] = mfma32(a, pf[(sl - 2 * NS) / NDB], acc[(sl - 2 * NS) % NDB]);
+        issue_part(sl - FIRST);
+        if constexpr (sl < 2 * NS) {
+          form_p(16 * sl / NS, 16 * (sl + 1) / NS);
+        } else {
+          constexpr int u = sl - 2 * NS;
+          if (!NEXT && u % NDB == 0 && u / NDB < 3) form_p(8 * (u / NDB + 1), 8 * (u / NDB + 2));
+          if constexpr (NEXT) {
+            // steps of the row maxima, over all but the last quarter of the slots
+            constexpr int SPAN = NS * 3 / 2 < 1 ? 1 : NS * 3 / 2, F = 2 * kMaxSteps * u / SPAN, L = 2 * kMaxSteps * (u + 1) / SPAN;
+            static_for<(u < SPAN ? L - F : 0)>([&](auto k) {
+              constexpr int t = F + decltype(k)::value, kb = t / kMaxSteps, st = t % kMaxSteps;
+              if (MASKED) mask(sn[kb], kb, st == 0 ? 0 : 2 * st + 1, st == 0 ? 3 : st < 7 ? 2 * st + 3 : 16, lim);
+              tm.template step<st>(kb, sn[kb]);
+            });
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      lsum = lsum * corr + psum;
+      if (NEXT) advance(tm);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) { fo.row[p] -= turn; fo.col[p] += turn; }
+      turn = -turn;
+      finish();
+    };
+    // ---- scores of the first tile
+    if (seen > 0) {
+      static_for<2 * NS>([&](auto i) {
+        constexpr int sl = decltype(i)::value;
+        if (sl % NS == 0) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) s0[sl / NS][e] = 0.f;
+        }
+        s0[sl / NS] = mfma32(lds_row8<D>(0, fo, 32 * (sl / NS), sl % NS), qf[sl % NS], s0[sl / NS]);
+      });
+      sched_reads_ahead_of_mfma<2 * NS, 1, 4>();
+      if (masked_tile(0)) {
+        const int lim = limit(0);
+        mask(s0[0], 0, 0, 16, lim);
+        mask(s0[1], 1, 0, 16, lim);
+      }
+      TileMax<VARIANT == 1> tm;
+      tm.all(s0);
+      advance(tm);
+    }
+    __syncthreads();                                   // K of the first tile is read out everywhere: its buffer is free
+#pragma unroll
+    for (int p = 0; p < 2; ++p) { fo.row[p] += TILE_BYTES; fo.col[p] += 2 * TILE_BYTES; }
+    int j = 0;
+    auto plain_next = [&]() { return j + 1 < seen && !masked_tile(j + 1); };
+    while (plain_next()) {
+      step(std::true_type{}, std::false_type{}, j++, s0, s1);
+      if (!plain_next()) {
+        s0[0] = s1[0];
+        s0[1] = s1[1];
+        break;
+      }
+      step(std::true_type{}, std::false_type{}, j++, s1, s0);
+    }
+    while (j + 1 < seen) {
+      step(std::true_type{}, std::true_type{}, j++, s0, s1);
+      s0[0] = s1[0];
+      s0[1] = s1[1];
+    }
+    if (j < seen) step(std::false_type{}, std::false_type{}, j++, s0, s1);
+    for (; j < ntiles; ++j) {                          // the other waves' tiles: this wave's share of the transfers
+      prepare(j);
+#pragma unroll
+      for (int i = 0; i < 2 * NLD; ++i) issue_part(i);
+      finish();
+    }
+  } else {
+    for (int j = tile0; j < ntiles; j += 2) {
+      tile_step(std::integral_constant<int, 0>{}, j);
+      if (j + 1 < ntiles) tile_step(std::integral_constant<int, 1>{}, j + 1);
+    }
   }
 
   if constexpr (SPLIT) {
     // the share's sums, as the registers hold them (16 bytes per lane, lanes consecutive)
-    const float l_share = sum_with_partner32(lsum);
+    const float l_share = MFMA_SUMS ? lsum : sum_with_partner32(lsum);
     if (qw < N) {
       float* p = share + (size_t)split * kPartFloats<D>;
 #pragma unroll
@@ -458,7 +648,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
   }
   // ---- epilogue (Alg. 1 steps 10-13).  Rounding points of Sec. 3.3.2: the unnormalised
   // output is rounded to bf16 first, then divided by l, then rounded again.
-  const float l = sum_with_partner32(lsum);
+  const float l = MFMA_SUMS ? lsum : sum_with_partner32(lsum);
   int ones_row = 0;
   if (EXTRAS) {   // the partner lane counted the other 32 keys of every tile
     auto sw = __builtin_amdgcn_permlane32_swap((unsigned)ones_cnt, (unsigned)ones_cnt, false, false);
@@ -580,7 +770,9 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, D <= 128 ? 2 : 1))) void at
             if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
       }
       float r_m;
-      m = fmaxf(m, tile_normaliser<VARIANT>(s, alpha, inv_alpha, beta, eps, may_be_unseen, [](float) { return true; }, r_m));
+      TileMax<VARIANT == 1> tm;
+      tm.all(s);
+      m = fmaxf(m, tile_normaliser<VARIANT>(tm, alpha, inv_alpha, beta, eps, may_be_unseen, [](float) { return true; }, r_m));
     }
     wait_vmem();
     __syncthreads();
@@ -651,7 +843,7 @@ __global__ __launch_bounds__(256) void attn_fwd_merge_kernel(
 
 extern "C" int attn_fwd_key_tile(int d) { return (d == 32 || d == 64 || d == 96 || d == 128 || d == 256) ? kBc : 0; }
 
-template <int D, bool CAUSAL, int VARIANT, bool RAGGED, bool EXTRAS>
+template <int D, bool CAUSAL, int VARIANT, bool RAGGED, int EXTRAS>
 static hipError_t launch_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
                              int BH, int N, float alpha, float beta, float eps, FwdExtras ex,
                              Layout lay, hipStream_t st) {
@@ -690,7 +882,7 @@ static hipError_t launch_fwd_split(const void* Q, const void* K, const void* V, 
   constexpr int smem = 4 * kBc * D * 2;
   static std::atomic<bool> attr_set{false};
   auto norms = attn_fwd_norms_kernel<D, CAUSAL, VARIANT>;
-  auto sums = attn_fwd_kernel<D, CAUSAL, VARIANT, true, false, true>;
+  auto sums = attn_fwd_kernel<D, CAUSAL, VARIANT, true, 0, true>;
   hipError_t e;
   if (!attr_set.load(std::memory_order_acquire)) {
     for (const void* kern : {reinterpret_cast<const void*>(norms), reinterpret_cast<const void*>(sums)})
@@ -756,38 +948,39 @@ hipError_t attn_fwd_split_dispatch(const void* Q, const void* K, const void* V, 
 }
 
 // Host-side dispatch used by the C ABI (api.hip).  Shapes are validated by the caller.
-// The optional outputs / switches select a second set of kernels (always the bounds-checking
+// The optional outputs / switches select further sets of kernels (always the bounds-checking
 // instantiation), so that the plain forward carries none of their instructions.
+template <int D, bool CAUSAL, int VARIANT>
+static hipError_t launch_fwd_form(bool ragged, int extras, const void* Q, const void* K, const void* V, void* O, float* LSE,
+                                  int BH, int N, float alpha, float beta, float eps, FwdExtras ex, Layout lay, hipStream_t st) {
+  if (extras == 2 && VARIANT != kRowStats)     // (the statistics pass has no such product)
+    return launch_fwd<D, CAUSAL, VARIANT, true, VARIANT == kRowStats ? 1 : 2>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st);
+  if (extras) return launch_fwd<D, CAUSAL, VARIANT, true, 1>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st);
+  // (whole-row rule: the bounds-checking kernels serve every N)
+  return ragged ? launch_fwd<D, CAUSAL, VARIANT, true, 0>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st)
+                : launch_fwd<D, CAUSAL, VARIANT, (VARIANT > 1), 0>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st);
+}
+
 hipError_t attn_fwd_dispatch(const void* Q, const void* K, const void* V, void* O, float* LSE,
                              int BH, int N, int d, int causal, float alpha, int variant,
                              float beta, float eps, float* O_hp, int* ones, int* fired,
                              int flags, Layout lay, hipStream_t st) {
   // flags: bit 0 = single rounding of the output, bit 1 = P-bar V in E4M3, bit 2 = guarded Alg. 3
-  const bool extras = O_hp != nullptr || ones != nullptr || fired != nullptr || flags != 0;
-  const FwdExtras ex{O_hp, ones, fired, flags & 1, (flags >> 1) & 1, (flags >> 2) & 1};
-  if (variant == 2) {   // whole-row detection: statistics pass, then the fixed-normaliser pass
-#define CASE2(DD, CC)                                                                           \
+  const int extras = (flags & 2) ? 2 : (O_hp != nullptr || ones != nullptr || fired != nullptr || flags != 0) ? 1 : 0;
+  const FwdExtras ex{O_hp, ones, fired, flags & 1, (flags >> 2) & 1};
+  const bool ragged = N % kBr != 0 || lay.Nk != N;
+#define CASE(DD, CC)                                                                            \
   if (d == DD && (causal != 0) == CC) {                                                          \
-    hipError_t e = launch_fwd<DD, CC, kRowStats, true, true>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
+    if (variant == 0) return launch_fwd_form<DD, CC, 0>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
+    if (variant == 1) return launch_fwd_form<DD, CC, 1>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
+    if (variant != 2) return hipErrorInvalidValue;                                               \
+    /* whole-row detection: statistics pass, then the fixed-normaliser pass */                   \
+    hipError_t e = launch_fwd_form<DD, CC, kRowStats>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
     if (e != hipSuccess) return e;                                                               \
-    return launch_fwd<DD, CC, kFixedNorm, true, true>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
+    return launch_fwd_form<DD, CC, kFixedNorm>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
   }
-    CASE2(32, false) CASE2(32, true) CASE2(64, false) CASE2(64, true) CASE2(128, false) CASE2(128, true)
-    CASE2(256, false) CASE2(256, true) CASE2(96, false) CASE2(96, true)
-#undef CASE2
-    return hipErrorInvalidValue;
-  }
-#define CASE(DD, CC, VV)                                                                      \
-  if (d == DD && (causal != 0) == CC && variant == VV) {                                       \
-    if (extras) return launch_fwd<DD, CC, VV, true, true>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
-    return (N % kBr || lay.Nk != N) ? launch_fwd<DD, CC, VV, true, false>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st) \
-                     : launch_fwd<DD, CC, VV, false, false>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
-  }
-  CASE(32, false, 0) CASE(32, false, 1) CASE(32, true, 0) CASE(32, true, 1)
-  CASE(64, false, 0) CASE(64, false, 1) CASE(64, true, 0) CASE(64, true, 1)
-  CASE(128, false, 0) CASE(128, false, 1) CASE(128, true, 0) CASE(128, true, 1)
-  CASE(256, false, 0) CASE(256, false, 1) CASE(256, true, 0) CASE(256, true, 1)
-  CASE(96, false, 0) CASE(96, false, 1) CASE(96, true, 0) CASE(96, true, 1)
+  CASE(32, false) CASE(32, true) CASE(64, false) CASE(64, true) CASE(128, false) CASE(128, true)
+  CASE(256, false) CASE(256, true) CASE(96, false) CASE(96, true)
 #undef CASE
   return hipErrorInvalidValue;
 }
