@@ -87,9 +87,12 @@ template <int D, int G> constexpr int kSmemDkDv =
     G > 1 ? max_int(kTilesEnd<D, G>, kExchangeBytes<D, G>)
           : kStageOverTiles<D, G> ? max_int(kTilesEnd<D, G>, kVBytes<D, G> + kStageBytes<D>) : kTilesEnd<D, G> + kStageBytes<D>;
 
-template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G>
+// DENSE (D <= 64): three waves on every SIMD at the price of a shorter read-ahead, for grids that have the work-groups
+// (launch_dkdv).
+template <int D, bool DENSE> constexpr int kDkDvWaves = DENSE ? 3 : kWavesPerSimd<D>;
+template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G, bool DENSE>
 __global__ __launch_bounds__(64 * kKeyWaves<G> * G)
-__attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void attn_bwd_dkdv_kernel(
+__attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>))) void attn_bwd_dkdv_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int N, float alpha, Layout lay, int pairs,
@@ -319,7 +322,7 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
         constexpr bool MASKED = decltype(masked_c)::value;
         constexpr int NB = decltype(nb_c)::value, qb = decltype(qb_c)::value;
         constexpr int NS = D / 16, NU = 2 * NDB, PB = 2 * NS + 2 * NU;    // slots of S or dP, of dV or dK, of a block
-        constexpr int AHEAD = kReadAhead<D>, RING = AHEAD + 1;
+        constexpr int AHEAD = DENSE ? 2 : kReadAhead<D>, RING = AHEAD + 1;
         auto fragment = [&](int i) -> bf16x8 {
           const int b = qb + i / PB, u = i % PB;
           if (u < NS) return lds_row8<D>(tQ, fo, 32 * b, u);
@@ -341,7 +344,11 @@ __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<D>, kWavesPerSimd<D>))) void at
           if (u == 0) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = 0.f;
-            if (MASKED) first_seen = kw + r - shift - qt0 - 32 * (b + grp) - 4 * h;
+            if (MASKED) {
+              int ln = lane;
+              if (DENSE) asm volatile("" : "+v"(ln));    // (formed here, not ahead of the tile loop: registers)
+              first_seen = (DENSE ? __builtin_amdgcn_readfirstlane(kw) : kw) + (ln & 31) - shift - qt0 - 32 * (b + grp) - 4 * (ln >> 5);
+            }
           }
           // -delta_i seeds the dP accumulator; L_i of the rows a lane sees
 #pragma unroll
@@ -835,13 +842,13 @@ static hipError_t set_smem(KernT kern, int smem, std::atomic<bool>& done) {
   return e;
 }
 
-template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G>
+template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G, bool DENSE = false>
 static hipError_t launch_dkdv_g(const void* Q, const void* K, const void* V, const void* dO,
                                 const float* LSE, const float* delta, void* dK, void* dV, int BH,
                                 int N, float alpha, Layout lay, hipStream_t st) {
   constexpr int smem = kSmemDkDv<D, G>;
   static std::atomic<bool> set{false};
-  auto k = attn_bwd_dkdv_kernel<D, CAUSAL, RAGGED, GROUPED, G>;
+  auto k = attn_bwd_dkdv_kernel<D, CAUSAL, RAGGED, GROUPED, G, DENSE>;
   hipError_t e;
   if ((e = set_smem(k, smem, set)) != hipSuccess) return e;
   constexpr int KEYS = 32 * kKeyWaves<G>, THREADS = 64 * kKeyWaves<G> * G;
@@ -889,6 +896,16 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
         if (blocks <= (CAUSAL ? 2 : 1) * kNumCUs)
           return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 2>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
     }
+  }
+  // More than two 128-key blocks per CU at D <= 64: three waves per SIMD.  Measured, two -> three (us): B8 H12 N1024 d64
+  // causal 41.3 -> 37.9, B32 H12 N512 d64 full 68.8 -> 67.1, B4 H32 N4096 d64 causal 515 -> 505, B8 H12 N1000 d64 full
+  // 63.6 -> 60.8, B8 H12 N1024 d32 causal 26.8 -> 23.4, B8 H16 N1001 d32 full 55.6 -> 52.0; below the limit: B4 H12
+  // N1024 d64 causal 24.7 -> 25.7, in pairs B1 H33 N2040 d64 66.4 -> 70.1, B5 H13 N1024 d32 27.4 -> 28.3; with grouped queries B4 H32/8 N2048 d64 causal 162 -> 170.
+  if constexpr (D <= 64 && !GROUPED) {
+    const int NK = RAGGED ? lay.Nk : N;
+    // (head counts the order table does not take run as pairs of blocks: half as many work-groups)
+    if ((long long)BH * ((NK + kKeysPerWG - 1) / kKeysPerWG) > (CAUSAL && BH % 8 != 0 ? 4 : 2) * kNumCUs)
+      return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1, true>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
   }
   return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
 }

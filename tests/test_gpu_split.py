@@ -36,6 +36,16 @@ def test_dkdv_with_two_wave_groups(lib, H, N, d, causal):
         check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"two groups H{H} N{N} d{d} c{causal}")
 
 
+@pytest.mark.parametrize("d", [32, 64])
+@pytest.mark.parametrize("H,N,causal", [(264, 200, True), (520, 65, True), (72, 1000, True), (513, 128, False), (260, 161, False)])
+def test_dkdv_with_three_waves_per_simd(lib, H, N, d, causal):
+    """More than two 128-key blocks per CU (four where blocks run in pairs): aligned, ragged, shorter than a block."""
+    x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
+    got = _run(lib, x, causal, d ** -0.5, 1)
+    for h in (0, H // 2, H - 1):
+        check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"three waves H{H} N{N} d{d} c{causal}")
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("N", [512, 577])
 def test_grouped_queries_with_wave_groups(lib, N, d):
