@@ -70,7 +70,8 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 template <int G> constexpr int kKeyWaves = G == 4 ? 2 : 4;               // waves per group, 32 keys each
 template <int D, int G> constexpr int kQTile = D == 128 || G == 4 ? 32 * G : 64;   // query rows per streamed tile
 // LDS fragments are read this many matrix instructions before their use.
-template <int D> constexpr int kReadAhead = D == 256 ? 6 : 4;
+// (At D = 128 what the registers allow: the fragments of V_j come from LDS too.)
+template <int D> constexpr int kReadAhead = D == 256 ? 6 : D == 128 ? 2 : 4;
 // dK / dV rows leave through a per-wave LDS staging area (store_rows_staged) where the row width
 // allows it; it overlays the tile buffers where it would otherwise cost a resident work-group, and
 // is left out at D = 256 (no room).
@@ -254,7 +255,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       const float* tL = ldsL + buf * QT;
       const float* tD = ldsD + buf * QT;
       const int qt0 = t * QT;
-      // V_j in LDS (no registers for what qblocks below keeps live): one 32-query block against this wave's 32 keys,
+      // V_j in LDS and wave groups (no registers for what qblocks below keeps live): one 32-query block against this wave's 32 keys,
       // in one code path (the block that crosses the diagonal only adds a masking step).  The next tile's transfer is
       // issued on the way.
       auto qblock = [&]() {
@@ -315,7 +316,9 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       // block lies under its own matrix instructions: P = exp(S - L) under dP, dS = P o (dP - delta) under dV,
       // and every LDS fragment is read AHEAD slots before its use (a fence per slot keeps that order).  Same bits as
       // phase after phase; us, whole kernel: B2 H8 N2048 d256 causal 120 -> 116, B1 H8 N1000 d256 causal 74 -> 59,
-      // B2 H16 N2048 d96 causal 68 -> 66, B4 H32 N4096 d64 causal 519 -> 510, B32 H12 N512 d64 full 67.5 -> 66.0.
+      // B2 H16 N2048 d96 causal 68 -> 66, B4 H32 N4096 d64 causal 519 -> 510, B32 H12 N512 d64 full 67.5 -> 66.0;
+      // d128, the whole training step: B4 H32 N4096 causal 2374 -> 2309, B1 H16 N16384 causal 4561 -> 4470,
+      // B4 H16 N1999 causal 334 -> 329.
       // The next tile's transfer is issued on the way.
       // MASKED: a block crosses the diagonal.
       auto qblocks = [&](auto masked_c, auto nb_c, auto qb_c) {
@@ -323,6 +326,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
         constexpr int NB = decltype(nb_c)::value, qb = decltype(qb_c)::value;
         constexpr int NS = D / 16, NU = 2 * NDB, PB = 2 * NS + 2 * NU;    // slots of S or dP, of dV or dK, of a block
         constexpr int AHEAD = DENSE ? 2 : kReadAhead<D>, RING = AHEAD + 1;
+        constexpr int AHEAD_V = 1, RING_V = AHEAD_V + 1;       // kVInLds: V_j's fragments
         auto fragment = [&](int i) -> bf16x8 {
           const int b = qb + i / PB, u = i % PB;
           if (u < NS) return lds_row8<D>(tQ, fo, 32 * b, u);
@@ -330,7 +334,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
           const int w = (u - 2 * NS) % NU;
           return lds_col8<D>(u < 2 * NS + NU ? tdO : tQ, fo_upd, 32 * b + 16 * (w / NDB), w % NDB);
         };
-        bf16x8 ring[RING];
+        bf16x8 ring[RING], ring_v[kVInLds<D> ? RING_V : 1];
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) ring[i] = fragment(i);
         f32x16 s, dp;
@@ -341,13 +345,16 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
           constexpr int sl = decltype(slot)::value, u = sl % PB, b = qb + sl / PB;
           const int stat = 32 * (b + grp) + 4 * h;
           if (sl + AHEAD < NB * PB) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+          constexpr int uv = u + AHEAD_V - NS;
+          if constexpr (kVInLds<D> && uv >= 0 && uv < NS) ring_v[uv % RING_V] = lds_row8<D>(0, fo_v, 0, uv);
           if (u == 0) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = 0.f;
             if (MASKED) {
               int ln = lane;
-              if (DENSE) asm volatile("" : "+v"(ln));    // (formed here, not ahead of the tile loop: registers)
-              first_seen = (DENSE ? __builtin_amdgcn_readfirstlane(kw) : kw) + (ln & 31) - shift - qt0 - 32 * (b + grp) - 4 * (ln >> 5);
+              constexpr bool LATE = DENSE || kVInLds<D>;         // formed here, not ahead of the tile loop: registers
+              if (LATE) asm volatile("" : "+v"(ln));
+              first_seen = (LATE ? __builtin_amdgcn_readfirstlane(kw) : kw) + (ln & 31) - shift - qt0 - 32 * (b + grp) - 4 * (ln >> 5);
             }
           }
           // -delta_i seeds the dP accumulator; L_i of the rows a lane sees
@@ -365,7 +372,8 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
           if constexpr (u < NS) {
             s = mfma32(a, kf[u], s);
           } else if constexpr (u < 2 * NS) {
-            dp = mfma32(a, vf[u - NS], dp);
+            if constexpr (kVInLds<D>) dp = mfma32(a, ring_v[(u - NS) % RING_V], dp);
+            else dp = mfma32(a, vf[u - NS], dp);
           } else if constexpr (u < 2 * NS + NU) {
             constexpr int w = u - 2 * NS;
             dVt[w % NDB] = mfma32(a, pf[w / NDB], dVt[w % NDB]);
@@ -401,7 +409,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       const int q_first = qt0 + 32 * grp, q_last = q_first + 32 * NBT - 1;     // first and last query of them
       if ((CAUSAL && q_last + shift < kw) || (RAGGED && q_first >= N)) {
         // no query sees a key of the wave, or nothing but padding
-      } else if constexpr (kVInLds<D>) {
+      } else if constexpr (kVInLds<D> && G > 1) {
         qblock();
       } else if (!CAUSAL || q_first + shift >= kw + 31) {
         asm volatile("; every entry counts");                // (differs from the other path: nothing is merged in front of the branch)
