@@ -52,7 +52,7 @@ DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, in
 template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // The kernel wants two waves on every SIMD: one wave alone leaves the matrix cores idle whenever
 // any of its instructions waits.  That means at most 256 registers per lane (a few wave-group instantiations
-// at D = 96 and 128 spill two to eleven, outside their loops or one read a tile).  At D = 128 the
+// at D = 96 and 128 spill two to eleven, outside their tile loops).  At D = 128 the
 // accumulators (128) and the K fragments (32) leave no room for the V fragments: V_j is kept in LDS
 // for the whole block (8 more fragment reads per 32 queries to 48) and the query tiles shrink to 32
 // rows per wave group, so that two work-groups fit a CU.  Measured against one wave per SIMD with
@@ -99,12 +99,12 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int N, float alpha, Layout lay, int pairs,
     BlockOrder ord) {
   constexpr int QT = kQTile<D, G>;
-  constexpr int TILE_BYTES = QT * D * 2;
-  constexpr int T0 = kVBytes<D, G>;                    // the tile buffers follow V_j
+  constexpr int TILE_BYTES = QT * D * 2, GT = TILE_BYTES / G;
+  constexpr int T0 = kVBytes<D, G>;                    // the tile buffers follow V_j: per wave group Q [2][GT], dO [2][GT]
   constexpr int KW = kKeyWaves<G>, KEYS = 32 * KW;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* ldsQ = smem + T0;
-  char* ldsdO = ldsQ + 2 * TILE_BYTES;
+  char* ldsdO = ldsQ + 2 * GT;
   float* ldsL = reinterpret_cast<float*>(smem + T0 + 4 * TILE_BYTES);
   float* ldsD = ldsL + 2 * QT;
 
@@ -148,13 +148,23 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
   for (int p = 0; p < 2; ++p) {
     if (kVInLds<D>) fo_v.row[p] += 2 * wave * kRowBlockBytes<D>;
     if (DS > 1) fo_upd.col[p] += 1024 * db0;
-    if (G > 1) {                                       // group g reads the g-th 32 rows of a tile
-      fo.row[p] += 2 * grp * kRowBlockBytes<D>;
-      fo_upd.col[p] += 2 * grp * kRowBlockBytes<D>;
+    if (G > 1) {
+      fo.row[p] += 4 * grp * GT;
+      fo_upd.col[p] += 4 * grp * GT;
     }
   }
+  // Group g reads the g-th 32 rows of a tile, which are the rows that its own waves fetch.  Its four buffers lie next
+  // to one another (tiles as a whole would not), within the 64 KB that the immediate offset of an LDS read reaches:
+  // one base register for all of them, which is what leaves the registers for the stream of qblocks below at D = 128 (with
+  // whole tiles it spills 33 to 55, now 6 to 9, outside the loop).  us, whole tiles and phase after phase -> now, same
+  // bits: B2 H16 N2048 d128 causal 95.5 -> 88.1, B2 H8 N2048 d128 full 71.6 -> 67.2, B1 H4 N4096 d128 causal 69.2 -> 66.0,
+  // B2 H32/8 N2048 d128 causal 176 -> 172; at D <= 96, where only the layout changes, within 2 % either way.
   TileLoader<D, QT, KW * G> loader;
   loader.init(tid, sn);
+  if (G > 1) {
+    static_assert(G == 1 || GT == 2 * kRowBlockBytes<D>, "32 rows per group");
+    loader.lds_wave += 3 * grp * GT;
+  }
 
   for (int part = 0; part < (CAUSAL ? 2 : 1); ++part) {
     const int kt = (part == 0) ? kt_first : nkt - 1 - kt_first;
@@ -242,75 +252,19 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
         tn = t0;
       }
       constexpr int NLD = decltype(loader)::NI;
-      const auto pendQ = loader.template prepare<RAGGED>(ldsQ + (buf ^ 1) * TILE_BYTES, Qh, tn * QT, N);
-      const auto pendD = loader.template prepare<RAGGED>(ldsdO + (buf ^ 1) * TILE_BYTES, dOh, tn * QT, N);
+      const auto pendQ = loader.template prepare<RAGGED>(ldsQ + (buf ^ 1) * GT, Qh, tn * QT, N);
+      const auto pendD = loader.template prepare<RAGGED>(ldsdO + (buf ^ 1) * GT, dOh, tn * QT, N);
       auto issue_part = [&](int i) {
         if (i < NLD) loader.issue(pendQ, i);
         else if (i < 2 * NLD) loader.issue(pendD, i - NLD);
       };
       bool issued = false;
       if (has_next) load_stats(Lh, Dh, tn);
-      constexpr int tQ = T0 + buf * TILE_BYTES;     // byte offsets of this tile's Q and dO in smem
-      constexpr int tdO = T0 + (2 + buf) * TILE_BYTES;
+      constexpr int tQ = T0 + buf * GT;             // byte offsets of this tile's Q and dO in smem
+      constexpr int tdO = T0 + (2 + buf) * GT;
       const float* tL = ldsL + buf * QT;
       const float* tD = ldsD + buf * QT;
       const int qt0 = t * QT;
-      // V_j in LDS and wave groups (no registers for what qblocks below keeps live): one 32-query block against this wave's 32 keys,
-      // in one code path (the block that crosses the diagonal only adds a masking step).  The next tile's transfer is
-      // issued on the way.
-      auto qblock = [&]() {
-        const int qb0 = qt0 + 32 * grp;
-        // ---- S = Q_i K_j^T and dP = dO_i V_j^T (Alg. 2 steps 8, 11); rows = queries, lane = key
-        f32x16 s, dp;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + 32 * grp + 8 * g + 4 * h);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { s[4 * g + e] = 0.f; dp[4 * g + e] = d4[e]; }
-        }
-#pragma unroll
-        for (int kc = 0; kc < D / 16; ++kc) {
-          s = mfma32(lds_row8<D>(tQ, fo, 0, kc), kf[kc], s);
-          dp = mfma32(lds_row8<D>(tdO, fo, 0, kc), lds_row8<D>(0, fo_v, 0, kc), dp);
-          issue_part(kc);
-        }
-#pragma unroll
-        for (int i = D / 16; i < 2 * NLD; ++i) issue_part(i);
-        issued = true;
-        sched_3_reads_per_2_mfma<D / 16, 8>();
-        __builtin_amdgcn_sched_barrier(0);          // (2 to 5 % faster than leaving the compiler to mix the phases)
-        // element i of this lane is query qb0 + 4h + c with c = 8 (i / 4) + i % 4 a compile-time constant
-        // ---- P = exp(S - L) (step 9), dS = P o (dP - delta) (step 12)
-        bf16x8 pf[2], dsf[2];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(tL + 32 * grp + 8 * g + 4 * h);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) s[4 * g + e] = __builtin_fmaf(s[4 * g + e], c2, -l4[e]);
-        }
-        if (CAUSAL && qb0 + shift < kw + 31) {
-          // the block crosses the diagonal: a masked entry contributes exactly nothing, whatever its row holds
-          const int first_seen = kw + r - shift - qb0 - 4 * h;   // queries with c below it do not see this lane's key
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (8 * (i >> 2) + (i & 3) < first_seen) { s[i] = -INFINITY; dp[i] = 0.f; }
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float p = __builtin_amdgcn_exp2f(s[i]);
-          pf[i >> 3][i & 7] = (bf16_t)p;
-          dsf[i >> 3][i & 7] = (bf16_t)(p * dp[i]);     // dp already holds dP - delta
-        }
-        // ---- dV_j^T += dO_i^T P ,  dK_j^T += Q_i^T dS  (steps 10, 14)
-#pragma unroll
-        for (int cc = 0; cc < 2; ++cc)
-#pragma unroll
-          for (int db = 0; db < NDB; ++db) {
-            dVt[db] = mfma32(lds_col8<D>(tdO, fo_upd, 16 * cc, db), pf[cc], dVt[db]);
-            dKt[db] = mfma32(lds_col8<D>(tQ, fo_upd, 16 * cc, db), dsf[cc], dKt[db]);
-          }
-        sched_reads_ahead_of_mfma<4 * NDB, 2, 4>();
-      };
       // The NB 32-query blocks of a tile that belong to this wave's group against its 32 keys, as one stream of matrix
       // instructions ("slots"):  S (D/16 slots) | dP | dV (2 NDB) | dK, block after block.  The vector work of a
       // block lies under its own matrix instructions: P = exp(S - L) under dP, dS = P o (dP - delta) under dV,
@@ -409,8 +363,6 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       const int q_first = qt0 + 32 * grp, q_last = q_first + 32 * NBT - 1;     // first and last query of them
       if ((CAUSAL && q_last + shift < kw) || (RAGGED && q_first >= N)) {
         // no query sees a key of the wave, or nothing but padding
-      } else if constexpr (kVInLds<D> && G > 1) {
-        qblock();
       } else if (!CAUSAL || q_first + shift >= kw + 31) {
         asm volatile("; every entry counts");                // (differs from the other path: nothing is merged in front of the branch)
         qblocks(std::false_type{}, std::integral_constant<int, NBT>{}, std::integral_constant<int, 0>{});

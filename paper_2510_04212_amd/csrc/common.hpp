@@ -357,21 +357,6 @@ template <int N, int PER, int AHEAD_> DEVI void sched_reads_ahead_of_mfma() {
   for (int i = 0; i < AHEAD; ++i) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
 }
 
-// As above for STEPS steps of two matrix instructions that take three LDS fragment reads between
-// them (one has both operands in LDS): reads are issued AHEAD (even) matrix instructions early.
-template <int STEPS, int AHEAD> DEVI void sched_3_reads_per_2_mfma() {
-  __builtin_amdgcn_sched_group_barrier(0x100, 3 * AHEAD / 2, 0);
-#pragma unroll
-  for (int i = 0; i < STEPS - AHEAD / 2; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < AHEAD; ++i) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-}
-
 // Work-group index remap: consecutive hardware work-group ids go round-robin over the 8 XCDs
 // (each with its own L2).  Give every XCD a contiguous range of logical ids so that the
 // work-groups sharing one head's K/V run on the same L2.  Only applied when the grid is a
