@@ -904,10 +904,14 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
   // N2048 d128 causal 50 -> 45, B1 H8 the same 44 -> 30, d64 30 -> 18, B1 H4 N4096 d128 79 -> 48, B1 H8
   // N2048 d128 full 44 -> 32, B1 H1 N8192 d64 101 -> 47; beyond the limits: B2 H12 N2048 d128 causal 52 -> 66,
   // B2 H8 N2048 d128 full 57 -> 64.  At D = 256 (one wave per SIMD) two groups on 64 queries are what fits:
-  // B1 H8 N2048 full 73 -> 57, beyond the limit B2 H8 95 -> 109.
+  // B1 H8 N2048 full 73 -> 57, beyond the limit B2 H8 95 -> 109.  There the causal mask takes the limit to one block per CU
+  // only where the order table balances the halved blocks (head counts in eights), in square problems (with more keys than
+  // queries the blocks differ less) and from 1500 keys on: B2 H8 N2048 85 -> 79, B1 H8 N4000 145 -> 124, B1 H16 N1900 78 -> 73,
+  // B2 H8 N1500 61 -> 54; not taken: B1 H15 N2048 82 -> 98, B1 H24 N1280 57 -> 60, B4 H8 N1024 51 -> 53, B2 H12 N2048 91 -> 116.
   if constexpr (MODE != kRecomputeDelta) {
     const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
-    if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (CAUSAL && D <= 128 ? kNumCUs : kNumCUs / 2))
+    const bool balanced = CAUSAL && (D <= 128 || (BH % 8 == 0 && lay.Nk == N && N >= 1500));
+    if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (balanced ? kNumCUs : kNumCUs / 2))
       return launch_dq_g<D, CAUSAL, RAGGED, MODE, (D <= 128 ? 4 : 2)>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
   }
   return launch_dq_g<D, CAUSAL, RAGGED, MODE, 1>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);

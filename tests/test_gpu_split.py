@@ -46,6 +46,23 @@ def test_dkdv_with_three_waves_per_simd(lib, H, N, d, causal):
         check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"three waves H{H} N{N} d{d} c{causal}")
 
 
+@pytest.mark.parametrize("H,N,causal", [(130, 520, True), (104, 640, True), (70, 600, False), (66, 512, False), (300, 97, True)])
+def test_dkdv_with_one_wave_group_at_128(lib, H, N, causal):
+    """More key blocks than the wave groups take (512 with, 256 without a mask), or short sequences: one group, V_j in LDS."""
+    x = _inputs(H + N, 1, H, N, N, 128, scale=1.25)
+    got = _run(lib, x, causal, 128 ** -0.5, 1)
+    for h in (0, H - 1):
+        check_head(got, x, 0, h, causal, 128 ** -0.5, 1, label=f"one group H{H} N{N} c{causal}")
+
+
+@pytest.mark.parametrize("H,N", [(16, 1500), (16, 1536), (8, 3970), (16, 2048), (16, 1499), (17, 1500), (16, 2049)])
+def test_dq_at_256_with_two_wave_groups(lib, H, N):
+    """Causal, 129 to 256 query blocks, head counts in eights, from 1500 keys on: two groups on 64 queries; one beside that."""
+    x = _inputs(H + N, 1, H, N, N, 256, scale=1.25)
+    got = _run(lib, x, True, 1.0 / 16, 1)
+    check_head(got, x, 0, H - 1, True, 1.0 / 16, 1, label=f"two groups H{H} N{N}")
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("N", [512, 577])
 def test_grouped_queries_with_wave_groups(lib, N, d):
