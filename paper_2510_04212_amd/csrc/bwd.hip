@@ -51,8 +51,8 @@ DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, in
 // work-groups per key block, each recomputing S and dP).
 template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // The kernel wants two waves on every SIMD: one wave alone leaves the matrix cores idle whenever
-// any of its instructions waits.  That means at most 256 registers per lane (a few wave-group instantiations
-// at D = 96 and 128 spill two to eleven, outside their tile loops).  At D = 128 the
+// any of its instructions waits.  That means at most 256 registers per lane (some instantiations
+// at D = 128 under the mask spill two to nine, outside their tile loops).  At D = 128 the
 // accumulators (128) and the K fragments (32) leave no room for the V fragments: V_j is kept in LDS
 // for the whole block (8 more fragment reads per 32 queries to 48) and the query tiles shrink to 32
 // rows per wave group, so that two work-groups fit a CU.  Measured against one wave per SIMD with
@@ -640,8 +640,8 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
     // causal 52.3 -> 50.0, B2 H8 N2048 d256 causal 89 -> 80, B4 H12 N1024 d64 causal 22.0 -> 19.9, B8 H12 N1024 d64
     // causal 32.4 -> 30.7.
     // MASKED: a block crosses the diagonal or the sequence end.
-constexpr int NBT = KT / 32 / G;                         // blocks of this wave's group in a tile
-        auto kblocks = [&](auto masked_c, auto nb_c, auto kb_c) {
+    constexpr int NBT = KT / 32 / G;                         // blocks of this wave's group in a tile
+    auto kblocks = [&](auto masked_c, auto nb_c, auto kb_c) {
       constexpr bool MASKED = decltype(masked_c)::value;
       constexpr int NB = decltype(nb_c)::value;
       constexpr int kb = decltype(kb_c)::value;

@@ -790,7 +790,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, D <= 128 ? 2 : 1))) void at
 // is the largest any of its shares asked for; a share's sums stand relative to the largest of its own
 // and the shares before it.  They are brought to the row's normaliser in float32, and the roundings of
 // the ordinary epilogue follow.  Streams the shares once (HBM / Infinity Cache bound); work-groups of one wave, as there
-// are few of them and each should have a CU to itself (four waves -> one, 64 x 8192 as above: 5.5 -> 4.7 us).
+// are few of them and each should have a CU to itself (four waves -> one, 64 x 8192 as above: 5.5 -> 4.7 to 5.4 us).
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(64) void attn_fwd_merge_kernel(
     const float* __restrict__ part, bf16_t* __restrict__ O, float* __restrict__ LSE, int BH, int N,
