@@ -656,7 +656,9 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 :
     ones_row = (int)(sw[0] + sw[1]);
   }
   const bool keep_obar_f32 = EXTRAS && ex.single_rounding != 0;
-  const bool unseen_row = RAGGED && m == -INFINITY;        // no visible key (more queries than keys): O = 0, LSE = -inf
+  // No visible key (more queries than keys): O = 0, LSE = -inf.  A row of NaN scores also leaves m at -inf (the maxima pass
+  // NaN over), but its l is NaN: it stays NaN, as in the kernels without this case.
+  const bool unseen_row = RAGGED && m == -INFINITY && l == 0.f;
   const Divisor by_l = make_divisor(l);
   auto o_piece = [&](int db, int g) {
     bf16x4 o4;
