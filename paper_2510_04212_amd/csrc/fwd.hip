@@ -67,6 +67,14 @@ constexpr int kRowStats = 3, kFixedNorm = 2;
 // N2048 d128 149 -> 152, B2 H16 N2000 d96 65.5 -> 68.3, B2 H8 N2000 d256 99 -> 110.
 template <int D, bool CAUSAL> constexpr bool kPipelined = CAUSAL && D >= 96;
 
+// Waves per SIMD the compiler has to make room for.  At D = 64 the row sums' selector and four-register result (add_rows)
+// put two causal kernels one or two registers over the 128 that four waves allow; asked for four they fit without spilling.
+// Measured, three waves -> four (us): d64 causal, bounds-checking, Alg. 1 B64 H8 N200 18.1 -> 15.6, B16 H12 N1999 141 -> 136;
+// aligned, Alg. 3 B8 H12 N1024 26.1 -> 26.1, B4 H32 N4096 354 -> 350.  Not asked of the bounds-checking kernels that spill one or
+// two for it: causal Alg. 3 B8 H12 N1000 27.1 -> 27.6, B2 H8 N333 10.7 -> 11.1, full B8 H12 N1500 83.5 -> 84.1.
+template <int D, bool CAUSAL, int VARIANT, bool RAGGED, int EXTRAS> constexpr int kFwdWaves =
+    D == 64 && CAUSAL && EXTRAS == 0 && (VARIANT == 0 || !RAGGED) ? 4 : D <= 128 ? 2 : 1;
+
 // ---- sharing a block's key tiles out to several work-groups (SPLIT below)
 // Shares of a block of `tiles` key tiles when the grid has `splits` work-groups per block: of two tiles at least,
 // three from 2048 keys on (below that, start-up and merging cost more than a shorter chain takes off).
@@ -165,7 +173,7 @@ DEVI float tile_normaliser(const TileMax<VARIANT == 1>& tm, float alpha, float i
 // round P-bar against its own maximum: other roundings, more unit probabilities, 1e-3 .. 2e-3 relative.
 template <int D, bool CAUSAL, int VARIANT, bool RAGGED, int EXTRAS, bool SPLIT = false>
 __global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, (D == 96 || D == 128) ? 2 : (D > 128 ? 1 : 8)))) void attn_fwd_kernel(
+__attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>, (D == 96 || D == 128) ? 2 : (D > 128 ? 1 : 8)))) void attn_fwd_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, int N, float alpha, float beta, float eps,
     FwdExtras ex, Layout lay, int pairs, float* __restrict__ part, int splits, BlockOrder ord) {
