@@ -68,12 +68,21 @@ constexpr int kRowStats = 3, kFixedNorm = 2;
 template <int D, bool CAUSAL> constexpr bool kPipelined = CAUSAL && D >= 96;
 
 // Waves per SIMD the compiler has to make room for.  At D = 64 the row sums' selector and four-register result (add_rows)
-// put two causal kernels one or two registers over the 128 that four waves allow; asked for four they fit without spilling.
-// Measured, three waves -> four (us): d64 causal, bounds-checking, Alg. 1 B64 H8 N200 18.1 -> 15.6, B16 H12 N1999 141 -> 136;
-// aligned, Alg. 3 B8 H12 N1024 26.1 -> 26.1, B4 H32 N4096 354 -> 350.  Not asked of the bounds-checking kernels that spill one or
-// two for it: causal Alg. 3 B8 H12 N1000 27.1 -> 27.6, B2 H8 N333 10.7 -> 11.1, full B8 H12 N1500 83.5 -> 84.1.
+// put the aligned causal Alg. 3 kernel two registers over the 128 that four waves allow; asked for four it fits without
+// spilling.  Measured, three waves -> four (us): B64 H8 N256 18.8 -> 16.8, B4 H32 N4096 354 -> 350, B8 H12 N1024 even.  The
+// bounds-checking kernels would spill one to four (Alg. 1 causal, with kPlacedReads: B64 H8 N200 17.7 -> 16.5, B4 H32 N4000
+// 321 -> 315, but B8 H12 N1000 25.2 -> 26.3, B2 H8 N1999 30.7 -> 31.1; Alg. 3 and full: even or slower).
 template <int D, bool CAUSAL, int VARIANT, bool RAGGED, int EXTRAS> constexpr int kFwdWaves =
-    D == 64 && CAUSAL && EXTRAS == 0 && (VARIANT == 0 || !RAGGED) ? 4 : D <= 128 ? 2 : 1;
+    D == 64 && CAUSAL && EXTRAS == 0 && !RAGGED ? 4 : D <= 128 ? 2 : 1;
+
+// Kernels whose LDS reads are put ahead of their products by hand (a fence per product) where tiles come one after the
+// other.  The compiler gives the requested read-ahead up where registers are short: at D = 256 every product waited for
+// its own reads, at D = 64 under the mask with bounds checks those of the scores did.  Same bits; us, left to the compiler -> placed:
+// d256 B2 H8 N2000 full 104 -> 82, aligned N2048 95 -> 80, B3 H8 N1000 full 56 -> 45, whole-row rule B2 H8 N2048 causal 83 -> 62,
+// optional outputs B2 H8 N2048 causal 110 -> 87; d64 causal B2 H8 N1999 Alg. 1 32.3 -> 30.7, Alg. 3 35.0 -> 33.6, whole-row rule
+// B4 H12 N1024 11.0 + 18.3 -> 10.1 + 17.6.
+template <int D, bool CAUSAL, bool RAGGED, bool SPLIT> constexpr bool kPlacedReads =
+    D == 256 || (D == 64 && CAUSAL && RAGGED && !SPLIT);
 
 // ---- sharing a block's key tiles out to several work-groups (SPLIT below)
 // Shares of a block of `tiles` key tiles when the grid has `splits` work-groups per block: of two tiles at least,
@@ -309,16 +318,31 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+      if constexpr (kPlacedReads<D, CAUSAL, RAGGED, SPLIT>) {
+        constexpr int AHEAD = 2, RING = AHEAD + 1;
+        auto fragment = [&](int i) { return lds_row8<D>(tK, fo, 32 * (i % 2), i / 2); };
+        bf16x8 ring[RING];
 #pragma unroll
-      for (int kc = 0; kc < D / 16; ++kc) {
+        for (int i = 0; i < AHEAD; ++i) ring[i] = fragment(i);
+        static_for<D / 8>([&](auto slot) {
+          constexpr int sl = decltype(slot)::value;
+          if (sl + AHEAD < D / 8) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+          s[sl % 2] = mfma32(ring[sl % RING], qf[sl / 2], s[sl % 2]);
+          if (sl % 2) issue_part(sl / 2);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      } else {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) s[kb] = mfma32(lds_row8<D>(tK, fo, 32 * kb, kc), qf[kc], s[kb]);
-        issue_part(kc);
+        for (int kc = 0; kc < D / 16; ++kc) {
+#pragma unroll
+          for (int kb = 0; kb < 2; ++kb) s[kb] = mfma32(lds_row8<D>(tK, fo, 32 * kb, kc), qf[kc], s[kb]);
+          issue_part(kc);
+        }
+        sched_reads_ahead_of_mfma<D / 8, 1, 4>();
       }
 #pragma unroll
       for (int i = D / 16; i < 2 * NLD; ++i) issue_part(i);
       issued = true;
-      sched_reads_ahead_of_mfma<D / 8, 1, 4>();
       // ---- mask: causal (key > query) in the tile that crosses the diagonal, and keys beyond
       // the sequence end in the last, partial tile -> -inf
       if ((CAUSAL && (k0 + kBc - 1 > qw + shift)) || (RAGGED && k0 + kBc > NK)) {
@@ -430,10 +454,25 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
             for (int i = 0; i < 16; ++i) acc[db][i] *= corr;
         }
         const bool not_finite = MFMA_SUMS && __builtin_amdgcn_ballot_w64(psum[0] != psum[0]) != 0;
+        if constexpr (D == 256) {       // (kPlacedReads; at D = 64 the compiler keeps these reads ahead)
+          constexpr int NDB = D / 32, AHEAD = 3, RING = AHEAD + 1;
+          auto fragment = [&](int i) { return lds_col8<D>(tV, fo, 16 * (i / NDB), i % NDB); };
+          bf16x8 ring[RING];
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+          for (int i = 0; i < AHEAD; ++i) ring[i] = fragment(i);
+          __builtin_amdgcn_sched_barrier(0);
+          static_for<4 * NDB>([&](auto slot) {
+            constexpr int sl = decltype(slot)::value;
+            if (sl + AHEAD < 4 * NDB) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+            acc[sl % NDB] = mfma32(ring[sl % RING], pf[sl / NDB], acc[sl % NDB]);
+            __builtin_amdgcn_sched_barrier(0);
+          });
+        } else {
 #pragma unroll
-          for (int db = 0; db < D / 32; ++db) acc[db] = mfma32(lds_col8<D>(tV, fo, 16 * c, db), pf[c], acc[db]);
+          for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db) acc[db] = mfma32(lds_col8<D>(tV, fo, 16 * c, db), pf[c], acc[db]);
+        }
         if (MFMA_SUMS) {
           if (not_finite) psum[0] = row_sum_apart(pf);
           lsum = lsum * corr + psum[0];
