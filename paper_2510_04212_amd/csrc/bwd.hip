@@ -690,7 +690,10 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
         if constexpr (phase >= 2 * NB) dQt[u % NDB] = mfma32(a, dsf[phase - 2 * NB][u / NDB], dQt[u % NDB]);   // step 13
         else if constexpr (phase % 2 == 0) s[phase / 2] = mfma32(a, qf[u], s[phase / 2]);
         else dp[phase / 2] = mfma32(a, dof[u], u == 0 ? neg_delta : dp[phase / 2]);
-        if (kb == 0) issue_part(sl);
+        // (one transfer instruction per two slots: four waves that issue one each per slot ask for 128 bytes a clock where the
+        // load path takes 64, and stall.  us, one slot -> two: B1 H8 N2048 d256 full 59.0 -> 57.4, causal 51.0 -> 47.5; d <= 128 even.)
+        static_assert(2 * NLD <= NS, "all of the transfer is issued under S and dP");
+        if (kb == 0 && sl % 2 == 0) issue_part(sl / 2);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
           const int e = sl - 2 * NS * b - NS - 1;            // P of block b lies under the slots after its first dP^T
@@ -911,8 +914,14 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
   if constexpr (MODE != kRecomputeDelta) {
     const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
     const bool balanced = CAUSAL && (D <= 128 || (BH % 8 == 0 && lay.Nk == N && N >= 1500));
-    if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (balanced ? kNumCUs : kNumCUs / 2))
+    if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (balanced ? kNumCUs : kNumCUs / 2)) {
+      // (two groups without a mask: here the aligned kernel is the faster one and spills nothing, unlike that of one group; us,
+      // bounds-checking -> aligned: B1 H8 N2048 57.4 -> 56.2, B1 H4 N4096 100.7 -> 98.5, B1 H8 N512 20.8 -> 20.0)
+      if constexpr (D == 256 && !CAUSAL)
+        if (lay.Nk == N && N % kQPerWG == 0)
+          return launch_dq_g<D, CAUSAL, false, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
       return launch_dq_g<D, CAUSAL, RAGGED, MODE, (D <= 128 ? 4 : 2)>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+    }
   }
   return launch_dq_g<D, CAUSAL, RAGGED, MODE, 1>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
 }
