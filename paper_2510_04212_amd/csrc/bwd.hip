@@ -70,8 +70,11 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 template <int G> constexpr int kKeyWaves = G == 4 ? 2 : 4;               // waves per group, 32 keys each
 template <int D, int G> constexpr int kQTile = D == 128 || G == 4 ? 32 * G : 64;   // query rows per streamed tile
 // LDS fragments are read this many matrix instructions before their use.
-// (At D = 128 what the registers allow: the fragments of V_j come from LDS too.)
-template <int D> constexpr int kReadAhead = D == 256 ? 6 : D == 128 ? 2 : 4;
+// (At D = 128 what the registers allow: the fragments of V_j come from LDS too.  Four wave groups at small D: us, four ahead ->
+// two, B1 H4 N4096 d64 causal 41.1 -> 40.1, B1 H1 38.5 -> 37.7, B1 H2 N8192 d32 causal 54.0 -> 53.4, full 51.2 -> 50.5, B1 H8
+// N2000 d32 16.7 -> 16.4; d64 full even to 2 % slower: not there.)
+template <int D, int G, bool CAUSAL, bool DENSE> constexpr int kReadAhead =
+    DENSE || (G == 4 && (D == 32 || (D == 64 && CAUSAL))) ? 2 : D == 256 ? 6 : D == 128 ? 2 : 4;
 // dK / dV rows leave through a per-wave LDS staging area (store_rows_staged) where the row width
 // allows it; it overlays the tile buffers where it would otherwise cost a resident work-group, and
 // is left out at D = 256 (no room).
@@ -279,7 +282,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
         constexpr bool MASKED = decltype(masked_c)::value;
         constexpr int NB = decltype(nb_c)::value, qb = decltype(qb_c)::value;
         constexpr int NS = D / 16, NU = 2 * NDB, PB = 2 * NS + 2 * NU;    // slots of S or dP, of dV or dK, of a block
-        constexpr int AHEAD = DENSE ? 2 : kReadAhead<D>, RING = AHEAD + 1;
+        constexpr int AHEAD = kReadAhead<D, G, CAUSAL, DENSE>, RING = AHEAD + 1;
         constexpr int AHEAD_V = 1, RING_V = AHEAD_V + 1;       // kVInLds: V_j's fragments
         auto fragment = [&](int i) -> bf16x8 {
           const int b = qb + i / PB, u = i % PB;
