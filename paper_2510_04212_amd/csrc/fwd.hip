@@ -310,7 +310,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
     bool issued = false;
     const int k0 = j * kBc;
     // A wave whose 32 rows all lie above this key tile has nothing to do in it (causal); of a chunk of a few queries
-    // most waves hold no rows at all and only fetch (with the merge below, B2 H16 64 x 8192 d128: 49.5 -> 48.0 us).
+    // most waves hold no rows at all and only fetch.
     if ((!CAUSAL || (k0 <= qw + shift + 31)) && (!SPLIT || qw < N)) {
       // ---- S^T = K_j Q_i^T (Alg. 1 step 6); raw scores, alpha not yet applied
       f32x16 s[2];
@@ -838,20 +838,26 @@ __attribute__((amdgpu_waves_per_eu(D <= 128 ? 2 : 1, D <= 128 ? 2 : 1))) void at
 // Joins the shares of the SPLIT forward: one wave per 32 rows x 32 columns.  The normaliser of a row
 // is the largest any of its shares asked for; a share's sums stand relative to the largest of its own
 // and the shares before it.  They are brought to the row's normaliser in float32, and the roundings of
-// the ordinary epilogue follow.  Streams the shares once (HBM / Infinity Cache bound); work-groups of one wave, as there
-// are few of them and each should have a CU to itself (four waves -> one, 64 x 8192 as above: 5.5 -> 4.7 to 5.4 us).
+// the ordinary epilogue follow.  Streams the shares once; work-groups of one wave, as there are few of them and each
+// should have a CU to itself.  They take the heads and blocks in the order of the other two launches, so that a block is joined
+// on the XCD that summed it: its shares come from that XCD's L2, and the next call's sums are written to lines no other XCD
+// holds.  us, sums + merge, rows in their own order in work-groups of four waves -> of one -> now: B2 H4 64 x 4096 d64
+// 8.8 + 6.5 -> 8.6 + 10.1 -> 9.0 + 5.9, d32 8.0 + 9.4 -> 7.5 + 9.0 -> 7.5 + 5.8, B1 H8 2048 x 2048 causal d256 35.9 + 12.9
+// -> 35.8 + 14.1 -> 35.8 + 13.0, B1 H4 2048 x 2048 causal d128 17.6 + 7.1 -> 18.4 + 6.9 -> 14.8 + 6.7, B2 H16 64 x 8192 d128
+// 24.8 + 6.0 -> 24.7 + 5.5 -> 24.8 + 5.6.
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(64) void attn_fwd_merge_kernel(
-    const float* __restrict__ part, bf16_t* __restrict__ O, float* __restrict__ LSE, int BH, int N,
+    const float* __restrict__ part, bf16_t* __restrict__ O, float* __restrict__ LSE, int N,
     Layout lay, int splits) {
   constexpr int NDB = D / 32;
   const int lane = threadIdx.x & 63;
   const int r = lane & 31, h = lane >> 5;
   const int nrb = (N + 31) / 32;
-  const int id = blockIdx.x;
+  const int id = xcd_remap(blockIdx.x, gridDim.x);
   const int db = id % NDB;
-  const int rows = id / NDB;                  // 32-row block: head and place in it
-  const int bh = rows / nrb, qw = rows % nrb * 32;
+  const int bh = id / (NDB * nrb);
+  const int rb = nrb - 1 - id / NDB % nrb;    // 32-row block of the head, last ones first
+  const int rows = bh * nrb + rb, qw = rb * 32;
   const int shift = lay.Nk - N;
   const int kend = !CAUSAL ? lay.Nk : max(0, min(lay.Nk, qw / kBr * kBr + kBr + shift));
   const int shares = split_shares((kend + kBc - 1) / kBc, splits);
@@ -947,7 +953,7 @@ static hipError_t launch_fwd_split(const void* Q, const void* K, const void* V, 
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int waves = BH * ((N + 31) / 32) * (D / 32);
   hipLaunchKernelGGL((attn_fwd_merge_kernel<D, CAUSAL>), dim3(waves), dim3(64), 0, st, part,
-                     (bf16_t*)O, LSE, BH, N, lay, splits);
+                     (bf16_t*)O, LSE, N, lay, splits);
   return hipGetLastError();
 }
 
