@@ -37,13 +37,27 @@ def test_dkdv_with_two_wave_groups(lib, H, N, d, causal):
 
 
 @pytest.mark.parametrize("d", [32, 64])
-@pytest.mark.parametrize("H,N,causal", [(264, 200, True), (520, 65, True), (72, 1000, True), (513, 128, False), (260, 161, False)])
+@pytest.mark.parametrize("H,N,causal", [(264, 200, True), (520, 65, True), (72, 1000, True), (513, 128, False), (260, 161, False),
+                                        (515, 300, True), (342, 384, True), (341, 384, True)])
 def test_dkdv_with_three_waves_per_simd(lib, H, N, d, causal):
-    """More than two 128-key blocks per CU (four where blocks run in pairs): aligned, ragged, shorter than a block."""
+    """More than two 128-key blocks per CU: aligned, ragged, shorter than a block.  Head counts that are not in eights run as
+    mirrored pairs of blocks and take it from more than four blocks per CU on (342 heads of three; 341 are one too few)."""
     x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
     got = _run(lib, x, causal, d ** -0.5, 1)
     for h in (0, H // 2, H - 1):
         check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"three waves H{H} N{N} d{d} c{causal}")
+
+
+@pytest.mark.parametrize("d", [64, 96, 128, 256])
+@pytest.mark.parametrize("H,N", [(512, 400), (513, 384), (512, 385)])
+def test_causal_forward_and_dq_in_mirrored_pairs(lib, H, N, d):
+    """From 1024 pairs of query blocks on a work-group takes two blocks one after the other: ragged lengths, an odd number
+    of blocks (the middle one has no partner), a last block of one row.  (From d = 96 on the forward's pipeline starts anew.)"""
+    x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
+    for variant in (0, 1):
+        got = _run(lib, x, True, d ** -0.5, variant)
+        for h in (0, H // 2, H - 1):
+            check_head(got, x, 0, h, True, d ** -0.5, variant, label=f"pairs H{H} N{N} d{d} v{variant}")
 
 
 @pytest.mark.parametrize("H,N,causal", [(130, 520, True), (104, 640, True), (70, 600, False), (66, 512, False), (300, 97, True)])
