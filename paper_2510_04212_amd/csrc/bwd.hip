@@ -665,8 +665,12 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[b][i] = 0.f;
         const int kb0 = kt0 + 32 * (kb + b + grp);
-        lim[b] = CAUSAL ? qw + r + shift - kb0 - 4 * h : 0x7fffffff;
-        if (RAGGED) lim[b] = min(lim[b], NK - 1 - kb0 - 4 * h);
+        // (formed here and not ahead of the tile loop, which costs registers: at D = 64, causal, with bounds checks six were
+        // spilled.  us: 800 heads N65 15.0 -> 13.2, 400 heads N200 19.8 -> 17.6, B8 H12 N1000 29.6 -> 28.0)
+        int ln = lane;
+        if (MASKED) asm volatile("" : "+v"(ln));
+        lim[b] = CAUSAL ? __builtin_amdgcn_readfirstlane(qw) + (ln & 31) + shift - kb0 - 4 * (ln >> 5) : 0x7fffffff;
+        if (RAGGED) lim[b] = min(lim[b], NK - 1 - kb0 - 4 * (ln >> 5));
       }
       // P of entries i0 .. i1 - 1 of block b: keys in this lane's future and keys past the sequence end get
       // S = -inf, P = exp(-inf) = 0
@@ -693,10 +697,12 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
         if constexpr (phase >= 2 * NB) dQt[u % NDB] = mfma32(a, dsf[phase - 2 * NB][u / NDB], dQt[u % NDB]);   // step 13
         else if constexpr (phase % 2 == 0) s[phase / 2] = mfma32(a, qf[u], s[phase / 2]);
         else dp[phase / 2] = mfma32(a, dof[u], u == 0 ? neg_delta : dp[phase / 2]);
-        // (one transfer instruction per two slots: four waves that issue one each per slot ask for 128 bytes a clock where the
-        // load path takes 64, and stall.  us, one slot -> two: B1 H8 N2048 d256 full 59.0 -> 57.4, causal 51.0 -> 47.5; d <= 128 even.)
-        static_assert(2 * NLD <= NS, "all of the transfer is issued under S and dP");
-        if (kb == 0 && sl % 2 == 0) issue_part(sl / 2);
+        // (One transfer instruction per two slots at D = 256: four waves that issue one each per slot ask for 128 bytes a clock
+        // where the load path takes 64, and stall.  us, one slot -> two: B1 H8 N2048 d256 full 59.0 -> 57.4, causal 51.0 -> 47.5.
+        // d <= 128: even, and 0.1 to 0.2 us slower where a problem is one tile long, as the transfer ends later.)
+        constexpr int EVERY = D == 256 ? 2 : 1;
+        static_assert(2 * NLD * EVERY <= 2 * NS, "all of the transfer is issued under S and dP");
+        if (kb == 0 && sl % EVERY == 0) issue_part(sl / EVERY);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
           const int e = sl - 2 * NS * b - NS - 1;            // P of block b lies under the slots after its first dP^T
