@@ -169,12 +169,22 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     loader.lds_wave += 3 * grp * GT;
   }
 
+  // Three waves per SIMD at D = 64 under the mask: what depends on the lane is formed where it is used, from copies of the
+  // thread index that the compiler cannot see through.  Formed ahead of the loops it was spilled (eight or nine registers), and
+  // short problems waited for the reloads: us, 400 heads N200 23.2 -> 18.9, 472 heads N300 41.5 -> 34.3, B8 H12 N1000
+  // 39.0 -> 34.5, N1024 37.1 -> 36.2, B4 H32 N4000 526 -> 512.  (Elsewhere nothing is spilled, and it costs 2 %.)
+  constexpr bool FORM_LATE = DENSE && D == 64 && CAUSAL;
+  auto late = [](int x) {
+    if (FORM_LATE) asm volatile("" : "+v"(x));
+    return x;
+  };
+
   for (int part = 0; part < (CAUSAL ? 2 : 1); ++part) {
     const int kt = (part == 0) ? kt_first : nkt - 1 - kt_first;
     if (part == 1 && (!pairs || kt == kt_first)) break;   // no partner: one block per work-group, or the middle one of an odd number
     if (kStageOverTiles<D, G> && part > 0) __syncthreads();   // the first block's staging is done with the tile buffers
     const int k0 = kt * KEYS;
-    const int kw = k0 + 32 * wave;
+    const int kw = k0 + 32 * (FORM_LATE ? late(tid) >> 6 : wave);
 
     if constexpr (kVInLds<D>) {
       TileLoader<D, KEYS, KW * G> v_loader;
@@ -183,12 +193,12 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     }
     // K_j^T / V_j^T fragments (B operands): lane (r,h) holds K[kw + r][16kc + 8h .. +7]
     // (keys past the sequence end read the last row; their gradients are not stored)
-    const int keyc = (RAGGED && kw + r >= NK) ? NK - 1 : kw + r;
+    const int keyc = (RAGGED && kw + r >= NK) ? NK - 1 : kw + r, hk = late(h);
     bf16x8 kf[D / 16], vf[kVInLds<D> ? 1 : D / 16];
 #pragma unroll
     for (int kc = 0; kc < D / 16; ++kc) {
-      kf[kc] = *reinterpret_cast<const bf16x8*>(K + head_off + (size_t)keyc * sn + 16 * kc + 8 * h);
-      if constexpr (!kVInLds<D>) vf[kc] = *reinterpret_cast<const bf16x8*>(V + head_off + (size_t)keyc * sn + 16 * kc + 8 * h);
+      kf[kc] = *reinterpret_cast<const bf16x8*>(K + head_off + (size_t)keyc * sn + 16 * kc + 8 * hk);
+      if constexpr (!kVInLds<D>) vf[kc] = *reinterpret_cast<const bf16x8*>(V + head_off + (size_t)keyc * sn + 16 * kc + 8 * hk);
     }
     f32x16 dVt[NDB], dKt[NDB];
 #pragma unroll
@@ -212,22 +222,24 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     const float* Dh = delta + (size_t)bq0 * N;
     const int total = group * (nt - t0);
     auto load_stats = [&](const float* Lp, const float* Dp, int t) {
-      const int row = t * QT + (tid & (QT - 1));
+      const int tl = late(tid);
+      const int row = t * QT + (tl & (QT - 1));
       const int rowc = (RAGGED && row >= N) ? N - 1 : row;
-      if (tid < QT) {
+      if (tl < QT) {
         sreg = Lp[rowc];
-      } else if (tid < 2 * QT) sreg = Dp[rowc];
+      } else if (tl < 2 * QT) sreg = Dp[rowc];
       // (The loaded values are not touched before store_stats: any arithmetic on them here would
       // make the wave wait, at the start of the tile, for these loads and for the tile transfer
       // issued just before them.)
     };
     auto store_stats = [&](int buf, int tn) {      // tn: the tile they belong to
-      if (tid < QT) {
+      const int tl = late(tid);
+      if (tl < QT) {
         float l = sreg * kLog2e;
         if (RAGGED && l == -INFINITY) l = 0.f;         // a query that sees no key: all its scores are masked below
-        if (RAGGED && tn * QT + tid >= N) l = INFINITY;    // a row past the sequence end: P = exp(-inf) = 0, so it adds nothing to dK, dV
-        ldsL[buf * QT + tid] = l;
-      } else if (tid < 2 * QT) ldsD[buf * QT + tid - QT] = -sreg;   // LDS holds -delta
+        if (RAGGED && tn * QT + tl >= N) l = INFINITY;    // a row past the sequence end: P = exp(-inf) = 0, so it adds nothing to dK, dV
+        ldsL[buf * QT + tl] = l;
+      } else if (tl < 2 * QT) ldsD[buf * QT + tl - QT] = -sreg;   // LDS holds -delta
     };
     loader.template load_rows<RAGGED>(ldsQ, Qh, t0 * QT, N);
     loader.template load_rows<RAGGED>(ldsdO, dOh, t0 * QT, N);
