@@ -376,16 +376,21 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       };
       constexpr int NBT = QT / 32 / G;                       // blocks of this wave's group in a tile
       const int q_first = qt0 + 32 * grp, q_last = q_first + 32 * NBT - 1;     // first and last query of them
+      // Blocks past the sequence end are left out as if they saw no key.  (Not with three waves per SIMD at D = 64, which then
+      // spills 96 registers, and not without a mask, where it would take a second instance of qblocks.  us, computed -> left out: 801
+      // heads N65 d64 15.3 -> 14.6, 401 heads N200 d64 20.7 -> 19.6, d32 14.8 -> 14.3, B8 H12 N450 d96 21.3 -> 20.6, B2 H8 N200 d256 30.3 -> 28.8.)
+      constexpr bool SKIP_PADDING = RAGGED && CAUSAL && NBT > 1 && !(DENSE && D == 64);
       if ((CAUSAL && q_last + shift < kw) || (RAGGED && q_first >= N)) {
         // no query sees a key of the wave, or nothing but padding
-      } else if (!CAUSAL || q_first + shift >= kw + 31) {
+      } else if (!CAUSAL || q_first + shift >= (SKIP_PADDING && q_last - 31 >= N ? 0x7fffffff : kw + 31)) {
         asm volatile("; every entry counts");                // (differs from the other path: nothing is merged in front of the branch)
         qblocks(std::false_type{}, std::integral_constant<int, NBT>{}, std::integral_constant<int, 0>{});
         issued = true;
       } else {
         asm volatile("; masked");
         static_for<NBT>([&](auto qb) {
-          if (q_first + 32 * decltype(qb)::value + 31 + shift < kw) return;     // no query of the block sees a key of the wave
+          const int first = q_first + 32 * decltype(qb)::value;
+          if (first + 31 + shift < (SKIP_PADDING && first >= N ? 0x7fffffff : kw)) return;     // no query of the block sees a key of the wave
           qblocks(std::true_type{}, std::integral_constant<int, 1>{}, qb);
           if (decltype(qb)::value == 0) issued = true;
         });
