@@ -67,13 +67,14 @@ constexpr int kRowStats = 3, kFixedNorm = 2;
 // N2048 d128 149 -> 152, B2 H16 N2000 d96 65.5 -> 68.3, B2 H8 N2000 d256 99 -> 110.
 template <int D, bool CAUSAL> constexpr bool kPipelined = CAUSAL && D >= 96;
 
-// Waves per SIMD the compiler has to make room for.  At D = 64 the row sums' selector and four-register result (add_rows)
-// put the aligned causal Alg. 3 kernel two registers over the 128 that four waves allow; asked for four it fits without
-// spilling.  Measured, three waves -> four (us): B64 H8 N256 18.8 -> 16.8, B4 H32 N4096 354 -> 350, B8 H12 N1024 even.  The
-// bounds-checking kernels would spill one to four (Alg. 1 causal, with kPlacedReads: B64 H8 N200 17.7 -> 16.5, B4 H32 N4000
-// 321 -> 315, but B8 H12 N1000 25.2 -> 26.3, B2 H8 N1999 30.7 -> 31.1; Alg. 3 and full: even or slower).
+// Waves per SIMD the compiler has to make room for.  The row sums' selector and four-register result (add_rows) put some
+// kernels one to four registers over the 96 that five waves allow (D = 32, causal) or the 128 of four (D = 64, causal);
+// asked for the waves they fit without spilling.  Measured, a wave less -> now (us): d32 B13 H32 N520 Alg. 1 37.0 -> 31.8,
+// Alg. 3 41.7 -> 35.5, B4 H32 N4096 250 -> 244, B8 H12 N1024 even; d64 Alg. 1 B64 H8 N200 17.6 -> 15.7, B16 H12 N1999 144 -> 138,
+// B8 H12 N1000 even, aligned Alg. 3 B64 H8 N256 18.8 -> 16.8, B4 H32 N4096 354 -> 350, B8 H12 N1024 even.  Not asked of
+// the causal Alg. 3 kernel with bounds checks at d64, which would spill two: B16 H12 N1999 154 -> 150, but B8 H12 N1000 27.0 -> 28.3.
 template <int D, bool CAUSAL, int VARIANT, bool RAGGED, int EXTRAS> constexpr int kFwdWaves =
-    D == 64 && CAUSAL && EXTRAS == 0 && !RAGGED ? 4 : D <= 128 ? 2 : 1;
+    D == 32 && CAUSAL && EXTRAS == 0 ? 5 : D == 64 && CAUSAL && EXTRAS == 0 && (!RAGGED || VARIANT == 0) ? 4 : D <= 128 ? 2 : 1;
 
 // Kernels whose LDS reads are put ahead of their products by hand (a fence per product) where tiles come one after the
 // other.  The compiler gives the requested read-ahead up where registers are short: at D = 256 every product waited for
@@ -349,8 +350,11 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
         // element (kb, i) of this lane is key k0 + 4h + c with c = 32 kb + 8 (i / 4) + i % 4 a
         // compile-time constant: masked <=> c > lim, one per-lane limit for both conditions.  (Written
         // out here and not called: as a function its 32 comparisons come first and spill scalar registers.)
-        int lim = CAUSAL ? q + shift - k0 - 4 * h : 0x7fffffff;
-        if (RAGGED) lim = min(lim, NK - 1 - k0 - 4 * h);
+        // (At D <= 64 what it needs of the lane is formed here, from an opaque copy: ahead of the loop it costs registers.)
+        int ln = lane;
+        if (D <= 64) asm volatile("" : "+v"(ln));
+        int lim = CAUSAL ? __builtin_amdgcn_readfirstlane(qw) + (ln & 31) + shift - k0 - 4 * (ln >> 5) : 0x7fffffff;
+        if (RAGGED) lim = min(lim, NK - 1 - k0 - 4 * (ln >> 5));
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
