@@ -29,9 +29,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # one: measured 2-3 % on the dK/dV kernel at d = 128, nothing lost elsewhere.  The forward is
 # faster with the default strategy.
 # The forward's matrix instructions write ordinary registers.  By default a kernel that may use more than 256 (d = 256,
-# one wave per SIMD) has its accumulators in accumulation registers, which the vector unit reaches by copies only (1844
-# in the causal kernel, now 183).  Same bits; us: B2 H8 N2048 d256 causal 97 -> 81, B4 H8 N1999 126 -> 108, B2 H12 N300
-# 21.7 -> 19.3, full 106 -> 105, smaller head sizes as before.  The backward loses by it (dK/dV B2 H8 N2048 122 -> 131, dQ even).
+# one wave per SIMD) has its accumulators in accumulation registers, which the vector unit reaches by copies only.  The
+# scheduler then finds no room for reading ahead from LDS: kernels that need it place their reads themselves
+# (kPlacedReads in fwd.hip).  Same bits; us, without the flag -> with it: B2 H8 N2048 d256 causal 87.4 -> 72.6, B4 H8 N1999
+# 117 -> 100, B2 H12 N300 21.2 -> 18.5, full B2 H8 N2048 98.9 -> 82.7, N2000 102 -> 85; smaller head sizes as before.
+# The backward loses by it (dK/dV B2 H8 N2048 122 -> 131, dQ even).
 EXTRA_FLAGS = {"bwd.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"], "fwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 

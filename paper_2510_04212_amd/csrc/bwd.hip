@@ -867,14 +867,14 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
   // sequences do not pay for the final exchange.
   // Four groups on 64 keys, up to one 128-key block per CU (half of that without a mask, where all
   // blocks are equal and two per CU would run one after the other).  Measured, two groups -> four (us): B2
-  // H32/8 N2048 d128 causal 210 -> 157, B2 H8 N2048 d128 causal 57 -> 47, d96 44 -> 36, d64 34 -> 27, B1 H4 N4096
-  // d128 causal 106 -> 64, B1 H8 N2048 d128 full 50 -> 38, B1 H1 N1024 d64 full 17.5 -> 12.8; beyond the
-  // limits: B2 H12 N2048 d128 causal 62 -> 82, B4 H12 N1024 d64 causal 24 -> 35.
+  // H32/8 N2048 d128 causal 200 -> 149, B2 H8 N2048 d128 causal 54.8 -> 48.8, d96 45.0 -> 37.6, d64 35.3 -> 28.5, B1 H4 N4096
+  // d128 causal 93 -> 62, B1 H8 N2048 d128 full 50.4 -> 39.1, B1 H1 N1024 d64 full 17.1 -> 11.5; beyond the
+  // limits: B2 H12 N2048 d128 causal 62 -> 89, B4 H12 N1024 d64 causal 26.0 -> 37.5.
   // Two groups on 128 keys up to one block per CU; up to two under the causal mask at D >= 96, where the
-  // blocks differ in work and the CU with the heaviest one decides (D = 64 fits two work-groups with
-  // 64-row tiles and a pipeline on a CU and gains nothing there).  Measured, one group -> two (us): B2
-  // H16 N2048 d128 causal 89 -> 74, d96 64 -> 60; beyond the limits: B3 H8 N2048 d128 full 104 -> 112,
-  // B4 H12 N1024 d64 causal 23.0 -> 24.3.
+  // blocks differ in work and the CU with the heaviest one decides (at D = 64 two work-groups with 64-row tiles on a
+  // CU do as well).  Measured, one group -> two (us): B2 H12 N2048 d128 causal 70.8 -> 62.6, d96 53.2 -> 48.5, B2 H8 N2048
+  // d128 full 74.4 -> 66.5, at the limit of two per CU B2 H16 N2048 d128 causal 79.4 -> 76.6, d96 60.5 -> 61.9; beyond the
+  // limits: B5 H8 N2048 d128 causal 93 -> 129, B3 H8 N2048 d128 full 108 -> 114, B4 H12 N1024 d64 causal 24.5 -> 26.0.
   if constexpr (D <= 128) {
     const int NK = RAGGED ? lay.Nk : N;      // (the rule looks at the keys only: a chunk of queries gets the sums of the square problem)
     const long long blocks = (long long)(BH / lay.group) * ((NK + kKeysPerWG - 1) / kKeysPerWG);
@@ -887,9 +887,10 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
     }
   }
   // More than two 128-key blocks per CU at D <= 64: three waves per SIMD.  Measured, two -> three (us): B8 H12 N1024 d64
-  // causal 41.3 -> 37.9, B32 H12 N512 d64 full 68.8 -> 67.1, B4 H32 N4096 d64 causal 515 -> 505, B8 H12 N1000 d64 full
-  // 63.6 -> 60.8, B8 H12 N1024 d32 causal 26.8 -> 23.4, B8 H16 N1001 d32 full 55.6 -> 52.0; below the limit: B4 H12
-  // N1024 d64 causal 24.7 -> 25.7, in pairs B1 H33 N2040 d64 66.4 -> 70.1, B5 H13 N1024 d32 27.4 -> 28.3; with grouped queries B4 H32/8 N2048 d64 causal 162 -> 170.
+  // causal 39.1 -> 35.7, B32 H12 N512 d64 full 62.5 -> 58.6, B4 H32 N4096 d64 causal 557 -> 535, B8 H12 N1000 d64 full
+  // 60.7 -> 56.4, causal 40.1 -> 36.5, B8 H12 N1024 d32 causal 28.2 -> 23.4, B8 H16 N1001 d32 full 52.7 -> 51.2; just above the
+  // limit 400 heads N200 d64 causal 19.0 -> 19.2, B2 H16 N2050 47.8 -> 50.1; below it: B4 H12 N1024 d64 causal 24.5 -> 25.4, in pairs
+  // B1 H33 N2040 d64 even, B5 H13 N1024 d32 27.7 -> 27.9; with grouped queries B4 H32/8 N2048 d64 causal 164 -> 170.
   if constexpr (D <= 64 && !GROUPED) {
     const int NK = RAGGED ? lay.Nk : N;
     // (head counts the order table does not take run as pairs of blocks: half as many work-groups)
@@ -958,9 +959,9 @@ hipError_t attn_bwd_dkdv_dispatch(const void* Q, const void* K, const void* V, c
                                   const float* LSE, const float* delta, void* dK, void* dV,
                                   int BH, int N, int d, int causal, float alpha, Layout lay,
                                   hipStream_t st) {
-  // The aligned kernels carry no bounds handling.  At D = 256 without a mask there is none: with nothing that
-  // parts the tile from what follows, its registers spill (us, aligned -> bounds-checking: dK/dV B2 H8 N2048
-  // 204 -> 191, dQ 208 -> 96).
+  // The aligned kernels carry no bounds handling.  At D = 256 without a mask there is none but dQ with two wave groups: with
+  // nothing that parts the tile from what follows, the stream of matrix instructions spills 14 and 126 registers there (us, B2 H8
+  // N2048, phase after phase -> aligned stream -> bounds-checking stream: dK/dV 228 -> 232 -> 190, dQ 94 -> 194 -> 92).
   const bool ragged = (N % kKeysPerWG) != 0 || lay.Nk != N || (d == 256 && !causal);
   if (lay.group > 1) {   // grouped queries: the bounds-checking instantiation serves every N
 #define CASEG(DD, CC)                                 \

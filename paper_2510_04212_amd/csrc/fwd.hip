@@ -21,7 +21,9 @@ constexpr int kBc = 64;    // key rows per tile
 
 // Optional outputs and switches of the forward (the experiments of Sec. 3.2 / 3.3.2 and the
 // tie statistics of Sec. 3.3.2 / 4).  Only kernels instantiated with EXTRAS look at them (EXTRAS = 1; 2: with the
-// P-bar V product in E4M3, which costs registers).
+// P-bar V product in E4M3: one kernel for both products takes up to 67 registers more than either, d256 all 512.  us, both in one ->
+// apart, with O_hp and counts: B4 H12 N1024 d64 causal 27.6 -> 26.6, B8 H12 44.4 -> 38.4, B2 H16 N2048 d128 full 120 -> 111,
+// B2 H8 N2048 d256 causal 111 -> 89, B8 H12 N1024 d32 31.1 -> 30.1).
 struct FwdExtras {
   float* O_hp;          // [B,H,N,d] float32: accumulator / l with no bf16 rounding, or null
   int* ones;            // [B,H,N]: number of keys whose rounded P-bar was exactly 1, or null
@@ -61,10 +63,11 @@ DEVI long pack_e4m3(const float (&v)[8]) {
 constexpr int kRowStats = 3, kFixedNorm = 2;
 
 // Which kernels run as a software pipeline over tiles.  It needs 32 more registers for the next tile's scores: at
-// D <= 64 that costs a wave per SIMD.  Measured, tile after tile -> pipeline (us): causal B2 H8 N2048 d256 93.5 -> 87.9,
-// B4 H16 N4096 d256 774 -> 729, B2 H16 N2048 d96 47.7 -> 46.3, B2 H32/8 N2048 d128 90.5 -> 89.1, B16 H16 N200 d128
-// 16.8 -> 16.5; not taken: B4 H32 N4096 d64 342 -> 353, B8 H12 N1024 d64 27.4 -> 28.4, and without a mask B4 H16
-// N2048 d128 149 -> 152, B2 H16 N2000 d96 65.5 -> 68.3, B2 H8 N2000 d256 99 -> 110.
+// D <= 64 that costs a wave per SIMD.  Measured, tile after tile -> pipeline (us): causal B2 H16 N2048 d96 46.7 -> 43.7,
+// B8 H16 N512 d96 19.1 -> 18.3, B8 H16 N384 d128 17.4 -> 16.1, B2 H16 N512 d128 15.5 -> 14.6, B2 H32/8 N2048 d128
+// 93.5 -> 91, but B16 H16 N200 d128 16.6 -> 17.6; d256 (with kPlacedReads) even, B4 H16 N4096 693 -> 683; not taken: B4 H32
+// N4096 d64 342 -> 353, B8 H12 N1024 d64 27.4 -> 28.4, and without a mask B4 H16 N2048 d128 153 -> 205, B2 H16 N2000 d96
+// 70 -> 75, B2 H8 N2048 d256 83 -> 143 (spills).
 template <int D, bool CAUSAL> constexpr bool kPipelined = CAUSAL && D >= 96;
 
 // Waves per SIMD the compiler has to make room for.  The row sums' selector and four-register result (add_rows) put some
@@ -190,8 +193,9 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
   constexpr int TILE_BYTES = kBc * D * 2;
   constexpr bool PIPE = kPipelined<D, CAUSAL> && VARIANT <= 1 && !EXTRAS && !SPLIT;
   // Row sums by matrix instruction (add_rows) where the vector work is what bounds the kernel: at D <= 64, and without a
-  // mask at D <= 128 (us, dot products -> matrix instructions: B4 H16 N2048 d128 full 151 -> 148, B2 H16 N2000 d96 full
-  // 68.5 -> 67.0; not taken: B2 H8 N2000 d256 full 99 -> 106, B4 H32 N4096 d128 causal in the pipeline 601 -> 611).
+  // mask at D <= 128 (us, dot products -> matrix instructions: B8 H12 N1024 d64 causal 29.1 -> 28.0, B32 H12 N512 d64 full
+  // 48.5 -> 44.9, B4 H16 N2048 d128 full 156 -> 153, B2 H16 N2000 d96 full 74.3 -> 70.2; not taken: d256 full even (B2 H8 N2048
+  // 82.7 -> 82.6, B4 H16 N4096 1211 -> 1225), B4 H32 N4096 d128 causal in the pipeline 601 -> 611).
   // (One rule for all kernels of a head size and mask: they give the same bits.)
   constexpr bool MFMA_SUMS = D <= 64 || (D <= 128 && !CAUSAL);
   extern __shared__ __attribute__((aligned(16))) char smem[];
