@@ -355,10 +355,15 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
         // compile-time constant: masked <=> c > lim, one per-lane limit for both conditions.  (Written
         // out here and not called: as a function its 32 comparisons come first and spill scalar registers.)
         // (At D <= 64 what it needs of the lane is formed here, from an opaque copy: ahead of the loop it costs registers.)
-        int ln = lane;
-        if (D <= 64) asm volatile("" : "+v"(ln));
-        int lim = CAUSAL ? __builtin_amdgcn_readfirstlane(qw) + (ln & 31) + shift - k0 - 4 * (ln >> 5) : 0x7fffffff;
-        if (RAGGED) lim = min(lim, NK - 1 - k0 - 4 * (ln >> 5));
+        int ql = q, hl = h;
+        if constexpr (D <= 64) {
+          int ln = lane;
+          asm volatile("" : "+v"(ln));
+          ql = __builtin_amdgcn_readfirstlane(qw) + (ln & 31);
+          hl = ln >> 5;
+        }
+        int lim = CAUSAL ? ql + shift - k0 - 4 * hl : 0x7fffffff;
+        if (RAGGED) lim = min(lim, NK - 1 - k0 - 4 * hl);
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
