@@ -145,30 +145,37 @@ template <bool TWO> struct TileMax {
 
 // Normaliser a row asks for in one key tile (the two lanes of the row get the same): Alg. 1 (VARIANT 0) its
 // maximum r_m, Alg. 3 (VARIANT 1) what the rule makes of it.  tm: maxima of the raw scores, masked ones -inf.
+// In two pieces, which a caller can place apart: the largest (and second largest) raw scores of the row, and the rule.
+struct RowMax { float mx, second; };
+template <bool TWO> DEVI RowMax row_max(const TileMax<TWO>& tm) {
+  if (!TWO) return {max_with_partner32(tm.largest()), 0.f};
+  // Alg. 3's count r_s = #{ r_m - S <= eps } over the tile row only matters through "more than one", i.e. through
+  // whether the SECOND largest score of the row passes the test: the two lanes that share a query row merge the
+  // two largest of their 32 scores.
+  const float t1 = tm.largest(), t2 = tm.second();
+  const auto w1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(t1), __float_as_uint(t1), false, false);
+  const auto w2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(t2), __float_as_uint(t2), false, false);
+  const float x1 = __uint_as_float(w1[0]), y1 = __uint_as_float(w1[1]);       // the largest of either lane
+  return {fmaxf(x1, y1), fmaxf(fmaxf(fminf(x1, y1), __uint_as_float(w2[0])), __uint_as_float(w2[1]))};
+}
 // may_be_unseen: a row may see no key of the tile.  allowed(r_m): whether a guard lets the rule apply.
+// r_m: the tile row maximum of the alpha-scaled scores.
+template <int VARIANT, class AllowedF>
+DEVI float asked_normaliser(const RowMax& w, float alpha, float inv_alpha, float beta, float eps,
+                            bool may_be_unseen, AllowedF&& allowed, float& r_m) {
+  r_m = w.mx * alpha;
+  if (VARIANT != 1) return r_m;
+  // A repeated maximum moves the normaliser to beta*r_m (r_m > 0) or to 0 (r_m < 0).  The test
+  // r_m - alpha*s <= eps  in terms of the raw score:  s >= (r_m - eps) / alpha
+  // (a row with nothing visible in this tile has r_m = -inf: no rule, no update)
+  const bool repeated = w.second >= (w.mx * alpha - eps) * inv_alpha && (!may_be_unseen || w.mx > -INFINITY) && allowed(r_m);
+  const float m_prime = (repeated && r_m > 0.f) ? beta * r_m : r_m;
+  return (repeated && r_m < 0.f) ? 0.f : m_prime;
+}
 template <int VARIANT, class AllowedF>
 DEVI float tile_normaliser(const TileMax<VARIANT == 1>& tm, float alpha, float inv_alpha, float beta, float eps,
                            bool may_be_unseen, AllowedF&& allowed, float& r_m) {
-  if (VARIANT == 1) {
-    // Alg. 3: r_s = #{ r_m - S <= eps } over the tile row; a repeated maximum moves the
-    // normaliser to beta*r_m (r_m > 0) or to 0 (r_m < 0).  The count only matters through
-    // "more than one", i.e. through whether the SECOND largest score of the row passes the
-    // test: the two lanes that share a query row merge the two largest of their 32 scores.
-    const float t1 = tm.largest(), t2 = tm.second();
-    const auto w1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(t1), __float_as_uint(t1), false, false);
-    const auto w2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(t2), __float_as_uint(t2), false, false);
-    const float x1 = __uint_as_float(w1[0]), y1 = __uint_as_float(w1[1]);       // the largest of either lane
-    const float mx = fmaxf(x1, y1);
-    const float second = fmaxf(fmaxf(fminf(x1, y1), __uint_as_float(w2[0])), __uint_as_float(w2[1]));
-    // the test  r_m - alpha*s <= eps  in terms of the raw score:  s >= (r_m - eps) / alpha
-    // (a row with nothing visible in this tile has r_m = -inf: no rule, no update)
-    r_m = mx * alpha;
-    const bool repeated = second >= (mx * alpha - eps) * inv_alpha && (!may_be_unseen || mx > -INFINITY) && allowed(r_m);
-    const float m_prime = (repeated && r_m > 0.f) ? beta * r_m : r_m;
-    return (repeated && r_m < 0.f) ? 0.f : m_prime;
-  }
-  r_m = max_with_partner32(tm.largest()) * alpha;
-  return r_m;
+  return asked_normaliser<VARIANT>(row_max(tm), alpha, inv_alpha, beta, eps, may_be_unseen, allowed, r_m);
 }
 
 // Waves per SIMD are stated as a range, not only as a minimum: at D = 128 two work-groups fit a
@@ -505,6 +512,11 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
   // of tile j as one stream of 4 x D/16 matrix instructions ("slots", a fence each, LDS fragments read AHEAD
   // slots before their use), with the vector work under them: P-bar of tile j under the scores of tile j + 1,
   // the row maxima of tile j + 1 under the output product.  K is read one tile ahead of V.
+  // What no product covers makes a lone wave wait: so the first fragments of a step are read ahead of the accumulator's
+  // rescale, and the chain from the maxima to the next normaliser lies under the last products.  us, both outside -> now, same
+  // bits: B4 H32 N4096 d128 606 -> 596, B4 H16 N1999 d128 86.8 -> 85.5, B1 H8 N2048 d128 38.1 -> 36.5, B2 H16 N2048 d96
+  // 40.5 -> 39.8, B8 H16 N512 d128 even.  (These kernels run at the board's power limit on large grids - the same instructions on
+  // zeros take 0.71 of the time - where filling gaps gives less than it does on small ones.)
   static_assert(!PIPE || !MFMA_SUMS, "row sums of the pipeline");
   if constexpr (PIPE) {
     constexpr int NS = D / 16, NDB = D / 32, AHEAD = 4, RING = AHEAD + 1;
@@ -524,13 +536,15 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
       for (int i = lo; i < hi; ++i)
         s[i] = 32 * kb + 8 * (i >> 2) + (i & 3) > lim ? -INFINITY : s[i];
     };
-    // running normaliser after a tile, and what its P-bar needs
-    auto advance = [&](const TileMax<VARIANT == 1>& tm) {
-      float r_m;         // tile row maximum of the alpha-scaled scores
-      const float m_prime = tile_normaliser<VARIANT>(tm, alpha, inv_alpha, beta, eps, may_be_unseen, [](float) { return true; }, r_m);
+    // running normaliser after a tile, and what its P-bar needs (m_prime: what the tile asks for)
+    auto asked = [&](const RowMax& w) {
+      float r_m;
+      return asked_normaliser<VARIANT>(w, alpha, inv_alpha, beta, eps, may_be_unseen, [](float) { return true; }, r_m);
+    };
+    auto advance = [&](float m_prime, float& factor) {
       const float m_new = fmaxf(m, m_prime);         // Alg. 1 step 7 / Alg. 3
       const bool unseen = may_be_unseen && m_new == -INFINITY;   // nothing visible so far: P-bar = 0, nothing to rescale
-      corr = unseen ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * kLog2e);
+      factor = unseen ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * kLog2e);
       m = m_new;
       mneg = unseen ? 0.f : -m_new * kLog2e;
     };
@@ -560,6 +574,13 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
         return lds_col8<D>(0, fo, 16 * ((i - 2 * NS) / NDB), (i - 2 * NS) % NDB);
       };
       prepare(j);
+      bf16x8 ring[RING], pf[4];
+      float psum = 0.f;
+      TileMax<VARIANT == 1> tm;
+      const int lim = MASKED ? limit(j + 1) : 0;
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) ring[(FIRST + i) % RING] = fragment(FIRST + i);
+      __builtin_amdgcn_sched_barrier(0);               // (the reads' latency lies under what follows)
       // O^T <- diag(corr) O^T (Alg. 1 step 8); in the first tile the accumulator is still zero
       if (j > 0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
@@ -567,12 +588,8 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
 #pragma unroll
           for (int i = 0; i < 16; ++i) acc[db][i] *= corr;
       }
-      bf16x8 ring[RING], pf[4];
-      float psum = 0.f;
-      TileMax<VARIANT == 1> tm;
-      const int lim = MASKED ? limit(j + 1) : 0;
-#pragma unroll
-      for (int i = 0; i < AHEAD; ++i) ring[(FIRST + i) % RING] = fragment(FIRST + i);
+      RowMax row;
+      float m_prime = 0.f, corr_next = 1.f;
       if (NEXT) {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -602,19 +619,23 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
           constexpr int u = sl - 2 * NS;
           if (!NEXT && u % NDB == 0 && u / NDB < 3) form_p(8 * (u / NDB + 1), 8 * (u / NDB + 2));
           if constexpr (NEXT) {
-            // steps of the row maxima, over all but the last quarter of the slots
-            constexpr int SPAN = NS * 3 / 2 < 1 ? 1 : NS * 3 / 2, F = 2 * kMaxSteps * u / SPAN, L = 2 * kMaxSteps * (u + 1) / SPAN;
+            // steps of the row maxima, over all but the last quarter of the slots, and there, piece by piece, the chain of
+            // dependent instructions from them to the next tile's normaliser
+            constexpr int SPAN = NS * 3 / 2, Q = (2 * NS - SPAN) / 3, F = 2 * kMaxSteps * u / SPAN, L = 2 * kMaxSteps * (u + 1) / SPAN;
             static_for<(u < SPAN ? L - F : 0)>([&](auto k) {
               constexpr int t = F + decltype(k)::value, kb = t / kMaxSteps, st = t % kMaxSteps;
               if (MASKED) mask(sn[kb], kb, st == 0 ? 0 : 2 * st + 1, st == 0 ? 3 : st < 7 ? 2 * st + 3 : 16, lim);
               tm.template step<st>(kb, sn[kb]);
             });
+            if constexpr (u == SPAN) row = row_max(tm);
+            if constexpr (u == SPAN + Q) m_prime = asked(row);
+            if constexpr (u == SPAN + 2 * Q) advance(m_prime, corr_next);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
       });
       lsum = lsum * corr + psum;
-      if (NEXT) advance(tm);
+      corr = corr_next;
 #pragma unroll
       for (int p = 0; p < 2; ++p) { fo.row[p] -= turn; fo.col[p] += turn; }
       turn = -turn;
@@ -638,7 +659,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
       }
       TileMax<VARIANT == 1> tm;
       tm.all(s0);
-      advance(tm);
+      advance(asked(row_max(tm)), corr);
     }
     __syncthreads();                                   // K of the first tile is read out everywhere: its buffer is free
 #pragma unroll
