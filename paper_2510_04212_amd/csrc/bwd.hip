@@ -30,20 +30,6 @@ namespace {
 constexpr int kKeysPerWG = 128;   // dK/dV kernel: keys per work-group (32 per wave); 64 with four wave groups
 constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per wave); 64 with wave groups
 
-template <int NDB>
-DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, int h) {
-  // acc[db][i] = X^T[d = 32db + 8(i/4) + 4h + (i%4)][row of this lane]; 4 consecutive d -> 8 bytes
-#pragma unroll
-  for (int db = 0; db < NDB; ++db)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 o4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(acc[db][4 * g + e] * scale);
-      *reinterpret_cast<bf16x4*>(dst_row + 32 * db + 8 * g + 4 * h) = o4;
-    }
-}
-
 // GROUPED: grouped-query attention (lay.group > 1): the work-group serves several query heads.
 // Kept out of the ordinary kernel so that its tile loop has a fixed head and no bookkeeping.
 // At D = 256 the two accumulator sets of a full key block would not fit the register file next
@@ -52,7 +38,7 @@ DEVI void store_acc_T(bf16_t* dst_row, const f32x16 (&acc)[NDB], float scale, in
 template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // The kernel wants two waves on every SIMD: one wave alone leaves the matrix cores idle whenever
 // any of its instructions waits.  That means at most 256 registers per lane (some instantiations
-// at D = 128 under the mask spill two to nine, outside their tile loops).  At D = 128 the
+// at D = 128 under the mask spill three to nine, outside their tile loops).  At D = 128 the
 // accumulators (128) and the K fragments (32) leave no room for the V fragments: V_j is kept in LDS
 // for the whole block (8 more fragment reads per 32 queries to 48) and the query tiles shrink to 32
 // rows per wave group, so that two work-groups fit a CU.  Measured against one wave per SIMD with
@@ -115,7 +101,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
   const int lane = tid & 63;
   const int wave = (tid >> 6) % KW;                    // which 32 keys
   const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(tid / (64 * KW)) : 0;   // which 32-query blocks
-  const int r = lane & 31, h = lane >> 5;
+  const int r = lane & 15, g = lane >> 4;
 
   // RAGGED: the bounds-checking instantiation: N queries and NK keys, neither need be a multiple
   // of the block; causal mask  key <= query + shift.
@@ -129,9 +115,10 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
   // work-group, in the order the table `ord` gives.
   const int npw = pairs ? (nkt + 1) / 2 : nkt;         // work-groups per key/value head and column part
   constexpr int DS = kDSplit<D>;
-  constexpr int NDB = D / 32 / DS;                     // 32-column blocks of dK / dV this work-group owns
+  constexpr int NKC = D / 32;                          // 32-column blocks of a row
+  constexpr int NDT = D / 16 / DS;                     // 16-column tiles of dK / dV this work-group owns
   const int wg_all = logical_wg(ord, blockIdx.x, gridDim.x);
-  const int db0 = (DS > 1) ? (wg_all % DS) * NDB : 0;  // first of them
+  const int dt0 = (DS > 1) ? (wg_all % DS) * NDT : 0;  // first of them
   const int wg = wg_all / DS;
   // with grouped queries a work-group serves the `group` query heads that share its key/value
   // head, one after the other
@@ -143,23 +130,33 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
   const int sn = lay.sn;
   const size_t head_off = head_base_kv(lay, bq0);              // K, V, dK, dV
   const float c2 = alpha * kLog2e;
-  FragOffsets<D> fo;
-  init_frag_offsets<D>(fo, lane, lds_address(smem));
-  FragOffsets<D> fo_v = fo;                            // V_j fragments of this wave's keys
-  FragOffsets<D> fo_upd = fo;                          // update products: columns from block db0 on
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    if (kVInLds<D>) fo_v.row[p] += 2 * wave * kRowBlockBytes<D>;
-    if (DS > 1) fo_upd.col[p] += 1024 * db0;
-    if (G > 1) {
-      fo.row[p] += 4 * grp * GT;
-      fo_upd.col[p] += 4 * grp * GT;
-    }
+  TileFrags fo;
+  init_tile_frags(fo, lane, lds_address(smem));
+  int v_row = fo.row;                                  // V_j fragments of this wave's keys
+  if (kVInLds<D>) v_row += 2 * wave * kRowBlockBytes<D>;
+  if (G > 1) {
+    fo.row += 4 * grp * GT;
+    fo.col[0] += 4 * grp * GT;
+    fo.col[1] += 4 * grp * GT;
+  }
+  if (DS > 1) {                                        // update products: columns from tile dt0 on (an even one)
+    fo.col[0] += 512 * dt0;
+    fo.col[1] += 512 * dt0;
+  }
+  // D = 256: the dO buffers lie beyond the 64 KB that the immediate offset of an LDS read reaches, and have base registers of
+  // their own (one addition per read otherwise, which counts where a SIMD has one wave).
+  constexpr int FAR = 4 * GT > 65536 ? 2 * GT : 0;
+  TileFrags fo_dO = fo;
+  if (FAR) {
+    fo_dO.row += FAR;
+    fo_dO.col[0] += FAR;
+    fo_dO.col[1] += FAR;
+    asm volatile("" : "+v"(fo_dO.row), "+v"(fo_dO.col[0]), "+v"(fo_dO.col[1]));
   }
   // Group g reads the g-th 32 rows of a tile, which are the rows that its own waves fetch.  Its four buffers lie next
   // to one another (tiles as a whole would not), within the 64 KB that the immediate offset of an LDS read reaches:
   // one base register for all of them, which is what leaves the registers for the stream of qblocks below at D = 128 (with
-  // whole tiles it spills 33 to 55, now 6 to 9, outside the loop).  us, whole tiles and phase after phase -> now, same
+  // whole tiles it spills 33 to 55, now three to nine, outside the loop).  us, whole tiles and phase after phase -> now, same
   // bits: B2 H16 N2048 d128 causal 95.5 -> 88.1, B2 H8 N2048 d128 full 71.6 -> 67.2, B1 H4 N4096 d128 causal 69.2 -> 66.0,
   // B2 H32/8 N2048 d128 causal 176 -> 172; at D <= 96, where only the layout changes, within 2 % either way.
   TileLoader<D, QT, KW * G> loader;
@@ -172,7 +169,8 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
   // Three waves per SIMD at D = 64 under the mask: what depends on the lane is formed where it is used, from copies of the
   // thread index that the compiler cannot see through.  Formed ahead of the loops it was spilled (eight or nine registers), and
   // short problems waited for the reloads: us, 400 heads N200 23.2 -> 18.9, 472 heads N300 41.5 -> 34.3, B8 H12 N1000
-  // 39.0 -> 34.5, N1024 37.1 -> 36.2, B4 H32 N4000 526 -> 512.  (Elsewhere nothing is spilled, and it costs 2 %.)
+  // 39.0 -> 34.5, N1024 37.1 -> 36.2, B4 H32 N4000 526 -> 512.  (Elsewhere it costs 2 %, also at D = 128, where it takes away the
+  // few spills outside the tile loop: B4 H32 N4096 causal 900 -> 933.)
   constexpr bool FORM_LATE = DENSE && D == 64 && CAUSAL;
   auto late = [](int x) {
     if (FORM_LATE) asm volatile("" : "+v"(x));
@@ -184,27 +182,31 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     if (part == 1 && (!pairs || kt == kt_first)) break;   // no partner: one block per work-group, or the middle one of an odd number
     if (kStageOverTiles<D, G> && part > 0) __syncthreads();   // the first block's staging is done with the tile buffers
     const int k0 = kt * KEYS;
-    const int kw = k0 + 32 * (FORM_LATE ? late(tid) >> 6 : wave);
+    const int kw = k0 + 32 * (FORM_LATE ? (late(tid) >> 6) % KW : wave);
 
     if constexpr (kVInLds<D>) {
       TileLoader<D, KEYS, KW * G> v_loader;
       v_loader.init(tid, sn);
       v_loader.template load_rows<RAGGED>(smem, V + head_off, k0, NK);
     }
-    // K_j^T / V_j^T fragments (B operands): lane (r,h) holds K[kw + r][16kc + 8h .. +7]
+    // K_j^T / V_j^T fragments (B operands): lane (r, g) holds K[kw + 16n + r][32kc + 8g .. +7], n = 0, 1
     // (keys past the sequence end read the last row; their gradients are not stored)
-    const int keyc = (RAGGED && kw + r >= NK) ? NK - 1 : kw + r, hk = late(h);
-    bf16x8 kf[D / 16], vf[kVInLds<D> ? 1 : D / 16];
+    const int gk = late(g);
+    bf16x8 kf[2][NKC], vf[2][kVInLds<D> ? 1 : NKC];
 #pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc) {
-      kf[kc] = *reinterpret_cast<const bf16x8*>(K + head_off + (size_t)keyc * sn + 16 * kc + 8 * hk);
-      if constexpr (!kVInLds<D>) vf[kc] = *reinterpret_cast<const bf16x8*>(V + head_off + (size_t)keyc * sn + 16 * kc + 8 * hk);
+    for (int n = 0; n < 2; ++n) {
+      const int keyc = RAGGED ? min(kw + 16 * n + r, NK - 1) : kw + 16 * n + r;
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) {
+        kf[n][kc] = *reinterpret_cast<const bf16x8*>(K + head_off + (size_t)keyc * sn + 32 * kc + 8 * gk);
+        if constexpr (!kVInLds<D>) vf[n][kc] = *reinterpret_cast<const bf16x8*>(V + head_off + (size_t)keyc * sn + 32 * kc + 8 * gk);
+      }
     }
-    f32x16 dVt[NDB], dKt[NDB];
+    f32x4 dVt[NDT][2], dKt[NDT][2];
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+    for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) { dVt[db][i] = 0.f; dKt[db][i] = 0.f; }
+      for (int n = 0; n < 2; ++n) dVt[dt][n] = dKt[dt][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // first query tile that sees any key of this block (the last query sees every key: t0 < nt)
     const int t0 = !CAUSAL ? 0 : !RAGGED ? k0 / QT : max(0, k0 - shift) / QT;
@@ -247,10 +249,12 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     store_stats(0, t0);
     wait_vmem();
 #pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc) {
-      settle(kf[kc]);
-      if constexpr (!kVInLds<D>) settle(vf[kc]);
-    }
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) {
+        settle(kf[n][kc]);
+        if constexpr (!kVInLds<D>) settle(vf[n][kc]);
+      }
     __syncthreads();
 
     // One query tile; BUF (which LDS buffer holds it) is a compile-time constant so that every LDS
@@ -276,12 +280,12 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       bool issued = false;
       if (has_next) load_stats(Lh, Dh, tn);
       constexpr int tQ = T0 + buf * GT;             // byte offsets of this tile's Q and dO in smem
-      constexpr int tdO = T0 + (2 + buf) * GT;
+      constexpr int tdO = T0 + (2 + buf) * GT - FAR;       // (from fo_dO)
       const float* tL = ldsL + buf * QT;
       const float* tD = ldsD + buf * QT;
       const int qt0 = t * QT;
       // The NB 32-query blocks of a tile that belong to this wave's group against its 32 keys, as one stream of matrix
-      // instructions ("slots"):  S (D/16 slots) | dP | dV (2 NDB) | dK, block after block.  The vector work of a
+      // instructions ("slots"):  S (D/16 slots) | dP | dV (NDT) | dK, block after block.  The vector work of a
       // block lies under its own matrix instructions: P = exp(S - L) under dP, dS = P o (dP - delta) under dV,
       // and every LDS fragment is read AHEAD slots before its use (a fence per slot keeps that order).  Same bits as
       // phase after phase; us, whole kernel: B2 H8 N2048 d256 causal 120 -> 116, B1 H8 N1000 d256 causal 74 -> 59,
@@ -293,82 +297,104 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       auto qblocks = [&](auto masked_c, auto nb_c, auto qb_c) {
         constexpr bool MASKED = decltype(masked_c)::value;
         constexpr int NB = decltype(nb_c)::value, qb = decltype(qb_c)::value;
-        constexpr int NS = D / 16, NU = 2 * NDB, PB = 2 * NS + 2 * NU;    // slots of S or dP, of dV or dK, of a block
-        constexpr int AHEAD = kReadAhead<D, G, CAUSAL, DENSE>, RING = AHEAD + 1;
-        constexpr int AHEAD_V = 1, RING_V = AHEAD_V + 1;       // kVInLds: V_j's fragments
+        constexpr int NS = D / 16, NU = NDT, PB = 2 * NS + 2 * NU;        // slots of S or dP, of dV or dK, of a block
+        constexpr int AHEAD = MASKED && DENSE ? 1 : kReadAhead<D, G, CAUSAL, DENSE>;       // (1: two would spill)
+        // PAIRED: reads are issued two at a time, the later one first, so that one wait serves two slots.  Pays for the one wave
+        // of a SIMD at D = 256: B2 H8 N2048 causal 97.2 -> 95.3 us, B1 H8 90.7 -> 89.2; at smaller D even, or to 2 % slower.
+        constexpr bool PAIRED = D == 256;
+        static_assert(!PAIRED || AHEAD % 2 == 0, "pairs");
+        constexpr int RING = AHEAD + (PAIRED ? 2 : 1);
+        // S and dP: slot u is the 16-query tile u % 2 against 32-column block u / 2; dV and dK: column tile u
         auto fragment = [&](int i) -> bf16x8 {
           const int b = qb + i / PB, u = i % PB;
-          if (u < NS) return lds_row8<D>(tQ, fo, 32 * b, u);
-          if (u < 2 * NS) return lds_row8<D>(tdO, fo, 32 * b, u - NS);
-          const int w = (u - 2 * NS) % NU;
-          return lds_col8<D>(u < 2 * NS + NU ? tdO : tQ, fo_upd, 32 * b + 16 * (w / NDB), w % NDB);
+          if (u < 2 * NS) return lds_row16<D>(u < NS ? tQ : tdO, u < NS ? fo : fo_dO, 32 * b + 16 * (u % 2), u % NS / 2);
+          return lds_col16<D>(u < 2 * NS + NU ? tdO : tQ, u < 2 * NS + NU ? fo_dO : fo, 32 * b, (u - 2 * NS) % NU);
         };
-        bf16x8 ring[RING], ring_v[kVInLds<D> ? RING_V : 1];
+        auto v_fragment = [&](int n, int kc) -> bf16x8 {     // kVInLds: V_j's
+          TileFrags at;
+          at.row = v_row;
+          return lds_row16<D>(0, at, 16 * n, kc);
+        };
+        bf16x8 ring[RING], v_ring[2][2];
 #pragma unroll
-        for (int i = 0; i < AHEAD; ++i) ring[i] = fragment(i);
-        f32x16 s, dp;
-        f32x4 l4[4];
+        for (int i = 0; i < AHEAD; ++i) ring[PAIRED ? i ^ 1 : i] = fragment(PAIRED ? i ^ 1 : i);
+        f32x4 s[2][2], dp[2][2];         // [16-query tile][16-key tile]
+        f32x4 l4[2];
         bf16x8 pf[2], dsf[2];
-        int first_seen = 0;              // MASKED: entry c = 8 (i / 4) + i % 4 counts if c >= first_seen
+        int first_seen = 0;              // MASKED: entry 16m + i of 16-key tile n counts if 16 (m - n) + i >= first_seen
         static_for<NB * PB>([&](auto slot) {
           constexpr int sl = decltype(slot)::value, u = sl % PB, b = qb + sl / PB;
-          const int stat = 32 * (b + grp) + 4 * h;
-          if (sl + AHEAD < NB * PB) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
-          constexpr int uv = u + AHEAD_V - NS;
-          if constexpr (kVInLds<D> && uv >= 0 && uv < NS) ring_v[uv % RING_V] = lds_row8<D>(0, fo_v, 0, uv);
+          const int stat = 32 * (b + grp) + 4 * g;
+          if (PAIRED) {
+            if (sl % 2 == 0 && sl + AHEAD < NB * PB) {
+              ring[(sl + AHEAD + 1) % RING] = fragment(sl + AHEAD + 1);
+              ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+            }
+          } else if (sl + AHEAD < NB * PB) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
+          if constexpr (kVInLds<D>) {      // two slots ahead of their use
+            constexpr int uv = u + 2 - NS;
+            if constexpr (uv >= 0 && uv < NS) v_ring[uv % 2][uv / 2 % 2] = v_fragment(uv % 2, uv / 2);
+          }
           if (u == 0) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = 0.f;
+            for (int n = 0; n < 2; ++n) s[0][n] = s[1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (MASKED) {
               int ln = lane;
               constexpr bool LATE = DENSE || kVInLds<D>;         // formed here, not ahead of the tile loop: registers
               if (LATE) asm volatile("" : "+v"(ln));
-              first_seen = (LATE ? __builtin_amdgcn_readfirstlane(kw) : kw) + (ln & 31) - shift - qt0 - 32 * (b + grp) - 4 * (ln >> 5);
+              first_seen = (LATE ? __builtin_amdgcn_readfirstlane(kw) : kw) + (ln & 15) - shift - qt0 - 32 * (b + grp) - 4 * (ln >> 4);
             }
           }
           // -delta_i seeds the dP accumulator; L_i of the rows a lane sees
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
-            if (u == g * (NS < 4 ? NS : 4) / 4) {
-              const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + stat + 8 * g);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) dp[4 * g + e] = d4[e];
+          for (int m = 0; m < 2; ++m)
+            if (u == m * NS / 2) {
+              const f32x4 d4 = *reinterpret_cast<const f32x4*>(tD + stat + 16 * m);
+              dp[m][0] = dp[m][1] = d4;
             }
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
-            if (u == NS + g * NS / 4) l4[g] = *reinterpret_cast<const f32x4*>(tL + stat + 8 * g);
+          for (int m = 0; m < 2; ++m)
+            if (u == NS / 2 + m * NS / 2) l4[m] = *reinterpret_cast<const f32x4*>(tL + stat + 16 * m);
           const bf16x8 a = ring[sl % RING];
-          if constexpr (u < NS) {
-            s = mfma32(a, kf[u], s);
-          } else if constexpr (u < 2 * NS) {
-            if constexpr (kVInLds<D>) dp = mfma32(a, ring_v[(u - NS) % RING_V], dp);
-            else dp = mfma32(a, vf[u - NS], dp);
-          } else if constexpr (u < 2 * NS + NU) {
-            constexpr int w = u - 2 * NS;
-            dVt[w % NDB] = mfma32(a, pf[w / NDB], dVt[w % NDB]);
-          } else {
-            constexpr int w = u - 2 * NS - NU;
-            dKt[w % NDB] = mfma32(a, dsf[w / NDB], dKt[w % NDB]);
+#pragma unroll
+          for (int n = 0; n < 2; ++n) {
+            if constexpr (u < NS) {
+              s[u % 2][n] = mfma16(a, kf[n][u / 2], s[u % 2][n]);
+            } else if constexpr (u < 2 * NS) {
+              constexpr int w = u - NS;
+              if constexpr (kVInLds<D>) dp[w % 2][n] = mfma16(a, v_ring[n][w / 2 % 2], dp[w % 2][n]);
+              else dp[w % 2][n] = mfma16(a, vf[n][w / 2], dp[w % 2][n]);
+            } else if constexpr (u < 2 * NS + NU) {
+              dVt[u - 2 * NS][n] = mfma16(a, pf[n], dVt[u - 2 * NS][n]);
+            } else {
+              dKt[u - 2 * NS - NU][n] = mfma16(a, dsf[n], dKt[u - 2 * NS - NU][n]);
+            }
           }
           if (b == 0) issue_part(sl);
-          if (u > NS && u <= 2 * NS) {           // P = exp(S - L) (step 9)
+          // Entry e of a lane's 16: row (e & 3) of 16-query tile m = e / 8, 16-key tile n = (e >> 2) & 1.  Query tile by query
+          // tile, so that L of one tile at a time is live (key tile by key tile the three-wave kernels spilled two registers, one
+          // of them reloaded for every tile: 1120 heads N268 d64 causal 64.9 -> 60.9 us, B8 H12 N1000 35.2 -> 33.7).
+          if constexpr (u >= NS && u < 2 * NS) {                  // P = exp(S - L) (step 9)
+            constexpr int f = u - NS;
 #pragma unroll
-            for (int i = 16 * (u - NS - 1) / NS; i < 16 * (u - NS) / NS; ++i) {
-              float x = __builtin_fmaf(s[i], c2, -l4[i >> 2][i & 3]);
-              const int c = 8 * (i >> 2) + (i & 3);
-              if (MASKED && c < first_seen) x = -INFINITY;
-              s[i] = __builtin_amdgcn_exp2f(x);
-              pf[i >> 3][i & 7] = (bf16_t)s[i];
+            for (int e = 16 * f / NS; e < 16 * (f + 1) / NS; ++e) {
+              const int m = e >> 3, n = (e >> 2) & 1, i = e & 3;
+              float x = __builtin_fmaf(s[m][n][i], c2, -l4[m][i]);
+              if (MASKED && 16 * (m - n) + i < first_seen) x = -INFINITY;
+              s[m][n][i] = __builtin_amdgcn_exp2f(x);
+              pf[n][4 * m + i] = (bf16_t)s[m][n][i];
             }
           }
-          if (u > 2 * NS && u <= 2 * NS + NU) {  // dS = P o (dP - delta) (step 12); dp already holds dP - delta
+          if constexpr (u >= 2 * NS && u < 2 * NS + NU) {         // dS = P o (dP - delta) (step 12); dp already holds dP - delta
+            constexpr int f = u - 2 * NS;
 #pragma unroll
-            for (int i = 16 * (u - 2 * NS - 1) / NU; i < 16 * (u - 2 * NS) / NU; ++i) {
-              float ds = s[i] * dp[i];
+            for (int e = 16 * f / NU; e < 16 * (f + 1) / NU; ++e) {
+              const int m = e >> 3, n = (e >> 2) & 1, i = e & 3;
+              float ds = s[m][n][i] * dp[m][n][i];
               // a masked entry contributes exactly nothing, whatever its row holds
-              const int c = 8 * (i >> 2) + (i & 3);
-              if (MASKED && c < first_seen) ds = 0.f;
-              dsf[i >> 3][i & 7] = (bf16_t)ds;
+              if (MASKED && 16 * (m - n) + i < first_seen) ds = 0.f;
+              if (MASKED) asm("" : "+v"(ds));      // (the compiler would convert first and select 16 bits at a time)
+              dsf[n][4 * m + i] = (bf16_t)ds;
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -420,11 +446,11 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       }
     }
     const int rows_valid = RAGGED ? NK - kw : 32;
-    auto rounded = [&](const f32x16 (&acc)[NDB], float scale) {
-      return [&acc, scale](int db, int g) {
+    auto rounded = [&](const f32x4 (&acc)[NDT][2], float scale) {
+      return [&acc, scale](int dt, int n) {
         bf16x4 o4;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(acc[db][4 * g + e] * scale);
+        for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(acc[dt][n][e] * scale);
         return o4;
       };
     };
@@ -435,25 +461,16 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       // the last tile's barrier: the whole array is free.
       // (the lane index passes through an empty asm: addresses formed from the kernel's own copy would
       // be hoisted above the tile loop and held in registers through it)
-      constexpr int AREA = NDB * 4096;
+      constexpr int AREA = NDT * 2048;
       int ln = lane;
       asm volatile("" : "+v"(ln));
-      auto put = [&](const f32x16 (&acc)[NDB], char* give) {
+      auto put = [&](const f32x4 (&acc)[NDT][2], char* give) {
 #pragma unroll
-        for (int i = 0; i < 4 * NDB; ++i) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i >> 2][4 * (i & 3) + e];
-          *reinterpret_cast<f32x4*>(give + (i * 64 + ln) * 16) = v;
-        }
+        for (int i = 0; i < 2 * NDT; ++i) *reinterpret_cast<f32x4*>(give + (i * 64 + ln) * 16) = acc[i >> 1][i & 1];
       };
-      auto add = [&](f32x16 (&acc)[NDB], const char* take) {
+      auto add = [&](f32x4 (&acc)[NDT][2], const char* take) {
 #pragma unroll
-        for (int i = 0; i < 4 * NDB; ++i) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(take + (i * 64 + ln) * 16);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i >> 2][4 * (i & 3) + e] += v[e];
-        }
+        for (int i = 0; i < 2 * NDT; ++i) acc[i >> 1][i & 1] += *reinterpret_cast<const f32x4*>(take + (i * 64 + ln) * 16);
       };
       if constexpr (G == 4) {
         char* area = smem + ((grp & 1) * KW + wave) * 2 * AREA;
@@ -465,23 +482,25 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
       char* give = smem + (grp * KW + wave) * AREA;
       char* take = smem + ((grp ^ 1) * KW + wave) * AREA;
       // one output per group; the wave's `take` area, read out by then, serves as its staging area
-      auto finish = [&](f32x16 (&acc)[NDB], float scale, bf16_t* out) {
+      auto finish = [&](f32x4 (&acc)[NDT][2], float scale, bf16_t* out) {
         add(acc, take);
-        if constexpr (kStagedDkDv<D>)
-          store_rows_staged<NDB>(take, rounded(acc, scale), out + head_off + (size_t)kw * sn, sn, rows_valid, ln);
-        else if (!RAGGED || kw + r < NK)
-          store_acc_T<NDB>(out + head_off + (size_t)(kw + r) * sn, acc, scale, h);
+        bf16_t* dst = out + head_off + (size_t)kw * sn;
+        if constexpr (kStagedDkDv<D>) store_rows16_staged<NDT>(take, rounded(acc, scale), dst, sn, rows_valid, ln);
+        else store_rows16<NDT>(rounded(acc, scale), dst, sn, rows_valid, ln);
       };
       if (grp == 0) put(dKt, give); else if (grp == 1) put(dVt, give);
       __syncthreads();
       if (grp == 0) finish(dVt, 1.0f, dV); else if (grp == 1) finish(dKt, alpha, dK);
-    } else if constexpr (kStagedDkDv<D>) {
-      char* stage = smem + T0 + (kStageOverTiles<D, G> ? 0 : 4 * TILE_BYTES + 4 * QT * (int)sizeof(float));
-      store_rows_staged<NDB>(stage, rounded(dVt, 1.0f), dV + 32 * db0 + head_off + (size_t)kw * sn, sn, rows_valid, tid);
-      store_rows_staged<NDB>(stage, rounded(dKt, alpha), dK + 32 * db0 + head_off + (size_t)kw * sn, sn, rows_valid, tid);
-    } else if (!RAGGED || kw + r < NK) {
-      store_acc_T<NDB>(dV + 32 * db0 + head_off + (size_t)(kw + r) * sn, dVt, 1.0f, h);
-      store_acc_T<NDB>(dK + 32 * db0 + head_off + (size_t)(kw + r) * sn, dKt, alpha, h);
+    } else {
+      const size_t at = 16 * dt0 + head_off + (size_t)kw * sn;
+      if constexpr (kStagedDkDv<D>) {
+        char* stage = smem + T0 + (kStageOverTiles<D, G> ? 0 : 4 * TILE_BYTES + 4 * QT * (int)sizeof(float));
+        store_rows16_staged<NDT>(stage, rounded(dVt, 1.0f), dV + at, sn, rows_valid, tid);
+        store_rows16_staged<NDT>(stage, rounded(dKt, alpha), dK + at, sn, rows_valid, tid);
+      } else {
+        store_rows16<NDT>(rounded(dVt, 1.0f), dV + at, sn, rows_valid, lane);
+        store_rows16<NDT>(rounded(dKt, alpha), dK + at, sn, rows_valid, lane);
+      }
     }
   }
 }
@@ -522,7 +541,7 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
   constexpr bool DELTA_MODE = MODE == kRecomputeDelta;
   constexpr int QW = kQueryWaves<G>, QUERIES = 32 * QW, KT = kKeysPerTile<G>;
   constexpr int TILE_BYTES = KT * D * 2;
-  constexpr int NDB = D / 32;
+  constexpr int NKC = D / 32, NDT = D / 16;            // 32-column blocks of a row, 16-column tiles of dQ
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* ldsK = smem;
   char* ldsV = smem + 2 * TILE_BYTES;
@@ -531,7 +550,7 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
   const int lane = tid & 63;
   const int wave = (tid >> 6) % QW;                   // which 32 queries
   const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(tid / (64 * QW)) : 0;   // which 32-key blocks
-  const int r = lane & 31, h = lane >> 5;
+  const int r = lane & 15, g = lane >> 4;
 
   const int NK = RAGGED ? lay.Nk : N;                 // bounds-checking instantiation: N queries, NK keys,
   const int shift = RAGGED ? NK - N : 0;              // causal mask  key <= query + shift
@@ -551,14 +570,18 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
   const float c2 = alpha * kLog2e;
   TileLoader<D, KT, QW * G> loader;
   loader.init(tid, sn);
-  FragOffsets<D> fo;
-  init_frag_offsets<D>(fo, lane, lds_address(smem));
-  if (G > 1) {                                        // group g reads the g-th 32 rows of a tile
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      fo.row[p] += 2 * grp * kRowBlockBytes<D>;
-      fo.col[p] += 2 * grp * kRowBlockBytes<D>;
-    }
+  TileFrags fo;
+  init_tile_frags(fo, lane, lds_address(smem));
+  if (G > 1) {                                        // a group reads its own 32 rows of a tile
+    fo.row += 2 * grp * kRowBlockBytes<D>;
+    fo.col[0] += 2 * grp * kRowBlockBytes<D>;
+    fo.col[1] += 2 * grp * kRowBlockBytes<D>;
+  }
+  constexpr int FAR = 4 * TILE_BYTES > 65536 ? 2 * TILE_BYTES : 0;      // see the dK/dV kernel
+  TileFrags fo_v = fo;
+  if (FAR) {
+    fo_v.row += FAR;
+    asm volatile("" : "+v"(fo_v.row));
   }
 
   for (int part = 0; part < (pairs ? 2 : 1); ++part) {
@@ -569,56 +592,66 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
   const int q0 = qt * QUERIES;
   const int qw = q0 + 32 * wave;
 
-  // Q_i^T / dO_i^T fragments (B operands): lane (r,h) holds Q[qw + r][16kc + 8h .. +7]
+  // Q_i^T / dO_i^T fragments (B operands): lane (r, g) holds Q[qw + 16n + r][32kc + 8g .. +7], n = 0, 1
   // (rows past the sequence end read the last row; their dQ is not stored)
-  const int qc = (RAGGED && qw + r >= N) ? N - 1 : qw + r;
-  bf16x8 qf[D / 16], dof[D / 16];
+  bf16x8 qf[2][NKC], dof[2][NKC];
+  int qc[2];
+  float l2[2], dl[2] = {0.f, 0.f};
 #pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) {
-    qf[kc] = *reinterpret_cast<const bf16x8*>(Q + head_off + (size_t)qc * sn + 16 * kc + 8 * h);
-    dof[kc] = *reinterpret_cast<const bf16x8*>(dO + head_off + (size_t)qc * sn + 16 * kc + 8 * h);
-  }
-  float l2 = LSE[(size_t)bh * N + qc] * kLog2e;
-  if (RAGGED && l2 == -INFINITY) l2 = 0.f;             // a query that sees no key: all its scores are masked below
-  float dl = 0.f;
-  if (MODE == kGivenDelta) dl = delta[(size_t)bh * N + qc];
-  if (MODE == kOwnDelta) {
-    // this lane holds chunks 2kc + h of its row: the chains of its chunks, the tree levels that
-    // stay inside one parity class, and the last level (chunk 0 + chunk 1 classes) across the
-    // two lanes of the row
-    constexpr int NCS = kPow2D<D> / 16;     // D = 96: the tree of a 128-wide row whose last chunks are zero
-    float cs[NCS];
+  for (int n = 0; n < 2; ++n) {
+    qc[n] = RAGGED ? min(qw + 16 * n + r, N - 1) : qw + 16 * n + r;
+    const size_t at = head_off + (size_t)qc[n] * sn + 8 * g;
 #pragma unroll
-    for (int kc = 0; kc < NCS; ++kc) cs[kc] = 0.f;
-#pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc) {
-      const bf16x8 o8 = *reinterpret_cast<const bf16x8*>(O + head_off + (size_t)qc * sn + 16 * kc + 8 * h);
-      float c = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) c = __builtin_fmaf((float)o8[e], (float)dof[kc][e], c);
-      cs[kc] = c;
+    for (int kc = 0; kc < NKC; ++kc) {
+      qf[n][kc] = *reinterpret_cast<const bf16x8*>(Q + at + 32 * kc);
+      dof[n][kc] = *reinterpret_cast<const bf16x8*>(dO + at + 32 * kc);
     }
-#pragma unroll
-    for (int off = NCS / 2; off >= 1; off >>= 1)
-#pragma unroll
-      for (int kc = 0; kc < off; ++kc) cs[kc] += cs[kc + off];
-    dl = sum_with_partner32(cs[0]);
-    if (h == 0 && grp == 0 && (!RAGGED || qw + r < N)) delta_out[(size_t)bh * N + qw + r] = dl;
+    l2[n] = LSE[(size_t)bh * N + qc[n]] * kLog2e;
+    if (RAGGED && l2[n] == -INFINITY) l2[n] = 0.f;       // a query that sees no key: all its scores are masked below
+    if (MODE == kGivenDelta) dl[n] = delta[(size_t)bh * N + qc[n]];
   }
-  float pdp = 0.f;                                   // DELTA_MODE: this lane's share of sum_k P dP
-  // -delta_i in all 16 accumulator slots of the lane: the third operand of the first dP^T matrix
-  // instruction of every key block, which then delivers dP - delta with no vector instruction
+  if (MODE == kOwnDelta) {
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      // this lane holds chunks 4kc + g of its row: the chains of its chunks, the tree levels that stay inside one
+      // residue class, and the last two levels across the four lanes of the row
+      constexpr int NCS = kPow2D<D> / 32;     // D = 96: the tree of a 128-wide row whose last chunks are zero
+      float cs[NCS];
+#pragma unroll
+      for (int kc = 0; kc < NCS; ++kc) cs[kc] = 0.f;
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) {
+        const bf16x8 o8 = *reinterpret_cast<const bf16x8*>(O + head_off + (size_t)qc[n] * sn + 32 * kc + 8 * g);
+        float c = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c = __builtin_fmaf((float)o8[e], (float)dof[n][kc][e], c);
+        cs[kc] = c;
+      }
+#pragma unroll
+      for (int off = NCS / 2; off >= 1; off >>= 1)
+#pragma unroll
+        for (int kc = 0; kc < off; ++kc) cs[kc] += cs[kc + off];
+      dl[n] = sum_over_groups(cs[0]);
+      if (g == 0 && grp == 0 && (!RAGGED || qw + 16 * n + r < N)) delta_out[(size_t)bh * N + qw + 16 * n + r] = dl[n];
+    }
+  }
+  float pdp[2] = {0.f, 0.f};                         // DELTA_MODE: this lane's share of sum_k P dP
+  // -delta_i in all accumulator slots of the lane: the third operand of the first dP^T matrix
+  // instructions of every key block, which then deliver dP - delta with no vector instruction
   // (Alg. 2: dS = P o (dP - delta)).  Kept opaque so that it stays resident instead of being
   // rebuilt per block.
-  f32x16 neg_delta;
+  f32x4 neg_delta[2];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) neg_delta[i] = -dl;
-  asm volatile("" : "+v"(neg_delta));
-  f32x16 dQt[D / 32];
+  for (int n = 0; n < 2; ++n) {
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+    for (int i = 0; i < 4; ++i) neg_delta[n][i] = -dl[n];
+    asm volatile("" : "+v"(neg_delta[n]));
+  }
+  f32x4 dQt[NDT][2];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) dQt[db][i] = 0.f;
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int n = 0; n < 2; ++n) dQt[dt][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int kend = !CAUSAL ? NK : !RAGGED ? q0 + QUERIES : max(0, min(NK, q0 + QUERIES + shift));
   const int ntiles = RAGGED || KT > QUERIES ? (kend + KT - 1) / KT : kend / KT;
@@ -627,8 +660,11 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
   loader.template load_rows<RAGGED>(ldsV, Vh, 0, NK);
   wait_vmem();
 #pragma unroll
-  for (int kc = 0; kc < D / 16; ++kc) { settle(qf[kc]); settle(dof[kc]); }
-  settle(l2);
+  for (int n = 0; n < 2; ++n) {
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) { settle(qf[n][kc]); settle(dof[n][kc]); }
+    settle(l2[n]);
+  }
   __syncthreads();
 
   // One key tile; BUF (which LDS buffer holds it) is a compile-time constant so that every LDS
@@ -636,7 +672,7 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
   auto tile_step = [&](auto buf_c, int j) {
     constexpr int buf = decltype(buf_c)::value;
     constexpr int tK = buf * TILE_BYTES;            // byte offsets of this tile's K and V in smem
-    constexpr int tV = (2 + buf) * TILE_BYTES;
+    constexpr int tV = (2 + buf) * TILE_BYTES - FAR;          // (from fo_v)
     // The next tile lands in the other buffer while this one is being processed; its transfer
     // instructions are issued one per step of the first block's score products rather than in one
     // burst behind the barrier.  After the last tile the current one is fetched once more into the
@@ -665,55 +701,82 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
       constexpr bool MASKED = decltype(masked_c)::value;
       constexpr int NB = decltype(nb_c)::value;
       constexpr int kb = decltype(kb_c)::value;
-      constexpr int NS = D / 16, SLOTS = (DELTA_MODE ? 2 : 3) * NB * NS;
-      constexpr int AHEAD = kReadAheadDq<D>, RING = AHEAD + 1;
+      constexpr bool HOLD = NB == 1 && !DELTA_MODE && (D <= 64 || (G > 1 && D <= 128));
+      constexpr int NS = D / 16, READS = (DELTA_MODE ? 2 : 3) * NB * NS, SLOTS = READS + (HOLD ? NS : 0);
+      constexpr int AHEAD = NB == 1 && D <= 64 ? 4 : kReadAheadDq<D>;
+      // PAIRED: see the dK/dV kernel.  us: B4 H12 N1024 d64 causal 19.0 -> 18.5, B1 H4 N2048 d96 causal 19.4 -> 19.0; without wave
+      // groups, and at D >= 128, even or slower (B1 H8 N2048 d256 causal 47.0 -> 48.2).
+      constexpr bool PAIRED = G > 1 && D <= 96;
+      static_assert(!PAIRED || AHEAD % 2 == 0, "pairs");
+      constexpr int RING = AHEAD + (PAIRED ? 2 : 1);
+      // phases of S^T and dP^T: slot u is the 16-key tile u % 2 against 32-column block u / 2; of dQ: column tile u
       auto fragment = [&](int i) -> bf16x8 {
         const int phase = i / NS, u = i % NS;
-        if (phase < 2 * NB) return lds_row8<D>(phase % 2 ? tV : tK, fo, 32 * (kb + phase / 2), u);
-        return lds_col8<D>(tK, fo, 32 * (kb + phase - 2 * NB) + 16 * (u / NDB), u % NDB);
+        if (phase < 2 * NB) return lds_row16<D>(phase % 2 ? tV : tK, phase % 2 ? fo_v : fo, 32 * (kb + phase / 2) + 16 * (u % 2), u / 2);
+        return lds_col16<D>(tK, fo, 32 * (kb + phase - 2 * NB), u);
       };
-      bf16x8 ring[RING], dsf[NB][2];
-      f32x16 s[NB], dp[NB];
-      int lim[NB];                       // MASKED: last visible entry, c = 8 (i / 4) + i % 4
+      // HOLD: with one block to a tile, dS has no other block's products to lie under.  The dQ products of the first 16 queries
+      // go first, with dS of the other 16 under them, and the fragments stay for those.  us: B1 H8 N2048 d64 causal 17.3 -> 16.9,
+      // d128 27.0 -> 26.5, B1 H1 N5120 d64 32.0 -> 30.9.
+      bf16x8 ring[RING], held[HOLD ? NS : 1], dsf[NB][2];
+      auto read = [&](int i) {
+        if (HOLD && i >= 2 * NS) held[HOLD ? i - 2 * NS : 0] = fragment(i);
+        else ring[i % RING] = fragment(i);
+      };
+      f32x4 s[NB][2][2], dp[NB][2][2];   // [block][16-key tile][16-query tile]
+      int lim[NB][2];                    // MASKED: last visible entry 16m + i of a 16-query tile
 #pragma unroll
-      for (int i = 0; i < AHEAD; ++i) ring[i] = fragment(i);
+      for (int i = 0; i < AHEAD; ++i) read(PAIRED ? i ^ 1 : i);
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[b][i] = 0.f;
         const int kb0 = kt0 + 32 * (kb + b + grp);
         // (formed here and not ahead of the tile loop, which costs registers: at D = 64, causal, with bounds checks six were
         // spilled.  us: 800 heads N65 15.0 -> 13.2, 400 heads N200 19.8 -> 17.6, B8 H12 N1000 29.6 -> 28.0)
         int ln = lane;
         if (MASKED) asm volatile("" : "+v"(ln));
-        lim[b] = CAUSAL ? __builtin_amdgcn_readfirstlane(qw) + (ln & 31) + shift - kb0 - 4 * (ln >> 5) : 0x7fffffff;
-        if (RAGGED) lim[b] = min(lim[b], NK - 1 - kb0 - 4 * (ln >> 5));
-      }
-      // P of entries i0 .. i1 - 1 of block b: keys in this lane's future and keys past the sequence end get
-      // S = -inf, P = exp(-inf) = 0
-      auto form_p = [&](int b, int i0, int i1) {
 #pragma unroll
-        for (int i = i0; i < i1; ++i) {
-          if (MASKED && 8 * (i >> 2) + (i & 3) > lim[b]) s[b][i] = -INFINITY;
-          s[b][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][i], c2, -l2));
+        for (int n = 0; n < 2; ++n) {
+          s[b][0][n] = s[b][1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+          lim[b][n] = CAUSAL ? __builtin_amdgcn_readfirstlane(qw) + 16 * n + (ln & 15) + shift - kb0 - 4 * (ln >> 4) : 0x7fffffff;
+          if (RAGGED) lim[b][n] = min(lim[b][n], NK - 1 - kb0 - 4 * (ln >> 4));
+        }
+      }
+      // P of entries e0 .. e1 - 1 of a lane's 16 of block b (entry e: row (e & 3) of 16-key tile m = e / 8, 16-query tile
+      // n = (e >> 2) & 1): keys in this lane's future and keys past the sequence end get S = -inf, P = exp(-inf) = 0
+      auto form_p = [&](int b, int e0, int e1) {
+#pragma unroll
+        for (int e = e0; e < e1; ++e) {
+          const int m = e >> 3, n = (e >> 2) & 1, i = e & 3;
+          if (MASKED && 16 * m + i > lim[b][n]) s[b][m][n][i] = -INFINITY;
+          s[b][m][n][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][m][n][i], c2, -l2[n]));
         }
       };
-      // dS of the same; dp already holds dP - delta
-      auto form_ds = [&](int b, int i0, int i1) {
+      // dS of the same (of one block, query tile by query tile: see HOLD); dp already holds dP - delta
+      auto form_ds = [&](int b, int e0, int e1) {
 #pragma unroll
-        for (int i = i0; i < i1; ++i) {
-          if (DELTA_MODE) pdp = __builtin_fmaf(s[b][i], dp[b][i], pdp);
-          else dsf[b][i >> 3][i & 7] = (bf16_t)(s[b][i] * dp[b][i]);
+        for (int e = e0; e < e1; ++e) {
+          const int m = NB > 1 ? e >> 3 : (e >> 2) & 1, n = NB > 1 ? (e >> 2) & 1 : e >> 3, i = e & 3;
+          if (DELTA_MODE) pdp[n] = __builtin_fmaf(s[b][m][n][i], dp[b][m][n][i], pdp[n]);
+          else dsf[b][n][4 * m + i] = (bf16_t)(s[b][m][n][i] * dp[b][m][n][i]);
         }
       };
       static_for<SLOTS>([&](auto slot) {
         constexpr int sl = decltype(slot)::value, phase = sl / NS, u = sl % NS;
-        if (sl + AHEAD < SLOTS) ring[(sl + AHEAD) % RING] = fragment(sl + AHEAD);
-        if (NB == 1 && sl == 2 * NS) form_ds(0, 0, 8);
-        const bf16x8 a = ring[sl % RING];
-        if constexpr (phase >= 2 * NB) dQt[u % NDB] = mfma32(a, dsf[phase - 2 * NB][u / NDB], dQt[u % NDB]);   // step 13
-        else if constexpr (phase % 2 == 0) s[phase / 2] = mfma32(a, qf[u], s[phase / 2]);
-        else dp[phase / 2] = mfma32(a, dof[u], u == 0 ? neg_delta : dp[phase / 2]);
+        if (PAIRED) {
+          if (sl % 2 == 0 && sl + AHEAD < READS) {
+            read(sl + AHEAD + 1);
+            read(sl + AHEAD);
+          }
+        } else if (sl + AHEAD < READS) read(sl + AHEAD);
+        const bf16x8 a = HOLD && phase >= 2 ? held[HOLD ? u : 0] : ring[sl % RING];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          if (HOLD && phase >= 2 && n != phase - 2) continue;
+          if (NB == 1 && sl == 2 * NS) form_ds(0, 8 * n, 8 * n + 8);
+          if constexpr (phase >= 2 * NB) dQt[u][n] = mfma16(a, dsf[HOLD ? 0 : phase - 2 * NB][n], dQt[u][n]);   // step 13
+          else if constexpr (phase % 2 == 0) s[phase / 2][u % 2][n] = mfma16(a, qf[n][u / 2], s[phase / 2][u % 2][n]);
+          else dp[phase / 2][u % 2][n] = mfma16(a, dof[n][u / 2], u < 2 ? neg_delta[n] : dp[phase / 2][u % 2][n]);
+        }
         // (One transfer instruction per two slots at D = 256: four waves that issue one each per slot ask for 128 bytes a clock
         // where the load path takes 64, and stall.  us, one slot -> two: B1 H8 N2048 d256 full 59.0 -> 57.4, causal 51.0 -> 47.5.
         // d <= 128: even, and 0.1 to 0.2 us slower where a problem is one tile long, as the transfer ends later.)
@@ -722,16 +785,15 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
         if (kb == 0 && sl % EVERY == 0) issue_part(sl / EVERY);
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-          const int e = sl - 2 * NS * b - NS - 1;            // P of block b lies under the slots after its first dP^T
+          // P of block b lies under its dP^T, dS under the phase after; both are whole when the phase ends
+          const int e = sl - 2 * NS * b - NS, f = e - NS;
           if (e >= 0 && e < NS) form_p(b, 16 * e / NS, 16 * (e + 1) / NS);
-          const int f = e - NS;                              // dS of block b
+          if (HOLD && phase == 2) form_ds(0, 8 + 8 * u / NS, 8 + 8 * (u + 1) / NS);
           if (NB > 1 && !DELTA_MODE && f >= 0 && f < NS) form_ds(b, 16 * f / NS, 16 * (f + 1) / NS);
         }
-        if (NB == 1 && sl == 2 * NS) form_ds(0, 8, 16);
         __builtin_amdgcn_sched_barrier(0);
       });
       if (DELTA_MODE) {
-        form_p(NB - 1, 16 * (NS - 1) / NS, 16);              // (the slot these would lie under is a dQ product)
 #pragma unroll
         for (int b = 0; b < NB; ++b) form_ds(b, 0, 16);
       }
@@ -767,8 +829,11 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
   }
   if (DELTA_MODE) {
     static_assert(!DELTA_MODE || G == 1, "the recomputed delta has no wave groups");
-    const float dsum = sum_with_partner32(pdp);      // the partner lane holds the other keys of every block
-    if (h == 0 && (!RAGGED || qw + r < N)) delta_out[(size_t)bh * N + qw + r] = dsum;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const float dsum = sum_over_groups(pdp[n]);    // the other three lanes of a row hold the other keys of every block
+      if (g == 0 && (!RAGGED || qw + 16 * n + r < N)) delta_out[(size_t)bh * N + qw + 16 * n + r] = dsum;
+    }
     continue;
   }
   if constexpr (G > 1) {
@@ -780,45 +845,34 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_ker
 #pragma unroll
     for (int half = G / 2; half >= 1; half >>= 1) {
       if (grp < 2 * half) {
-        char* area = smem + ((grp % half) * QW + wave) * (NDB * 4096);
+        char* area = smem + ((grp % half) * QW + wave) * (NDT * 2048);
         if (grp >= half) {
 #pragma unroll
-          for (int i = 0; i < 4 * NDB; ++i) {
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = dQt[i >> 2][4 * (i & 3) + e];
-            *reinterpret_cast<f32x4*>(area + (i * 64 + ln) * 16) = v;
-          }
+          for (int i = 0; i < 2 * NDT; ++i) *reinterpret_cast<f32x4*>(area + (i * 64 + ln) * 16) = dQt[i >> 1][i & 1];
         }
       }
       __syncthreads();
       if (grp < half) {
-        const char* area = smem + (grp * QW + wave) * (NDB * 4096);
+        const char* area = smem + (grp * QW + wave) * (NDT * 2048);
 #pragma unroll
-        for (int i = 0; i < 4 * NDB; ++i) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(area + (i * 64 + ln) * 16);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dQt[i >> 2][4 * (i & 3) + e] += v[e];
-        }
+        for (int i = 0; i < 2 * NDT; ++i) dQt[i >> 1][i & 1] += *reinterpret_cast<const f32x4*>(area + (i * 64 + ln) * 16);
       }
       __syncthreads();
     }
     if (grp != 0) continue;
   }
-  if constexpr (kCanStage<D / 32>) {
-    // the tile buffers are free now (every wave is past the last tile's barrier): they serve as
-    // the staging areas of store_rows_staged; the barrier at the top of the part loop keeps the
-    // next block's tile transfers from overwriting an area a slower wave is still reading
-    auto piece = [&](int db, int g) {
-      bf16x4 o4;
+  auto piece = [&](int dt, int n) {
+    bf16x4 o4;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(dQt[db][4 * g + e] * alpha);
-      return o4;
-    };
-    store_rows_staged<D / 32>(smem, piece, dQ + head_off + (size_t)qw * sn, sn, RAGGED ? N - qw : 32, tid);
-  } else if (!RAGGED || qw + r < N) {
-    store_acc_T<D / 32>(dQ + head_off + (size_t)(qw + r) * sn, dQt, alpha, h);
-  }
+    for (int e = 0; e < 4; ++e) o4[e] = (bf16_t)(dQt[dt][n][e] * alpha);
+    return o4;
+  };
+  bf16_t* dst = dQ + head_off + (size_t)qw * sn;
+  // the tile buffers are free now (every wave is past the last tile's barrier): they serve as
+  // the staging areas of store_rows16_staged; the barrier at the top of the part loop keeps the
+  // next block's tile transfers from overwriting an area a slower wave is still reading
+  if constexpr (kCanStage<D / 32>) store_rows16_staged<NDT>(smem, piece, dst, sn, RAGGED ? N - qw : 32, tid);
+  else store_rows16<NDT>(piece, dst, sn, RAGGED ? N - qw : 32, lane);
   }   // part
 }
 

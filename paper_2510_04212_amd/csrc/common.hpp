@@ -42,7 +42,7 @@ DEVI f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // ---- LDS tile layout.  A tile of R rows x D bf16 columns is cut into macro blocks of 16 rows x 32
 // columns (64 bytes per row), 1024 bytes each: block (rg, cg) lies at (rg * D/32 + cg) * 1024.  Inside a
 // block row r (0..15) takes 64 consecutive bytes and its four 16-byte chunks are permuted by
-// chunk ^ (r >> 2), so that (a) 16 lanes reading the same chunk of the block's 16 rows and (b) a
+// chunk ^ slot_mask(r >> 2), so that (a) 16 lanes reading the same chunk of the block's 16 rows and (b) a
 // transposing read of 8 rows x 64 bytes (512 consecutive bytes) both spread over all 64 LDS banks.
 // Everything a fragment's address depends on besides the lane - row block, column block, tile
 // buffer - adds a multiple of 1024 bytes: two per-lane registers serve every row-major fragment and
@@ -50,6 +50,11 @@ DEVI f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // D columns and the chunk index XOR-ed over the full row, D/16 + D/16 such registers were
 // needed, and rows had to be a power of two wide: D = 96 moved and held a third more.)
 template <int D> constexpr int kColBlocks = D / 32;
+// Slot of chunk c of row r: c ^ slot_mask(r >> 2), slot_mask = 0, 2, 3, 1.  A ds_read_b128 serves lanes 0-3, 12-15, 20-23 and 24-27
+// together (then the other half of the 32, then the upper 32), a transposing read 32 lanes: with this order neither finds two
+// lanes on a bank, whichever of the fragments below they read (clocks per 1 KB, measured: 4.0 and 5.1; with 0, 1, 2, 3
+// 16-row fragments take 8.0 and 8.0, with 0, 2, 1, 3 8.0 and 5.1).
+__host__ DEVI constexpr int slot_mask(int x) { return (((x ^ (x >> 1)) & 1) << 1) | (x >> 1); }
 // D rounded up to a power of two: the lanes (and the summation tree) of one row in rowsum(dO o O)
 template <int D> constexpr int kPow2D = (D == 96) ? 128 : D;
 // bytes from one 16-row block of a tile to the next
@@ -72,14 +77,14 @@ template <int D> DEVI void init_frag_offsets(FragOffsets<D>& fo, int lane, int s
   const int r = lane & 31, h = lane >> 5, i = lane & 15;
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    fo.row[p] = shared_base + (r >> 4) * kRowBlockBytes<D> + (r & 15) * 64 + (((2 * p + h) ^ ((r & 15) >> 2)) << 4);
+    fo.row[p] = shared_base + (r >> 4) * kRowBlockBytes<D> + (r & 15) * 64 + (((2 * p + h) ^ slot_mask((r & 15) >> 2)) << 4);
     asm volatile("" : "+v"(fo.row[p]));
   }
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     const int row = 4 * h + 8 * half + (i >> 2);              // row >> 2 = h + 2 half
     const int chunk = ((lane & 16) >> 3) + ((i & 3) >> 1);
-    fo.col[half] = shared_base + row * 64 + ((chunk ^ (h + 2 * half)) << 4) + ((i & 1) << 3);
+    fo.col[half] = shared_base + row * 64 + ((chunk ^ slot_mask(h + 2 * half)) << 4) + ((i & 1) << 3);
     asm volatile("" : "+v"(fo.col[half]));
   }
 }
@@ -105,6 +110,56 @@ template <int D> DEVI bf16x8 lds_col8(int tile, const FragOffsets<D>& fo, int ro
   return u.v;
 }
 
+// ---- the same tiles read for v_mfma_f32_16x16x32_bf16, D[16x16] += A[16x32] * B[32x16] (lane l, r = l & 15, g = l >> 4):
+//   A operand: lane holds A[r][8g .. 8g+7];  B operand: B[8g .. 8g+7][r];  D / C: register i holds D[4g + i][r].
+// Two C tiles one above the other (rows 0..15 and 16..31) are a B operand whose k-slot (g, j) is row
+// 16*(j/4) + 4g + (j%4).  A fragment (1 KB) is one macro block of a tile and feeds as many multiplications as one of the
+// 32x32x16 instruction: two of these, against 16 columns each.
+//
+// Why this instruction: on large grids the kernels run at the board's power limit (the same instructions on zeros take 0.7 of
+// the time), and per multiplication it costs less energy, as an accumulator is read and written half as often.  Loops of
+// matrix instructions on N(0,1) data: 32x32x16 1760 TFLOP/s, 16x16x32 2150; with a fragment from LDS each 1500 and 1640; with 2.5
+// vector instructions per fragment as well 1370 and 1450; on zeros (no limit) 2450 both.  The two backward kernels, us, 32x32x16
+// -> this, with equal error against 64 bits:  dK/dV, causal  B4 H32 N4096 d128 922 -> 890, B1 H16 N16384 d128 1765 -> 1645,
+// B2 H32/8 N2048 d128 139 -> 133, B8 H12 N1024 d64 33.7 -> 32.8, B2 H16 N2048 d96 56.3 -> 53.1, B2 H8 N2048 d256 104.5 -> 95.7,
+// full  B4 H16 N4096 d128 865 -> 807, B16 H16 N2048 d64 473 -> 444;  dQ, causal  B4 H32 N4096 d128 681 -> 651, B4 H16 N1999 d128
+// 98.3 -> 93.6, B4 H32 N4096 d64 371 -> 364, full  B2 H8 N2000 d256 89.8 -> 83.2.  Grids that leave most SIMDs with one wave or none are
+// not at the limit, and one instruction more per fragment shows there: dK/dV B1 H8 N2048 d64 20.2 -> 20.2, B1 H1 N5120 d64
+// 44.3 -> 45.4, d128 66.6 -> 69.6; dQ 17.0 -> 16.8, 29.8 -> 30.5, 47.8 -> 47.5.
+DEVI f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+struct TileFrags {
+  int row;                  // natural read of row (lane & 15), columns 32kc + 8g .. +7
+  int col[2];               // transposing read of rows 4g .. 4g+3 of a 16-row block, column 16dt + (lane & 15), by parity of dt
+};
+DEVI void init_tile_frags(TileFrags& fo, int lane, int shared_base) {
+  const int r = lane & 15, g = lane >> 4;
+  fo.row = shared_base + r * 64 + ((g ^ slot_mask(r >> 2)) << 4);
+  asm volatile("" : "+v"(fo.row));                   // (absolute addresses, opaque: see init_frag_offsets)
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    fo.col[c] = shared_base + (4 * g + (r >> 2)) * 64 + (((2 * c + ((r & 3) >> 1)) ^ slot_mask(g)) << 4) + ((r & 1) << 3);
+    asm volatile("" : "+v"(fo.col[c]));
+  }
+}
+// A or B operand whose contraction index runs along the tile's columns: rows row_base + (lane & 15) (row_base a multiple of
+// 16), columns 32kc + 8g .. +7.
+template <int D> DEVI bf16x8 lds_row16(int tile, const TileFrags& fo, int row_base, int kc) {
+  typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+  return *reinterpret_cast<lds_bf16x8*>((unsigned long)(unsigned)(fo.row + tile + (row_base >> 4) * kRowBlockBytes<D> + kc * 1024));
+}
+// Operand whose contraction index runs along the tile's ROWS: k-slot (g, j) is row row_base + 16*(j/4) + 4g + (j%4) (row_base a
+// multiple of 16), the lane's own index column 16dt + (lane & 15).
+template <int D> DEVI bf16x8 lds_col16(int tile, const TileFrags& fo, int row_base, int dt) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  union { struct { s16x4 lo, hi; } p; bf16x8 v; } u;
+  const int at = fo.col[dt & 1] + tile + (row_base >> 4) * kRowBlockBytes<D> + (dt >> 1) * 1024;
+  u.p.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(unsigned long)(unsigned)at);
+  u.p.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(unsigned long)(unsigned)(at + kRowBlockBytes<D>));
+  return u.v;
+}
+
 // Value held by the lane 32 positions away (lane ^ 32).
 DEVI float partner32(float x) {
   unsigned u = __float_as_uint(x);
@@ -122,6 +177,14 @@ DEVI float sum_with_partner32(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+
+// Sum over the two lanes 16 positions apart (lane ^ 16), and over the four that share lane & 15.
+DEVI float sum_with_partner16(float x) {
+  unsigned u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+DEVI float sum_over_groups(float x) { return sum_with_partner16(sum_with_partner32(x)); }
 
 // Addressing of the bf16 tensors Q, K, V, O, dO, dQ, dK, dV: element (b, h, n, k) lives at
 // b*sb + h*sh + n*sn + k (the last dimension is contiguous).  [B,H,N,d] contiguous is
@@ -154,7 +217,7 @@ DEVI size_t head_base_kv(const Layout& lay, int bh) {
 // (global_load_lds_dwordx4: no registers are involved; completion is tracked by vmcnt).
 // One wave-instruction moves 64 x 16 bytes to LDS base + 16*lane, i.e. one macro block of the layout
 // above: 16 rows x 64 bytes.  The chunk permutation is applied on the GLOBAL side: the lane that
-// lands in slot s of row r fetches chunk s ^ (r >> 2) of that row.  NW waves share a tile; a wave stays inside its own 16-row block(s), so that one per-lane offset (per row block) serves
+// lands in slot s of row r fetches chunk s ^ slot_mask(r >> 2) of that row.  NW waves share a tile; a wave stays inside its own 16-row block(s), so that one per-lane offset (per row block) serves
 // all its instructions and only the scalar base moves along the columns.
 // The caller must execute wait_vmem() and a barrier before any wave reads the tile.
 //
@@ -193,7 +256,7 @@ template <int D, int R = 64, int NW = 4> struct TileLoader {
     col0 = wave % WPR;
     sn = row_stride;
     row = rg * 16 + (lane >> 2);
-    chunk = ((lane & 3) ^ (lane >> 4)) * 16;
+    chunk = ((lane & 3) ^ slot_mask(lane >> 4)) * 16;
     lds_wave = (unsigned)(rg * kRowBlockBytes<D> + col0 * 1024);
   }
   // A tile transfer prepared once (operands) and issued one instruction at a time, so that a caller
@@ -338,6 +401,41 @@ DEVI void store_rows_staged(char* stage_wave0, PieceF&& piece, bf16_t* dst_row0,
     const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * PITCH + c * 16);
     if (row < rows_valid) *reinterpret_cast<u32x4*>(dst_row0 + (size_t)row * sn + c * 8) = v;
   }
+}
+
+// The same for a tile in accumulator layout of 16x16 tiles: lane (r, g) has, for its rows 16n + r (n = 0, 1), the columns
+// 16dt + 4g .. +3; NDT = width / 16.  piece(dt, n) returns the four bf16 values of that position.
+template <int NDT, class PieceF>
+DEVI void store_rows16_staged(char* stage_wave0, PieceF&& piece, bf16_t* dst_row0, int sn, int rows_valid, int tid) {
+  static_assert(NDT % 2 == 0 && kCanStage<NDT / 2>, "row width");
+  constexpr int PITCH = kStagePitch<NDT / 2>, CPR = 2 * NDT, RPI = 64 / CPR;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
+  char* stage = stage_wave0 + (tid >> 6) * (32 * PITCH);
+  const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+      *reinterpret_cast<bf16x4*>(stage + (16 * n + r) * PITCH + (16 * dt + 4 * g) * 2) = piece(dt, n);
+#pragma unroll
+  for (int it = 0; it < 32 / RPI; ++it) {
+    const int row = it * RPI + lane / CPR, c = lane % CPR;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * PITCH + c * 16);
+    if (row < rows_valid) *reinterpret_cast<u32x4*>(dst_row0 + (size_t)row * sn + c * 8) = v;
+  }
+}
+// ... and without staging (widths that do not divide 64 lanes): 8 bytes per lane and store.
+template <int NDT, class PieceF>
+DEVI void store_rows16(PieceF&& piece, bf16_t* dst_row0, int sn, int rows_valid, int lane) {
+  const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+    if (16 * n + r < rows_valid) {
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt)
+        *reinterpret_cast<bf16x4*>(dst_row0 + (size_t)(16 * n + r) * sn + 16 * dt + 4 * g) = piece(dt, n);
+    }
 }
 
 // Issue-order hints for one scheduling region (basic block) that holds N matrix instructions,

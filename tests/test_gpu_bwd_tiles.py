@@ -1,0 +1,47 @@
+"""GPU test of the two backward kernels where their tiles end: sequence lengths around 16, 32, 64 and 128 rows, at every head
+size, on grids that take one, two and four wave groups and the kernels with three waves per SIMD.
+
+The kernels get LSE and delta rounded from float64, so every entry has a bound of its own: P and dS are rounded to bf16 once
+as operands and the result once when stored (each 2^-8 relative), and the float32 sums behind S, dP and the exponent add
+less than 2^-12 of the absolute values that enter them.  A row or column in the wrong place is off by its own size.
+"""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+U, SLACK = 2.0 ** -8, 2.0 ** -12
+
+
+@pytest.mark.parametrize("N", [1, 15, 17, 33, 64, 65, 127, 128, 256, 320])
+@pytest.mark.parametrize("B,H,d,causal", [
+    (1, 1, 32, True), (1, 2, 64, False), (1, 2, 64, True), (2, 1, 96, True), (1, 2, 128, True), (1, 1, 128, False), (1, 1, 256, True),
+    (9, 15, 64, True), (9, 15, 128, True), (9, 15, 256, False), (24, 32, 64, True), (24, 32, 64, False), (24, 32, 32, True), (8, 32, 128, True)])
+def test_every_entry_at_the_edges_of_the_tiles(lib, B, H, N, d, causal):
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    q, k, v, do = (torch.randn((B, H, N, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(4))
+    alpha = 1.0 / math.sqrt(d)
+    Q, K, V, G = (t.double() for t in (q, k, v, do))
+    S = alpha * (Q @ K.transpose(-1, -2))
+    if causal:
+        S = S.masked_fill(torch.ones((N, N), dtype=torch.bool, device=DEV).triu(1), -math.inf)
+    L = torch.logsumexp(S, -1)
+    P = torch.exp(S - L[..., None])
+    dP = G @ V.transpose(-1, -2)
+    delta = (P * dP).sum(-1)
+    dS = P * (dP - delta[..., None])
+    inner = P * (G.abs() @ V.abs().transpose(-1, -2) + delta.abs()[..., None])       # what the float32 sums of dS run over
+    t = lambda x: x.transpose(-1, -2)
+    want = {"dQ": alpha * (dS @ K), "dK": alpha * (t(dS) @ Q), "dV": t(P) @ G}
+    part = {"dQ": alpha * ((U * dS.abs() + SLACK * inner) @ K.abs()), "dK": alpha * (t(U * dS.abs() + SLACK * inner) @ Q.abs()),
+            "dV": (U + SLACK) * (t(P) @ G.abs())}
+    dK, dV = lib.attn_bwd_dkdv(q, k, v, do, L.float(), delta.float(), causal, alpha)
+    dQ = lib.attn_bwd_dq(q, k, v, do, L.float(), delta.float(), causal, alpha)
+    torch.cuda.synchronize()
+    for name, got in (("dQ", dQ), ("dK", dK), ("dV", dV)):
+        bound = part[name] + U * (want[name].abs() + part[name]) + 1e-30
+        over = (got.double() - want[name]).abs() / bound
+        assert not got.isnan().any() and float(over.max()) <= 1.0, (name, float(over.max()))
