@@ -525,7 +525,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
     const int seen = qu + 31 < 0 ? 0 : min(ntiles, (qu + 31) / kBc + 1);
     f32x16 s0[2], s1[2];                               // raw scores of even and odd tiles
     float corr = 1.f, mneg = 0.f;                      // of the tile whose P-bar is next
-    auto masked_tile = [&](int j) { return j * kBc + kBc - 1 > qu || (RAGGED && (j + 1) * kBc > NK); };
+    const int plain = min(seen, min(RAGGED ? NK / kBc : ntiles, max(0, qu + 1) / kBc));     // tiles that need no mask: the first ones
     auto limit = [&](int j) {                          // last visible c = 32 kb + 8 (i / 4) + i % 4 of tile j
       const int lim = q + shift - j * kBc - 4 * h;
       return RAGGED ? min(lim, NK - 1 - j * kBc - 4 * h) : lim;
@@ -652,7 +652,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
         s0[sl / NS] = mfma32(lds_row8<D>(0, fo, 32 * (sl / NS), sl % NS), qf[sl % NS], s0[sl / NS]);
       });
       sched_reads_ahead_of_mfma<2 * NS, 1, 4>();
-      if (masked_tile(0)) {
+      if (plain == 0) {
         const int lim = limit(0);
         mask(s0[0], 0, 0, 16, lim);
         mask(s0[1], 1, 0, 16, lim);
@@ -664,23 +664,29 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
     __syncthreads();                                   // K of the first tile is read out everywhere: its buffer is free
 #pragma unroll
     for (int p = 0; p < 2; ++p) { fo.row[p] += TILE_BYTES; fo.col[p] += 2 * TILE_BYTES; }
+    // Counted loops, two steps a turn where no mask is needed.  (With the test for the mask between the two steps the loop had
+    // another way out, on which the compiler kept the accumulator a second time: 20 moves a tile.  us, that -> now, same bits:
+    // B4 H32 N4096 d128 597 -> 589, B1 H16 N16384 1053 -> 1040, B4 H16 N1999 85.4 -> 83.2, B1 H8 N2048 36.4 -> 35.5, B2 H16
+    // N2048 d96 39.7 -> 39.2, d256 B1 H8 65.4 -> 64.7.)
     int j = 0;
-    auto plain_next = [&]() { return j + 1 < seen && !masked_tile(j + 1); };
-    while (plain_next()) {
-      step(std::true_type{}, std::false_type{}, j++, s0, s1);
-      if (!plain_next()) {
-        s0[0] = s1[0];
-        s0[1] = s1[1];
-        break;
-      }
-      step(std::true_type{}, std::false_type{}, j++, s1, s0);
+    for (; j + 2 < plain; j += 2) {
+      step(std::true_type{}, std::false_type{}, j, s0, s1);
+      step(std::true_type{}, std::false_type{}, j + 1, s1, s0);
     }
-    while (j + 1 < seen) {
-      step(std::true_type{}, std::true_type{}, j++, s0, s1);
+    if (j + 1 < plain) {
+      step(std::true_type{}, std::false_type{}, j++, s0, s1);
       s0[0] = s1[0];
       s0[1] = s1[1];
     }
-    if (j < seen) step(std::false_type{}, std::false_type{}, j++, s0, s1);
+    for (; j + 1 < seen; ++j) {
+      step(std::true_type{}, std::true_type{}, j, s0, s1);
+      s0[0] = s1[0];
+      s0[1] = s1[1];
+    }
+    if (j < seen) {
+      step(std::false_type{}, std::false_type{}, j, s0, s1);
+      ++j;
+    }
     for (; j < ntiles; ++j) {                          // the other waves' tiles: this wave's share of the transfers
       prepare(j);
 #pragma unroll
