@@ -52,15 +52,16 @@ DEVI long pack_e4m3(const float (&v)[8]) {
   return (long)(((unsigned long long)(unsigned)w1 << 32) | (unsigned)w0);
 }
 
-// VARIANT: 0 = Alg. 1, 1 = Alg. 3 (repeated maximum looked for inside each key tile, as the
-// algorithm is written), and the two passes of the tile-size-independent form of Alg. 3
-// (the rule of Sec. 4 applied to the whole row, as in the paper's untiled analysis):
-//   kRowStats   scores only; per row the two largest scores over ALL keys decide the normaliser
-//               (a repeated maximum <=> the second largest is within eps of the largest), which
-//               is written to LSE[] as a scratch value;
-//   kFixedNorm  the forward with that fixed per-row normaliser read back from LSE[] (no running
-//               maximum, no accumulator rescale), LSE[] then receives m + log l as usual.
-constexpr int kRowStats = 3, kFixedNorm = 2;
+// VARIANT: 0 = Alg. 1, 1 = Alg. 3 (repeated maximum looked for inside each key tile, as the algorithm is written), and
+//   kWholeRow   the tile-size-independent form of Alg. 3 (the rule of Sec. 4 applied to the whole row, as in the paper's
+//               untiled analysis), in two passes over the key tiles: scores only, whose two largest per row over ALL keys
+//               decide the normaliser (a repeated maximum <=> the second largest is within eps of the largest), and the
+//               forward with that fixed normaliser (no running maximum, no accumulator rescale).
+// Both passes are one launch: a work-group's rows need nothing of another's.  As two launches, with the normaliser through memory,
+// Q was fetched twice, the grid drained twice and short problems waited for the second launch.  Same bits; us, two launches -> one:
+// B1 H1 N128 d64 causal 10.1 -> 7.3, B64 H8 N200 22.6 -> 17.7, B4 H12 N1024 26.4 -> 23.3, B32 H12 N512 full 54.5 -> 47.2,
+// B1 H16 N768 d128 causal 27.2 -> 24.9, B4 H32 N4096 789 -> 778, B12 H16 N1408 d256 452 -> 407, B4 H16 N1999 d32 44.8 -> 41.6.
+constexpr int kWholeRow = 2;
 
 // Which kernels run as a software pipeline over tiles.  It needs 32 more registers for the next tile's scores: at
 // D <= 64 that costs a wave per SIMD.  Measured, tile after tile -> pipeline (us): causal B2 H16 N2048 d96 46.7 -> 43.7,
@@ -268,7 +269,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
   const int tile0 = SPLIT ? share_begin(all_tiles, split, shares) : 0;
   const int ntiles = SPLIT ? share_begin(all_tiles, split + 1, shares) : all_tiles;
   loader.template load_rows<RAGGED>(smem, Kh, tile0 * kBc, NK);
-  if (VARIANT != kRowStats) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, tile0 * kBc, NK);
+  if (VARIANT != kWholeRow) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, tile0 * kBc, NK);
   if (PIPE) loader.template load_rows<RAGGED>(smem + TILE_BYTES, Kh, (ntiles > 1 ? 1 : 0) * kBc, NK);
 
   // Q_i^T fragments: lane (r,h) holds Q[qw + r][16kc + 8h .. +7] for every kc.
@@ -284,10 +285,8 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
     for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
 
   int ones_cnt = 0, fired_cnt = 0;   // EXTRAS only
-  float top1 = -INFINITY, top2 = -INFINITY;   // kRowStats: the lane's two largest raw scores so far
-  // running normaliser, natural-log units of the alpha-scaled scores (kFixedNorm: the row's
-  // normaliser chosen by the kRowStats pass)
-  float m = (VARIANT == kFixedNorm) ? LSE[(size_t)bh * N + qc] : -INFINITY;
+  float top1 = -INFINITY, top2 = -INFINITY;   // kWholeRow: the lane's two largest raw scores so far
+  float m = -INFINITY;      // running normaliser, natural-log units of the alpha-scaled scores (kWholeRow: the row's, once chosen)
   float* share = SPLIT ? part + ((size_t)bh * ((N + 31) / 32) + qw / 32) * splits * kPartFloats<D> : nullptr;   // the rows' first share
   if (SPLIT && qw < N) m = largest_norm<D>(share, split, r);
   float lsum = 0.f;         // running row sum (the same in both lanes of a row; without MFMA_SUMS this lane's share of it)
@@ -295,13 +294,15 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
   wait_vmem();
 #pragma unroll
   for (int kc = 0; kc < D / 16; ++kc) settle(qf[kc]);
-  if (VARIANT == kFixedNorm || SPLIT) settle(m);
+  if (SPLIT) settle(m);
   __syncthreads();
 
   FragOffsets<D> fo = fo0;
   // One key tile; BUF (which LDS buffer holds it) is a compile-time constant so that every LDS
   // address is a precomputed per-lane offset plus an immediate.
-  auto tile_step = [&](auto buf_c, int j) {
+  // STATS (kWholeRow's first pass): scores and their maxima only; V is fetched under the last tile, for the second pass's first.
+  auto tile_step = [&](auto stats_c, auto buf_c, int j) {
+    constexpr bool STATS = decltype(stats_c)::value;
     constexpr int BUF = decltype(buf_c)::value;
     constexpr int tK = BUF * TILE_BYTES;          // byte offsets of this tile's K and V in smem
     constexpr int tV = (2 + BUF) * TILE_BYTES;
@@ -311,13 +312,14 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
     // them) but one per step of the score product.  After the last tile the current one is
     // fetched once more into the idle buffer: harmless, and the instruction stream stays free of
     // branches.
-    const int jn = (j + 1 < ntiles) ? j + 1 : j;
+    const bool last = j + 1 >= ntiles;
+    const int jn = !last ? j + 1 : STATS ? 0 : j;
     constexpr int NLD = TileLoader<D>::NI;
     const auto pendK = loader.template prepare<RAGGED>(smem + (BUF ^ 1) * TILE_BYTES, Kh, jn * kBc, NK);
     const auto pendV = loader.template prepare<RAGGED>(smem + (2 + (BUF ^ 1)) * TILE_BYTES, Vh, jn * kBc, NK);
     auto issue_part = [&](int i) {
       if (i < NLD) loader.issue(pendK, i);
-      else if (i < 2 * NLD && VARIANT != kRowStats) loader.issue(pendV, i - NLD);
+      else if (i < 2 * NLD && (!STATS || last)) loader.issue(pendV, i - NLD);
     };
     bool issued = false;
     const int k0 = j * kBc;
@@ -377,7 +379,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
           for (int i = 0; i < 16; ++i)
             if (32 * kb + 8 * (i >> 2) + (i & 3) > lim) s[kb][i] = -INFINITY;
       }
-      if (VARIANT == kRowStats) {
+      if constexpr (STATS) {
         TileMax<true> tm;                // merged into the two largest this lane has seen
         tm.all(s);
         const float t1 = tm.largest(), t2 = tm.second();
@@ -386,7 +388,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
       } else {
         float corr = 1.f;    // factor the accumulated output and row sum are multiplied by
         float mneg;          // -m log2(e) of the normaliser used for this tile
-        if (VARIANT == kFixedNorm) {
+        if (VARIANT == kWholeRow) {
           mneg = (RAGGED && m == -INFINITY) ? 0.f : -m * kLog2e;   // a query that sees no key at all
         } else {
           float r_m;         // tile row maximum of the alpha-scaled scores
@@ -431,7 +433,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
               }
             }
           lsum = lsum * corr + (MFMA_SUMS ? sum_with_partner32(psum8) : psum8);
-          if (VARIANT != kFixedNorm && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+          if (VARIANT != kWholeRow && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -467,7 +469,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
         if (!MFMA_SUMS) lsum = lsum * corr + psum[0];
         // ---- O^T <- diag(corr) O^T + V_j^T P-bar^T (Alg. 1 step 8); in the first tile the
         // accumulator is still zero (corr = exp(-inf) = 0 there), nothing to rescale
-        if (VARIANT != kFixedNorm && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+        if (VARIANT != kWholeRow && j > tile0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
           for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -694,9 +696,29 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
       finish();
     }
   } else {
-    for (int j = tile0; j < ntiles; j += 2) {
-      tile_step(std::integral_constant<int, 0>{}, j);
-      if (j + 1 < ntiles) tile_step(std::integral_constant<int, 1>{}, j + 1);
+    constexpr std::integral_constant<int, 0> buf0;
+    constexpr std::integral_constant<int, 1> buf1;
+    int begin = tile0;
+    if constexpr (VARIANT == kWholeRow) {
+      for (int j = 0; j < ntiles; j += 2) {
+        tile_step(std::true_type{}, buf0, j);
+        if (j + 1 < ntiles) tile_step(std::true_type{}, buf1, j + 1);
+      }
+      // merge the two lanes of a row, then the rule of Sec. 4 on the whole row
+      const float o1 = partner32(top1), o2 = partner32(top2);
+      const float M1 = fmaxf(top1, o1);
+      const float M2 = fmaxf(fminf(top1, o1), fmaxf(top2, o2));
+      const float r_m = M1 * alpha;
+      bool repeated = (r_m - M2 * alpha) <= eps;            // r_s > 1
+      if (EXTRAS && ex.guard != 0) repeated = repeated && guard_allows(r_m, beta);
+      m = (repeated && r_m > 0.f) ? beta * r_m : r_m;
+      m = (repeated && r_m < 0.f) ? 0.f : m;
+      if (EXTRAS && ex.fired != nullptr && h == 0 && q < N) ex.fired[(size_t)bh * N + q] = (m != r_m) ? 1 : 0;
+      begin = -(ntiles & 1);           // the first tile again: in the buffer after the last one's
+    }
+    for (int j = begin; j < ntiles; j += 2) {
+      if (VARIANT != kWholeRow || j >= 0) tile_step(std::false_type{}, buf0, j);
+      if (j + 1 < ntiles) tile_step(std::false_type{}, buf1, j + 1);
     }
   }
 
@@ -717,22 +739,6 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
       if (h == 0) p[32 * D + 32 + r] = l_share;
     }
     return;
-  }
-  if (VARIANT == kRowStats) {
-    // merge the two lanes of a row, then the rule of Sec. 4 on the whole row
-    const float o1 = partner32(top1), o2 = partner32(top2);
-    const float M1 = fmaxf(top1, o1);
-    const float M2 = fmaxf(fminf(top1, o1), fmaxf(top2, o2));
-    const float r_m = M1 * alpha;
-    bool repeated = (r_m - M2 * alpha) <= eps;            // r_s > 1
-    if (EXTRAS && ex.guard != 0) repeated = repeated && guard_allows(r_m, beta);
-    float m_row = (repeated && r_m > 0.f) ? beta * r_m : r_m;
-    m_row = (repeated && r_m < 0.f) ? 0.f : m_row;
-    if (h == 0 && (!RAGGED || q < N)) {
-      LSE[(size_t)bh * N + q] = m_row;
-      if (EXTRAS && ex.fired != nullptr) ex.fired[(size_t)bh * N + q] = (m_row != r_m) ? 1 : 0;
-    }
-    continue;
   }
   // ---- epilogue (Alg. 1 steps 10-13).  Rounding points of Sec. 3.3.2: the unnormalised
   // output is rounded to bf16 first, then divided by l, then rounded again.
@@ -785,7 +791,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
   if (h == 0) {
     LSE[(size_t)bh * N + q] = m + __logf(l);
     if (EXTRAS && ex.ones != nullptr) ex.ones[(size_t)bh * N + q] = ones_row;
-    if (EXTRAS && VARIANT != kFixedNorm && ex.fired != nullptr) ex.fired[(size_t)bh * N + q] = fired_cnt;
+    if (EXTRAS && VARIANT != kWholeRow && ex.fired != nullptr) ex.fired[(size_t)bh * N + q] = fired_cnt;
   }
   }
   }   // part
@@ -1049,8 +1055,7 @@ hipError_t attn_fwd_split_dispatch(const void* Q, const void* K, const void* V, 
 template <int D, bool CAUSAL, int VARIANT>
 static hipError_t launch_fwd_form(bool ragged, int extras, const void* Q, const void* K, const void* V, void* O, float* LSE,
                                   int BH, int N, float alpha, float beta, float eps, FwdExtras ex, Layout lay, hipStream_t st) {
-  if (extras == 2 && VARIANT != kRowStats)     // (the statistics pass has no such product)
-    return launch_fwd<D, CAUSAL, VARIANT, true, VARIANT == kRowStats ? 1 : 2>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st);
+  if (extras == 2) return launch_fwd<D, CAUSAL, VARIANT, true, 2>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st);
   if (extras) return launch_fwd<D, CAUSAL, VARIANT, true, 1>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st);
   // (whole-row rule: the bounds-checking kernels serve every N)
   return ragged ? launch_fwd<D, CAUSAL, VARIANT, true, 0>(Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st)
@@ -1069,11 +1074,8 @@ hipError_t attn_fwd_dispatch(const void* Q, const void* K, const void* V, void* 
   if (d == DD && (causal != 0) == CC) {                                                          \
     if (variant == 0) return launch_fwd_form<DD, CC, 0>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
     if (variant == 1) return launch_fwd_form<DD, CC, 1>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
-    if (variant != 2) return hipErrorInvalidValue;                                               \
-    /* whole-row detection: statistics pass, then the fixed-normaliser pass */                   \
-    hipError_t e = launch_fwd_form<DD, CC, kRowStats>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
-    if (e != hipSuccess) return e;                                                               \
-    return launch_fwd_form<DD, CC, kFixedNorm>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
+    if (variant == kWholeRow) return launch_fwd_form<DD, CC, kWholeRow>(ragged, extras, Q, K, V, O, LSE, BH, N, alpha, beta, eps, ex, lay, st); \
+    return hipErrorInvalidValue;                                                                 \
   }
   CASE(32, false) CASE(32, true) CASE(64, false) CASE(64, true) CASE(128, false) CASE(128, true)
   CASE(256, false) CASE(256, true) CASE(96, false) CASE(96, true)
