@@ -560,8 +560,8 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
       pendV = loader.template prepare<RAGGED>(smem + (2 + (par ^ 1)) * TILE_BYTES, Vh, min(j + 1, ntiles - 1) * kBc, NK);
     };
     auto issue_part = [&](int i) {
-      if (i < NLD) loader.issue(pendK, i);
-      else if (i < 2 * NLD) loader.issue(pendV, i - NLD);
+      if (i < NLD) loader.template issue<true>(pendK, i);
+      else if (i < 2 * NLD) loader.template issue<true>(pendV, i - NLD);
     };
     auto finish = [&]() {
       wait_vmem();
@@ -583,8 +583,12 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
 #pragma unroll
       for (int i = 0; i < AHEAD; ++i) ring[(FIRST + i) % RING] = fragment(FIRST + i);
       __builtin_amdgcn_sched_barrier(0);               // (the reads' latency lies under what follows)
-      // O^T <- diag(corr) O^T (Alg. 1 step 8); in the first tile the accumulator is still zero
-      if (j > 0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
+      // O^T <- diag(corr) O^T (Alg. 1 step 8); in the first tile the accumulator is still zero.
+      // SPREAD: always, and under the scores.  D = 256 has 128 products to rescale and the least vector work per matrix
+      // instruction, which hides them: us, B2 H8 N2048 66.1 -> 62.4, B1 H8 64.0 -> 60.7.  At D = 128 B1 H8 N2048 35.0 -> 34.8, but
+      // B1 H16 N16384 1005 -> 1043, where two tiles of three need none.
+      constexpr bool SPREAD = NEXT && D == 256;
+      if (!SPREAD && j > 0 && __builtin_amdgcn_ballot_w64(corr != 1.f) != 0) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -614,8 +618,16 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
         const bf16x8 a = ring[sl % RING];
         if constexpr (sl < 2 * NS) sn[sl / NS] = mfma32(a, qf[sl % NS], sn[sl / NS]);
         else acc[(sl - 2 * NS) % NDB] = mfma32(a, pf[(sl - 2 * NS) / NDB], acc[(sl - 2 * NS) % NDB]);
-        issue_part(sl - FIRST);
+        // (one transfer instruction per two slots: us, one slot -> two, and the immediate offset, B4 H32 N4096 d128 583 -> 575, B1 H8
+        // N2048 35.5 -> 34.7, B2 H16 N2048 d96 37.4 -> 37.1, B2 H8 N2048 d256 66.2 -> 64.4)
+        if (!NEXT) issue_part(sl - FIRST);
+        else if (sl % 2 == 0) issue_part(sl / 2);
         if constexpr (sl < 2 * NS) {
+          if constexpr (SPREAD) {
+            constexpr int each = 16 * NDB / (2 * NS);
+#pragma unroll
+            for (int i = each * sl; i < each * (sl + 1); ++i) acc[i / 16][i % 16] *= corr;
+          }
           form_p(16 * sl / NS, 16 * (sl + 1) / NS);
         } else {
           constexpr int u = sl - 2 * NS;
