@@ -98,15 +98,21 @@ __host__ DEVI int split_shares(int tiles, int splits) {
 }
 // floats of a share of 32 rows in the workspace: the 32 x D accumulator, 32 normalisers, 32 row sums
 template <int D> constexpr int kPartFloats = 32 * D + 64;
-// largest normaliser the first n shares of a 32-row block ask for in row r (eight loads in flight)
+// largest normaliser the first n shares of a 32-row block ask for in row r (16 loads in flight)
 template <int D> DEVI float largest_norm(const float* rows, int n, int r) {
   float m = -INFINITY;
-  for (int s0 = 0; s0 < n; s0 += 8) {
-    float v[8];
+  for (int s0 = 0; s0 < n; s0 += 16) {
+    float v[16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = rows[(size_t)min(s0 + i, n - 1) * kPartFloats<D> + 32 * D + r];
+    for (int i = 0; i < 16; ++i) {
+      if (i % 8 == 0 && s0 + i >= n) break;
+      v[i] = rows[(size_t)min(s0 + i, n - 1) * kPartFloats<D> + 32 * D + r];
+    }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) m = fmaxf(m, v[i]);
+    for (int i = 0; i < 16; ++i) {
+      if (i % 8 == 0 && s0 + i >= n) break;
+      m = fmaxf(m, v[i]);
+    }
   }
   return m;
 }
