@@ -1,13 +1,13 @@
 // Flash-attention backward for gfx950 (Alg. 2 of arXiv 2510.04212), as two kernels so that no
 // gradient needs a cross-work-group reduction (no atomics, deterministic):
 //
-//   attn_bwd_dkdv_kernel  one work-group per (batch, head, 128-key block; 64 on small grids) -- under the causal mask
+//   attn_bwd_dkdv_kernel  one work-group per (batch, head, 128-key block; 64 or 32 on small grids) -- under the causal mask
 //                         per pair of mirrored blocks, one after the other, unless the grid is
 //                         small (then one block each, in a balanced order); K_j / V_j fragments
 //                         stay in registers (V_j in LDS at D = 128), query tiles (Q_i, dO_i, L_i,
 //                         delta_i; 64 rows, 32 at D = 128) stream through LDS.  Per tile:  S = Q_i K_j^T,  P = exp(S - L),  dP = dO_i V_j^T,
 //                         dS = P o (dP - delta),  dV_j^T += dO_i^T P,  dK_j^T += Q_i^T dS.
-//   attn_bwd_dq_kernel    one work-group per (batch, head, 128-query block; 64 on small grids); Q_i / dO_i fragments,
+//   attn_bwd_dq_kernel    one work-group per (batch, head, 128-query block; 64 or 32 on small grids); Q_i / dO_i fragments,
 //                         L_i and delta_i stay in registers, key tiles (K_j, V_j; 64 rows) stream
 //                         through LDS.  Per tile:  S^T = K_j Q_i^T,  dP^T = V_j dO_i^T,
 //                         dS^T = P^T o (dP^T - delta),  dQ_i^T += K_j^T dS^T.
@@ -27,8 +27,8 @@
 
 namespace {
 
-constexpr int kKeysPerWG = 128;   // dK/dV kernel: keys per work-group (32 per wave); 64 with four wave groups
-constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per wave); 64 with wave groups
+constexpr int kKeysPerWG = 128;   // dK/dV kernel: keys per work-group (32 per wave); 64 or 32 with four or eight wave groups
+constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per wave); 64 or 32 with wave groups
 
 // GROUPED: grouped-query attention (lay.group > 1): the work-group serves several query heads.
 // Kept out of the ordinary kernel so that its tile loop has a fixed head and no bookkeeping.
@@ -52,15 +52,15 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 // the groups share the work-group's keys and take alternate 32-query blocks, each into accumulators
 // of its own, which are added through LDS at the end.  G = 4 splits further: 64 keys (two waves) per
 // group, so that a grid has twice the work-groups of half the length; a query tile is then read
-// from L2 for half as many keys.
-template <int G> constexpr int kKeyWaves = G == 4 ? 2 : 4;               // waves per group, 32 keys each
-template <int D, int G> constexpr int kQTile = D == 128 || G == 4 ? 32 * G : 64;   // query rows per streamed tile
+// from L2 for half as many keys.  G = 8 (D <= 64, LDS) once more: 32 keys, one wave per group.
+template <int G> constexpr int kKeyWaves = G == 8 ? 1 : G == 4 ? 2 : 4;               // waves per group, 32 keys each
+template <int D, int G> constexpr int kQTile = D == 128 || G >= 4 ? 32 * G : 64;   // query rows per streamed tile
 // LDS fragments are read this many matrix instructions before their use.
 // (At D = 128 what the registers allow: the fragments of V_j come from LDS too.  Four wave groups at small D: us, four ahead ->
 // two, B1 H4 N4096 d64 causal 41.1 -> 40.1, B1 H1 38.5 -> 37.7, B1 H2 N8192 d32 causal 54.0 -> 53.4, full 51.2 -> 50.5, B1 H8
 // N2000 d32 16.7 -> 16.4; d64 full even to 2 % slower: not there.)
 template <int D, int G, bool CAUSAL, bool DENSE> constexpr int kReadAhead =
-    DENSE || (G == 4 && (D == 32 || (D == 64 && CAUSAL))) ? 2 : D == 256 ? 6 : D == 128 ? 2 : 4;
+    DENSE || (G >= 4 && (D == 32 || (D == 64 && CAUSAL))) ? 2 : D == 256 ? 6 : D == 128 ? 2 : 4;
 // dK / dV rows leave through a per-wave LDS staging area (store_rows_staged) where the row width
 // allows it; it overlays the tile buffers where it would otherwise cost a resident work-group, and
 // is left out at D = 256 (no room).
@@ -457,7 +457,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     if constexpr (G > 1) {
       // The groups add their partial sums: group 1 hands over its dV, group 0 its dK, each through an
       // area of its own per wave (16 bytes per lane, lanes consecutive), and group 0 finishes dV,
-      // group 1 dK; before that groups 2 and 3 hand both over to groups 0 and 1.  Every wave is past
+      // group 1 dK; before that the upper half of the groups hands both over to the lower half, until two are left.  Every wave is past
       // the last tile's barrier: the whole array is free.
       // (the lane index passes through an empty asm: addresses formed from the kernel's own copy would
       // be hoisted above the tile loop and held in registers through it)
@@ -472,11 +472,12 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
 #pragma unroll
         for (int i = 0; i < 2 * NDT; ++i) acc[i >> 1][i & 1] += *reinterpret_cast<const f32x4*>(take + (i * 64 + ln) * 16);
       };
-      if constexpr (G == 4) {
-        char* area = smem + ((grp & 1) * KW + wave) * 2 * AREA;
-        if (grp >= 2) { put(dVt, area); put(dKt, area + AREA); }
+#pragma unroll
+      for (int half = G / 2; half >= 2; half >>= 1) {
+        char* area = smem + ((grp % half) * KW + wave) * 2 * AREA;
+        if (grp >= half && grp < 2 * half) { put(dVt, area); put(dKt, area + AREA); }
         __syncthreads();
-        if (grp < 2) { add(dVt, area); add(dKt, area + AREA); }
+        if (grp < half) { add(dVt, area); add(dKt, area + AREA); }
         __syncthreads();
       }
       char* give = smem + (grp * KW + wave) * AREA;
@@ -522,8 +523,8 @@ constexpr int kGivenDelta = 0, kRecomputeDelta = 1, kOwnDelta = 2;
 // work-group's queries, take alternate 32-key blocks of every tile and add their sums through LDS at the
 // end.  kQueryWaves waves of 32 queries per group; a tile has as many 32-key blocks as there are groups
 // (two with one group).
-template <int G> constexpr int kQueryWaves = G == 1 ? 4 : 2;
-template <int G> constexpr int kKeysPerTile = G == 4 ? 128 : 64;
+template <int G> constexpr int kQueryWaves = G == 1 ? 4 : G == 8 ? 1 : 2;
+template <int G> constexpr int kKeysPerTile = G >= 4 ? 32 * G : 64;
 template <int D, int G> constexpr int kSmemDq = 4 * kKeysPerTile<G> * D * 2;
 // Small head sizes need more waves per SIMD next to one another (four at D = 32, three at D = 64) than a long
 // read-ahead: dQ at D = 64 with two waves and fragments read four slots ahead -> three and two (us): B8 H12 N1024
@@ -933,6 +934,18 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
     const int NK = RAGGED ? lay.Nk : N;      // (the rule looks at the keys only: a chunk of queries gets the sums of the square problem)
     const long long blocks = (long long)(BH / lay.group) * ((NK + kKeysPerWG - 1) / kKeysPerWG);
     if (NK >= 512) {
+      // Eight groups on 32 keys as long as every work-group gets a CU of its own (head counts the order table does not take run
+      // as pairs of blocks: half as many).  us, four -> eight, d64 causal: B1 H1 N5120 45.1 -> 29.8, B1 H4 N2048 24.4 -> 19.3, B1 H8
+      // N1024 12.9 -> 10.5, B1 H4 N4096 (pairs) 38.5 -> 28.4, N5000 46.3 -> 33.5, B1 H1 N512 13.5 -> 13.1, full B1 H1 N8192
+      // 58.0 -> 40.5, d32 B1 H4 N2000 17.6 -> 14.1; beyond the limits: B2 H8 N1024 13.3 -> 15.9, B8 H8 N512 15.0 -> 26.1.
+      if constexpr (D <= 64) {
+        const int heads = BH / lay.group;
+        if (blocks <= (CAUSAL && heads % 8 != 0 ? 2 : 1) * kNumCUs / 4 && lay.sn <= kRowStrideLimit / 2) {
+          if (RAGGED || N % kQTile<D, 8> != 0)
+            return launch_dkdv_g<D, CAUSAL, true, GROUPED, 8>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+          return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 8>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+        }
+      }
       if (blocks <= (CAUSAL ? kNumCUs : kNumCUs / 2))
         return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 4>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
       if constexpr (!CAUSAL || D >= 96)
@@ -994,6 +1007,15 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
   // B2 H8 N1500 61 -> 54; not taken: B1 H15 N2048 82 -> 98, B1 H24 N1280 57 -> 60, B4 H8 N1024 51 -> 53, B2 H12 N2048 91 -> 116.
   if constexpr (MODE != kRecomputeDelta) {
     const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
+    // Eight groups on 32 queries, as in launch_dkdv, up to one work-group per CU.  us, four -> eight, d64 causal: B1 H1 N5120 30.4 ->
+    // 20.1, B1 H4 N2048 16.3 -> 12.6, B1 H8 N1024 11.5 -> 9.9, B1 H1 N5000 31.3 -> 20.6, B1 H1 N512 8.6 -> 7.9, full B1 H1 N8192
+    // 44.7 -> 33.7, d32 B1 H4 N2000 11.7 -> 8.8; beyond the limit: B1 H12 N1024 11.4 -> 15.6, B1 H1 N16384 91 -> 132.
+    if constexpr (D <= 64)
+      if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= kNumCUs / 4 && lay.sn <= kRowStrideLimit / 2) {
+        if (RAGGED || N % kKeysPerTile<8> != 0)
+          return launch_dq_g<D, CAUSAL, true, MODE, 8>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+        return launch_dq_g<D, CAUSAL, RAGGED, MODE, 8>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+      }
     const bool balanced = CAUSAL && (D <= 128 || (BH % 8 == 0 && lay.Nk == N && N >= 1500));
     if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (balanced ? kNumCUs : kNumCUs / 2)) {
       // (two groups without a mask: here the aligned kernel is the faster one and spills nothing, unlike that of one group; us,

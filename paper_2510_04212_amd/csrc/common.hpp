@@ -237,7 +237,8 @@ DEVI const bf16_t* wave_uniform(const bf16_t* p) {
 }
 
 template <int D, int R = 64, int NW = 4> struct TileLoader {
-  static_assert((R == 32 || R == 64 || R == 128) && R <= kMaxTileRows, "rows per tile");
+  // (256 rows: a launcher that takes them sees to it that the row stride is at most half of kRowStrideLimit)
+  static_assert(R == 32 || R == 64 || R == 128 || R == 2 * kMaxTileRows, "rows per tile");
   static constexpr int NRB = R / 16;             // 16-row blocks
   static constexpr int NCB = kColBlocks<D>;
   static constexpr int WPR = NW > NRB ? NW / NRB : 1;    // waves that share a 16-row block ...

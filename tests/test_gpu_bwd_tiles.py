@@ -1,5 +1,5 @@
 """GPU test of the two backward kernels where their tiles end: sequence lengths around 16, 32, 64 and 128 rows, at every head
-size, on grids that take one, two and four wave groups and the kernels with three waves per SIMD.
+size, on grids that take one, two, four and eight wave groups and the kernels with three waves per SIMD.
 
 The kernels get LSE and delta rounded from float64, so every entry has a bound of its own: P and dS are rounded to bf16 once
 as operands and the result once when stored (each 2^-8 relative), and the float32 sums behind S, dP and the exponent add
@@ -16,11 +16,7 @@ DEV = "cuda:0"
 U, SLACK = 2.0 ** -8, 2.0 ** -12
 
 
-@pytest.mark.parametrize("N", [1, 15, 17, 33, 64, 65, 127, 128, 256, 320])
-@pytest.mark.parametrize("B,H,d,causal", [
-    (1, 1, 32, True), (1, 2, 64, False), (1, 2, 64, True), (2, 1, 96, True), (1, 2, 128, True), (1, 1, 128, False), (1, 1, 256, True),
-    (9, 15, 64, True), (9, 15, 128, True), (9, 15, 256, False), (24, 32, 64, True), (24, 32, 64, False), (24, 32, 32, True), (8, 32, 128, True)])
-def test_every_entry_at_the_edges_of_the_tiles(lib, B, H, N, d, causal):
+def _check(lib, B, H, N, d, causal):
     g = torch.Generator(device=DEV).manual_seed(N + d)
     q, k, v, do = (torch.randn((B, H, N, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(4))
     alpha = 1.0 / math.sqrt(d)
@@ -45,3 +41,19 @@ def test_every_entry_at_the_edges_of_the_tiles(lib, B, H, N, d, causal):
         bound = part[name] + U * (want[name].abs() + part[name]) + 1e-30
         over = (got.double() - want[name]).abs() / bound
         assert not got.isnan().any() and float(over.max()) <= 1.0, (name, float(over.max()))
+
+
+@pytest.mark.parametrize("B,H,N,d,causal", [
+    # eight wave groups: tiles of 256 rows, grids up to and just beyond a work-group per CU
+    (1, 1, 512, 64, True), (1, 1, 513, 64, True), (1, 3, 640, 32, True), (2, 4, 1000, 64, False), (1, 8, 1024, 64, True),
+    (2, 8, 1024, 64, True), (1, 12, 1024, 64, True), (1, 13, 1025, 32, False)])
+def test_every_entry_on_small_grids_of_longer_sequences(lib, B, H, N, d, causal):
+    _check(lib, B, H, N, d, causal)
+
+
+@pytest.mark.parametrize("N", [1, 15, 17, 33, 64, 65, 127, 128, 256, 320])
+@pytest.mark.parametrize("B,H,d,causal", [
+    (1, 1, 32, True), (1, 2, 64, False), (1, 2, 64, True), (2, 1, 96, True), (1, 2, 128, True), (1, 1, 128, False), (1, 1, 256, True),
+    (9, 15, 64, True), (9, 15, 128, True), (9, 15, 256, False), (24, 32, 64, True), (24, 32, 64, False), (24, 32, 32, True), (8, 32, 128, True)])
+def test_every_entry_at_the_edges_of_the_tiles(lib, N, B, H, d, causal):
+    _check(lib, B, H, N, d, causal)
