@@ -48,13 +48,16 @@ template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // the same) the single code path for masked and unmasked blocks alone took 140 -> 109.
 template <int D> constexpr bool kVInLds = D == 128;
 template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
-// G: wave groups.  G = 2 (512 threads) is for grids that give a CU only one work-group:
+// FORM: how many wave groups a work-group has.  2 (512 threads) is for grids that give a CU only one work-group:
 // the groups share the work-group's keys and take alternate 32-query blocks, each into accumulators
-// of its own, which are added through LDS at the end.  G = 4 splits further: 64 keys (two waves) per
+// of its own, which are added through LDS at the end.  4 splits further: 64 keys (two waves) per
 // group, so that a grid has twice the work-groups of half the length; a query tile is then read
-// from L2 for half as many keys.  G = 8 (D <= 64, LDS) once more: 32 keys, one wave per group.
-template <int G> constexpr int kKeyWaves = G == 8 ? 1 : G == 4 ? 2 : 4;               // waves per group, 32 keys each
-template <int D, int G> constexpr int kQTile = D == 128 || G >= 4 ? 32 * G : 64;   // query rows per streamed tile
+// from L2 for half as many keys.  The smallest grids take 32 keys, one wave per group: 8 groups at D <= 64, and four, kNarrow,
+// where the tiles of eight would not fit the LDS.
+constexpr int kNarrow = 5;
+template <int FORM> constexpr int kGroups = FORM == kNarrow ? 4 : FORM;
+template <int FORM> constexpr int kKeyWaves = FORM == 8 || FORM == kNarrow ? 1 : FORM == 4 ? 2 : 4;               // waves per group, 32 keys each
+template <int D, int FORM> constexpr int kQTile = D == 128 || FORM >= 4 ? 32 * kGroups<FORM> : 64;   // query rows per streamed tile
 // LDS fragments are read this many matrix instructions before their use.
 // (At D = 128 what the registers allow: the fragments of V_j come from LDS too.  Four wave groups at small D: us, four ahead ->
 // two, B1 H4 N4096 d64 causal 41.1 -> 40.1, B1 H1 38.5 -> 37.7, B1 H2 N8192 d32 causal 54.0 -> 53.4, full 51.2 -> 50.5, B1 H8
@@ -80,17 +83,17 @@ template <int D, int G> constexpr int kSmemDkDv =
 // DENSE (D <= 64): three waves on every SIMD at the price of a shorter read-ahead, for grids that have the work-groups
 // (launch_dkdv).
 template <int D, bool DENSE> constexpr int kDkDvWaves = DENSE ? 3 : kWavesPerSimd<D>;
-template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int G, bool DENSE>
-__global__ __launch_bounds__(64 * kKeyWaves<G> * G)
+template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int FORM, bool DENSE>
+__global__ __launch_bounds__(64 * kKeyWaves<FORM> * kGroups<FORM>)
 __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>))) void attn_bwd_dkdv_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int N, float alpha, Layout lay, int pairs,
     BlockOrder ord) {
-  constexpr int QT = kQTile<D, G>;
+  constexpr int G = kGroups<FORM>, QT = kQTile<D, FORM>;
   constexpr int TILE_BYTES = QT * D * 2, GT = TILE_BYTES / G;
-  constexpr int T0 = kVBytes<D, G>;                    // the tile buffers follow V_j: per wave group Q [2][GT], dO [2][GT]
-  constexpr int KW = kKeyWaves<G>, KEYS = 32 * KW;
+  constexpr int T0 = kVBytes<D, FORM>;                    // the tile buffers follow V_j: per wave group Q [2][GT], dO [2][GT]
+  constexpr int KW = kKeyWaves<FORM>, KEYS = 32 * KW;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   char* ldsQ = smem + T0;
   char* ldsdO = ldsQ + 2 * GT;
@@ -182,7 +185,9 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
     if (part == 1 && (!pairs || kt == kt_first)) break;   // no partner: one block per work-group, or the middle one of an odd number
     if (kStageOverTiles<D, G> && part > 0) __syncthreads();   // the first block's staging is done with the tile buffers
     const int k0 = kt * KEYS;
-    const int kw = k0 + 32 * (FORM_LATE ? (late(tid) >> 6) % KW : wave);
+    int kw = k0 + 32 * (FORM_LATE ? (late(tid) >> 6) % KW : wave);
+    // (in a vector register: behind a branch that the compiler knows to be uniform it spills hundreds)
+    if (KW == 1) asm volatile("" : "+v"(kw));
 
     if constexpr (kVInLds<D>) {
       TileLoader<D, KEYS, KW * G> v_loader;
@@ -298,7 +303,7 @@ __attribute__((amdgpu_waves_per_eu(kDkDvWaves<D, DENSE>, kDkDvWaves<D, DENSE>)))
         constexpr bool MASKED = decltype(masked_c)::value;
         constexpr int NB = decltype(nb_c)::value, qb = decltype(qb_c)::value;
         constexpr int NS = D / 16, NU = NDT, PB = 2 * NS + 2 * NU;        // slots of S or dP, of dV or dK, of a block
-        constexpr int AHEAD = MASKED && DENSE ? 1 : kReadAhead<D, G, CAUSAL, DENSE>;       // (1: two would spill)
+        constexpr int AHEAD = MASKED && DENSE ? 1 : kReadAhead<D, FORM, CAUSAL, DENSE>;       // (1: two would spill)
         // PAIRED: reads are issued two at a time, the later one first, so that one wait serves two slots.  Pays for the one wave
         // of a SIMD at D = 256: B2 H8 N2048 causal 97.2 -> 95.3 us, B1 H8 90.7 -> 89.2; at smaller D even, or to 2 % slower.
         constexpr bool PAIRED = D == 256;
@@ -523,8 +528,8 @@ constexpr int kGivenDelta = 0, kRecomputeDelta = 1, kOwnDelta = 2;
 // work-group's queries, take alternate 32-key blocks of every tile and add their sums through LDS at the
 // end.  kQueryWaves waves of 32 queries per group; a tile has as many 32-key blocks as there are groups
 // (two with one group).
-template <int G> constexpr int kQueryWaves = G == 1 ? 4 : G == 8 ? 1 : 2;
-template <int G> constexpr int kKeysPerTile = G >= 4 ? 32 * G : 64;
+template <int FORM> constexpr int kQueryWaves = FORM == 1 ? 4 : FORM == 8 || FORM == kNarrow ? 1 : 2;
+template <int FORM> constexpr int kKeysPerTile = FORM >= 4 ? 32 * kGroups<FORM> : 64;
 template <int D, int G> constexpr int kSmemDq = 4 * kKeysPerTile<G> * D * 2;
 // Small head sizes need more waves per SIMD next to one another (four at D = 32, three at D = 64) than a long
 // read-ahead: dQ at D = 64 with two waves and fragments read four slots ahead -> three and two (us): B8 H12 N1024
@@ -532,15 +537,15 @@ template <int D, int G> constexpr int kSmemDq = 4 * kKeysPerTile<G> * D * 2;
 template <int D, int G> constexpr int kDqWavesPerSimd = D == 32 && G == 1 ? 4 : D == 64 && G == 1 ? 3 : kWavesPerSimd<D>;
 template <int D> constexpr int kReadAheadDq = D <= 64 ? 2 : D == 256 ? 6 : 4;
 
-template <int D, bool CAUSAL, bool RAGGED, int MODE, int G>
-__global__ __launch_bounds__(64 * kQueryWaves<G> * G)
-__attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, G>))) void attn_bwd_dq_kernel(
+template <int D, bool CAUSAL, bool RAGGED, int MODE, int FORM>
+__global__ __launch_bounds__(64 * kQueryWaves<FORM> * kGroups<FORM>)
+__attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, FORM>))) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ delta,
     const bf16_t* __restrict__ O, bf16_t* __restrict__ dQ, float* __restrict__ delta_out, int N,
     float alpha, Layout lay, int pairs, BlockOrder ord) {
   constexpr bool DELTA_MODE = MODE == kRecomputeDelta;
-  constexpr int QW = kQueryWaves<G>, QUERIES = 32 * QW, KT = kKeysPerTile<G>;
+  constexpr int G = kGroups<FORM>, QW = kQueryWaves<FORM>, QUERIES = 32 * QW, KT = kKeysPerTile<FORM>;
   constexpr int TILE_BYTES = KT * D * 2;
   constexpr int NKC = D / 32, NDT = D / 16;            // 32-column blocks of a row, 16-column tiles of dQ
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -895,7 +900,7 @@ static hipError_t launch_dkdv_g(const void* Q, const void* K, const void* V, con
   auto k = attn_bwd_dkdv_kernel<D, CAUSAL, RAGGED, GROUPED, G, DENSE>;
   hipError_t e;
   if ((e = set_smem(k, smem, set)) != hipSuccess) return e;
-  constexpr int KEYS = 32 * kKeyWaves<G>, THREADS = 64 * kKeyWaves<G> * G;
+  constexpr int KEYS = 32 * kKeyWaves<G>, THREADS = 64 * kKeyWaves<G> * kGroups<G>;
   const int nkt = ((RAGGED ? lay.Nk : N) + KEYS - 1) / KEYS;
   // Under the causal mask: one block per work-group in a balanced order when that grid is at most
   // one and a half rounds of work-groups (measured: beyond that, mirrored pairs of blocks are as
@@ -934,17 +939,18 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
     const int NK = RAGGED ? lay.Nk : N;      // (the rule looks at the keys only: a chunk of queries gets the sums of the square problem)
     const long long blocks = (long long)(BH / lay.group) * ((NK + kKeysPerWG - 1) / kKeysPerWG);
     if (NK >= 512) {
-      // Eight groups on 32 keys as long as every work-group gets a CU of its own (head counts the order table does not take run
-      // as pairs of blocks: half as many).  us, four -> eight, d64 causal: B1 H1 N5120 45.1 -> 29.8, B1 H4 N2048 24.4 -> 19.3, B1 H8
-      // N1024 12.9 -> 10.5, B1 H4 N4096 (pairs) 38.5 -> 28.4, N5000 46.3 -> 33.5, B1 H1 N512 13.5 -> 13.1, full B1 H1 N8192
-      // 58.0 -> 40.5, d32 B1 H4 N2000 17.6 -> 14.1; beyond the limits: B2 H8 N1024 13.3 -> 15.9, B8 H8 N512 15.0 -> 26.1.
-      if constexpr (D <= 64) {
-        const int heads = BH / lay.group;
-        if (blocks <= (CAUSAL && heads % 8 != 0 ? 2 : 1) * kNumCUs / 4 && lay.sn <= kRowStrideLimit / 2) {
-          if (RAGGED || N % kQTile<D, 8> != 0)
-            return launch_dkdv_g<D, CAUSAL, true, GROUPED, 8>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-          return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 8>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-        }
+      // Blocks of 32 keys as long as every work-group gets a CU of its own (head counts the order table does not take run as
+      // pairs of blocks: half as many).  us, four groups on 64 keys -> this; d64, eight groups: causal B1 H1 N5120 45.1 -> 29.4, B1 H4
+      // N2048 24.4 -> 19.0, B1 H8 N1024 12.9 -> 10.3, B1 H4 N5000 46.3 -> 31.4, B1 H1 N512 13.5 -> 13.1, full B1 H1 N8192 58.0 ->
+      // 40.5, d32 B1 H4 N2000 17.6 -> 14.1; d128, four: causal B1 H1 N5120 69.3 -> 48.5, B1 H4 N4096 (pairs) 59.5 -> 44.0, B1 H8 N1024
+      // 20.0 -> 15.1, B1 H32/8 N1000 55.5 -> 43.2, full B1 H4 N2048 27.9 -> 20.6, d96 B1 H4 N2000 29.6 -> 22.1; beyond the limits
+      // (eight groups) B2 H8 N1024 d64 13.3 -> 15.9, B8 H8 N512 15.0 -> 26.1.
+      const int heads = BH / lay.group;
+      if (blocks <= (CAUSAL && heads % 8 != 0 ? 2 : 1) * kNumCUs / 4 && (D > 64 || lay.sn <= kRowStrideLimit / 2)) {
+        constexpr int FORM = D <= 64 ? 8 : kNarrow;
+        if (RAGGED || N % kQTile<D, FORM> != 0)
+          return launch_dkdv_g<D, CAUSAL, true, GROUPED, FORM>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+        return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, FORM>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
       }
       if (blocks <= (CAUSAL ? kNumCUs : kNumCUs / 2))
         return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 4>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
@@ -972,7 +978,7 @@ static hipError_t launch_dq_g(const void* Q, const void* K, const void* V, const
                               const float* LSE, const float* delta, const void* O, void* dQ,
                               float* delta_out, int BH, int N, float alpha, Layout lay, hipStream_t st) {
   constexpr int smem = kSmemDq<D, G>;
-  constexpr int QUERIES = 32 * kQueryWaves<G>, THREADS = 64 * kQueryWaves<G> * G;
+  constexpr int QUERIES = 32 * kQueryWaves<G>, THREADS = 64 * kQueryWaves<G> * kGroups<G>;
   static std::atomic<bool> set{false};
   auto k = attn_bwd_dq_kernel<D, CAUSAL, RAGGED, MODE, G>;
   hipError_t e;
@@ -1007,14 +1013,17 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
   // B2 H8 N1500 61 -> 54; not taken: B1 H15 N2048 82 -> 98, B1 H24 N1280 57 -> 60, B4 H8 N1024 51 -> 53, B2 H12 N2048 91 -> 116.
   if constexpr (MODE != kRecomputeDelta) {
     const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
-    // Eight groups on 32 queries, as in launch_dkdv, up to one work-group per CU.  us, four -> eight, d64 causal: B1 H1 N5120 30.4 ->
-    // 20.1, B1 H4 N2048 16.3 -> 12.6, B1 H8 N1024 11.5 -> 9.9, B1 H1 N5000 31.3 -> 20.6, B1 H1 N512 8.6 -> 7.9, full B1 H1 N8192
-    // 44.7 -> 33.7, d32 B1 H4 N2000 11.7 -> 8.8; beyond the limit: B1 H12 N1024 11.4 -> 15.6, B1 H1 N16384 91 -> 132.
-    if constexpr (D <= 64)
-      if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= kNumCUs / 4 && lay.sn <= kRowStrideLimit / 2) {
-        if (RAGGED || N % kKeysPerTile<8> != 0)
-          return launch_dq_g<D, CAUSAL, true, MODE, 8>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
-        return launch_dq_g<D, CAUSAL, RAGGED, MODE, 8>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+    // Blocks of 32 queries, as in launch_dkdv, up to one work-group per CU.  us, four groups on 64 queries -> this; d64, eight groups:
+    // causal B1 H1 N5120 30.4 -> 20.1, B1 H4 N2048 16.3 -> 12.6, B1 H8 N1024 11.5 -> 9.9, B1 H1 N512 8.6 -> 7.9, full B1 H1 N8192 44.7 ->
+    // 33.7, d32 B1 H4 N2000 11.7 -> 8.8; d128, four: causal B1 H1 N5120 47.0 -> 31.9, B1 H4 N2048 25.3 -> 18.0, B1 H8 N1024 18.0 ->
+    // 12.7, full B1 H4 N2048 25.2 -> 19.4, d96 B1 H4 N2000 19.2 -> 16.9; beyond the limit (eight groups) B1 H12 N1024 d64 11.4 -> 15.6, B1
+    // H1 N16384 91 -> 132.
+    if constexpr (D <= 128)
+      if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= kNumCUs / 4 && (D > 64 || lay.sn <= kRowStrideLimit / 2)) {
+        constexpr int FORM = D <= 64 ? 8 : kNarrow;
+        if (RAGGED || N % kKeysPerTile<FORM> != 0)
+          return launch_dq_g<D, CAUSAL, true, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+        return launch_dq_g<D, CAUSAL, RAGGED, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
       }
     const bool balanced = CAUSAL && (D <= 128 || (BH % 8 == 0 && lay.Nk == N && N >= 1500));
     if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (balanced ? kNumCUs : kNumCUs / 2)) {

@@ -44,9 +44,10 @@ def _check(lib, B, H, N, d, causal):
 
 
 @pytest.mark.parametrize("B,H,N,d,causal", [
-    # eight wave groups: tiles of 256 rows, grids up to and just beyond a work-group per CU
+    # blocks of 32 rows (eight wave groups at d <= 64, four beyond), grids up to and just above a work-group per CU
     (1, 1, 512, 64, True), (1, 1, 513, 64, True), (1, 3, 640, 32, True), (2, 4, 1000, 64, False), (1, 8, 1024, 64, True),
-    (2, 8, 1024, 64, True), (1, 12, 1024, 64, True), (1, 13, 1025, 32, False)])
+    (2, 8, 1024, 64, True), (1, 12, 1024, 64, True), (1, 13, 1025, 32, False),
+    (1, 1, 512, 128, True), (1, 2, 700, 128, True), (1, 3, 1000, 96, False), (1, 8, 1024, 128, True), (2, 4, 640, 128, False)])
 def test_every_entry_on_small_grids_of_longer_sequences(lib, B, H, N, d, causal):
     _check(lib, B, H, N, d, causal)
 
