@@ -1035,6 +1035,16 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
       return launch_dq_g<D, CAUSAL, RAGGED, MODE, (D <= 128 ? 4 : 2)>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
     }
   }
+  // Above that, at D <= 64, two groups on 64 queries as long as all work-groups are resident at once (three of four waves per CU, at
+  // D = 32 four: there up to two blocks per CU under the causal mask).  us, one group on 128 queries -> two on 64: d64 causal B3 H8
+  // N2048 29.7 -> 25.6, B4 H12 N1024 18.4 -> 16.6, B1 H19 N2048 36.6 -> 31.2, full B5 H8 N1024 24.1 -> 22.1, B6 H8 24.9 -> 24.0; d32
+  // causal B5 H8 N1000 13.0 -> 9.7, B2 H16 N2000 22.1 -> 19.5, full B6 H8 N1000 17.9 -> 15.5; beyond the limits: d64 causal B7 H8 N1024
+  // 19.2 -> 22.0, N256 (24 x 8 heads) 10.1 -> 11.0, full B4 H8 N1024 15.9 -> 16.9; d32 full B8 H8 N1000 18.4 -> 19.2.
+  if constexpr (D <= 64 && MODE != kRecomputeDelta) {
+    const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
+    if ((RAGGED ? lay.Nk : N) >= 512 && blocks > kNumCUs && blocks <= (D == 32 && CAUSAL ? 4 : 3) * kNumCUs / 2)
+      return launch_dq_g<D, CAUSAL, RAGGED, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+  }
   return launch_dq_g<D, CAUSAL, RAGGED, MODE, 1>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
 }
 
