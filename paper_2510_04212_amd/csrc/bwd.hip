@@ -53,10 +53,11 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 // of its own, which are added through LDS at the end.  4 splits further: 64 keys (two waves) per
 // group, so that a grid has twice the work-groups of half the length; a query tile is then read
 // from L2 for half as many keys.  The smallest grids take 32 keys, one wave per group: 8 groups at D <= 64, and four, kNarrow,
-// where the tiles of eight would not fit the LDS.
-constexpr int kNarrow = 5;
-template <int FORM> constexpr int kGroups = FORM == kNarrow ? 4 : FORM;
-template <int FORM> constexpr int kKeyWaves = FORM == 8 || FORM == kNarrow ? 1 : FORM == 4 ? 2 : 4;               // waves per group, 32 keys each
+// where the tiles of eight would not fit the LDS.  kHalf (dK/dV at D <= 64): two groups on 64 keys, 256 threads, for grids whose
+// work-groups are all resident at once that way.
+constexpr int kNarrow = 5, kHalf = 6;
+template <int FORM> constexpr int kGroups = FORM == kNarrow ? 4 : FORM == kHalf ? 2 : FORM;
+template <int FORM> constexpr int kKeyWaves = FORM == 8 || FORM == kNarrow ? 1 : FORM == 4 || FORM == kHalf ? 2 : 4;               // waves per group, 32 keys each
 template <int D, int FORM> constexpr int kQTile = D == 128 || FORM >= 4 ? 32 * kGroups<FORM> : 64;   // query rows per streamed tile
 // LDS fragments are read this many matrix instructions before their use.
 // (At D = 128 what the registers allow: the fragments of V_j come from LDS too.  Four wave groups at small D: us, four ahead ->
@@ -74,7 +75,7 @@ template <int D, int G> constexpr bool kStageOverTiles = D == 128 || G > 1;
 template <int D, int G> constexpr int kVBytes = kVInLds<D> ? 32 * kKeyWaves<G> * D * 2 : 0;
 template <int D, int G> constexpr int kTilesEnd = kVBytes<D, G> + 4 * kQTile<D, G> * D * 2 + 4 * kQTile<D, G> * 4;
 template <int D> constexpr int kStageBytes = kStagedDkDv<D> ? 4 * 32 * kStagePitch<D / 32 / kDSplit<D>> : 0;
-template <int D, int G> constexpr int kExchangeBytes = G > 1 ? 2 * 4 * (D / 32) * 4096 : 0;
+template <int D, int G> constexpr int kExchangeBytes = G > 1 ? kGroups<G> * kKeyWaves<G> * (D / 32) * 4096 : 0;
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
 template <int D, int G> constexpr int kSmemDkDv =
     G > 1 ? max_int(kTilesEnd<D, G>, kExchangeBytes<D, G>)
@@ -966,6 +967,15 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
   // B1 H33 N2040 d64 even, B5 H13 N1024 d32 27.7 -> 27.9; with grouped queries B4 H32/8 N2048 d64 causal 164 -> 170.
   if constexpr (D <= 64 && !GROUPED) {
     const int NK = RAGGED ? lay.Nk : N;
+    const long long blocks = (long long)BH * ((NK + kKeysPerWG - 1) / kKeysPerWG);
+    // One to one and a half 128-key blocks per CU: half of the CUs had two work-groups and the others one, a wave or two on a SIMD.
+    // Two groups on 64 keys are all resident at once, three waves per SIMD everywhere, and walk the queries in half the steps.  us, one
+    // group on 128 keys -> this: d64 causal B4 H12 N1024 24.5 -> 21.5, B3 H8 N2048 39.1 -> 33.8, B12 H8 N512 15.1 -> 14.0, B5 H8 N1000 22.5 ->
+    // 19.4, in pairs B1 H19 N2048 39.8 -> 39.1, full B1 H20 N2048 53.7 -> 46.5, B6 H8 N1024 31.5 -> 28.9; d32 causal B5 H8 N1000 16.6 ->
+    // 12.4, B2 H16 N1500 22.8 -> 17.2, full B6 H8 N1000 22.0 -> 18.9; beyond the limits: B7 H8 N1024 d64 causal 23.3 -> 23.1, B8 H8
+    // 24.2 -> 26.5, four groups on 64 keys instead B2 H8 N2048 26.8 -> 28.4, full B4 H8 N1024 20.4 -> 21.1; even at N128.
+    if (NK >= 512 && blocks > kNumCUs && blocks <= 3 * kNumCUs / 2)
+      return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, kHalf, true>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
     // (head counts the order table does not take run as pairs of blocks: half as many work-groups)
     if ((long long)BH * ((NK + kKeysPerWG - 1) / kKeysPerWG) > (CAUSAL && BH % 8 != 0 ? 4 : 2) * kNumCUs)
       return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1, true>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);

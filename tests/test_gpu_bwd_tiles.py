@@ -48,7 +48,7 @@ def _check(lib, B, H, N, d, causal):
     (1, 1, 512, 64, True), (1, 1, 513, 64, True), (1, 3, 640, 32, True), (2, 4, 1000, 64, False), (1, 8, 1024, 64, True),
     (2, 8, 1024, 64, True), (1, 12, 1024, 64, True), (1, 13, 1025, 32, False),
     (1, 1, 512, 128, True), (1, 2, 700, 128, True), (1, 3, 1000, 96, False), (1, 8, 1024, 128, True), (2, 4, 640, 128, False),
-    # dQ at d <= 64 with two wave groups on 64 queries: just above one block of 128 per CU, at the rule's upper limits, one block beyond
+    # dQ and dK/dV at d <= 64 with two wave groups on 64 rows: just above one block of 128 per CU, at the rule's upper limits, one block beyond
     (5, 13, 512, 64, True), (4, 13, 513, 64, True), (8, 12, 512, 64, False), (1, 97, 512, 64, True), (1, 33, 1000, 32, False),
     (8, 16, 512, 32, True), (1, 129, 512, 32, True)])
 def test_every_entry_on_small_grids_of_longer_sequences(lib, B, H, N, d, causal):
