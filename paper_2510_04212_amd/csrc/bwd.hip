@@ -53,7 +53,7 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 // of its own, which are added through LDS at the end.  4 splits further: 64 keys (two waves) per
 // group, so that a grid has twice the work-groups of half the length; a query tile is then read
 // from L2 for half as many keys.  The smallest grids take 32 keys, one wave per group: 8 groups at D <= 64, and four, kNarrow,
-// where the tiles of eight would not fit the LDS.  kHalf (dK/dV at D <= 64): two groups on 64 keys, 256 threads, for grids whose
+// where the tiles of eight would not fit the LDS.  kHalf (dK/dV at D <= 96): two groups on 64 keys, 256 threads, for grids whose
 // work-groups are all resident at once that way.
 constexpr int kNarrow = 5, kHalf = 6;
 template <int FORM> constexpr int kGroups = FORM == kNarrow ? 4 : FORM == kHalf ? 2 : FORM;
@@ -953,6 +953,21 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
           return launch_dkdv_g<D, CAUSAL, true, GROUPED, FORM>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
         return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, FORM>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
       }
+      // Two groups on 64 keys at D <= 96, one to one and a half 128-key blocks per CU, with short sequences under the mask from half a
+      // block on: all of these work-groups are resident at once (three per CU at D <= 64, with three waves per SIMD), which those of
+      // four groups are not, and those of one group leave a SIMD a wave or two.  us, one group on 128 keys (d96 under the mask: two)
+      // -> this: d64 causal B4 H12 N1024 24.5 -> 21.5, B3 H8 N2048 39.1 -> 33.8, B12 H8 N512 15.1 -> 14.0, B5 H8 N1000 22.5 -> 19.4, full B1 H20 N2048 53.7 -> 46.5, B6 H8 N1024 31.5 -> 28.9; d32 causal B5 H8 N1000 16.6 -> 12.4, B2 H16 N1500 22.8
+      // -> 17.2, full B6 H8 N1000 22.0 -> 18.9; d96 causal B2 H24 N1024 30.8 -> 27.9, B1 H24 N2048 46.3 -> 43.9, full B1 H22 N2048 74.4 -> 66.9,
+      // B2 H24 N1024 42.8 -> 39.2, B4 H10 N1000 41.0 -> 41.9; four groups on 64 keys -> this, causal: d64 B4 H8 N1024 18.5 -> 16.9, B6 H8 N512 15.0
+      // -> 11.3, B3 H8 N700 13.5 -> 12.7, d96 B4 H8 N1024 22.4 -> 19.5, B6 H8 N512 17.7 -> 12.7, B1 H18 N1024 21.4 -> 20.1.  Beyond the limits: B7 H8
+      // N1024 d64 causal 23.3 -> 23.1, B8 H8 24.2 -> 26.5, B2 H8 N2048 26.8 -> 28.4, in pairs B3 H20 N704 20.3 -> 21.3, B1 H19 N2048 39.8 -> 39.1, full B4 H8 N1024 20.4 -> 21.1; d96
+      // causal B2 H16 N2000 54.6 -> 55.0, B1 H14 N2048 31.2 -> 31.8, B2 H8 N1024 16.3 -> 17.1, full B1 H16 N2048 45.5 -> 46.8.
+      if constexpr (D <= 96 && !GROUPED) {
+        const int above = CAUSAL && NK <= 1024 ? kNumCUs / 2 : kNumCUs;
+        const bool balanced = !CAUSAL || D == 96 || heads % 8 == 0;
+        if (balanced && blocks > above && blocks <= 3 * kNumCUs / 2)
+          return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, kHalf, (D <= 64)>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+      }
       if (blocks <= (CAUSAL ? kNumCUs : kNumCUs / 2))
         return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 4>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
       if constexpr (!CAUSAL || D >= 96)
@@ -967,15 +982,6 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
   // B1 H33 N2040 d64 even, B5 H13 N1024 d32 27.7 -> 27.9; with grouped queries B4 H32/8 N2048 d64 causal 164 -> 170.
   if constexpr (D <= 64 && !GROUPED) {
     const int NK = RAGGED ? lay.Nk : N;
-    const long long blocks = (long long)BH * ((NK + kKeysPerWG - 1) / kKeysPerWG);
-    // One to one and a half 128-key blocks per CU: half of the CUs had two work-groups and the others one, a wave or two on a SIMD.
-    // Two groups on 64 keys are all resident at once, three waves per SIMD everywhere, and walk the queries in half the steps.  us, one
-    // group on 128 keys -> this: d64 causal B4 H12 N1024 24.5 -> 21.5, B3 H8 N2048 39.1 -> 33.8, B12 H8 N512 15.1 -> 14.0, B5 H8 N1000 22.5 ->
-    // 19.4, in pairs B1 H19 N2048 39.8 -> 39.1, full B1 H20 N2048 53.7 -> 46.5, B6 H8 N1024 31.5 -> 28.9; d32 causal B5 H8 N1000 16.6 ->
-    // 12.4, B2 H16 N1500 22.8 -> 17.2, full B6 H8 N1000 22.0 -> 18.9; beyond the limits: B7 H8 N1024 d64 causal 23.3 -> 23.1, B8 H8
-    // 24.2 -> 26.5, four groups on 64 keys instead B2 H8 N2048 26.8 -> 28.4, full B4 H8 N1024 20.4 -> 21.1; even at N128.
-    if (NK >= 512 && blocks > kNumCUs && blocks <= 3 * kNumCUs / 2)
-      return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, kHalf, true>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
     // (head counts the order table does not take run as pairs of blocks: half as many work-groups)
     if ((long long)BH * ((NK + kKeysPerWG - 1) / kKeysPerWG) > (CAUSAL && BH % 8 != 0 ? 4 : 2) * kNumCUs)
       return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1, true>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
@@ -1035,6 +1041,24 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
           return launch_dq_g<D, CAUSAL, true, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
         return launch_dq_g<D, CAUSAL, RAGGED, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
       }
+    // Two groups on 64 queries, where nearly all of these work-groups are resident at once (three per CU, at D = 128 two), which those of
+    // four groups are not, and those of one group leave a SIMD a wave or two.  Under the mask and above 1024 keys the longest
+    // block decides at first, which four groups walk faster, the longer the sequence the further.  us, one group on 128 queries -> this: d64 causal B3 H8 N2048 29.7 -> 25.6,
+    // B4 H12 N1024 18.4 -> 16.6, full B5 H8 N1024 24.1 -> 22.1, d32 causal B5 H8 N1000 13.0 -> 9.7, B2 H16 N2000 22.1 -> 19.5, full B6 H8 N1000
+    // 17.9 -> 15.5, d96 causal B1 H20 N2048 44.9 -> 37.9, B2 H24 N1024 21.9 -> 20.9, full B1 H22 N2048 55.0 -> 51.1, d128 causal B1 H20 N2048 55.5 ->
+    // 47.2; four groups on 64 queries -> this: causal B4 H8 N1024 d64 15.9 -> 12.4, d96 18.3 -> 14.6, d128 25.2 -> 18.9, B1 H16 N2048 21.4 -> 19.6,
+    // 25.4 -> 23.9, 34.3 -> 30.2, B6 H8 N512 12.5 -> 10.1, 14.2 -> 10.2, 19.6 -> 12.9, B1 H18 N1024 (144 blocks) 15.5 -> 13.8, 17.2 -> 16.0, 23.6 ->
+    // 20.6, d128 B1 H9 N1024 16.1 -> 15.0, full B1 H12 N1024 16.4 -> 14.7, B1 H8 N2048 27.1 -> 25.7.  Beyond the limits: d64 causal B7 H8
+    // N1024 19.2 -> 22.0, B1 H12 N2048 20.1 -> 22.8, B1 H8 N3328 25.4 -> 28.3, B2 H8 N1024 even, full B4 H8 N1024 14.7 -> 15.4; d96 causal B1 H12 N2048 24.2 -> 28.3,
+    // B2 H8 N1024 12.6 -> 13.0; d128 causal B2 H24 N1024 26.6 -> 28.7, B1 H10 N2048 31.4 -> 34.8, full B1 H10 N2048 35.9 -> 39.8, above one
+    // block per CU between 67.7 -> 64.5 (B1 H20 N2048) and 37.8 -> 38.2 (B4 H10 N1000): not taken; d32 full B8 H8 N1000 18.4 -> 19.2.
+    if constexpr (D <= 128) {
+      const int NK = RAGGED ? lay.Nk : N;
+      const int above = !CAUSAL ? (D == 128 ? kNumCUs / 4 : kNumCUs) : NK > 2048 ? kNumCUs : NK > 1536 ? 13 * kNumCUs / 16 : NK > 1024 ? 3 * kNumCUs / 4 : D == 128 ? kNumCUs / 4 : kNumCUs / 2;
+      const int limit = D == 128 ? (CAUSAL ? 5 * kNumCUs / 4 : kNumCUs / 2) : D == 32 && CAUSAL ? 2 * kNumCUs : 3 * kNumCUs / 2;
+      if (NK >= 512 && blocks > above && blocks <= limit)
+        return launch_dq_g<D, CAUSAL, RAGGED, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+    }
     const bool balanced = CAUSAL && (D <= 128 || (BH % 8 == 0 && lay.Nk == N && N >= 1500));
     if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (balanced ? kNumCUs : kNumCUs / 2)) {
       // (two groups without a mask: here the aligned kernel is the faster one and spills nothing, unlike that of one group; us,
@@ -1044,16 +1068,6 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
           return launch_dq_g<D, CAUSAL, false, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
       return launch_dq_g<D, CAUSAL, RAGGED, MODE, (D <= 128 ? 4 : 2)>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
     }
-  }
-  // Above that, at D <= 64, two groups on 64 queries as long as all work-groups are resident at once (three of four waves per CU, at
-  // D = 32 four: there up to two blocks per CU under the causal mask).  us, one group on 128 queries -> two on 64: d64 causal B3 H8
-  // N2048 29.7 -> 25.6, B4 H12 N1024 18.4 -> 16.6, B1 H19 N2048 36.6 -> 31.2, full B5 H8 N1024 24.1 -> 22.1, B6 H8 24.9 -> 24.0; d32
-  // causal B5 H8 N1000 13.0 -> 9.7, B2 H16 N2000 22.1 -> 19.5, full B6 H8 N1000 17.9 -> 15.5; beyond the limits: d64 causal B7 H8 N1024
-  // 19.2 -> 22.0, N256 (24 x 8 heads) 10.1 -> 11.0, full B4 H8 N1024 15.9 -> 16.9; d32 full B8 H8 N1000 18.4 -> 19.2.
-  if constexpr (D <= 64 && MODE != kRecomputeDelta) {
-    const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
-    if ((RAGGED ? lay.Nk : N) >= 512 && blocks > kNumCUs && blocks <= (D == 32 && CAUSAL ? 4 : 3) * kNumCUs / 2)
-      return launch_dq_g<D, CAUSAL, RAGGED, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
   }
   return launch_dq_g<D, CAUSAL, RAGGED, MODE, 1>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
 }

@@ -50,7 +50,10 @@ def _check(lib, B, H, N, d, causal):
     (1, 1, 512, 128, True), (1, 2, 700, 128, True), (1, 3, 1000, 96, False), (1, 8, 1024, 128, True), (2, 4, 640, 128, False),
     # dQ and dK/dV at d <= 64 with two wave groups on 64 rows: just above one block of 128 per CU, at the rule's upper limits, one block beyond
     (5, 13, 512, 64, True), (4, 13, 513, 64, True), (8, 12, 512, 64, False), (1, 97, 512, 64, True), (1, 33, 1000, 32, False),
-    (8, 16, 512, 32, True), (1, 129, 512, 32, True)])
+    (8, 16, 512, 32, True), (1, 129, 512, 32, True),
+    # the same at every head size, below one block per CU (short and longer sequences under the mask) and above
+    (1, 33, 513, 64, True), (1, 33, 512, 32, True), (3, 8, 1025, 64, True), (1, 25, 1100, 96, True), (1, 33, 513, 96, True), (8, 12, 512, 96, False),
+    (5, 13, 513, 96, True), (1, 17, 512, 128, True), (2, 33, 513, 128, True), (1, 80, 512, 128, True), (1, 17, 513, 128, False), (4, 8, 512, 128, False)])
 def test_every_entry_on_small_grids_of_longer_sequences(lib, B, H, N, d, causal):
     _check(lib, B, H, N, d, causal)
 
