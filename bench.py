@@ -231,8 +231,8 @@ def main():
 
     # The forward's only other per-row output is LSE (4 bytes per row, written by the forward's
     # epilogue: there is no separate LSE pass).  The one extra pass over rows the library has is
-    # the row-statistics pass of the whole-row stabilised variant (scores only: reads Q and K,
-    # writes one float per row); its time is that variant's forward minus the per-tile variant's.
+    # the row-statistics pass of the whole-row stabilised variant (scores only, in the launch of its
+    # output pass); its time is that variant's forward minus the per-tile variant's.
     if not args.only_headline:
         tv = {}
         for var in (binding.MITIGATED, binding.MITIGATED_ROW):

@@ -1,7 +1,7 @@
 // Shared device helpers for the gfx950 attention kernels: vector types, the matrix-core
 // wrappers, the LDS tile layout (macro blocks with permuted 16-byte chunks) and cross-lane exchanges.
 //
-// Matrix-core fragment layouts used throughout (wave64, v_mfma_f32_32x32x16_bf16,
+// Matrix-core fragment layouts of the forward (wave64, v_mfma_f32_32x32x16_bf16; those of the backward stand at mfma16,
 // D[32x32] += A[32x16] * B[16x32]; lane l, r = l & 31, h = l >> 5):
 //   A operand: lane holds A[r][8h .. 8h+7]            (8 consecutive k of one row)
 //   B operand: lane holds B[8h .. 8h+7][r]            (8 consecutive k of one column)
