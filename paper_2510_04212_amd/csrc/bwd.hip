@@ -1049,12 +1049,12 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
     // 47.2; four groups on 64 queries -> this: causal B4 H8 N1024 d64 15.9 -> 12.4, d96 18.3 -> 14.6, d128 25.2 -> 18.9, B1 H16 N2048 21.4 -> 19.6,
     // 25.4 -> 23.9, 34.3 -> 30.2, B6 H8 N512 12.5 -> 10.1, 14.2 -> 10.2, 19.6 -> 12.9, B1 H18 N1024 (144 blocks) 15.5 -> 13.8, 17.2 -> 16.0, 23.6 ->
     // 20.6, d128 B1 H9 N1024 16.1 -> 15.0, full B1 H12 N1024 16.4 -> 14.7, B1 H8 N2048 27.1 -> 25.7.  Beyond the limits: d64 causal B7 H8
-    // N1024 19.2 -> 22.0, B1 H12 N2048 20.1 -> 22.8, B1 H8 N3328 25.4 -> 28.3, B2 H8 N1024 even, full B4 H8 N1024 14.7 -> 15.4; d96 causal B1 H12 N2048 24.2 -> 28.3,
+    // N1024 19.2 -> 22.0, B1 H12 N2048 20.1 -> 22.8, B1 H8 N3328 25.4 -> 28.3, d32 B1 H14 N2048 16.5 -> 17.7, d64 B2 H8 N1024 even, full B4 H8 N1024 14.7 -> 15.4; d96 causal B1 H12 N2048 24.2 -> 28.3,
     // B2 H8 N1024 12.6 -> 13.0; d128 causal B2 H24 N1024 26.6 -> 28.7, B1 H10 N2048 31.4 -> 34.8, full B1 H10 N2048 35.9 -> 39.8, above one
     // block per CU between 67.7 -> 64.5 (B1 H20 N2048) and 37.8 -> 38.2 (B4 H10 N1000): not taken; d32 full B8 H8 N1000 18.4 -> 19.2.
     if constexpr (D <= 128) {
       const int NK = RAGGED ? lay.Nk : N;
-      const int above = !CAUSAL ? (D == 128 ? kNumCUs / 4 : kNumCUs) : NK > 2048 ? kNumCUs : NK > 1536 ? 13 * kNumCUs / 16 : NK > 1024 ? 3 * kNumCUs / 4 : D == 128 ? kNumCUs / 4 : kNumCUs / 2;
+      const int above = !CAUSAL ? (D == 128 ? kNumCUs / 4 : kNumCUs) : NK > 2048 || (D == 32 && NK > 1536) ? kNumCUs : NK > 1536 ? 13 * kNumCUs / 16 : NK > 1024 ? 3 * kNumCUs / 4 : D == 128 ? kNumCUs / 4 : kNumCUs / 2;
       const int limit = D == 128 ? (CAUSAL ? 5 * kNumCUs / 4 : kNumCUs / 2) : D == 32 && CAUSAL ? 2 * kNumCUs : 3 * kNumCUs / 2;
       if (NK >= 512 && blocks > above && blocks <= limit)
         return launch_dq_g<D, CAUSAL, RAGGED, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
