@@ -947,7 +947,7 @@ static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const
       // 20.0 -> 15.1, B1 H32/8 N1000 55.5 -> 43.2, full B1 H4 N2048 27.9 -> 20.6, d96 B1 H4 N2000 29.6 -> 22.1; beyond the limits
       // (eight groups) B2 H8 N1024 d64 13.3 -> 15.9, B8 H8 N512 15.0 -> 26.1.
       const int heads = BH / lay.group;
-      if (blocks <= (CAUSAL && heads % 8 != 0 ? 2 : 1) * kNumCUs / 4 && (D > 64 || lay.sn <= kRowStrideLimit / 2)) {
+      if (blocks <= (CAUSAL && heads % 8 != 0 ? 2 : 1) * kNumCUs / 4) {
         constexpr int FORM = D <= 64 ? 8 : kNarrow;
         if (RAGGED || N % kQTile<D, FORM> != 0)
           return launch_dkdv_g<D, CAUSAL, true, GROUPED, FORM>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
@@ -1035,7 +1035,7 @@ static hipError_t launch_dq(const void* Q, const void* K, const void* V, const v
     // 12.7, full B1 H4 N2048 25.2 -> 19.4, d96 B1 H4 N2000 19.2 -> 16.9; beyond the limit (eight groups) B1 H12 N1024 d64 11.4 -> 15.6, B1
     // H1 N16384 91 -> 132.
     if constexpr (D <= 128)
-      if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= kNumCUs / 4 && (D > 64 || lay.sn <= kRowStrideLimit / 2)) {
+      if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= kNumCUs / 4) {
         constexpr int FORM = D <= 64 ? 8 : kNarrow;
         if (RAGGED || N % kKeysPerTile<FORM> != 0)
           return launch_dq_g<D, CAUSAL, true, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);

@@ -237,8 +237,7 @@ DEVI const bf16_t* wave_uniform(const bf16_t* p) {
 }
 
 template <int D, int R = 64, int NW = 4> struct TileLoader {
-  // (256 rows: a launcher that takes them sees to it that the row stride is at most half of kRowStrideLimit)
-  static_assert(R == 32 || R == 64 || R == 128 || R == 2 * kMaxTileRows, "rows per tile");
+  static_assert(R == 32 || R == 64 || R == 128 || R == 256, "rows per tile");
   static constexpr int NRB = R / 16;             // 16-row blocks
   static constexpr int NCB = kColBlocks<D>;
   static constexpr int WPR = NW > NRB ? NW / NRB : 1;    // waves that share a 16-row block ...
@@ -246,7 +245,11 @@ template <int D, int R = 64, int NW = 4> struct TileLoader {
   static constexpr int CPW = (NCB + WPR - 1) / WPR;  // column blocks per wave and row block
   static constexpr int NI = RPW * CPW;           // instructions per wave
   static constexpr int kBytes = R * D * 2;
-  int row, chunk;                                // per lane: first row of the tile it fetches, byte offset of its chunk
+  // A tile of more rows than 32-bit offsets span at the largest row stride: every wave counts its own few rows from the first of them.
+  static constexpr bool FROM_WAVE = R > kMaxTileRows;
+  static_assert((FROM_WAVE ? 16 * RPW : R) <= kMaxTileRows, "rows that one base address serves");
+  int row, chunk;                                // per lane: first row it fetches, from the base address's row; byte offset of its chunk
+  int row0_wave;                                 // row of the tile that the wave's base address stands for (scalar)
   int col0;                                      // first column block of this wave (scalar)
   int sn;                                        // distance between consecutive rows of the source, in elements
   unsigned lds_wave;                             // LDS offset of the wave's first macro block (scalar)
@@ -256,7 +259,8 @@ template <int D, int R = 64, int NW = 4> struct TileLoader {
     const int rg = wave / WPR * RPW;             // first row block of this wave
     col0 = wave % WPR;
     sn = row_stride;
-    row = rg * 16 + (lane >> 2);
+    row0_wave = FROM_WAVE ? rg * 16 : 0;
+    row = (FROM_WAVE ? 0 : rg * 16) + (lane >> 2);
     chunk = ((lane & 3) ^ slot_mask(lane >> 4)) * 16;
     lds_wave = (unsigned)(rg * kRowBlockBytes<D> + col0 * 1024);
   }
@@ -270,6 +274,7 @@ template <int D, int R = 64, int NW = 4> struct TileLoader {
   template <bool RAGGED>
   DEVI Pending prepare(const char* tile, const bf16_t* tensor, int row0, int N) const {
     Pending p;
+    if (FROM_WAVE) row0 = RAGGED ? min(row0 + row0_wave, N - 1) : row0 + row0_wave;
     p.src = wave_uniform(tensor + (size_t)row0 * sn + col0 * 32);
     p.base = __builtin_amdgcn_readfirstlane((unsigned)lds_address(tile)) + lds_wave;
 #pragma unroll

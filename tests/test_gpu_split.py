@@ -188,11 +188,11 @@ def test_shares_with_infinite_scores(lib, N, variant):
     assert ref_O[0, 0, 5].isnan().all().item() == (N % 128 == 0)
 
 
-@pytest.mark.parametrize("N,stride", [(200, (1 << 24) - 8), (512, 9_000_000)])
-def test_rows_far_apart(lib, N, stride):
-    """Row strides at which the last rows of a 128-row tile lie 2 to 4 GiB behind its first (V_j at d = 128,
-    and the 128-row tiles of four wave groups): the bits of the contiguous call."""
-    d = 128
+@pytest.mark.parametrize("N,stride,d", [(200, (1 << 24) - 8, 128), (512, 9_000_000, 128), (512, 8_388_616, 64), (600, (1 << 24) - 8, 64),
+                                        (700, 9_000_000, 32)])
+def test_rows_far_apart(lib, N, stride, d):
+    """Row strides at which the last rows of a 128-row tile lie 2 to 4 GiB behind its first (V_j at d = 128, and the 128-row
+    tiles of wave groups), and those of a 256-row tile (eight groups at d <= 64) up to 8 GiB: the bits of the contiguous call."""
     x = _inputs(N, 1, 1, N, N, d)
     far = torch.empty((N - 1) * stride + 8 * d, dtype=torch.bfloat16, device=DEV)
     view = lambda i: far[i * d:].as_strided((1, 1, N, d), (8, 8, stride, 1))
