@@ -17,6 +17,7 @@
 #include <algorithm>
 
 constexpr int kCUsPerXCD = 32;
+constexpr int kNumCUs = 8 * kCUsPerXCD;
 constexpr int kMaxOrder = 255;
 
 struct BlockOrder {

@@ -20,6 +20,7 @@
 // Rounding points: P (float32) -> bf16 as the operand of dO^T P; dS = P o (dP - delta) is formed
 // from the float32 P and rounded to bf16 as an operand; accumulators are float32; alpha
 // multiplies the float32 dQ / dK accumulators once; outputs are rounded to bf16 when stored.
+#include "bwd_forms.hpp"
 #include "common.hpp"
 
 #include <atomic>
@@ -53,9 +54,8 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 // of its own, which are added through LDS at the end.  4 splits further: 64 keys (two waves) per
 // group, so that a grid has twice the work-groups of half the length; a query tile is then read
 // from L2 for half as many keys.  The smallest grids take 32 keys, one wave per group: 8 groups at D <= 64, and four, kNarrow,
-// where the tiles of eight would not fit the LDS.  kHalf (dK/dV at D <= 96): two groups on 64 keys, 256 threads, for grids whose
-// work-groups are all resident at once that way.
-constexpr int kNarrow = 5, kHalf = 6;
+// where the tiles of eight would not fit the LDS.  kHalf (dK/dV at D <= 96): two groups on 64 keys, 256 threads.  bwd_forms.hpp has the
+// rules that choose.
 template <int FORM> constexpr int kGroups = FORM == kNarrow ? 4 : FORM == kHalf ? 2 : FORM;
 template <int FORM> constexpr int kKeyWaves = FORM == 8 || FORM == kNarrow ? 1 : FORM == 4 || FORM == kHalf ? 2 : 4;               // waves per group, 32 keys each
 template <int D, int FORM> constexpr int kQTile = D == 128 || FORM >= 4 ? 32 * kGroups<FORM> : 64;   // query rows per streamed tile
@@ -920,73 +920,28 @@ static hipError_t launch_dkdv_g(const void* Q, const void* K, const void* V, con
   return hipGetLastError();
 }
 
+// calls f(integral_constant<FORM>) for every form
+template <class F> static void each_form(F&& f) {
+  f(std::integral_constant<int, 1>{}); f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 4>{}); f(std::integral_constant<int, 8>{});
+  f(std::integral_constant<int, kNarrow>{}); f(std::integral_constant<int, kHalf>{}); f(std::integral_constant<int, kDense>{});
+}
+
 template <int D, bool CAUSAL, bool RAGGED, bool GROUPED>
 static hipError_t launch_dkdv(const void* Q, const void* K, const void* V, const void* dO,
                               const float* LSE, const float* delta, void* dK, void* dV, int BH,
                               int N, float alpha, Layout lay, hipStream_t st) {
-  // Wave groups where one-group work-groups would leave the SIMDs with a single wave each.  Short
-  // sequences do not pay for the final exchange.
-  // Four groups on 64 keys, up to one 128-key block per CU (half of that without a mask, where all
-  // blocks are equal and two per CU would run one after the other).  Measured, two groups -> four (us): B2
-  // H32/8 N2048 d128 causal 200 -> 149, B2 H8 N2048 d128 causal 54.8 -> 48.8, d96 45.0 -> 37.6, d64 35.3 -> 28.5, B1 H4 N4096
-  // d128 causal 93 -> 62, B1 H8 N2048 d128 full 50.4 -> 39.1, B1 H1 N1024 d64 full 17.1 -> 11.5; beyond the
-  // limits: B2 H12 N2048 d128 causal 62 -> 89, B4 H12 N1024 d64 causal 26.0 -> 37.5.
-  // Two groups on 128 keys up to one block per CU; up to two under the causal mask at D >= 96, where the
-  // blocks differ in work and the CU with the heaviest one decides (at D = 64 two work-groups with 64-row tiles on a
-  // CU do as well).  Measured, one group -> two (us): B2 H12 N2048 d128 causal 70.8 -> 62.6, d96 53.2 -> 48.5, B2 H8 N2048
-  // d128 full 74.4 -> 66.5, at the limit of two per CU B2 H16 N2048 d128 causal 79.4 -> 76.6, d96 60.5 -> 61.9; beyond the
-  // limits: B5 H8 N2048 d128 causal 93 -> 129, B3 H8 N2048 d128 full 108 -> 114, B4 H12 N1024 d64 causal 24.5 -> 26.0.
-  if constexpr (D <= 128) {
-    const int NK = RAGGED ? lay.Nk : N;      // (the rule looks at the keys only: a chunk of queries gets the sums of the square problem)
-    const long long blocks = (long long)(BH / lay.group) * ((NK + kKeysPerWG - 1) / kKeysPerWG);
-    if (NK >= 512) {
-      // Blocks of 32 keys as long as every work-group gets a CU of its own (head counts the order table does not take run as
-      // pairs of blocks: half as many).  us, four groups on 64 keys -> this; d64, eight groups: causal B1 H1 N5120 45.1 -> 29.4, B1 H4
-      // N2048 24.4 -> 19.0, B1 H8 N1024 12.9 -> 10.3, B1 H4 N5000 46.3 -> 31.4, B1 H1 N512 13.5 -> 13.1, full B1 H1 N8192 58.0 ->
-      // 40.5, d32 B1 H4 N2000 17.6 -> 14.1; d128, four: causal B1 H1 N5120 69.3 -> 48.5, B1 H4 N4096 (pairs) 59.5 -> 44.0, B1 H8 N1024
-      // 20.0 -> 15.1, B1 H32/8 N1000 55.5 -> 43.2, full B1 H4 N2048 27.9 -> 20.6, d96 B1 H4 N2000 29.6 -> 22.1; beyond the limits
-      // (eight groups) B2 H8 N1024 d64 13.3 -> 15.9, B8 H8 N512 15.0 -> 26.1.
-      const int heads = BH / lay.group;
-      if (blocks <= (CAUSAL && heads % 8 != 0 ? 2 : 1) * kNumCUs / 4) {
-        constexpr int FORM = D <= 64 ? 8 : kNarrow;
-        if (RAGGED || N % kQTile<D, FORM> != 0)
-          return launch_dkdv_g<D, CAUSAL, true, GROUPED, FORM>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-        return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, FORM>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-      }
-      // Two groups on 64 keys at D <= 96, one to one and a half 128-key blocks per CU, with short sequences under the mask from half a
-      // block on: all of these work-groups are resident at once (three per CU at D <= 64, with three waves per SIMD), which those of
-      // four groups are not, and those of one group leave a SIMD a wave or two.  us, one group on 128 keys (d96 under the mask: two)
-      // -> this: d64 causal B4 H12 N1024 24.5 -> 21.5, B3 H8 N2048 39.1 -> 33.8, B12 H8 N512 15.1 -> 14.0, B5 H8 N1000 22.5 -> 19.4, full B1 H20 N2048 53.7 -> 46.5, B6 H8 N1024 31.5 -> 28.9; d32 causal B5 H8 N1000 16.6 -> 12.4, B2 H16 N1500 22.8
-      // -> 17.2, full B6 H8 N1000 22.0 -> 18.9; d96 causal B2 H24 N1024 30.8 -> 27.9, B1 H24 N2048 46.3 -> 43.9, full B1 H22 N2048 74.4 -> 66.9,
-      // B2 H24 N1024 42.8 -> 39.2, B4 H10 N1000 41.0 -> 41.9; four groups on 64 keys -> this, causal: d64 B4 H8 N1024 18.5 -> 16.9, B6 H8 N512 15.0
-      // -> 11.3, B3 H8 N700 13.5 -> 12.7, d96 B4 H8 N1024 22.4 -> 19.5, B6 H8 N512 17.7 -> 12.7, B1 H18 N1024 21.4 -> 20.1.  Beyond the limits: B7 H8
-      // N1024 d64 causal 23.3 -> 23.1, B8 H8 24.2 -> 26.5, B2 H8 N2048 26.8 -> 28.4, in pairs B3 H20 N704 20.3 -> 21.3, B1 H19 N2048 39.8 -> 39.1, full B4 H8 N1024 20.4 -> 21.1; d96
-      // causal B2 H16 N2000 54.6 -> 55.0, B1 H14 N2048 31.2 -> 31.8, B2 H8 N1024 16.3 -> 17.1, full B1 H16 N2048 45.5 -> 46.8.
-      if constexpr (D <= 96 && !GROUPED) {
-        const int above = CAUSAL && NK <= 1024 ? kNumCUs / 2 : kNumCUs;
-        const bool balanced = !CAUSAL || D == 96 || heads % 8 == 0;
-        if (balanced && blocks > above && blocks <= 3 * kNumCUs / 2)
-          return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, kHalf, (D <= 64)>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-      }
-      if (blocks <= (CAUSAL ? kNumCUs : kNumCUs / 2))
-        return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 4>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-      if constexpr (!CAUSAL || D >= 96)
-        if (blocks <= (CAUSAL ? 2 : 1) * kNumCUs)
-          return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 2>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-    }
-  }
-  // More than two 128-key blocks per CU at D <= 64: three waves per SIMD.  Measured, two -> three (us): B8 H12 N1024 d64
-  // causal 39.1 -> 35.7, B32 H12 N512 d64 full 62.5 -> 58.6, B4 H32 N4096 d64 causal 557 -> 535, B8 H12 N1000 d64 full
-  // 60.7 -> 56.4, causal 40.1 -> 36.5, B8 H12 N1024 d32 causal 28.2 -> 23.4, B8 H16 N1001 d32 full 52.7 -> 51.2; just above the
-  // limit 400 heads N200 d64 causal 19.0 -> 19.2, B2 H16 N2050 47.8 -> 50.1; below it: B4 H12 N1024 d64 causal 24.5 -> 25.4, in pairs
-  // B1 H33 N2040 d64 even, B5 H13 N1024 d32 27.7 -> 27.9; with grouped queries B4 H32/8 N2048 d64 causal 164 -> 170.
-  if constexpr (D <= 64 && !GROUPED) {
-    const int NK = RAGGED ? lay.Nk : N;
-    // (head counts the order table does not take run as pairs of blocks: half as many work-groups)
-    if ((long long)BH * ((NK + kKeysPerWG - 1) / kKeysPerWG) > (CAUSAL && BH % 8 != 0 ? 4 : 2) * kNumCUs)
-      return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1, true>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
-  }
-  return launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, 1>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+  const int form = dkdv_form(D, CAUSAL, GROUPED, BH / lay.group, RAGGED ? lay.Nk : N);
+  hipError_t e = hipErrorInvalidValue;
+  each_form([&](auto f) {
+    constexpr int ANY = decltype(f)::value, FORM = ANY == kDense ? 1 : ANY;
+    constexpr bool DENSE = ANY == kDense || (ANY == kHalf && D <= 64);      // three waves per SIMD
+    if constexpr (dkdv_has_form(D, CAUSAL, GROUPED, ANY))
+      if (form == ANY)       // (the aligned kernels want whole tiles)
+        e = RAGGED || N % kQTile<D, FORM> != 0
+                ? launch_dkdv_g<D, CAUSAL, true, GROUPED, FORM, DENSE>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st)
+                : launch_dkdv_g<D, CAUSAL, RAGGED, GROUPED, FORM, DENSE>(Q, K, V, dO, LSE, delta, dK, dV, BH, N, alpha, lay, st);
+  });
+  return e;
 }
 
 template <int D, bool CAUSAL, bool RAGGED, int MODE, int G>
@@ -1018,58 +973,22 @@ template <int D, bool CAUSAL, bool RAGGED, int MODE>
 static hipError_t launch_dq(const void* Q, const void* K, const void* V, const void* dO,
                             const float* LSE, const float* delta, const void* O, void* dQ,
                             float* delta_out, int BH, int N, float alpha, Layout lay, hipStream_t st) {
-  // Wave groups on small grids, as in launch_dkdv: up to one 128-query block per CU under the causal mask,
-  // half of that without one, from 512 keys on.  Measured, one group -> four groups on 64 queries (us): B2 H8
-  // N2048 d128 causal 50 -> 45, B1 H8 the same 44 -> 30, d64 30 -> 18, B1 H4 N4096 d128 79 -> 48, B1 H8
-  // N2048 d128 full 44 -> 32, B1 H1 N8192 d64 101 -> 47; beyond the limits: B2 H12 N2048 d128 causal 52 -> 66,
-  // B2 H8 N2048 d128 full 57 -> 64.  At D = 256 (one wave per SIMD) two groups on 64 queries are what fits:
-  // B1 H8 N2048 full 73 -> 57, beyond the limit B2 H8 95 -> 109.  There the causal mask takes the limit to one block per CU
-  // only where the order table balances the halved blocks (head counts in eights), in square problems (with more keys than
-  // queries the blocks differ less) and from 1500 keys on: B2 H8 N2048 85 -> 79, B1 H8 N4000 145 -> 124, B1 H16 N1900 78 -> 73,
-  // B2 H8 N1500 61 -> 54; not taken: B1 H15 N2048 82 -> 98, B1 H24 N1280 57 -> 60, B4 H8 N1024 51 -> 53, B2 H12 N2048 91 -> 116.
-  if constexpr (MODE != kRecomputeDelta) {
-    const long long blocks = (long long)BH * ((N + kQPerWG - 1) / kQPerWG);
-    // Blocks of 32 queries, as in launch_dkdv, up to one work-group per CU.  us, four groups on 64 queries -> this; d64, eight groups:
-    // causal B1 H1 N5120 30.4 -> 20.1, B1 H4 N2048 16.3 -> 12.6, B1 H8 N1024 11.5 -> 9.9, B1 H1 N512 8.6 -> 7.9, full B1 H1 N8192 44.7 ->
-    // 33.7, d32 B1 H4 N2000 11.7 -> 8.8; d128, four: causal B1 H1 N5120 47.0 -> 31.9, B1 H4 N2048 25.3 -> 18.0, B1 H8 N1024 18.0 ->
-    // 12.7, full B1 H4 N2048 25.2 -> 19.4, d96 B1 H4 N2000 19.2 -> 16.9; beyond the limit (eight groups) B1 H12 N1024 d64 11.4 -> 15.6, B1
-    // H1 N16384 91 -> 132.
-    if constexpr (D <= 128)
-      if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= kNumCUs / 4) {
-        constexpr int FORM = D <= 64 ? 8 : kNarrow;
-        if (RAGGED || N % kKeysPerTile<FORM> != 0)
-          return launch_dq_g<D, CAUSAL, true, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
-        return launch_dq_g<D, CAUSAL, RAGGED, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
-      }
-    // Two groups on 64 queries, where nearly all of these work-groups are resident at once (three per CU, at D = 128 two), which those of
-    // four groups are not, and those of one group leave a SIMD a wave or two.  Under the mask and above 1024 keys the longest
-    // block decides at first, which four groups walk faster, the longer the sequence the further.  us, one group on 128 queries -> this: d64 causal B3 H8 N2048 29.7 -> 25.6,
-    // B4 H12 N1024 18.4 -> 16.6, full B5 H8 N1024 24.1 -> 22.1, d32 causal B5 H8 N1000 13.0 -> 9.7, B2 H16 N2000 22.1 -> 19.5, full B6 H8 N1000
-    // 17.9 -> 15.5, d96 causal B1 H20 N2048 44.9 -> 37.9, B2 H24 N1024 21.9 -> 20.9, full B1 H22 N2048 55.0 -> 51.1, d128 causal B1 H20 N2048 55.5 ->
-    // 47.2; four groups on 64 queries -> this: causal B4 H8 N1024 d64 15.9 -> 12.4, d96 18.3 -> 14.6, d128 25.2 -> 18.9, B1 H16 N2048 21.4 -> 19.6,
-    // 25.4 -> 23.9, 34.3 -> 30.2, B6 H8 N512 12.5 -> 10.1, 14.2 -> 10.2, 19.6 -> 12.9, B1 H18 N1024 (144 blocks) 15.5 -> 13.8, 17.2 -> 16.0, 23.6 ->
-    // 20.6, d128 B1 H9 N1024 16.1 -> 15.0, full B1 H12 N1024 16.4 -> 14.7, B1 H8 N2048 27.1 -> 25.7.  Beyond the limits: d64 causal B7 H8
-    // N1024 19.2 -> 22.0, B1 H12 N2048 20.1 -> 22.8, B1 H8 N3328 25.4 -> 28.3, d32 B1 H14 N2048 16.5 -> 17.7, d64 B2 H8 N1024 even, full B4 H8 N1024 14.7 -> 15.4; d96 causal B1 H12 N2048 24.2 -> 28.3,
-    // B2 H8 N1024 12.6 -> 13.0; d128 causal B2 H24 N1024 26.6 -> 28.7, B1 H10 N2048 31.4 -> 34.8, full B1 H10 N2048 35.9 -> 39.8, above one
-    // block per CU between 67.7 -> 64.5 (B1 H20 N2048) and 37.8 -> 38.2 (B4 H10 N1000): not taken; d32 full B8 H8 N1000 18.4 -> 19.2.
-    if constexpr (D <= 128) {
-      const int NK = RAGGED ? lay.Nk : N;
-      const int above = !CAUSAL ? (D == 128 ? kNumCUs / 4 : kNumCUs) : NK > 2048 || (D == 32 && NK > 1536) ? kNumCUs : NK > 1536 ? 13 * kNumCUs / 16 : NK > 1024 ? 3 * kNumCUs / 4 : D == 128 ? kNumCUs / 4 : kNumCUs / 2;
-      const int limit = D == 128 ? (CAUSAL ? 5 * kNumCUs / 4 : kNumCUs / 2) : D == 32 && CAUSAL ? 2 * kNumCUs : 3 * kNumCUs / 2;
-      if (NK >= 512 && blocks > above && blocks <= limit)
-        return launch_dq_g<D, CAUSAL, RAGGED, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+  const int form = MODE == kRecomputeDelta ? 1 : dq_form(D, CAUSAL, BH, N, RAGGED ? lay.Nk : N);
+  hipError_t e = hipErrorInvalidValue;
+  each_form([&](auto f) {
+    constexpr int FORM = decltype(f)::value;
+    // At D = 256 without a mask the bounds-checking kernels serve aligned sizes too (attn_bwd_dq_dispatch), but for two groups, where
+    // the aligned one is the faster and spills nothing: us, bounds-checking -> aligned: B1 H8 N2048 57.4 -> 56.2, B1 H4 N4096
+    // 100.7 -> 98.5, B1 H8 N512 20.8 -> 20.0.
+    constexpr bool ALIGNED_256 = D == 256 && !CAUSAL && FORM == 2;
+    if constexpr (dq_has_form(D, FORM) && (MODE != kRecomputeDelta || FORM == 1)) {
+      if (form != FORM) return;
+      const bool aligned = ALIGNED_256 ? lay.Nk == N && N % kQPerWG == 0 : !RAGGED && N % kKeysPerTile<FORM> == 0;
+      e = aligned ? launch_dq_g<D, CAUSAL, RAGGED && !ALIGNED_256, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st)
+                  : launch_dq_g<D, CAUSAL, true, MODE, FORM>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
     }
-    const bool balanced = CAUSAL && (D <= 128 || (BH % 8 == 0 && lay.Nk == N && N >= 1500));
-    if ((RAGGED ? lay.Nk : N) >= 512 && blocks <= (balanced ? kNumCUs : kNumCUs / 2)) {
-      // (two groups without a mask: here the aligned kernel is the faster one and spills nothing, unlike that of one group; us,
-      // bounds-checking -> aligned: B1 H8 N2048 57.4 -> 56.2, B1 H4 N4096 100.7 -> 98.5, B1 H8 N512 20.8 -> 20.0)
-      if constexpr (D == 256 && !CAUSAL)
-        if (lay.Nk == N && N % kQPerWG == 0)
-          return launch_dq_g<D, CAUSAL, false, MODE, 2>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
-      return launch_dq_g<D, CAUSAL, RAGGED, MODE, (D <= 128 ? 4 : 2)>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
-    }
-  }
-  return launch_dq_g<D, CAUSAL, RAGGED, MODE, 1>(Q, K, V, dO, LSE, delta, O, dQ, delta_out, BH, N, alpha, lay, st);
+  });
+  return e;
 }
 
 }  // namespace

@@ -502,7 +502,6 @@ DEVI int small_grid_rotation(int bh, int nblk, int grid, int capacity) {
 }
 
 // ---- host side of the order table --------------------------------------------------------------
-constexpr int kNumCUs = 256;
 
 // Work-groups of `kern` (`threads` threads, `smem` bytes of dynamic LDS) that a compute unit holds at
 // once; asked of the runtime once per kernel instantiation.
