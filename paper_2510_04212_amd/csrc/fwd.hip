@@ -73,8 +73,9 @@ template <int D, bool CAUSAL> constexpr bool kPipelined = CAUSAL && D >= 96;
 
 // Waves per SIMD the compiler has to make room for.  The row sums' selector and four-register result (add_rows) put some
 // kernels one to four registers over the 96 that five waves allow (D = 32, causal) or the 128 of four (D = 64, causal);
-// asked for the waves they fit without spilling.  Measured, a wave less -> now (us): d32 B13 H32 N520 Alg. 1 37.0 -> 31.8,
-// Alg. 3 41.7 -> 35.5, B4 H32 N4096 250 -> 244, B8 H12 N1024 even; d64 Alg. 1 B64 H8 N200 17.6 -> 15.7, B16 H12 N1999 144 -> 138,
+// asked for the waves they fit without spilling, but for the whole-row rule at D = 32, causal, which spills two outside its tile loops.
+// Measured, a wave less -> now (us): d32 B13 H32 N520 Alg. 1 37.0 -> 31.8, Alg. 3 41.7 -> 35.5, B4 H32 N4096 250 -> 244, B8 H12 N1024
+// even, whole rows 192 heads N1000 37.0 -> 35.6, 48 heads N4096 106.6 -> 103.1, one tile (768 heads N64) 8.05 -> 8.30; d64 Alg. 1 B64 H8 N200 17.6 -> 15.7, B16 H12 N1999 144 -> 138,
 // B8 H12 N1000 even, aligned Alg. 3 B64 H8 N256 18.8 -> 16.8, B4 H32 N4096 354 -> 350, B8 H12 N1024 even.  Not asked of
 // the causal Alg. 3 kernel with bounds checks at d64, which would spill two: B16 H12 N1999 154 -> 150, but B8 H12 N1000 27.0 -> 28.3.
 template <int D, bool CAUSAL, int VARIANT, bool RAGGED, int EXTRAS> constexpr int kFwdWaves =
@@ -275,7 +276,12 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
   const int tile0 = SPLIT ? share_begin(all_tiles, split, shares) : 0;
   const int ntiles = SPLIT ? share_begin(all_tiles, split + 1, shares) : all_tiles;
   loader.template load_rows<RAGGED>(smem, Kh, tile0 * kBc, NK);
-  if (VARIANT != kWholeRow) loader.template load_rows<RAGGED>(smem + 2 * TILE_BYTES, Vh, tile0 * kBc, NK);
+  // kWholeRow: the buffer that the second pass begins with, filled in one burst ahead of the first pass's last scores, at D = 32 right
+  // here.  (Spread over those scores like other transfers, every instruction needs a branch in every tile, which a SIMD with one
+  // wave waits for; right here, short sequences wait for it.  us, spread -> here -> burst: H2 N4096 d128 causal 100.6 -> 92.5 -> 94.0,
+  // H1 N4096 d96 full 77.6 -> 73.9 -> 74.8, H768 N100 d128 full 23.3 -> 25.0 -> 23.6, but H1 N4096 d32 full 53.9 -> 50.5 -> 52.1.)
+  constexpr bool V_FIRST = VARIANT != kWholeRow || D == 32;
+  if (V_FIRST) loader.template load_rows<RAGGED>(smem + (2 + (VARIANT == kWholeRow ? ntiles & 1 : 0)) * TILE_BYTES, Vh, tile0 * kBc, NK);
   if (PIPE) loader.template load_rows<RAGGED>(smem + TILE_BYTES, Kh, (ntiles > 1 ? 1 : 0) * kBc, NK);
 
   // Q_i^T fragments: lane (r,h) holds Q[qw + r][16kc + 8h .. +7] for every kc.
@@ -306,7 +312,7 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
   FragOffsets<D> fo = fo0;
   // One key tile; BUF (which LDS buffer holds it) is a compile-time constant so that every LDS
   // address is a precomputed per-lane offset plus an immediate.
-  // STATS (kWholeRow's first pass): scores and their maxima only; V is fetched under the last tile, for the second pass's first.
+  // STATS (kWholeRow's first pass): scores and their maxima only.
   auto tile_step = [&](auto stats_c, auto buf_c, int j) {
     constexpr bool STATS = decltype(stats_c)::value;
     constexpr int BUF = decltype(buf_c)::value;
@@ -325,8 +331,11 @@ __attribute__((amdgpu_waves_per_eu(kFwdWaves<D, CAUSAL, VARIANT, RAGGED, EXTRAS>
     const auto pendV = loader.template prepare<RAGGED>(smem + (2 + (BUF ^ 1)) * TILE_BYTES, Vh, jn * kBc, NK);
     auto issue_part = [&](int i) {
       if (i < NLD) loader.issue(pendK, i);
-      else if (i < 2 * NLD && (!STATS || last)) loader.issue(pendV, i - NLD);
+      else if (i < 2 * NLD && !STATS) loader.issue(pendV, i - NLD);
     };
+    if (STATS && !V_FIRST && last)
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) loader.issue(pendV, i);
     bool issued = false;
     const int k0 = j * kBc;
     // A wave whose 32 rows all lie above this key tile has nothing to do in it (causal); of a chunk of a few queries
