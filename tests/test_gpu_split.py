@@ -16,20 +16,39 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("Nq,Nk", [(511, 511), (512, 512), (545, 545), (640, 640), (33, 600), (700, 520), (1, 513)])
 def test_backward_with_wave_groups(lib, Nq, Nk, d, causal):
-    """From 512 keys on, few heads: wave groups take alternate 32-query blocks (dK/dV) or 32-key blocks
-    (dQ) - numbers of them no group count divides, partial ones, groups that meet none at all -
-    and add their sums."""
+    """From 512 keys on, two heads: blocks of 32 rows whose eight wave groups (d = 96, 128: four; dK/dV at d = 64 under the mask: two on
+    64 keys) take alternate 32-query blocks (dK/dV) or 32-key blocks (dQ) - numbers of them no group count divides, partial
+    ones, groups that meet none at all - and add their sums."""
     x = _inputs(3 * Nq + Nk + d, 1, 2, Nq, Nk, d, scale=1.25)
     got = _run(lib, x, causal, d ** -0.5, 1)
     for h in range(2):
         check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"groups {Nq}x{Nk} d{d} c{causal}")
 
 
+# heads, queries, keys, d, mask -> the forms of dQ and dK/dV (csrc/bwd_forms.hpp; 6: two groups on 64 keys)
+RECTANGLES = [
+    (16, 577, 700, 64, True, 4, 4), (16, 700, 577, 64, True, 4, 4), (17, 640, 1000, 32, True, 4, 4), (16, 1000, 1025, 96, True, 4, 4),
+    (16, 1100, 1101, 128, True, 4, 4), (14, 700, 640, 64, False, 4, 4), (15, 600, 1000, 96, False, 4, 4), (21, 500, 600, 32, False, 4, 4),
+    (32, 577, 700, 64, True, 2, 6), (40, 640, 520, 32, True, 2, 6), (33, 530, 600, 96, True, 2, 6), (48, 700, 900, 64, True, 2, 6),
+    (24, 500, 600, 128, True, 2, 4), (18, 700, 530, 128, False, 2, 4), (24, 300, 700, 128, True, 2, 4),
+    (64, 560, 600, 64, False, 2, 6), (60, 600, 513, 32, False, 2, 6), (52, 575, 570, 96, False, 2, 6), (40, 130, 1024, 96, False, 4, 6)]
+
+
+@pytest.mark.parametrize("H,Nq,Nk,d,causal,dq,dkdv", RECTANGLES, ids=str)
+def test_four_and_two_wave_groups_on_rectangles(lib, H, Nq, Nk, d, causal, dq, dkdv):
+    """Between 65 and 384 blocks: four groups and two on 64 rows, with more keys than queries and fewer (a mask that is shifted
+    either way, queries that see no key), against the oracle."""
+    x = _inputs(H + 3 * Nq + Nk + d, 1, H, Nq, Nk, d, scale=1.25)
+    got = _run(lib, x, causal, d ** -0.5, 1)
+    for h in (0, H - 1):
+        check_head(got, x, 0, h, causal, d ** -0.5, 1, label=f"rectangle H{H} {Nq}x{Nk} d{d} c{causal}")
+
+
 @pytest.mark.parametrize("d", [32, 64, 96, 128])
 @pytest.mark.parametrize("H,N,causal", [(33, 1024, True), (40, 897, True), (17, 1024, False), (20, 1000, False)])
 def test_dkdv_with_two_wave_groups(lib, H, N, d, causal):
-    """More blocks than the four-group rule takes (256 with, 128 without a mask): two groups, or one at
-    d < 96 under the mask."""
+    """More blocks than the four-group rule takes (256 with, 128 without a mask): two groups on 128 keys, or, up to one and a half
+    blocks per CU under the mask, two on 64 at d < 128 (33 heads, which run in pairs: one at d < 96)."""
     x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
     got = _run(lib, x, causal, d ** -0.5, 1)
     for h in (0, H - 1):
@@ -253,10 +272,12 @@ def test_the_caller_decides_about_the_workspace(lib):
 @pytest.mark.parametrize("layout", ["bnhd", "fused"])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("H,N,d", [(2, 512, 32), (2, 512, 64), (3, 700, 64), (2, 640, 96), (2, 512, 128), (3, 1025, 128),
-                                   (2, 512, 256), (2, 600, 256), (33, 1024, 96), (33, 1024, 128), (17, 1000, 128)], ids=str)
+                                   (2, 512, 256), (2, 600, 256), (33, 1024, 96), (33, 1024, 128), (17, 1000, 128),
+                                   (72, 512, 64), (72, 513, 32), (40, 600, 64), (40, 600, 96), (52, 570, 96), (16, 577, 64),
+                                   (16, 700, 96), (24, 600, 128)], ids=str)
 def test_strides_with_wave_groups(lib, H, N, d, causal, layout):
-    """The wave-group kernels (four groups, two groups, dQ's two at d = 256) on strided tensors: the bits of
-    the contiguous call, which the oracle tests above cover."""
+    """The wave-group kernels (blocks of 32 rows, four groups, two on 64 and on 128 rows, dQ's two at d = 256) on strided tensors: the
+    bits of the contiguous call, which the oracle tests cover."""
     x = _inputs(H + N + d, 1, H, N, N, d, scale=1.25)
     O, L = lib.attn_fwd(x["Q"], x["K"], x["V"], causal, d ** -0.5, 1)
     want = lib.attn_bwd(x["Q"], x["K"], x["V"], O, x["dO"], L, causal, d ** -0.5, 1)
@@ -281,7 +302,9 @@ def test_strides_with_wave_groups(lib, H, N, d, causal, layout):
 
 @pytest.mark.parametrize("Hkv,group,N,d,causal", [
     (2, 2, 512, 32, False), (2, 2, 512, 32, True), (2, 4, 577, 64, False), (2, 2, 545, 96, True), (2, 2, 512, 96, False),
-    (1, 4, 700, 128, False), (2, 2, 640, 128, True),                                  # four groups
+    (1, 4, 700, 128, False), (2, 2, 640, 128, True),                                  # dK/dV: blocks of 32 keys
+    (16, 2, 577, 32, True), (16, 2, 577, 64, True), (16, 2, 640, 128, True), (27, 2, 600, 96, True), (34, 2, 512, 64, True),
+    (16, 2, 600, 128, False), (16, 4, 520, 64, False), (20, 2, 640, 96, False),       # four groups (65 to 256 key blocks, 128 without a mask)
     (52, 2, 640, 96, True), (52, 2, 640, 128, True), (65, 2, 500 + 12, 128, True),    # two groups (257 to 512 key blocks)
     (27, 2, 640, 32, False), (27, 2, 640, 64, False), (27, 3, 600, 96, False), (33, 2, 512, 128, False),   # two (129 to 256)
     (52, 2, 640, 64, True), (52, 2, 640, 64, False), (2, 2, 640, 256, False)], ids=str)                        # one

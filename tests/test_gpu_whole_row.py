@@ -39,3 +39,33 @@ def test_both_passes_see_every_tile(lib, Nq, Nk, d, causal):
     assert float(over.max()) <= 1.0, float(over.max())
     assert torch.equal(torch.isneginf(LSE), ~some.expand_as(LSE))
     assert float((LSE.double() - L)[:, :, some].abs().max()) <= U + SLACK * 8
+
+
+@pytest.mark.parametrize("N", [1, 63, 64, 65, 128, 200, 320, 449])
+@pytest.mark.parametrize("d,causal", [(32, True), (64, True), (64, False), (96, True), (128, False), (256, True)])
+def test_the_rule_fires_on_whole_rows(lib, N, d, causal):
+    """Which rows the rule moved, against the two largest scores of the whole row in float64.  Repeated keys, in one tile and
+    tiles apart, and queries close to them.  A score's float32 sum is off by at most d 2^-24 of the sum of its products'
+    magnitudes: a row whose gap (two scores) lies that close to eps may go either way, unless its two largest scores belong to
+    equal keys, whose scores are equal bit for bit."""
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    q, k, v = (torch.randn((2, 3, N, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(3))
+    k[:, :, N // 2] = k[:, :, 0]              # a tie across the tiles
+    k[:, :, N - 1] = k[:, :, N // 3]
+    q[:, :, ::2] += k[:, :, N // 2].unsqueeze(2)
+    q[:, :, 1::2] -= k[:, :, N // 3].unsqueeze(2)
+    alpha, eps = 1.0 / math.sqrt(d), 1e-3
+    Q, K = q.double(), k.double()
+    seen = torch.ones((N, N), dtype=torch.bool, device=DEV)
+    if causal:
+        seen = seen.tril()
+    S = (alpha * (Q @ K.transpose(-1, -2))).masked_fill(~seen, -math.inf)
+    top = S.topk(min(2, N), -1).values
+    gap = top[..., 0] - top[..., -1] if N > 1 else torch.full_like(top[..., 0], math.inf)
+    slack = 2 * d * 2.0 ** -24 * alpha * (Q.abs() @ K.abs().transpose(-1, -2)).amax(-1)
+    got = lib.attn_fwd_opt(q, k, v, causal, alpha, lib.MITIGATED_ROW, eps=eps, want_counts=True)["fired"]
+    sure = (((gap - eps).abs() > slack) | (gap < 1e-12)) & (top[..., 0].abs() > slack)
+    assert torch.equal(got[sure] != 0, (gap <= eps)[sure])
+    assert sure.double().mean() > 0.9
+    if N >= 64:
+        assert (got != 0).any() and (got == 0).any()

@@ -4,6 +4,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_split import RECTANGLES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER_DIR = os.path.join(ROOT, "paper_2510_04212_amd", "csrc")
 
@@ -71,3 +73,9 @@ def test_every_compiled_form_is_used_and_every_used_one_compiled(ask):
     (1, 128, 1, 16, 1000, 4), (1, 64, 0, 400, 200, DENSE)])
 def test_the_faster_form_is_taken(ask, kernel, d, causal, heads, n, form):
     assert ask([(kernel, d, causal, 0, heads, n, n)])[0][0][0] == form
+
+
+def test_the_rectangles_reach_the_forms_they_name(ask):
+    """The GPU test of these sizes says which kernels it is about."""
+    cases = [(k, d, int(c), 0, H, nq, nk) for H, nq, nk, d, c, _, _ in RECTANGLES for k in (0, 1)]
+    assert [f for f, _ in ask(cases)[0]] == [f for r in RECTANGLES for f in r[5:]]
