@@ -261,7 +261,8 @@ def main():
                                 "clocks_per_instruction_per_simd": round(mc["clocks_per_mfma"], 2),
                                 "frac_of_measured_mfma_rate": round(tflops / mc["tflops"], 4),
                                 "note": "pure v_mfma_f32_32x32x16_bf16 loop, no memory traffic; every work-group records its own "
-                                        "clock; rate = mean clock x 4096 FLOP/clk/CU x 256 CUs x 32 / clocks_per_instruction; "
+                                        "clock; rate = mean clock x 4096 FLOP/clk/CU x 256 CUs x 32 / clocks_per_instruction (the backward's "
+                                        "v_mfma_f32_16x16x32_bf16 holds a higher clock on normal data: profiles/matrix_instruction_loops.txt); "
                                         f"nominal peak {PEAK_BF16_TFLOPS:.0f} TFLOP/s assumes 2.4 GHz"}
 
     # and what the LDS delivers to the operand fragments of the kernels' tile layout: every matrix

@@ -39,7 +39,8 @@ constexpr int kQPerWG = 128;      // dQ kernel: queries per work-group (32 per w
 template <int D> constexpr int kDSplit = D > 128 ? 2 : 1;
 // The kernel wants two waves on every SIMD: one wave alone leaves the matrix cores idle whenever
 // any of its instructions waits.  That means at most 256 registers per lane (some instantiations
-// at D = 128 under the mask spill three to nine, outside their tile loops).  At D = 128 the
+// at D = 128 under the mask spill three to nine, kHalf's bounds-checking one at D = 64 under the mask three,
+// all outside their tile loops).  At D = 128 the
 // accumulators (128) and the K fragments (32) leave no room for the V fragments: V_j is kept in LDS
 // for the whole block (8 more fragment reads per 32 queries to 48) and the query tiles shrink to 32
 // rows per wave group, so that two work-groups fit a CU.  Measured against one wave per SIMD with
@@ -57,7 +58,8 @@ template <int D> constexpr int kWavesPerSimd = D <= 128 ? 2 : 1;
 // where the tiles of eight would not fit the LDS.  kHalf (dK/dV at D <= 96): two groups on 64 keys, 256 threads.  bwd_forms.hpp has the
 // rules that choose.
 template <int FORM> constexpr int kGroups = FORM == kNarrow ? 4 : FORM == kHalf ? 2 : FORM;
-template <int FORM> constexpr int kKeyWaves = FORM == 8 || FORM == kNarrow ? 1 : FORM == 4 || FORM == kHalf ? 2 : 4;               // waves per group, 32 keys each
+// waves per group, 32 keys each
+template <int FORM> constexpr int kKeyWaves = FORM == 8 || FORM == kNarrow ? 1 : FORM == 4 || FORM == kHalf ? 2 : 4;
 template <int D, int FORM> constexpr int kQTile = D == 128 || FORM >= 4 ? 32 * kGroups<FORM> : 64;   // query rows per streamed tile
 // LDS fragments are read this many matrix instructions before their use.
 // (At D = 128 what the registers allow: the fragments of V_j come from LDS too.  Four wave groups at small D: us, four ahead ->
@@ -82,7 +84,7 @@ template <int D, int G> constexpr int kSmemDkDv =
           : kStageOverTiles<D, G> ? max_int(kTilesEnd<D, G>, kVBytes<D, G> + kStageBytes<D>) : kTilesEnd<D, G> + kStageBytes<D>;
 
 // DENSE (D <= 64): three waves on every SIMD at the price of a shorter read-ahead, for grids that have the work-groups
-// (launch_dkdv).
+// (bwd_forms.hpp).
 template <int D, bool DENSE> constexpr int kDkDvWaves = DENSE ? 3 : kWavesPerSimd<D>;
 template <int D, bool CAUSAL, bool RAGGED, bool GROUPED, int FORM, bool DENSE>
 __global__ __launch_bounds__(64 * kKeyWaves<FORM> * kGroups<FORM>)
@@ -812,7 +814,9 @@ __attribute__((amdgpu_waves_per_eu(kDqWavesPerSimd<D, FORM>))) void attn_bwd_dq_
     if ((!CAUSAL || last <= qw + shift) && (!RAGGED || last < NK)) {
       asm volatile("; every key counts");                    // (differs from the other path: nothing is merged in front of the branch)
       constexpr int NB = D == 32 ? 1 : NBT;
-      static_for<NBT / NB>([&](auto i) { kblocks(std::false_type{}, std::integral_constant<int, NB>{}, std::integral_constant<int, NB * decltype(i)::value>{}); });
+      static_for<NBT / NB>([&](auto i) {
+        kblocks(std::false_type{}, std::integral_constant<int, NB>{}, std::integral_constant<int, NB * decltype(i)::value>{});
+      });
       issued = true;
     } else {
       asm volatile("; masked");

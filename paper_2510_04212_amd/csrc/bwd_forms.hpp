@@ -37,7 +37,7 @@ constexpr bool dq_has_form(int d, int form) {
   return form == 1 || form == 2 || (form == 4 && d <= 128) || (form == 8 && d <= 64) || (form == kNarrow && d > 64 && d <= 128);
 }
 
-// kHalf.  All of its work-groups are resident at once up to two per CU at d = 96 (222 to 237 registers) and three at d <= 64.
+// kHalf.  Resident at once: three work-groups per CU at d <= 64, two at d = 96 (222 to 237 registers).
 constexpr bool dkdv_takes_half(int d, bool causal, bool grouped, long long heads, int nk) {
   if (!dkdv_has_form(d, causal, grouped, kHalf)) return false;
   const long long blocks = heads * ((nk + 127) / 128), halves = heads * ((nk + 63) / 64);
@@ -86,7 +86,7 @@ constexpr int dkdv_form(int d, bool causal, bool grouped, long long heads, int n
   return 1;
 }
 
-// Two groups on 64 queries.  Resident at once: three work-groups per CU at d <= 64, two at d = 96 and 128.
+// Two groups on 64 queries.  Resident at once: four work-groups per CU at d = 32, three at d = 64, two at d = 96 and 128.
 constexpr bool dq_takes_two(int d, bool causal, long long heads, int nq, int nk) {
   const long long blocks = heads * ((nq + 127) / 128), halves = heads * ((nq + 63) / 64);
   const bool ordered = heads % 8 == 0;
