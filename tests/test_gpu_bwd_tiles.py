@@ -53,7 +53,11 @@ def _check(lib, B, H, N, d, causal):
     (8, 16, 512, 32, True), (1, 129, 512, 32, True),
     # the same at every head size, below one block per CU (short and longer sequences under the mask) and above
     (1, 33, 513, 64, True), (1, 33, 512, 32, True), (3, 8, 1025, 64, True), (1, 25, 1100, 96, True), (1, 33, 513, 96, True), (8, 12, 512, 96, False),
-    (5, 13, 513, 96, True), (1, 17, 512, 128, True), (2, 33, 513, 128, True), (1, 80, 512, 128, True), (1, 17, 513, 128, False), (4, 8, 512, 128, False)])
+    (5, 13, 513, 96, True), (1, 17, 512, 128, True), (2, 33, 513, 128, True), (1, 80, 512, 128, True), (1, 17, 513, 128, False), (4, 8, 512, 128, False),
+    # at and beyond the lines that leave two groups for one or four: short sequences at d = 128, grids that do not divide over the XCDs, keys in the
+    # thousands, dK/dV at d = 64 in pairs of blocks
+    (1, 53, 768, 128, True), (1, 64, 512, 128, True), (1, 20, 1100, 128, True), (1, 58, 640, 96, False), (1, 64, 640, 96, False), (1, 54, 576, 96, False),
+    (1, 3, 3000, 128, False), (1, 5, 2048, 128, False), (1, 22, 640, 64, True), (1, 11, 768, 64, True), (1, 24, 768, 32, True), (1, 23, 1024, 32, True)])
 def test_every_entry_on_small_grids_of_longer_sequences(lib, B, H, N, d, causal):
     _check(lib, B, H, N, d, causal)
 
